@@ -6,7 +6,7 @@
 // [W_1 (d_out x d_in, row-major), b_1, W_2, b_2, ...]; gradients use the same layout, so the
 // update kernel can stream both without any gather.
 //
-// fp32 precision: an LDS-tiled SGEMM with fused bias/ReLU (forward) and ReLU-mask (dgrad)
+// fp32 precision: an fp32 matrix-core GEMM with fused bias/ReLU (forward) and ReLU-mask (dgrad)
 // epilogues.  bf16 precision (fp32 master weights): the matrix-core GEMM of
 // hdet_gemm_bf16.hip on the bf16 copy of the parameters; every activation and activation
 // gradient that goes to memory is bf16 except the logits; biases, loss and parameter

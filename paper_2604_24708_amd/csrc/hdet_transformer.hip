@@ -10,8 +10,8 @@
 // rate being replica r's value of the dropout channel; the mask is regenerated in the backward
 // pass from Philox-4x32-10 keyed on (seed, step, replica, site, element), never stored.
 //
-// All matrix products go through the replica-batched GEMMs (matrix cores in bf16 precision,
-// LDS-tiled fp32 otherwise); attention is the unfused chain scores -> softmax -> P V with the
+// All matrix products go through the replica-batched GEMMs (matrix cores, on bf16 operands in mixed precision
+// or in fp32 otherwise); attention is the unfused chain scores -> softmax -> P V with the
 // (replica, sequence, head) triple as the batch index.  Activations that go to memory are of
 // type T: float, or bfloat16 in mixed precision (logits, attention scores and LayerNorm
 // statistics stay fp32).

@@ -1,0 +1,83 @@
+"""Gradients of MLPs whose products reach every branch of the GEMM dispatch -- tile sizes, K splits, ragged edges,
+K tails -- against plain autograd in 64 bits."""
+import numpy as np
+import pytest
+import torch
+
+import hdet_inputs as I
+import paper_2604_24708_amd as H
+
+pytestmark = pytest.mark.gpu
+
+
+def mlp_grads(widths, batch, n, shared=False, bf16=False, seed=3):
+    """Gradients [n, P] (shared: [1, P], the sum over the replicas) from the library and from autograd in fp64, and the layers."""
+    P = I.mlp_param_count(widths)
+    stride = (P + 3) // 4 * 4
+    rng = np.random.Generator(np.random.Philox(seed))
+    theta = np.zeros((n, stride), np.float32)
+    theta[:, :P] = I.mlp_init(n, widths, seed) + 0.01 * rng.standard_normal((n, P), dtype=np.float32)
+    # Hidden biases of +-8^(layer): every other unit is open, the rest shut, and none is near the kink, where the two sides may
+    # take different (both valid) subgradients -- a layer's products are below 8^(layer - 1) * 6 / sqrt(3) in size (six standard
+    # deviations) for weights U(+-1 / sqrt(fan in)).  The output layer is scaled back, so that the softmax is not saturated.
+    off, L = 0, len(widths) - 1
+    for i in range(L):
+        k = widths[i + 1] * widths[i]
+        if i + 1 < L:
+            theta[:, off + k:off + k + widths[i + 1]] += np.where(np.arange(widths[i + 1]) % 2 == 0, 8.0, -8.0) * 8.0 ** i
+        else:
+            theta[:, off:off + k] /= 8.0 ** i
+        off += k + widths[i + 1]
+    x = rng.standard_normal((n, batch, widths[0]), dtype=np.float32)
+    y = rng.integers(0, widths[-1], (n, batch)).astype(np.int32)
+    dev = "cuda:0"
+    td, g, m, v = (torch.from_numpy(theta).to(dev), *(torch.full((n, stride), 7.0, device=dev) for _ in range(3)))
+    shadow = torch.zeros((n, stride), dtype=torch.bfloat16, device=dev) if bf16 else None
+    cfg = H.make_config(n_replicas=n, sync_interval=4, total_steps=10, lr_max=1e-3, alpha=0.1, widths=widths, batch=batch,
+                        model_kind=H.HDET_MLP, optimizer=H.HDET_ADAMW, precision=H.HDET_BF16_GEMM_FP32_MASTER if bf16 else H.HDET_FP32,
+                        grad_mode=H.HDET_GRAD_SHARED if shared else H.HDET_GRAD_PER_REPLICA)
+    ws = torch.empty(max(H.hdet_workspace_bytes(cfg, stride)[2], 16), dtype=torch.uint8, device=dev)
+    h = H.hdet_create(cfg, td, m, v, grads=g, params_bf16=shadow, workspace=ws, plane_stride=stride)
+    H.hdet_forward_backward(h, torch.from_numpy(x).to(dev), torch.from_numpy(y).to(dev), want_losses=True)
+    got = g.double().cpu().numpy()
+    H.hdet_destroy(h)
+    L = len(widths) - 1
+    ref = np.zeros((n, P))
+    for r in range(n):
+        par, off = [], 0
+        for i in range(L):
+            for shape in ((widths[i + 1], widths[i]), (widths[i + 1],)):
+                k = int(np.prod(shape))
+                t = torch.from_numpy(theta[r, off:off + k].copy()).view(*shape)
+                par.append((t.bfloat16().double() if bf16 and len(shape) == 2 else t.double()).requires_grad_())
+                off += k
+        a = torch.from_numpy(x[r])
+        a = (a.bfloat16() if bf16 else a).double()
+        for i in range(L):
+            a = a @ par[2 * i].T + par[2 * i + 1]
+            if i + 1 < L:
+                a = torch.relu(a)
+        torch.nn.functional.cross_entropy(a, torch.from_numpy(y[r]).long()).backward()
+        ref[r] = torch.cat([t.grad.reshape(-1) for t in par]).numpy()
+    slices, off = [], 0
+    for i in range(L):
+        for k in (widths[i + 1] * widths[i], widths[i + 1]):
+            slices.append(slice(off, off + k))
+            off += k
+    if shared:
+        return got[:1, :P], ref.sum(0, keepdims=True), slices
+    return got[:, :P], ref, slices
+
+
+# (widths, batch, replicas): products with few tiles, up to one block of each tile size per compute unit, more, many
+FP32 = [([33, 31, 9], 7, 2), ([1, 3, 1, 2], 5, 3), ([1003, 250, 70], 500, 4), ([77, 1030, 130], 515, 4), ([41, 2050, 8], 1030, 4)]
+
+
+@pytest.mark.parametrize("shared", [False, True])
+@pytest.mark.parametrize("widths,batch,n", FP32)
+def test_fp32_products_of_every_tile_size(widths, batch, n, shared):
+    got, ref, slices = mlp_grads(widths, batch, n, shared)
+    for s in slices:
+        # a sum of K fp32 products in any order is off by about sqrt(K) 2^-24 of its terms (K up to n * batch = 4120: 4e-6),
+        # three such products in a chain
+        assert np.linalg.norm(got[:, s] - ref[:, s]) <= 1.2e-5 * np.linalg.norm(ref[:, s]) + 1e-30, s
