@@ -20,10 +20,20 @@
 //     transposing LDS load of gfx950 (ds_read_b64_tr_b16, two per fragment), so that no
 //     transposed copy of weights or activations ever exists in HBM.
 //
-// Tiling: each wavefront owns a 64x64 output tile (2x2 blocks of v_mfma_f32_32x32x16_bf16); a
-// block is 2x2 wavefronts (128x128 tile).  K step 32, LDS double-buffered (one barrier per K
+// Tiling: each wavefront owns a 64x64 (or 32x32) output tile (2x2 blocks or one of v_mfma_f32_32x32x16_bf16);
+// a block is 2x2 wavefronts (128x128 or 64x64 tile).  K step 32, LDS double-buffered (one barrier per K
 // step), the next step's global loads in flight during the MFMAs; launch indices are remapped so
 // that each XCD's L2 serves a contiguous range of tiles.
+//
+// Loads of operands that are not made of aligned chunks: memory is read in aligned dwords (16 bytes per
+// lane; global loads need no more than dword alignment) and, where a chunk starts at an odd element, one
+// dword more and a funnel shift by 16 bits.  Rows beyond the matrix read its last row or first chunk again
+// (their results are not stored), so that only the last K step looks at the extent of anything.
+//
+// Measured against predicated 2-byte loads of such chunks: 96 x 700, K = 1500 (rows of 1500 elements, 6 replicas, 128 x 128
+// tiles) 282 -> 28.6 us, 700 x 1500, K = 576 77 -> 14.8 us; 256 x 4095, K = 4095, 8 replicas: 337 us (204 TFLOP/s).
+//
+// Products with few output tiles take a second kernel (hdet_bgemm_frag_kernel below).
 
 #include "hdet_internal.h"
 
@@ -53,14 +63,37 @@ __device__ __forceinline__ unsigned short f2bf(float x) {
 }
 __device__ __forceinline__ float bf2f(unsigned short h) { return __uint_as_float((unsigned)h << 16); }
 
-// 8 consecutive elements starting at src[idx], of which the first `valid` exist (others 0);
-// one 128-bit access when the chunk is whole and 16-byte aligned
-__device__ __forceinline__ us8 load8(const uint16_t* src, int64_t idx, int valid, bool vec_ok) {
-  if (valid >= 8 && vec_ok) return *reinterpret_cast<const us8*>(src + idx);
+typedef unsigned int u4a __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+
+// 8 consecutive elements starting at src[idx], all of them readable.  src is 2-byte aligned; `odd_possible` (uniform) says
+// whether &src[idx] may be no multiple of 4 bytes.  The fifth dword of an odd chunk holds its last element, that of an even one
+// is its fourth again: nothing beyond the dword of the last element is touched.
+__device__ __forceinline__ us8 load8_any(const uint16_t* src, int64_t idx, bool odd_possible) {
+  const uint16_t* q = src + idx;
+  if (!odd_possible) return __builtin_bit_cast(us8, (u4)*reinterpret_cast<const u4a*>(q));
+  const unsigned odd = ((unsigned)(uintptr_t)q >> 1) & 1u;
+  const unsigned int* p = reinterpret_cast<const unsigned int*>(q - odd);
+  const u4a d = *reinterpret_cast<const u4a*>(p);
+  const unsigned e = p[3 + odd], sh = odd << 4;
+  const u4 r = {__builtin_amdgcn_alignbit(d[1], d[0], sh), __builtin_amdgcn_alignbit(d[2], d[1], sh), __builtin_amdgcn_alignbit(d[3], d[2], sh),
+                __builtin_amdgcn_alignbit(e, d[3], sh)};
+  return __builtin_bit_cast(us8, r);
+}
+// ... of which the first `valid` count (others 0), in an operand of `extent` elements
+__device__ __forceinline__ us8 load8(const uint16_t* src, int64_t idx, int valid, int64_t extent, bool odd_possible) {
   us8 r = {0, 0, 0, 0, 0, 0, 0, 0};
+  if (valid <= 0) return r;
+  if (idx + 8 <= extent) {
+    r = load8_any(src, idx, odd_possible);
 #pragma unroll
-  for (int j = 0; j < 8; ++j)
-    if (j < valid) r[j] = src[idx + j];
+    for (int j = 1; j < 8; ++j)
+      if (j >= valid) r[j] = 0;
+  } else {
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (j < valid) r[j] = src[idx + j];
+  }
   return r;
 }
 
@@ -72,20 +105,32 @@ struct operand {
   static constexpr int NCH = ROWS * 4 / THREADS;   // 8-element chunks per thread and K step
   static constexpr int RCH = ROWS / 8;         // chunks per k-row of a [k][row] tile
   us8 reg[NCH];
-  __device__ __forceinline__ void fetch(const uint16_t* src, int64_t ld, int row0, int rows, int k0, int kdim,
-                                        bool vec_ok, int tid) {
+  // K step that lies inside the matrix and is not its last one: rows beyond `rows` repeat others
+  __device__ __forceinline__ void fetch(const uint16_t* src, int64_t ld, int row0, int rows, int k0, bool odd, int tid) {
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
       const int c = tid + i * THREADS;
-      int valid;
       if (KMAJOR) {
         const int row = row0 + (c >> 2), k = k0 + ((c & 3) << 3);
-        valid = row < rows ? kdim - k : 0;
-        reg[i] = load8(src, (int64_t)row * ld + k, valid, vec_ok);
+        reg[i] = load8_any(src, (int64_t)(row < rows ? row : rows - 1) * ld + k, odd);
       } else {
         const int k = k0 + c / RCH, row = row0 + ((c % RCH) << 3);
-        valid = k < kdim ? rows - row : 0;
-        reg[i] = load8(src, (int64_t)k * ld + row, valid, vec_ok);
+        reg[i] = load8_any(src, (int64_t)k * ld + (row < rows ? row : row0), odd);
+      }
+    }
+  }
+  // last K step: zeros beyond the contraction, nothing beyond the operand's extent is read
+  __device__ __forceinline__ void fetch_last(const uint16_t* src, int64_t ld, int row0, int rows, int k0, int kdim, bool odd, int tid) {
+    const int64_t extent = (int64_t)((KMAJOR ? rows : kdim) - 1) * ld + (KMAJOR ? kdim : rows);
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) {
+      const int c = tid + i * THREADS;
+      if (KMAJOR) {
+        const int row = row0 + (c >> 2), k = k0 + ((c & 3) << 3);
+        reg[i] = load8(src, (int64_t)row * ld + k, row < rows ? kdim - k : 0, extent, odd);
+      } else {
+        const int k = k0 + c / RCH, row = row0 + ((c % RCH) << 3);
+        reg[i] = load8(src, (int64_t)k * ld + row, k < kdim ? rows - row : 0, extent, odd);
       }
     }
   }
@@ -118,6 +163,22 @@ struct operand {
   }
 };
 
+// one element of C with the epilogue EPI
+template <int EPI>
+__device__ __forceinline__ void put_element(const hdet_bgemm_args& g, int z, int64_t c_base, int row, int col, float v) {
+  if (row >= g.m || col >= g.n) return;
+  const int64_t off = c_base + (int64_t)row * g.ldc + col;
+  if (EPI == HDET_EPI_BIAS_RELU_BF16 || EPI == HDET_EPI_BIAS_F32 || EPI == HDET_EPI_BIAS_BF16) v += g.bias[(int64_t)z * g.bias_bs + col];
+  if (EPI == HDET_EPI_F32 || EPI == HDET_EPI_BIAS_F32) {
+    reinterpret_cast<float*>(g.c)[off] = v;
+    return;
+  }
+  if (EPI == HDET_EPI_BIAS_RELU_BF16) v = v > 0.f ? v : 0.f;
+  if (EPI == HDET_EPI_MASK_BF16)         // gradient through the ReLU of the layer below
+    v = bf2f(g.mask[(int64_t)z * g.mask_bs + (int64_t)row * g.mask_ld + col]) > 0.f ? v : 0.f;
+  reinterpret_cast<uint16_t*>(g.c)[off] = f2bf(v);
+}
+
 }  // namespace
 
 // WMT x WNT: 32x32 MFMA blocks per wavefront in m and n; WGM x 2 wavefronts per block
@@ -149,8 +210,8 @@ __global__ __launch_bounds__(128 * WGM, WGM) void hdet_bgemm_kernel(const hdet_b
   const int m0 = by * TM, n0 = bx * TN;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = (wave >> 1) * (32 * WMT), wn = (wave & 1) * (32 * WNT);
-  const bool a_vec = (g.lda & 7) == 0 && (reinterpret_cast<uintptr_t>(A) & 15) == 0;
-  const bool b_vec = (g.ldb & 7) == 0 && (reinterpret_cast<uintptr_t>(B) & 15) == 0;
+  const bool a_odd = (g.lda & 1) != 0 || (reinterpret_cast<uintptr_t>(A) & 3) != 0;
+  const bool b_odd = (g.ldb & 1) != 0 || (reinterpret_cast<uintptr_t>(B) & 3) != 0;
 
   f16v acc[WMT][WNT];
 #pragma unroll
@@ -162,20 +223,28 @@ __global__ __launch_bounds__(128 * WGM, WGM) void hdet_bgemm_kernel(const hdet_b
 
   // One register stage: the global loads of K step kt + 1 are issued before the MFMAs of step
   // kt and written to the other LDS buffer after them (one barrier per step); other blocks
-  // on the same CU cover the rest of the memory latency.  The step past the end loads nothing
-  // (all chunks absent) and its zeros are never used.
+  // on the same CU cover the rest of the memory latency.
   operand<A_KMAJOR, TM, THREADS> oa;
   operand<B_KMAJOR, TN, THREADS> ob;
   const int nk = (g.k + TK - 1) / TK;
-  oa.fetch(A, g.lda, m0, g.m, 0, g.k, a_vec, tid);
-  ob.fetch(B, g.ldb, n0, g.n, 0, g.k, b_vec, tid);
+  // a chunk at the end of a k-row reads on into the next one, which has to be long enough for that
+  const bool roomy = (A_KMAJOR || g.lda >= 8) && (B_KMAJOR || g.ldb >= 8);
+  auto request = [&](int kt) {
+    if (kt + 1 < nk && roomy) {
+      oa.fetch(A, g.lda, m0, g.m, kt * TK, a_odd, tid);
+      ob.fetch(B, g.ldb, n0, g.n, kt * TK, b_odd, tid);
+    } else {
+      oa.fetch_last(A, g.lda, m0, g.m, kt * TK, g.k, a_odd, tid);
+      ob.fetch_last(B, g.ldb, n0, g.n, kt * TK, g.k, b_odd, tid);
+    }
+  };
+  request(0);
   oa.commit(As[0], tid);
   ob.commit(Bs[0], tid);
   __syncthreads();
   for (int kt = 0; kt < nk; ++kt) {
     const int buf = kt & 1;
-    oa.fetch(A, g.lda, m0, g.m, (kt + 1) * TK, g.k, a_vec, tid);
-    ob.fetch(B, g.ldb, n0, g.n, (kt + 1) * TK, g.k, b_vec, tid);
+    if (kt + 1 < nk) request(kt + 1);
     __builtin_amdgcn_sched_barrier(0);     // keep the loads ahead of the MFMAs ...
 #pragma unroll
     for (int ks = 0; ks < TK; ks += 16) {
@@ -201,60 +270,216 @@ __global__ __launch_bounds__(128 * WGM, WGM) void hdet_bgemm_kernel(const hdet_b
 #pragma unroll
   for (int i = 0; i < WMT; ++i)
 #pragma unroll
-    for (int j = 0; j < WNT; ++j) {
-      const int col = n0 + wn + j * 32 + (lane & 31);
-      if (col >= g.n) continue;
-      float bias = 0.f;
-      if (EPI == HDET_EPI_BIAS_RELU_BF16 || EPI == HDET_EPI_BIAS_F32 || EPI == HDET_EPI_BIAS_BF16)
-        bias = g.bias[(int64_t)z * g.bias_bs + col];
+    for (int j = 0; j < WNT; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int row = m0 + wm + i * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
-        if (row >= g.m) continue;
-        float v = acc[i][j][e];
-        const int64_t off = c_base + (int64_t)row * g.ldc + col;
-        if (EPI == HDET_EPI_F32) {
-          reinterpret_cast<float*>(g.c)[off] = v;
-        } else if (EPI == HDET_EPI_BIAS_F32) {
-          reinterpret_cast<float*>(g.c)[off] = v + bias;
-        } else if (EPI == HDET_EPI_BF16) {
-          reinterpret_cast<uint16_t*>(g.c)[off] = f2bf(v);
-        } else if (EPI == HDET_EPI_BIAS_BF16) {
-          reinterpret_cast<uint16_t*>(g.c)[off] = f2bf(v + bias);
-        } else if (EPI == HDET_EPI_BIAS_RELU_BF16) {
-          v += bias;
-          reinterpret_cast<uint16_t*>(g.c)[off] = f2bf(v > 0.f ? v : 0.f);
-        } else {   // HDET_EPI_MASK_BF16: gradient through the ReLU of the layer below
-          const float act = bf2f(g.mask[(int64_t)z * g.mask_bs + (int64_t)row * g.mask_ld + col]);
-          reinterpret_cast<uint16_t*>(g.c)[off] = f2bf(act > 0.f ? v : 0.f);
+      for (int e = 0; e < 16; ++e)
+        put_element<EPI>(g, z, c_base, m0 + wm + i * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3), n0 + wn + j * 32 + (lane & 31), acc[i][j][e]);
+}
+
+// Products with few output tiles: what counts there is the length of a block's K loop and the wavefronts in flight, as for
+// the fp32 products (hdet_gemm_f32.hip), and the kernel is built the same way.  A wavefront loads the fragments of its
+// (32 WTM) x (32 WTN) tile straight from global memory, U steps of 16 k ahead, without LDS and without a barrier; WK wavefronts
+// share the contraction and add their partial tiles through LDS in ascending order of k.  An operand contiguous along k is one
+// 16-byte load per lane and fragment (with the funnel shift where chunks start at odd elements); one contiguous along its
+// output axis is eight 2-byte loads, 32 consecutive elements at a time, so that no alignment is needed at all.
+template <bool KMAJOR>
+__device__ __forceinline__ us8 frag_load(const uint16_t* src, int64_t lane_off, int64_t ld, bool odd) {
+  if (KMAJOR) return load8_any(src, lane_off, odd);
+  us8 r;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) r[j] = (src + j * ld)[lane_off];
+  return r;
+}
+template <bool KMAJOR>
+__device__ __forceinline__ us8 frag_load_tail(const uint16_t* src, int64_t lane_off, int64_t ld, int valid) {
+  us8 r = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+  for (int j = 0; j < 8; ++j)
+    if (j < valid) r[j] = KMAJOR ? src[lane_off + j] : (src + j * ld)[lane_off];
+  return r;
+}
+
+template <bool A_KMAJOR, bool B_KMAJOR, int EPI, int WTM, int WTN, int WK, int U>
+__global__ __launch_bounds__(64 * WK) void hdet_bgemm_frag_kernel(const hdet_bgemm_args g) {
+  constexpr int NW = WTM * WTN * 16;                                // accumulator registers
+  static_assert(NW % WK == 0, "the wavefronts of a K split share the tile's registers evenly");
+  __shared__ float part[WK > 1 ? WK * NW * 64 : 1];
+  unsigned bx, by, bz;
+  {   // launch order -> tile: XCD x (launch index mod 8) takes the x-th of eight contiguous ranges of tiles
+    const unsigned total = gridDim.x * gridDim.y * gridDim.z;
+    unsigned t = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
+    const unsigned x = t & 7u, rem = total & 7u;
+    t = x * (total >> 3) + (x < rem ? x : rem) + (t >> 3);
+    bx = t % gridDim.x;
+    by = (t / gridDim.x) % gridDim.y;
+    bz = t / (gridDim.x * gridDim.y);
+  }
+  const hdet_batch_index bi = hdet_split_batch(bz, g.n1, g.n2);
+  const int z = bi.z0;
+  const uint16_t* A = g.a + hdet_batch_offset(bi, g.a_s);
+  const uint16_t* B = g.b + hdet_batch_offset(bi, g.b_s);
+  const int64_t c_base = hdet_batch_offset(bi, g.c_s);
+  const int lane = threadIdx.x & 63, half = lane >> 5;
+  const int wk = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m0 = by * (32 * WTM), n0 = bx * (32 * WTN);
+  const bool a_odd = (g.lda & 1) != 0 || (reinterpret_cast<uintptr_t>(A) & 3) != 0;
+  const bool b_odd = (g.ldb & 1) != 0 || (reinterpret_cast<uintptr_t>(B) & 3) != 0;
+
+  f16v acc[WTM][WTN];
+#pragma unroll
+  for (int i = 0; i < WTM; ++i)
+#pragma unroll
+    for (int j = 0; j < WTN; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+
+  // lane l: row r0 + l % 32 (the matrix's last row again beyond it; a 32-row group beyond the matrix repeats the first one), k = 8 (l / 32) + 0..7
+  int64_t aoff[WTM], boff[WTN];
+#pragma unroll
+  for (int i = 0; i < WTM; ++i) {
+    int row = (m0 + 32 * i < g.m ? m0 + 32 * i : m0) + (lane & 31);
+    if (row >= g.m) row = g.m - 1;
+    aoff[i] = A_KMAJOR ? row * g.lda + half * 8 : half * 8 * g.lda + row;
+  }
+#pragma unroll
+  for (int j = 0; j < WTN; ++j) {
+    int row = (n0 + 32 * j < g.n ? n0 + 32 * j : n0) + (lane & 31);
+    if (row >= g.n) row = g.n - 1;
+    boff[j] = B_KMAJOR ? row * g.ldb + half * 8 : half * 8 * g.ldb + row;
+  }
+  const int64_t astep = A_KMAJOR ? 16 : 16 * g.lda, bstep = B_KMAJOR ? 16 : 16 * g.ldb;
+  const int nfull = g.k >> 4, per = (nfull + WK - 1) / WK;
+  const int c0 = wk * per < nfull ? wk * per : nfull, c1 = c0 + per < nfull ? c0 + per : nfull;
+
+  us8 a[2][U][WTM], b[2][U][WTN];
+  auto fetch = [&](int buf, int c) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int cc = c + u < c1 ? c + u : c1 - 1;                   // past the end: the last step again, not used
+#pragma unroll
+      for (int i = 0; i < WTM; ++i) a[buf][u][i] = frag_load<A_KMAJOR>(A + cc * astep, aoff[i], g.lda, a_odd);
+#pragma unroll
+      for (int j = 0; j < WTN; ++j) b[buf][u][j] = frag_load<B_KMAJOR>(B + cc * bstep, boff[j], g.ldb, b_odd);
+    }
+  };
+  auto step = [&](us8 (&av)[WTM], us8 (&bv)[WTN]) {
+#pragma unroll
+    for (int i = 0; i < WTM; ++i)
+#pragma unroll
+      for (int j = 0; j < WTN; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av[i]), __builtin_bit_cast(bf16x8, bv[j]), acc[i][j], 0, 0, 0);
+  };
+  if (c0 < c1) {
+    fetch(0, c0);
+    for (int c = c0; c < c1; c += 2 * U) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int cur = c + h * U;
+        if (cur < c1) {
+          if (cur + U < c1) fetch(h ^ 1, cur + U);
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+            if (u == 0 || cur + u < c1) step(a[h][u], b[h][u]);
         }
       }
     }
+  }
+  const int kleft = g.k & 15;
+  if (kleft && wk == WK - 1) {
+    us8 av[WTM], bv[WTN];
+#pragma unroll
+    for (int i = 0; i < WTM; ++i) av[i] = frag_load_tail<A_KMAJOR>(A + nfull * astep, aoff[i], g.lda, kleft - half * 8);
+#pragma unroll
+    for (int j = 0; j < WTN; ++j) bv[j] = frag_load_tail<B_KMAJOR>(B + nfull * bstep, boff[j], g.ldb, kleft - half * 8);
+    step(av, bv);
+  }
+
+  auto put = [&](int q, float v) {                                  // q: accumulator register of the tile
+    const int e = q % 16, i = q / (16 * WTN), j = (q / 16) % WTN;
+    put_element<EPI>(g, z, c_base, m0 + 32 * i + (e >> 2) * 8 + half * 4 + (e & 3), n0 + 32 * j + (lane & 31), v);
+  };
+  if (WK == 1) {
+#pragma unroll
+    for (int q = 0; q < NW; ++q) put(q, acc[q / (16 * WTN)][(q / 16) % WTN][q % 16]);
+  } else {
+    float* mine = part + wk * (NW * 64) + lane;                     // [register][lane] of this wavefront's partial tile
+#pragma unroll
+    for (int q = 0; q < NW; ++q) mine[q * 64] = acc[q / (16 * WTN)][(q / 16) % WTN][q % 16];
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < NW / WK; ++t) {
+      const int q = wk * (NW / WK) + t;
+      float v = part[q * 64 + lane];
+#pragma unroll
+      for (int p = 1; p < WK; ++p) v += part[(p * NW + q) * 64 + lane];
+      put(q, v);
+    }
+  }
 }
+
+namespace {
+
+// blocks of tm x tn a product would have over its batch
+int64_t tiles(const hdet_bgemm_args& g, int batch, int tm, int tn) {
+  return (int64_t)((g.m + tm - 1) / tm) * ((g.n + tn - 1) / tn) * batch;
+}
+// A product that leaves most of the chip idle in 64 x 64 tiles takes the fragment kernel with 32 x 32 tiles and K in 4, whatever its
+// K: that kernel reaches 50-65 TFLOP/s, the LDS kernels need about 0.5 us per 32 k and block, and the two meet at about 100
+// tiles of 64 x 64 on 256 CUs.  Measured (us, 256 CUs): 96 x 700, K = 100, 6 items (132 tiles) 4.3 | LDS 64 x 64 4.9; 96 x 100,
+// K = 700, 6 items 5.7 | 9.6; 64 x 512, K = 512, 8 items 4.7 | 7.8, LDS-direct 7.0; 96 x 1500, K = 784, 6 items (288 tiles)
+// 18.4 | 13.5, LDS-direct 9.4.
+bool few_tiles(const hdet_bgemm_args& g, int batch) { return tiles(g, batch, 64, 64) * 5 < 2 * (int64_t)hdet_compute_units(); }
+
+template <bool AK, bool BK, int EPI>
+hipError_t launch_general(const hdet_bgemm_args& g, int batch, hipStream_t s) {
+#define HDET_FRAG(WTM, WTN, WK, U)                                                                    \
+  hipLaunchKernelGGL((hdet_bgemm_frag_kernel<AK, BK, EPI, WTM, WTN, WK, U>),                          \
+                     dim3((g.n + 32 * WTN - 1) / (32 * WTN), (g.m + 32 * WTM - 1) / (32 * WTM), batch), dim3(64 * WK), 0, s, g)
+#define HDET_LDS(WT)                                                                                  \
+  hipLaunchKernelGGL((hdet_bgemm_kernel<AK, BK, EPI, WT, WT, 2>), dim3((g.n + 64 * WT - 1) / (64 * WT), (g.m + 64 * WT - 1) / (64 * WT), batch), dim3(256), 0, s, g)
+  const int64_t cus = hdet_compute_units();
+  if (few_tiles(g, batch)) HDET_FRAG(1, 1, 4, 4);
+  // less than one 64 x 64 block per CU and a long contraction: K in 8 (96 x 700, K = 1500, 6 items: 15.5 | LDS 64 x 64 26.6;
+  // 111 x 3193, K = 1788, 2 items, odd rows: 24 | 51; at K = 842 10.7 | 10.9)
+  else if (g.k >= 1024 && tiles(g, batch, 64, 64) < cus) HDET_FRAG(2, 2, 8, 2);
+  // 128 x 128 tiles once there are several rounds of them (256 x 4095, K = 4095, 8 items: 337 | 64 x 64 441; 700 x 1500, K = 576:
+  // 14.8 | 10.1; 1788 x 3193, K = 222: 18.4 | 14.7), unless they would be half empty
+  else if (tiles(g, batch, 128, 128) >= 4 * cus && g.m > 64 && g.n > 64) HDET_LDS(2);
+  else HDET_LDS(1);
+#undef HDET_LDS
+#undef HDET_FRAG
+  return hipGetLastError();
+}
+
+}  // namespace
 
 hipError_t hdet_launch_bgemm(const hdet_bgemm_args& g_in, bool a_kmajor, bool b_kmajor, int epi, int batch,
                              hipStream_t s) {
   hdet_bgemm_args g = g_in;
   if (g.n1 < 1) g.n1 = 1;
   if (g.n2 < 1) g.n2 = 1;
-  if (hdet_bgemm_dma_eligible(g, a_kmajor, b_kmajor, epi)) return hdet_launch_bgemm_dma(g, a_kmajor, b_kmajor, epi, batch, s);
-  dim3 grid((g.n + 127) / 128, (g.m + 127) / 128, batch);
-#define HDET_BGEMM(AK, BK, E) hipLaunchKernelGGL((hdet_bgemm_kernel<AK, BK, E, 2, 2, 2>), grid, dim3(256), 0, s, g)
-#define HDET_BGEMM_EPI(AK, BK)                                                                         \
-  switch (epi) {                                                                                       \
-    case HDET_EPI_F32: HDET_BGEMM(AK, BK, HDET_EPI_F32); break;                                        \
-    case HDET_EPI_BIAS_F32: HDET_BGEMM(AK, BK, HDET_EPI_BIAS_F32); break;                              \
-    case HDET_EPI_BIAS_RELU_BF16: HDET_BGEMM(AK, BK, HDET_EPI_BIAS_RELU_BF16); break;                  \
-    case HDET_EPI_MASK_BF16: HDET_BGEMM(AK, BK, HDET_EPI_MASK_BF16); break;                            \
-    case HDET_EPI_BF16: HDET_BGEMM(AK, BK, HDET_EPI_BF16); break;                                      \
-    case HDET_EPI_BIAS_BF16: HDET_BGEMM(AK, BK, HDET_EPI_BIAS_BF16); break;                            \
-    default: return hipErrorInvalidValue;                                                              \
+  // The LDS-direct kernel where the operands allow it, except for products of few tiles in the epilogues that the general kernels
+  // have.  Weight gradients stay: the update that the LDS-direct kernel can apply to them (HDET_EPI_ADAMW) has to see the same sums.
+  const bool plain = epi <= HDET_EPI_BIAS_BF16 && !g.colsum && a_kmajor;
+  if (hdet_bgemm_dma_eligible(g, a_kmajor, b_kmajor, epi) && !(plain && few_tiles(g, batch)))
+    return hdet_launch_bgemm_dma(g, a_kmajor, b_kmajor, epi, batch, s);
+  if (a_kmajor && b_kmajor) {            // forward
+    switch (epi) {
+      case HDET_EPI_F32: return launch_general<true, true, HDET_EPI_F32>(g, batch, s);
+      case HDET_EPI_BIAS_F32: return launch_general<true, true, HDET_EPI_BIAS_F32>(g, batch, s);
+      case HDET_EPI_BIAS_RELU_BF16: return launch_general<true, true, HDET_EPI_BIAS_RELU_BF16>(g, batch, s);
+      case HDET_EPI_BIAS_BF16: return launch_general<true, true, HDET_EPI_BIAS_BF16>(g, batch, s);
+      default: return hipErrorInvalidValue;
+    }
   }
-  if (a_kmajor && b_kmajor) { HDET_BGEMM_EPI(true, true) }            // forward
-  else if (a_kmajor && !b_kmajor) { HDET_BGEMM_EPI(true, false) }     // dgrad
-  else if (!a_kmajor && !b_kmajor) { HDET_BGEMM_EPI(false, false) }   // wgrad
-  else return hipErrorInvalidValue;
-#undef HDET_BGEMM_EPI
-#undef HDET_BGEMM
-  return hipGetLastError();
+  if (a_kmajor) {                        // dgrad
+    if (epi == HDET_EPI_MASK_BF16) return launch_general<true, false, HDET_EPI_MASK_BF16>(g, batch, s);
+    if (epi == HDET_EPI_BF16) return launch_general<true, false, HDET_EPI_BF16>(g, batch, s);
+    return hipErrorInvalidValue;
+  }
+  if (!b_kmajor) {                       // wgrad
+    if (epi == HDET_EPI_F32) return launch_general<false, false, HDET_EPI_F32>(g, batch, s);
+    if (epi == HDET_EPI_BF16) return launch_general<false, false, HDET_EPI_BF16>(g, batch, s);
+  }
+  return hipErrorInvalidValue;
 }

@@ -81,3 +81,20 @@ def test_fp32_products_of_every_tile_size(widths, batch, n, shared):
         # a sum of K fp32 products in any order is off by about sqrt(K) 2^-24 of its terms (K up to n * batch = 4120: 4e-6),
         # three such products in a chain
         assert np.linalg.norm(got[:, s] - ref[:, s]) <= 1.2e-5 * np.linalg.norm(ref[:, s]) + 1e-30, s
+
+
+# bf16 operands of every alignment (rows of odd, even and 4-element multiples; 8 and more take the LDS-direct kernel where
+# they have enough tiles): few tiles, a long contraction over less than one tile per compute unit, 64- and 128-wide tiles
+BF16 = [([33, 31, 9], 7, 2), ([3, 5, 2], 3, 2), ([40, 24, 16], 20, 2), ([1503, 702, 100], 97, 6), ([130, 702, 36], 66, 3), ([1031, 2111, 10], 65, 2),
+        ([787, 1501, 99], 96, 6), ([516, 2052, 12], 200, 5), ([999, 2055, 130], 260, 8)]
+
+
+@pytest.mark.parametrize("shared", [False, True])
+@pytest.mark.parametrize("widths,batch,n", BF16)
+def test_bf16_products_of_every_alignment(widths, batch, n, shared):
+    got, ref, slices = mlp_grads(widths, batch, n, shared, bf16=True)
+    for s in slices:
+        # activations and their gradients are rounded to bfloat16 (2^-9 each) where they are stored, one or two hidden layers deep;
+        # no unit is near its kink.  The open units' activations sit near 8, a rounding there moves the logits by their share of
+        # 2^-9 * 8 / 8 and the output gradient (p - y) by as much: 1e-2 in norm covers a chain of four such roundings.
+        assert np.linalg.norm(got[:, s] - ref[:, s]) <= 1e-2 * np.linalg.norm(ref[:, s]) + 1e-30, s
