@@ -207,7 +207,7 @@ int hdet_warm_init(hdet_handle* h, const float* theta0_dev, double nu, uint64_t 
  * same layout.  All pointers are device memory owned by the caller, 16-byte aligned, planes
  * plane_stride elements apart (>= n_params, a multiple of 4); theta0_dev [n_params] must not
  * overlap params_dev; stream: hipStream_t or NULL.  The partial sums of ||theta0||^2 live in a
- * fixed array of 8200 bytes inside the library, one copy per GPU for the life of the process;
+ * fixed array of 8 KiB inside the library, one copy per GPU for the life of the process;
  * the call allocates and frees nothing and does not wait for the stream.  Every entry of that
  * array that a call reads it has written before, so nothing carries over from one call to the
  * next; but all calls on one GPU share the array: calls that overlap in time on the same GPU

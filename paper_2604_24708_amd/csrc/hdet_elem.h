@@ -142,7 +142,10 @@ __device__ __forceinline__ float hdet_gelu_tanh_grad_fast(float z) {
   return __builtin_fmaf(sg, (z * (1.f - sg)) * __builtin_fmaf(k4, z2, k3), sg);
 }
 
-// Philox-4x32 with 10 rounds (Salmon et al., SC'11); used for dropout masks.
+// Philox-4x32 with 10 rounds (Salmon et al., SC'11); used for dropout masks and the warm initialisation.  From the fourth
+// round on all four words differ from lane to lane and the two exclusive ors of a word are one v_bitop3 (which the compiler
+// does not form from the written-out ones); before that most operands are uniform or do not change between replicas and are
+// left to the scalar unit and to hoisting.
 struct hdet_philox4 { uint32_t x[4]; };
 __device__ __forceinline__ hdet_philox4 hdet_philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                                            uint32_t k0, uint32_t k1) {
@@ -151,9 +154,10 @@ __device__ __forceinline__ hdet_philox4 hdet_philox4x32_10(uint32_t c0, uint32_t
     if (rnd > 0) { k0 += 0x9E3779B9u; k1 += 0xBB67AE85u; }
     const uint64_t p0 = (uint64_t)0xD2511F53u * c0;
     const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
-    const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0;
+    const uint32_t h0 = (uint32_t)(p0 >> 32), h1 = (uint32_t)(p1 >> 32);
+    const uint32_t n0 = rnd < 3 ? h1 ^ c1 ^ k0 : __builtin_amdgcn_bitop3_b32(h1, c1, k0, 0x96);
     const uint32_t n1 = (uint32_t)p1;
-    const uint32_t n2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
+    const uint32_t n2 = rnd < 3 ? h0 ^ c3 ^ k1 : __builtin_amdgcn_bitop3_b32(h0, c3, k1, 0x96);
     const uint32_t n3 = (uint32_t)p0;
     c0 = n0; c1 = n1; c2 = n2; c3 = n3;
   }

@@ -32,8 +32,7 @@ struct hdet_ctrl {
   int32_t nonfinite;
   int32_t n_lr;                                   // channels 0..n_lr-1 are learning rates (one per group)
   int32_t pad_;
-  double warm_sumsq;                              // ||theta0||^2 of the warm initialisation
-  double warm_partial[1024];                      // its per-block partial sums
+  double warm_partial[1024];                      // warm initialisation: per-block partial sums of ||theta0||^2
 };
 #define HDET_WARM_PARTIALS 1024
 
@@ -107,8 +106,8 @@ hipError_t hdet_launch_converge(const hdet_converge_args& a, int variant, int bl
 hipError_t hdet_launch_shadow(const float* theta, uint16_t* shadow, int64_t n_params, int64_t stride,
                               int n_replicas, int blocks, hipStream_t stream);
 hipError_t hdet_launch_controller(const hdet_controller_args& a, hipStream_t stream);
-hipError_t hdet_launch_warm_init(const float* theta0, float* theta, int64_t n_params, int64_t stride, int n_replicas,
-                                 double* partial, double* sumsq, double nu, uint64_t seed, hipStream_t stream);
+hipError_t hdet_launch_warm_init(const float* theta0, float* theta, uint16_t* shadow, int64_t n_params, int64_t stride, int n_replicas,
+                                 double* partial, double nu, uint64_t seed, hipStream_t stream);
 // the noise generator numbers blocks of four parameters with a 32-bit counter word
 #define HDET_WARM_MAX_PARAMS ((int64_t)1 << 34)
 // message that hdet_last_error(NULL) returns (entry points without a handle)

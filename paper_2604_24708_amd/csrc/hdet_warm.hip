@@ -2,10 +2,10 @@
 // eps_r ~ N(0, nu^2 ||theta0||^2 / d), independent per replica and element.
 //
 // Two passes over HBM: a deterministic fp64 sum of squares of the checkpoint (per-block
-// partials added in block order), then one kernel that reads theta0 once and writes the N
-// perturbed planes.  The noise is a pure function of (seed, replica, index):
-// elements 4b..4b+3 come from philox(counter = (b, replica, 0, "WARM"), key = seed) through
-// two Box-Muller pairs (see box_muller_f32).
+// partials), then one kernel that adds the partials up in a fixed order, reads theta0 once and
+// writes the N perturbed planes and, where there is one, their bfloat16 copy.  The noise is a pure
+// function of (seed, replica, index): elements 4b..4b+3 come from philox(counter = (b, replica, 0,
+// "WARM"), key = seed) through two Box-Muller pairs (see box_muller_f32).
 
 #include <mutex>
 #include <string>
@@ -16,6 +16,7 @@
 namespace {
 
 constexpr uint32_t kWarmStream = 0x5741524Du;   // "WARM"
+constexpr int kNoiseBlocks = 8192;
 
 // Each thread walks 16-byte columns with a grid stride and keeps one fp64 sum per component (four independent
 // chains); components, lanes, wavefronts and blocks are then added in a fixed order.
@@ -42,34 +43,60 @@ __global__ __launch_bounds__(256) void sumsq_partial_kernel(const float* theta0,
   if (threadIdx.x == 0) partial[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 
-__global__ void sumsq_final_kernel(const double* partial, int nblocks, double* out) {
-  double s = 0.0;
-  for (int i = 0; i < nblocks; ++i) s += partial[i];
-  *out = s;
-}
-
 // Box-Muller in single precision, arranged so that nothing the result depends on is lost to fp32:
-//   -ln u, u = (w0 + 1) / 2^32:  for u <= 1/2 the logarithm of u itself; for u > 1/2, where u is too close to 1 for
-//      fp32 to hold, -log1p(-x) of the exactly known small x = (2^32 - 1 - w0) / 2^32;
-//   the angle 2 pi v, v = w1 / 2^32, through sin/cos of pi * (2 v), whose range reduction is exact.
-// The deviates agree with a double-precision evaluation to about 1e-6 absolute (the angle keeps 24 of w1's 32 bits),
-// i.e. to 1e-8 of the parameter scale at nu = 0.01: far inside what an fp32 parameter resolves.
+//   -ln u, u = (w0 + 1) / 2^32: for u <= 1/2 from u itself; for u > 1/2, where u is too close to 1 for fp32 to hold,
+//      from the exactly known small x = 1 - u: ln(1 - x) = ln f + d / f + ... with f = fl(1 - x) and the exactly computed
+//      rounding remainder d = (1 - f) - x, |d| <= 2^-25 (1/f is replaced by 2 - f: right where ln f is small, and
+//      within 2^-26 where it is not).  ln f = ln 2 * the hardware's log2, whose error is relative also next to f = 1.
+//   2 pi v, v = w1 / 2^32: the nearest multiple of 1/4 is taken out of the integer w1, so the remainder in +-1/8 keeps 24
+//      bits however small it is; sine and cosine of it are their Taylor polynomials through a^9 and a^8 (remainders for
+//      |a| <= pi/4: a^11 / 11! < 2e-9 and a^10 / 10! < 3e-8), then swapped and signed by the quarter.
 __device__ __forceinline__ void box_muller_f32(uint32_t w0, uint32_t w1, float* z0, float* z1) {
-  float t;       // -ln u
-  if (w0 < 0x80000000u) t = -logf((float)(w0 + 1u) * 2.3283064365386963e-10f);
-  else t = -log1pf(-((float)(0xffffffffu - w0) * 2.3283064365386963e-10f));
-  const float rad = sqrtf(2.f * t);
-  float sn, cs;
-  sincospif((float)w1 * 4.6566128730773926e-10f, &sn, &cs);       // pi * (2 v)
-  *z0 = rad * cs;
-  *z1 = rad * sn;
+  const bool upper = w0 >= 0x80000000u;
+  const float x = (float)(upper ? ~w0 : w0 + 1u) * 2.3283064365386963e-10f;
+  const float f = upper ? 1.f - x : x;
+  const float d = upper ? (1.f - f) - x : 0.f;
+  const float t2 = -2.f * __builtin_fmaf(d, 2.f - f, 0.6931471805599453f * __builtin_amdgcn_logf(f));     // -2 ln u
+  const float rad = __builtin_amdgcn_sqrtf(fmaxf(t2, 0.f));
+  const uint32_t quarter = (w1 + 0x20000000u) >> 30;
+  const float a = (float)(int32_t)(w1 - (quarter << 30)) * 1.4629180792671596e-09f;       // 2 pi / 2^32
+  const float q = a * a;
+  float sn = __builtin_fmaf(q, 2.7557319e-6f, -1.9841270e-4f);
+  sn = __builtin_fmaf(q, sn, 8.3333333e-3f);
+  sn = __builtin_fmaf(q, sn, -0.16666667f);
+  sn = __builtin_fmaf(a * q, sn, a);
+  float cs = __builtin_fmaf(q, 2.4801587e-5f, -1.3888889e-3f);
+  cs = __builtin_fmaf(q, cs, 4.1666667e-2f);
+  cs = __builtin_fmaf(q, cs, -0.5f);
+  cs = __builtin_fmaf(q, cs, 1.f);
+  // quarter 0: (cs, sn), 1: (-sn, cs), 2: (-cs, -sn), 3: (sn, -cs)
+  const float c = (quarter & 1u) ? sn : cs, s = (quarter & 1u) ? cs : sn;
+  const uint32_t neg_c = ((quarter + 1u) << 30) & 0x80000000u, neg_s = (quarter << 30) & 0x80000000u;
+  *z0 = rad * __uint_as_float(__float_as_uint(c) ^ neg_c);
+  *z1 = rad * __uint_as_float(__float_as_uint(s) ^ neg_s);
 }
 
-// thread = one block of four elements in every replica: theta_0 comes from memory once
-__global__ __launch_bounds__(256) void warm_noise_kernel(const float* theta0, float* theta, int64_t n, int64_t stride, int n_replicas,
-                                                         const double* sumsq, double nu, uint32_t seed_lo, uint32_t seed_hi) {
+// thread = one block of four elements in every replica: theta_0 comes from memory once.  Every block first adds up the
+// partial sums of squares (at most 8 KiB from the L2), in the same order, so no launch of its own is needed for that.
+// Bound by the integer multiplies and the stores about equally; the bfloat16 copy rides along in the arithmetic's shadow.
+// N = 8, P = 64e6 with the copy: 671 us = 5.0 TB/s (with library functions 1022 us, and 572 us more for a pass of its own
+// that made the copy).
+__global__ __launch_bounds__(256) void warm_noise_kernel(const float* theta0, float* theta, uint16_t* shadow, int64_t n, int64_t stride,
+                                                         int n_replicas, const double* partial, int n_partial, double nu,
+                                                         uint32_t seed_lo, uint32_t seed_hi) {
   typedef float f4 __attribute__((ext_vector_type(4)));
-  const float sigma = (float)(nu * sqrt(*sumsq / (double)n));
+  __shared__ double red[4];
+  double s = 0.0;
+#pragma unroll
+  for (int k = 0; k < HDET_WARM_PARTIALS / 256; ++k) {
+    const int i = k * 256 + threadIdx.x;
+    if (i < n_partial) s += partial[i];
+  }
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  const double sumsq = ((red[0] + red[1]) + red[2]) + red[3];
+  const float sigma = (float)(nu * sqrt(sumsq / (double)n));
   const int64_t nblk = (n + 3) >> 2;
   for (int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x; b < nblk; b += (int64_t)gridDim.x * 256) {
     const int64_t i = b << 2;
@@ -79,39 +106,50 @@ __global__ __launch_bounds__(256) void warm_noise_kernel(const float* theta0, fl
     else
       for (int j = 0; j < 4; ++j)
         if (i + j < n) t0[j] = theta0[i + j];
-    for (int r = 0; r < n_replicas; ++r) {
+    int64_t off = i;
+    for (int r = 0; r < n_replicas; ++r, off += stride) {
       const hdet_philox4 w = hdet_philox4x32_10((uint32_t)b, (uint32_t)r, 0u, kWarmStream, seed_lo, seed_hi);
       float z[4];
       box_muller_f32(w.x[0], w.x[1], &z[0], &z[1]);
       box_muller_f32(w.x[2], w.x[3], &z[2], &z[3]);
-      const f4 o = {__builtin_fmaf(sigma, z[0], t0[0]), __builtin_fmaf(sigma, z[1], t0[1]), __builtin_fmaf(sigma, z[2], t0[2]),
-                    __builtin_fmaf(sigma, z[3], t0[3])};
-      float* dst = theta + (int64_t)r * stride + i;
-      if (whole) __builtin_nontemporal_store(o, reinterpret_cast<f4*>(dst));
-      else
+      const hdet_f4 o = {{__builtin_fmaf(sigma, z[0], t0[0]), __builtin_fmaf(sigma, z[1], t0[1]), __builtin_fmaf(sigma, z[2], t0[2]),
+                          __builtin_fmaf(sigma, z[3], t0[3])}};
+      if (whole) {
+        hdet_st4_stream(theta + off, o);
+        if (shadow) hdet_st4_stream(shadow + off, o);
+      } else {
         for (int j = 0; j < 4; ++j)
-          if (i + j < n) dst[j] = o[j];
+          if (i + j < n) {
+            theta[off + j] = o.v[j];
+            if (shadow) hdet_st(shadow + off + j, o.v[j]);
+          }
+      }
     }
   }
 }
 
 }  // namespace
 
-// partial: HDET_WARM_PARTIALS doubles, sumsq: one double, both device memory that the three kernels own
-// for the duration of the call (every entry that is read is written first: nothing has to start at zero)
-hipError_t hdet_launch_warm_init(const float* theta0, float* theta, int64_t n_params, int64_t stride, int n_replicas,
-                                 double* partial, double* sumsq, double nu, uint64_t seed, hipStream_t s) {
+// partial: HDET_WARM_PARTIALS doubles of device memory that the two kernels own for the duration of the call (every entry
+// that is read is written first: nothing has to start at zero).  shadow: the bfloat16 copy, or null.
+hipError_t hdet_launch_warm_init(const float* theta0, float* theta, uint16_t* shadow, int64_t n_params, int64_t stride, int n_replicas,
+                                 double* partial, double nu, uint64_t seed, hipStream_t s) {
   int64_t nb = (n_params + 256 * 64 - 1) / (256 * 64);
   if (nb > HDET_WARM_PARTIALS) nb = HDET_WARM_PARTIALS;
   if (nb < 1) nb = 1;
   hipLaunchKernelGGL(sumsq_partial_kernel, dim3((unsigned)nb), dim3(256), 0, s, theta0, n_params, partial);
-  hipLaunchKernelGGL(sumsq_final_kernel, dim3(1), dim3(1), 0, s, partial, (int)nb, sumsq);
   int64_t gb = ((n_params + 3) / 4 + 255) / 256;
-  if (gb > 262144) gb = 262144;
+  if (gb > kNoiseBlocks) gb = kNoiseBlocks;
   if (gb < 1) gb = 1;
-  hipLaunchKernelGGL(warm_noise_kernel, dim3((unsigned)gb), dim3(256), 0, s, theta0, theta, n_params, stride, n_replicas,
-                     sumsq, nu, (uint32_t)(seed & 0xffffffffu), (uint32_t)(seed >> 32));
-  return hipGetLastError();
+  // a copy that lies over the checkpoint can only be written once the checkpoint has been read
+  const char *c0 = (const char*)theta0, *c1 = (const char*)(theta0 + n_params);
+  const char *s0 = (const char*)shadow, *s1 = (const char*)(shadow + (int64_t)n_replicas * stride);
+  const bool after = shadow && s0 < c1 && c0 < s1;
+  hipLaunchKernelGGL(warm_noise_kernel, dim3((unsigned)gb), dim3(256), 0, s, theta0, theta, after ? nullptr : shadow, n_params, stride,
+                     n_replicas, partial, (int)nb, nu, (uint32_t)(seed & 0xffffffffu), (uint32_t)(seed >> 32));
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !after) return e;
+  return hdet_launch_shadow(theta, shadow, n_params, stride, n_replicas, 4096, s);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -122,8 +160,7 @@ hipError_t hdet_launch_warm_init(const float* theta0, float* theta, int64_t n_pa
 // ---------------------------------------------------------------------------------------
 namespace {
 
-constexpr int kScratchDoubles = HDET_WARM_PARTIALS + 1;                   // partial sums, then their total
-static __device__ __align__(256) double scratch[kScratchDoubles];        // 8200 bytes per GPU
+static __device__ __align__(256) double scratch[HDET_WARM_PARTIALS];     // 8 KiB per GPU
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
@@ -170,10 +207,7 @@ extern "C" int hdet_warm_init_noalloc(const float* theta0_dev, float* params_dev
   const int rc = scratch_on_current_device(&ptr, &why);
   if (rc != HDET_OK) return bad(rc, why);
   hipStream_t s = (hipStream_t)stream;
-  hipError_t e = hdet_launch_warm_init(theta0_dev, params_dev, n_params, plane_stride, n_replicas, ptr, ptr + HDET_WARM_PARTIALS,
-                                       nu, seed, s);
-  if (e == hipSuccess && params_bf16_dev)
-    e = hdet_launch_shadow(params_dev, params_bf16_dev, n_params, plane_stride, n_replicas, 4096, s);
+  const hipError_t e = hdet_launch_warm_init(theta0_dev, params_dev, params_bf16_dev, n_params, plane_stride, n_replicas, ptr, nu, seed, s);
   if (e != hipSuccess) return bad(HDET_EHIP, std::string("warm initialisation kernels: ") + hipGetErrorString(e));
   return HDET_OK;
 }
