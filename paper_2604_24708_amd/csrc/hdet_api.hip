@@ -401,7 +401,6 @@ int launch_converge(hdet_handle* h) {
   a.n_params = param_count(h->cfg);
   a.stride = h->buf.plane_stride;
   a.n_replicas = h->cfg.n_replicas;
-  a.tail_only = 0;
   hipError_t e = hdet_launch_converge(a, h->tune_variant, default_blocks(h), h->stream);
   if (e != hipSuccess) return hip_fail(h, e, "converge kernel");
   h->converged_at_t = h->t;

@@ -80,7 +80,6 @@ struct hdet_converge_args {
   int64_t n_params;
   int64_t stride;
   int32_t n_replicas;
-  int32_t tail_only;       // loop kernel: only the P mod 4 trailing parameters
 };
 
 struct hdet_controller_args {

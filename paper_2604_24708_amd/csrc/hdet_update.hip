@@ -15,12 +15,15 @@
 //             exchange along the replica axis.  One column per thread and a grid that covers
 //             the plane exactly streamed fastest on MI355X (about 6.4 TB/s, against 5.9 for
 //             persistent blocks with a grid-stride loop).
-//   wave   -- N <= 16: the wavefronts of a block are the replicas of one 64-column group;
-//             gradients (shared mode) and updated parameters (fused converge) cross the
+//   wave   -- the wavefronts of a block are the replicas of one 64-column group (beyond 16 replicas
+//             up to four replicas a wavefront); gradients (shared mode) and updated parameters (fused converge) cross the
 //             replica axis through LDS, each wavefront then writes its own plane.  Keeps
 //             the register footprint of the plane kernel instead of N columns per thread.
-//   loop   -- one thread walks the replica axis of a column; any N; also used for the
-//             P mod 4 trailing parameters.
+//   loop   -- one thread walks the replica axis of a column; on request (hdet_set_launch_shape) and
+//             for planes of more columns than a grid holds.
+// The P mod 4 trailing parameters are one more column in the plane and wave kernels, read and
+// written element by element (ld_col / st_col): a launch of their own cost 3 to 6 us, as much as
+// the whole update of a small model.
 // With AdamW on the mean gradient the moments are the same for every replica; they can be kept
 // once (one plane each), which takes a step from 28 N to 12 N + 16 bytes per element.
 
@@ -55,6 +58,32 @@ __device__ __forceinline__ void st_bf16(uint16_t* p, f4 x) {
 }
 __device__ __forceinline__ void st_bf16(uint16_t* p, float x) { *p = to_bf16(x); }
 
+// Column i of a plane of which `cnt` elements exist: 4, or P mod 4 in the last column (the others read as 0).
+__device__ __forceinline__ f4 ld_col(const float* p, int cnt) {
+  if (cnt >= 4) return ld<f4>(p);
+  f4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
+    if (c < cnt) x[c] = ld<float>(p + c);
+  return x;
+}
+__device__ __forceinline__ void st_col(float* p, f4 x, int cnt) {
+  if (cnt >= 4) { st<f4>(p, x); return; }
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
+    if (c < cnt) st<float>(p + c, x[c]);
+}
+__device__ __forceinline__ void st_bf16_col(uint16_t* p, f4 x, int cnt) {
+  if (cnt >= 4) { st_bf16(p, x); return; }
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
+    if (c < cnt) st_bf16(p + c, x[c]);
+}
+__device__ __forceinline__ int col_elements(int64_t n_params, int64_t i) {      // <= 0: no such column
+  const int64_t left = n_params - (i << 2);
+  return left < 4 ? (int)left : 4;
+}
+
 // ---------------------------------------------------------------------------------------
 // plane kernel: thread = (replica blockIdx.y, column blockIdx.x * 256 + threadIdx.x)
 // ---------------------------------------------------------------------------------------
@@ -64,45 +93,53 @@ __global__ __launch_bounds__(kThreads) void hdet_update_plane_kernel(const hdet_
   const rep_scalars s = replica_scalars(a, r);
   if (blockIdx.x == 0 && threadIdx.x == 0 && a.lr_channel == 0) a.ctrl_out->lr_used[r] = s.lr;
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i >= (a.n_params >> 2)) return;
+  if (i >= ((a.n_params + 3) >> 2)) return;
+  const int cnt = col_elements(a.n_params, i);
   const int64_t off = (int64_t)r * a.stride + (i << 2);
-  f4 th = ld<f4>(a.theta + off);
-  f4 g = ld<f4>(a.grad + (int64_t)r * a.grad_stride + (i << 2));
+  f4 th = ld_col(a.theta + off, cnt);
+  f4 g = ld_col(a.grad + (int64_t)r * a.grad_stride + (i << 2), cnt);
   if (a.grad_stride == 0) g = g * a.grad_scale;
-  f4 m = ld<f4>(a.m + off);
+  f4 m = ld_col(a.m + off, cnt);
   f4 v = splat<f4>(0.f);
-  if (OPT == HDET_ADAMW) v = ld<f4>(a.v + off);
+  if (OPT == HDET_ADAMW) v = ld_col(a.v + off, cnt);
   update_one<OPT, f4>(th, g, m, v, a, s);
-  st<f4>(a.m + off, m);
-  if (OPT == HDET_ADAMW) st<f4>(a.v + off, v);
-  st<f4>(a.theta + off, th);
-  if (a.shadow) st_bf16(a.shadow + off, th);
+  st_col(a.m + off, m, cnt);
+  if (OPT == HDET_ADAMW) st_col(a.v + off, v, cnt);
+  st_col(a.theta + off, th, cnt);
+  if (a.shadow) st_bf16_col(a.shadow + off, th, cnt);
 }
 
 // ---------------------------------------------------------------------------------------
-// wave kernel: block = `groups` column groups x N wavefronts; wavefront (grp, r) owns the
-// 64 columns of group grp in replica r.  ex[grp * N + r][lane] carries a column across the
-// replica axis.
+// wave kernel: block = `groups` column groups x W wavefronts, W = ceil(N / R); wavefront (grp, w)
+// owns the 64 columns of group grp in the replicas w, w + W, ... (R of them at most; R = 1 up to
+// 16 replicas).  ex carries a column across the replica axis.
+// R > 1 against one thread per column that walks the replicas (the loop kernel), N = 32 and one set of moments: the
+// loads of all replicas are in flight together, and 16 wavefronts share a column's exchange.
 // ---------------------------------------------------------------------------------------
 constexpr int kMaxWaves = 16;
 
 // LDS staging for a mean along the replica axis, structure-of-arrays so that every access
-// is free of bank conflicts.  val[w][c][lane]: component c of wavefront w's column.
-struct exchange_buf {
-  float val[kMaxWaves][4][64];
-  float mean[kMaxWaves][4][64];      // indexed by group
+// is free of bank conflicts.  val[grp * N + r][c][lane]: component c of replica r's column.
+template <int R> struct exchange_buf {
+  float val[kMaxWaves * R][4][64];
+  float mean[R == 1 ? kMaxWaves : 1][4][64];      // indexed by group (R > 1: one group)
 };
 
-// Every wavefront of group `grp` hands in its column x; all get back the group's replica
+// Every wavefront of group `grp` hands in its columns x; all get back the group's replica
 // mean.  The 256 scalars of a group are shared out over its threads, each summed once in
 // fp64 in the order r = 0..N-1 and rounded to fp32 once (same bits as the loop kernel).
 // Ends with every thread past both barriers, so the buffer can be reused at once.
-__device__ __forceinline__ f4 exchange_mean(exchange_buf& e, f4 x, int w, int grp, int r, int n, int lane) {
+template <int R>
+__device__ __forceinline__ f4 exchange_mean(exchange_buf<R>& e, const f4 (&x)[R], int grp, int w, int waves, int n, int lane) {
 #pragma unroll
-  for (int c = 0; c < 4; ++c) e.val[w][c][lane] = x[c];
+  for (int k = 0; k < R; ++k)
+    if (R == 1 || w + k * waves < n) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) e.val[grp * n + w + k * waves][c][lane] = x[k][c];
+    }
   __syncthreads();
   const double inv_n = 1.0 / (double)n;
-  for (int sidx = r * 64 + lane; sidx < 256; sidx += n * 64) {
+  for (int sidx = w * 64 + lane; sidx < 256; sidx += waves * 64) {
     const int c = sidx >> 6, l = sidx & 63;
     double sum = 0.0;
     for (int q = 0; q < n; ++q) sum += (double)e.val[grp * n + q][c][l];
@@ -115,80 +152,127 @@ __device__ __forceinline__ f4 exchange_mean(exchange_buf& e, f4 x, int w, int gr
 // SSTATE (AdamW on the mean gradient): m and v are single planes; the wavefront of replica 0
 // reads, advances and writes them, and hands m / (sqrt(v)/sqrt(1-b2^t) + eps) to the other
 // wavefronts of its group through LDS.
-template <int OPT, bool SHARED, bool CONV, bool SSTATE>
+template <int OPT, bool SHARED, bool CONV, bool SSTATE, int R>
 __global__ __launch_bounds__(kMaxWaves * 64) void hdet_update_wave_kernel(const hdet_update_args a,
-                                                                          const int groups) {
+                                                                          const int groups, const int waves) {
   static_assert(!SSTATE || (SHARED && OPT == HDET_ADAMW), "one set of moments needs AdamW on the mean gradient");
-  __shared__ exchange_buf ex;
+  __shared__ exchange_buf<R> ex;
   const int n = a.n_replicas;
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int grp = w / n, r = w - grp * n;
-  const rep_scalars s = replica_scalars(a, r);
-  if (blockIdx.x == 0 && grp == 0 && lane == 0 && a.lr_channel == 0) a.ctrl_out->lr_used[r] = s.lr;
-  const int64_t i = ((int64_t)blockIdx.x * groups + grp) * 64 + lane;
-  const bool ok = i < (a.n_params >> 2);
-  const int64_t off = (int64_t)r * a.stride + (i << 2);
-  const int64_t moff = SSTATE ? (i << 2) : off;
-  const bool mine = ok && (!SSTATE || r == 0);        // this thread holds moments
-  f4 th = splat<f4>(0.f), g = th, m = th, v = th;
-  if (ok) {
-    th = ld<f4>(a.theta + off);
-    g = ld<f4>(a.grad + (int64_t)r * a.grad_stride + (i << 2));
-    if (a.grad_stride == 0) g = g * a.grad_scale;
+  const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int grp = R == 1 ? wid / waves : 0, w = wid - grp * waves;
+  rep_scalars s[R];
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    const int r = w + k * waves;
+    s[k] = replica_scalars(a, r < n ? r : 0);
+    if (blockIdx.x == 0 && grp == 0 && lane == 0 && a.lr_channel == 0 && r < n) a.ctrl_out->lr_used[r] = s[k].lr;
   }
-  if (mine) {
-    m = ld<f4>(a.m + moff);
-    if (OPT == HDET_ADAMW) v = ld<f4>(a.v + moff);
+  const int64_t i = ((int64_t)blockIdx.x * groups + grp) * 64 + lane;
+  const int cnt = col_elements(a.n_params, i);
+  const bool ok = cnt > 0;
+  constexpr int RM = SSTATE ? 1 : R;                   // sets of moments a thread may hold
+  f4 th[R], g[R], m[RM], v[RM];
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    const int r = w + k * waves;
+    const bool on = ok && (R == 1 || r < n);
+    const int64_t off = (int64_t)r * a.stride + (i << 2);
+    th[k] = g[k] = splat<f4>(0.f);
+    if (on) {
+      th[k] = ld_col(a.theta + off, cnt);
+      g[k] = ld_col(a.grad + (int64_t)r * a.grad_stride + (i << 2), cnt);
+      if (a.grad_stride == 0) g[k] = g[k] * a.grad_scale;
+    }
+    if (k < RM) {
+      m[k] = v[k] = splat<f4>(0.f);
+      if (on && (!SSTATE || w == 0)) {
+        m[k] = ld_col(a.m + (SSTATE ? (i << 2) : off), cnt);
+        if (OPT == HDET_ADAMW) v[k] = ld_col(a.v + (SSTATE ? (i << 2) : off), cnt);
+      }
+    }
   }
   // the paper's gradient AllReduce: every replica applies the replica mean
-  if (SHARED) g = exchange_mean(ex, g, w, grp, r, n, lane);
+  if (SHARED) {
+    const f4 gbar = exchange_mean<R>(ex, g, grp, w, waves, n, lane);
+#pragma unroll
+    for (int k = 0; k < R; ++k) g[k] = gbar;
+  }
   if (SSTATE) {
-    if (r == 0) {
-      const f4 ratio = adamw_moments<f4>(g, m, v, a);
+    if (w == 0) {
+      const f4 ratio = adamw_moments<f4>(g[0], m[0], v[0], a);
 #pragma unroll
       for (int c = 0; c < 4; ++c) ex.mean[grp][c][lane] = ratio[c];
     }
     __syncthreads();
     const f4 ratio = {ex.mean[grp][0][lane], ex.mean[grp][1][lane], ex.mean[grp][2][lane], ex.mean[grp][3][lane]};
-    adamw_apply<f4>(th, ratio, s);
+#pragma unroll
+    for (int k = 0; k < R; ++k) adamw_apply<f4>(th[k], ratio, s[k]);
     if (CONV) __syncthreads();                        // ex.mean is written again below
   } else {
-    update_one<OPT, f4>(th, g, m, v, a, s);
+#pragma unroll
+    for (int k = 0; k < R; ++k) update_one<OPT, f4>(th[k], g[k], m[k], v[k], a, s[k]);
   }
-  if (mine) {
-    st<f4>(a.m + moff, m);
-    if (OPT == HDET_ADAMW) st<f4>(a.v + moff, v);
+#pragma unroll
+  for (int k = 0; k < RM; ++k) {
+    const int r = w + k * waves;
+    const int64_t moff = SSTATE ? (i << 2) : (int64_t)r * a.stride + (i << 2);
+    if (ok && (R == 1 || r < n) && (!SSTATE || w == 0)) {
+      st_col(a.m + moff, m[k], cnt);
+      if (OPT == HDET_ADAMW) st_col(a.v + moff, v[k], cnt);
+    }
   }
   // Eq. 3 on the freshly updated parameters
-  if (CONV) th = exchange_mean(ex, th, w, grp, r, n, lane);
-  if (ok) {
-    st<f4>(a.theta + off, th);
-    if (a.shadow) st_bf16(a.shadow + off, th);
+  if (CONV) {
+    const f4 mean = exchange_mean<R>(ex, th, grp, w, waves, n, lane);
+#pragma unroll
+    for (int k = 0; k < R; ++k) th[k] = mean;
+  }
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    const int r = w + k * waves;
+    const int64_t off = (int64_t)r * a.stride + (i << 2);
+    if (ok && (R == 1 || r < n)) {
+      st_col(a.theta + off, th[k], cnt);
+      if (a.shadow) st_bf16_col(a.shadow + off, th[k], cnt);
+    }
   }
 }
 
 // Standalone converge (Eq. 3) in the same shape: 4 B read + 4 B written per replica-element.
+template <int R>
 __global__ __launch_bounds__(kMaxWaves * 64) void hdet_converge_wave_kernel(const hdet_converge_args a,
-                                                                            const int groups) {
-  __shared__ exchange_buf ex;
+                                                                            const int groups, const int waves) {
+  __shared__ exchange_buf<R> ex;
   const int n = a.n_replicas;
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int grp = w / n, r = w - grp * n;
+  const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int grp = R == 1 ? wid / waves : 0, w = wid - grp * waves;
   const int64_t i = ((int64_t)blockIdx.x * groups + grp) * 64 + lane;
-  const bool ok = i < (a.n_params >> 2);
-  const int64_t off = (int64_t)r * a.stride + (i << 2);
-  f4 th = splat<f4>(0.f);
-  if (ok) th = ld<f4>(a.theta + off);
-  th = exchange_mean(ex, th, w, grp, r, n, lane);
-  if (ok) {
-    st<f4>(a.theta + off, th);
-    if (a.shadow) st_bf16(a.shadow + off, th);
+  const int cnt = col_elements(a.n_params, i);
+  const bool ok = cnt > 0;
+  f4 th[R];
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    const int r = w + k * waves;
+    th[k] = splat<f4>(0.f);
+    if (ok && (R == 1 || r < n)) th[k] = ld_col(a.theta + (int64_t)r * a.stride + (i << 2), cnt);
+  }
+  const f4 mean = exchange_mean<R>(ex, th, grp, w, waves, n, lane);
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    const int r = w + k * waves;
+    const int64_t off = (int64_t)r * a.stride + (i << 2);
+    if (ok && (R == 1 || r < n)) {
+      st_col(a.theta + off, mean, cnt);
+      if (a.shadow) st_bf16_col(a.shadow + off, mean, cnt);
+    }
   }
 }
 
 // ---------------------------------------------------------------------------------------
-// loop kernel: one thread walks the replica axis of a column of width T (f4 or float).
+// loop kernel: one thread walks the replica axis of a column of width T (f4 or float).  Bound by the loads in flight: a
+// column's replicas are a chain of memory latencies unless several are requested at once (kAhead).
 // ---------------------------------------------------------------------------------------
+
 template <int OPT, bool SHARED, bool CONV, bool SSTATE, typename T>
 __device__ __forceinline__ void update_column(const hdet_update_args& a, const rep_scalars* s,
                                               int64_t col) {
@@ -248,11 +332,8 @@ __device__ __forceinline__ void update_column(const hdet_update_args& a, const r
   }
 }
 
-// tail_only: skip the 16-byte columns (another kernel has done them) and handle only the
-// P mod 4 trailing parameters.
 template <int OPT, bool SHARED, bool CONV, bool SSTATE>
-__global__ __launch_bounds__(kThreads) void hdet_update_loop_kernel(const hdet_update_args a,
-                                                                    const int tail_only) {
+__global__ __launch_bounds__(kThreads) void hdet_update_loop_kernel(const hdet_update_args a) {
   __shared__ rep_scalars s[HDET_MAX_REPLICAS];
   if ((int)threadIdx.x < a.n_replicas) {
     s[threadIdx.x] = replica_scalars(a, threadIdx.x);
@@ -260,43 +341,38 @@ __global__ __launch_bounds__(kThreads) void hdet_update_loop_kernel(const hdet_u
   }
   __syncthreads();
   const int64_t nvec = a.n_params >> 2;
-  if (!tail_only) {
-    const int64_t gstride = (int64_t)gridDim.x * kThreads;
-    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < nvec; i += gstride)
-      update_column<OPT, SHARED, CONV, SSTATE, f4>(a, s, i << 2);
-  }
-  if (blockIdx.x == gridDim.x - 1) {
+  const int64_t gstride = (int64_t)gridDim.x * kThreads;
+  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < nvec; i += gstride)
+    update_column<OPT, SHARED, CONV, SSTATE, f4>(a, s, i << 2);
+  if (blockIdx.x == gridDim.x - 1) {                        // the P mod 4 trailing parameters
     const int64_t col = (nvec << 2) + threadIdx.x;
     if (col < a.n_params) update_column<OPT, SHARED, CONV, SSTATE, float>(a, s, col);
   }
 }
 
 // Standalone converge (Eq. 3): 4 B read + 4 B written per replica-element.
-template <int NT, typename T>
+template <typename T>
 __device__ __forceinline__ void converge_column(const hdet_converge_args& a, int64_t col) {
   const int n = a.n_replicas;
   auto acc = widen(splat<T>(0.f));     // fp64 sum, one rounding to fp32 (see update_column)
-#pragma unroll
-  for (int q = 0; q < (NT ? NT : n); ++q) acc = acc + widen(ld<T>(a.theta + (int64_t)q * a.stride + col));
+#pragma unroll 4
+  for (int q = 0; q < n; ++q) acc = acc + widen(ld<T>(a.theta + (int64_t)q * a.stride + col));
   const T mean = narrow(acc * (1.0 / (double)n));
-#pragma unroll
-  for (int q = 0; q < (NT ? NT : n); ++q) {
+  for (int q = 0; q < n; ++q) {
     const int64_t off = (int64_t)q * a.stride + col;
     st<T>(a.theta + off, mean);
     if (a.shadow) st_bf16(a.shadow + off, mean);
   }
 }
 
-template <int NT>
 __global__ __launch_bounds__(kThreads) void hdet_converge_kernel(const hdet_converge_args a) {
   const int64_t nvec = a.n_params >> 2;
   const int64_t gstride = (int64_t)gridDim.x * kThreads;
-  if (!a.tail_only)
-    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < nvec; i += gstride)
-      converge_column<NT, f4>(a, i << 2);
+  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < nvec; i += gstride)
+    converge_column<f4>(a, i << 2);
   if (blockIdx.x == gridDim.x - 1) {
     const int64_t col = (nvec << 2) + threadIdx.x;
-    if (col < a.n_params) converge_column<NT, float>(a, col);
+    if (col < a.n_params) converge_column<float>(a, col);
   }
 }
 
@@ -320,38 +396,56 @@ int clamp_blocks(int64_t n_params, int blocks) {
   return (int)(need < blocks ? need : blocks);
 }
 
+// Shape of a wave-kernel launch: R replicas per wavefront, 512-thread blocks of several column groups while R = 1.
+struct wave_shape {
+  int r, groups, waves;
+  int64_t bx;
+};
+wave_shape wave_launch(int64_t n_params, int n) {
+  wave_shape w;
+  w.r = (n + kMaxWaves - 1) / kMaxWaves;
+  w.waves = (n + w.r - 1) / w.r;
+  w.groups = w.r == 1 && n < 8 ? 8 / n : 1;
+  const int64_t ncol = (n_params + 3) >> 2;        // the last one may hold fewer than four parameters
+  w.bx = (ncol + 64 * (int64_t)w.groups - 1) / (64 * (int64_t)w.groups);
+  return w;
+}
+
+// Beyond 16 replicas the loop kernel stays where its grid is resident in one piece and still fills the chip (2.5 to 4.5
+// blocks of 256 columns per CU, 0.65 to 1.2 million parameters): it then walks the planes one after the other, which the
+// memory side likes better than the wave kernel's N planes side by side.  us, one set of moments, loop / wave:
+//   N = 32:  P = 0.1e6 20 / 10,  0.3e6 64 / 26,  1e6 67 / 74,  2e6 161 / 145,  8e6 608 / 574
+//   N = 64:  P = 0.1e6 57 / 19,  0.3e6 125 / 52,  0.7e6 106 / 112,  2e6 333 / 311
+bool loop_walks_better(int64_t n_params, int n) {
+  const int64_t columns = n_params >> 2;
+  return n > kMaxWaves && 2 * columns >= 5 * 256 * kThreads && 2 * columns <= 9 * 256 * kThreads;
+}
+
 template <int OPT, bool SHARED, bool CONV, bool SSTATE = false>
 void launch_variant(const hdet_update_args& a, int variant, int blocks, hipStream_t stream) {
-  const int64_t nvec = a.n_params >> 2;
-  const bool tail = (a.n_params & 3) != 0;
   const int n = a.n_replicas;
   const bool exchange = SHARED || CONV;
-  bool columns_done = false;
-  if (variant == 0 && nvec > 0) {
-    // with one gradient plane for all replicas the wave kernel is taken as well: the replicas of a column share a
-    // block, so the plane comes from memory once
-    if (!exchange && !(a.grad_stride == 0 && n > 1 && n <= kMaxWaves)) {
-      const int64_t bx = (nvec + kThreads - 1) / kThreads;
-      if (bx <= 0x7fffffff) {
-        hipLaunchKernelGGL((hdet_update_plane_kernel<OPT>), dim3((unsigned)bx, n), dim3(kThreads), 0, stream, a);
-        columns_done = true;
-      }
-    } else if (n <= kMaxWaves) {
-      int groups = 8 / n;                    // aim at 512-thread blocks
-      if (groups < 1) groups = 1;
-      const int64_t bx = (nvec + 64 * (int64_t)groups - 1) / (64 * (int64_t)groups);
-      if (bx <= 0x7fffffff) {
-        hipLaunchKernelGGL((hdet_update_wave_kernel<OPT, SHARED, CONV, SSTATE>), dim3((unsigned)bx), dim3(64 * groups * n), 0,
-                           stream, a, groups);
-        columns_done = true;
-      }
+  // with one gradient plane for all replicas the wave kernel is taken as well: the replicas of a column share a
+  // block, so the plane comes from memory once
+  if (variant == 0 && !exchange && !(a.grad_stride == 0 && n > 1 && n <= kMaxWaves)) {
+    const int64_t bx = (((a.n_params + 3) >> 2) + kThreads - 1) / kThreads;
+    if (bx <= 0x7fffffff) {
+      hipLaunchKernelGGL((hdet_update_plane_kernel<OPT>), dim3((unsigned)bx, n), dim3(kThreads), 0, stream, a);
+      return;
+    }
+  } else if (variant == 0 && !loop_walks_better(a.n_params, n)) {
+    const wave_shape w = wave_launch(a.n_params, n);
+    if (w.bx <= 0x7fffffff) {
+      const dim3 grid((unsigned)w.bx), block(64 * w.groups * w.waves);
+      if (w.r == 1) hipLaunchKernelGGL((hdet_update_wave_kernel<OPT, SHARED, CONV, SSTATE, 1>), grid, block, 0, stream, a, w.groups, w.waves);
+      else if (w.r == 2) hipLaunchKernelGGL((hdet_update_wave_kernel<OPT, SHARED, CONV, SSTATE, 2>), grid, block, 0, stream, a, w.groups, w.waves);
+      else if (w.r == 3) hipLaunchKernelGGL((hdet_update_wave_kernel<OPT, SHARED, CONV, SSTATE, 3>), grid, block, 0, stream, a, w.groups, w.waves);
+      else hipLaunchKernelGGL((hdet_update_wave_kernel<OPT, SHARED, CONV, SSTATE, 4>), grid, block, 0, stream, a, w.groups, w.waves);
+      return;
     }
   }
-  if (!columns_done)
-    hipLaunchKernelGGL((hdet_update_loop_kernel<OPT, SHARED, CONV, SSTATE>), dim3(clamp_blocks(a.n_params, blocks)),
-                       dim3(kThreads), 0, stream, a, 0);
-  else if (tail)
-    hipLaunchKernelGGL((hdet_update_loop_kernel<OPT, SHARED, CONV, SSTATE>), dim3(1), dim3(kThreads), 0, stream, a, 1);
+  hipLaunchKernelGGL((hdet_update_loop_kernel<OPT, SHARED, CONV, SSTATE>), dim3(clamp_blocks(a.n_params, blocks)),
+                     dim3(kThreads), 0, stream, a);
 }
 
 template <int OPT>
@@ -379,23 +473,16 @@ hipError_t hdet_launch_update(const hdet_update_args& a, int optimizer, bool sha
 }
 
 hipError_t hdet_launch_converge(const hdet_converge_args& a, int variant, int blocks, hipStream_t stream) {
-  const int64_t nvec = a.n_params >> 2;
-  const int n = a.n_replicas;
-  if (variant == 0 && nvec > 0 && n <= kMaxWaves) {
-    int groups = 8 / n;
-    if (groups < 1) groups = 1;
-    const int64_t bx = (nvec + 64 * (int64_t)groups - 1) / (64 * (int64_t)groups);
-    if (bx <= 0x7fffffff) {
-      hipLaunchKernelGGL(hdet_converge_wave_kernel, dim3((unsigned)bx), dim3(64 * groups * n), 0, stream, a, groups);
-      if (a.n_params & 3) {                     // P mod 4 trailing parameters
-        hdet_converge_args t = a;
-        t.tail_only = 1;
-        hipLaunchKernelGGL(hdet_converge_kernel<0>, dim3(1), dim3(kThreads), 0, stream, t);
-      }
-      return hipGetLastError();
-    }
+  const wave_shape w = wave_launch(a.n_params, a.n_replicas);
+  if (variant == 0 && w.bx <= 0x7fffffff) {
+    const dim3 grid((unsigned)w.bx), block(64 * w.groups * w.waves);
+    if (w.r == 1) hipLaunchKernelGGL(hdet_converge_wave_kernel<1>, grid, block, 0, stream, a, w.groups, w.waves);
+    else if (w.r == 2) hipLaunchKernelGGL(hdet_converge_wave_kernel<2>, grid, block, 0, stream, a, w.groups, w.waves);
+    else if (w.r == 3) hipLaunchKernelGGL(hdet_converge_wave_kernel<3>, grid, block, 0, stream, a, w.groups, w.waves);
+    else hipLaunchKernelGGL(hdet_converge_wave_kernel<4>, grid, block, 0, stream, a, w.groups, w.waves);
+    return hipGetLastError();
   }
-  hipLaunchKernelGGL(hdet_converge_kernel<0>, dim3(clamp_blocks(a.n_params, blocks)), dim3(kThreads), 0, stream, a);
+  hipLaunchKernelGGL(hdet_converge_kernel, dim3(clamp_blocks(a.n_params, blocks)), dim3(kThreads), 0, stream, a);
   return hipGetLastError();
 }
 
