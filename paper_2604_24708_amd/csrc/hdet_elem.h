@@ -164,3 +164,19 @@ __device__ __forceinline__ hdet_philox4 hdet_philox4x32_10(uint32_t c0, uint32_t
   hdet_philox4 o = {{c0, c1, c2, c3}};
   return o;
 }
+
+// Mean of one replica's row losses in a fixed tree order, the step loss l(theta_r, B_r) of Algorithm 1, and its accumulation
+// into L_acc (Sec. 3.4).  One block of 256 threads; part: four doubles of LDS.
+template <typename CTRL>
+__device__ __forceinline__ void hdet_reduce_loss(const float* row_loss, int rows, CTRL* ctrl, int r, double* part) {
+  double s = 0.0;
+  for (int b = threadIdx.x; b < rows; b += 256) s += (double)row_loss[(int64_t)r * rows + b];
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const double mean = (part[0] + part[1] + part[2] + part[3]) / (double)rows;
+    ctrl->l_step[r] = (float)mean;
+    ctrl->l_acc[r] += mean;
+  }
+}

@@ -19,6 +19,10 @@
 //   512 x 256, K = 1024 (NT)  152 -> 17;   512 x 256, K = 4000 (NN)  270 -> 46;   4000 x 256, K = 512 (TN)  104 -> 46 (91 TFLOP/s);
 //   128 x 64, K = 64 (NT)     15 -> 4;     128 x 64, K = 512 (NN)    80 -> 6.
 
+#include <algorithm>
+#include <type_traits>
+
+#include "hdet_elem.h"
 #include "hdet_internal.h"
 
 namespace {
@@ -57,22 +61,28 @@ __device__ __forceinline__ void load_tail(float (&v)[4], const float* base, int6
   }
 }
 
-// Wave tile (32 WTM) x (32 WTN); WM x WN x WK wavefronts; U: 8-k steps loaded ahead.
-template <bool AK, bool BK, int EPI, int WTM, int WTN, int WM, int WN, int WK, int U>
-__global__ __launch_bounds__(64 * WM * WN * WK) void sgemm_kernel(const hdet_sgemm_args g) {
+// operand orders: forward (NT: both contiguous along k), dgrad (NN: A along k), wgrad (TN: neither)
+enum { kNT = 0, kNN = 1, kTN = 2 };
+
+constexpr int kThreads = 256;      // every tile configuration is four wavefronts: they can share a launch
+
+// One block's tile, tile index t of tx x ty x batch.  Wave tile (32 WTM) x (32 WTN); WM x WN x WK wavefronts; U: 8-k steps
+// loaded ahead.  `part`: the block's LDS (lds_floats).
+template <int WTM, int WTN, int WM, int WN, int WK> constexpr int lds_floats() { return WM * WN * WK * WTM * WTN * 16 * 64; }
+
+template <bool AK, bool BK, int WTM, int WTN, int WM, int WN, int WK, int U>
+__device__ __forceinline__ void sgemm_tile(const hdet_sgemm_args& g, int epi, unsigned t, unsigned tx, unsigned ty, unsigned total, float* part) {
   constexpr int NW = WTM * WTN * 16;                                // accumulator registers
-  static_assert(WK == 1 || NW % WK == 0, "the wavefronts of a K split share the tile's registers evenly");
-  __shared__ float part[WK > 1 ? WM * WN * WK * NW * 64 : 1];
+  static_assert(WK > 1 && NW % WK == 0, "the wavefronts of a K split share the tile's registers evenly");
+  static_assert(WM * WN * WK * 64 == kThreads, "four wavefronts");
   // launch order -> tile: XCD x (own L2; launch index mod 8) takes the x-th of eight contiguous ranges of tiles
   unsigned bx, by, bz;
   {
-    const unsigned total = gridDim.x * gridDim.y * gridDim.z;
-    unsigned t = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
     const unsigned x = t & 7u, rem = total & 7u;
     t = x * (total >> 3) + (x < rem ? x : rem) + (t >> 3);
-    bx = t % gridDim.x;
-    by = (t / gridDim.x) % gridDim.y;
-    bz = t / (gridDim.x * gridDim.y);
+    bx = t % tx;
+    by = (t / tx) % ty;
+    bz = t / (tx * ty);
   }
   const hdet_batch_index bi = hdet_split_batch(bz, g.n1, g.n2);
   const int z = bi.z0;                                              // replica: bias and mask are per replica
@@ -83,6 +93,11 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void sgemm_kernel(const hdet_sge
   const int wk = w % WK, wmn = w / WK;
   const int m0 = (by * WM + wmn / WN) * (32 * WTM), n0 = (bx * WN + wmn % WN) * (32 * WTN);
   const bool active = m0 < g.m && n0 < g.n;                         // uniform over the wavefront
+  const bool block_sums = !AK && g.rowsum && bx == 0;               // the wavefronts of the first tile column also add up A's rows
+  const bool sums = block_sums && n0 == 0 && active;
+  float rs[WTM];
+#pragma unroll
+  for (int i = 0; i < WTM; ++i) rs[i] = 0.f;
   const int64_t lda = AK ? g.a_rs : g.a_cs, ldb = BK ? g.b_cs : g.b_rs;
 
   f16v acc[WTM][WTN];
@@ -125,6 +140,10 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void sgemm_kernel(const hdet_sge
       }
     };
     auto step = [&](float (&av)[WTM][4], float (&bv)[WTN][4]) {
+      if (!AK && sums) {
+#pragma unroll
+        for (int i = 0; i < WTM; ++i) rs[i] += (av[i][0] + av[i][1]) + (av[i][2] + av[i][3]);
+      }
 #pragma unroll
       for (int q = 0; q < 4; ++q)
 #pragma unroll
@@ -159,53 +178,96 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void sgemm_kernel(const hdet_sge
   }
 
   float* C = g.c + hdet_batch_offset(bi, g.c_s);
-  // accumulator register e of lane l is C(row, col) with row = (e / 4) * 8 + (l / 32) * 4 + e % 4, col = l % 32 in its block
-  auto put = [&](int i, int j, int e, float v) {
-    const int row = m0 + 32 * i + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3), col = n0 + 32 * j + (lane & 31);
-    if (row >= g.m || col >= g.n) return;
-    if (EPI == HDET_SEPI_BIAS || EPI == HDET_SEPI_BIAS_RELU) v += g.bias[(int64_t)z * g.bias_bs + col];
-    if (EPI == HDET_SEPI_BIAS_RELU) v = v > 0.f ? v : 0.f;
-    if (EPI == HDET_SEPI_MASK) v = g.mask[(int64_t)z * g.mask_bs + (int64_t)row * g.mask_rs + col] > 0.f ? v : 0.f;
-    C[(int64_t)row * g.c_rs + col] = v;
-  };
-  if (WK == 1) {
-    if (!active) return;
+  float* mine = part + (wmn * WK + wk) * (NW * 64) + lane;          // [register][lane] of this wavefront's partial tile
 #pragma unroll
-    for (int i = 0; i < WTM; ++i)
+  for (int i = 0; i < WTM; ++i)
 #pragma unroll
-      for (int j = 0; j < WTN; ++j)
+    for (int j = 0; j < WTN; ++j)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) put(i, j, e, acc[i][j][e]);
-  } else {
-    float* mine = part + (wmn * WK + wk) * (NW * 64) + lane;        // [register][lane] of this wavefront's partial tile
+      for (int e = 0; e < 16; ++e) mine[((i * WTN + j) * 16 + e) * 64] = acc[i][j][e];
+  __syncthreads();
+  const float* all = part + wmn * WK * (NW * 64) + lane;
+  // accumulator register e of lane l is C(row, col) with row = (e / 4) * 8 + (l / 32) * 4 + e % 4, col = l % 32 in its block;
+  // the epilogue is uniform over the launch
+  auto finish = [&](auto kind) {
+    constexpr int EPI = decltype(kind)::value;
+    constexpr bool kBias = EPI == HDET_SEPI_BIAS || EPI == HDET_SEPI_BIAS_RELU || EPI == HDET_SEPI_BIAS_GELU || EPI == HDET_SEPI_BIAS_RESID;
+    constexpr bool kMask = EPI == HDET_SEPI_MASK || EPI == HDET_SEPI_BIAS_RESID || EPI == HDET_SEPI_GELUGRAD;
+    constexpr int CH = NW / WK < 8 ? NW / WK : 8;                   // elements whose second operand is requested together
 #pragma unroll
-    for (int i = 0; i < WTM; ++i)
+    for (int t0 = 0; t0 < NW / WK; t0 += CH) {
+      float x[CH], bias[CH];
 #pragma unroll
-      for (int j = 0; j < WTN; ++j)
+      for (int u = 0; u < CH; ++u) {
+        const int q = wk * (NW / WK) + t0 + u, e = q % 16;
+        const int row = m0 + 32 * (q / (16 * WTN)) + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3), col = n0 + 32 * ((q / 16) % WTN) + (lane & 31);
+        if (row < g.m && col < g.n) {
+          if (kBias) bias[u] = g.bias[(int64_t)z * g.bias_bs + col];
+          if (kMask) x[u] = g.mask[(int64_t)z * g.mask_bs + (int64_t)row * g.mask_rs + col];
+        }
+      }
 #pragma unroll
-        for (int e = 0; e < 16; ++e) mine[((i * WTN + j) * 16 + e) * 64] = acc[i][j][e];
-    __syncthreads();
-    if (!active) return;
-    const float* all = part + wmn * WK * (NW * 64) + lane;
+      for (int u = 0; u < CH; ++u) {
+        const int q = wk * (NW / WK) + t0 + u, e = q % 16;
+        float v = all[q * 64];
 #pragma unroll
-    for (int t = 0; t < NW / WK; ++t) {
-      const int q = wk * (NW / WK) + t;
-      float v = all[q * 64];
-#pragma unroll
-      for (int p = 1; p < WK; ++p) v += all[(p * NW + q) * 64];
-      put(q / (16 * WTN), (q / 16) % WTN, q % 16, v);
+        for (int p = 1; p < WK; ++p) v += all[(p * NW + q) * 64];
+        const int row = m0 + 32 * (q / (16 * WTN)) + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3), col = n0 + 32 * ((q / 16) % WTN) + (lane & 31);
+        if (row >= g.m || col >= g.n) continue;
+        const int64_t at = (int64_t)row * g.c_rs + col;
+        if (kBias) v += bias[u];
+        if (EPI == HDET_SEPI_BIAS_RELU) v = v > 0.f ? v : 0.f;
+        if (EPI == HDET_SEPI_MASK) v = x[u] > 0.f ? v : 0.f;
+        if (EPI == HDET_SEPI_BIAS_RESID) v += x[u];
+        if (EPI == HDET_SEPI_GELUGRAD) v *= hdet_gelu_tanh_grad(x[u]);
+        C[at] = v;
+        if (EPI == HDET_SEPI_BIAS_GELU) (g.c2 + hdet_batch_offset(bi, g.c_s))[at] = hdet_gelu_tanh(v);
+      }
     }
+  };
+  if (active) switch (epi) {
+    case HDET_SEPI_NONE: finish(std::integral_constant<int, HDET_SEPI_NONE>{}); break;
+    case HDET_SEPI_BIAS: if (AK && BK) finish(std::integral_constant<int, HDET_SEPI_BIAS>{}); break;
+    case HDET_SEPI_BIAS_RELU: if (AK && BK) finish(std::integral_constant<int, HDET_SEPI_BIAS_RELU>{}); break;
+    case HDET_SEPI_BIAS_GELU: if (AK && BK) finish(std::integral_constant<int, HDET_SEPI_BIAS_GELU>{}); break;
+    case HDET_SEPI_BIAS_RESID: if (AK && BK) finish(std::integral_constant<int, HDET_SEPI_BIAS_RESID>{}); break;
+    case HDET_SEPI_MASK: if (AK && !BK) finish(std::integral_constant<int, HDET_SEPI_MASK>{}); break;
+    case HDET_SEPI_GELUGRAD: if (AK && !BK) finish(std::integral_constant<int, HDET_SEPI_GELUGRAD>{}); break;
+  }
+  if (block_sums) {
+    float* rpart = part + wmn * WK * (WTM * 32);                    // [K part][row] of this wavefront's row sums
+    __syncthreads();
+    if (sums) {
+#pragma unroll
+      for (int i = 0; i < WTM; ++i) {
+        const float v = rs[i] + __shfl_xor(rs[i], 32);              // the two halves of a step's k
+        if (lane < 32) rpart[wk * (WTM * 32) + 32 * i + lane] = v;
+      }
+    }
+    __syncthreads();
+    if (sums)
+      for (int r = wk * 64 + lane; r < WTM * 32; r += WK * 64) {
+        if (m0 + r >= g.m) continue;
+        float v = rpart[r];
+#pragma unroll
+        for (int p = 1; p < WK; ++p) v += rpart[p * (WTM * 32) + r];
+        g.rowsum[(int64_t)z * g.rowsum_bs + m0 + r] = v;
+      }
   }
 }
 
-// operand orders: forward (NT: both contiguous along k), dgrad (NN: A along k), wgrad (TN: neither)
-enum { kNT = 0, kNN = 1, kTN = 2 };
+template <int FORM, int WTM, int WTN, int WM, int WN, int WK, int U>
+__global__ __launch_bounds__(kThreads) void sgemm_kernel(const hdet_sgemm_args g, int epi, unsigned tx, unsigned ty) {
+  __shared__ float part[lds_floats<WTM, WTN, WM, WN, WK>()];
+  sgemm_tile<FORM != kTN, FORM == kNT, WTM, WTN, WM, WN, WK, U>(g, epi, blockIdx.x, tx, ty, gridDim.x, part);
+}
 
-template <int FORM, int EPI, int WTM, int WTN, int WM, int WN, int WK, int U>
-void launch_cfg(const hdet_sgemm_args& g, int batch, hipStream_t s) {
-  const int tm = 32 * WTM * WM, tn = 32 * WTN * WN;
-  const dim3 grid((g.n + tn - 1) / tn, (g.m + tm - 1) / tm, batch);
-  hipLaunchKernelGGL((sgemm_kernel<FORM != kTN, FORM == kNT, EPI, WTM, WTN, WM, WN, WK, U>), grid, dim3(64 * WM * WN * WK), 0, s, g);
+constexpr int64_t kMaxBlocks = 0xffffff;      // blocks of 256 threads in a grid of less than 2^32 threads
+struct tiles { unsigned x, y, total; };
+template <int WTM, int WTN, int WM, int WN>
+tiles tile_grid(const hdet_sgemm_args& g, int batch) {
+  const unsigned x = (g.n + 32 * WTN * WN - 1) / (32 * WTN * WN), y = (g.m + 32 * WTM * WM - 1) / (32 * WTM * WM);
+  return {x, y, x * y * (unsigned)batch};
 }
 
 // Tile and K split by the number of blocks a launch would have, b(tm x tn) = tiles over the whole batch, on 256 CUs
@@ -218,39 +280,124 @@ void launch_cfg(const hdet_sgemm_args& g, int batch, hipStream_t s) {
 //   more: 64 x 128, K in 2             512 x 1024, K = 256, 4 items: 18.0 | 64 x 64 24.6 | 64 x 32 27.2
 //   many, an operand contiguous along k: 64 x 64 with two steps in flight instead of four, whose smaller register count lets a
 //         CU hold more of them         4096 x 2048, K = 512, 8 items: 798 | 64 x 128 910 (wgrad: 914 | 64 x 128 588)
-template <int FORM, int EPI>
-void launch_form(const hdet_sgemm_args& g, int batch, hipStream_t s) {
-  auto blocks = [&](int tm, int tn) { return (int64_t)((g.m + tm - 1) / tm) * ((g.n + tn - 1) / tn) * batch; };
-  const int cus = hdet_compute_units();
-  const int64_t b32 = blocks(64, 32), b128 = blocks(64, 128);
-  if (b32 * 8 < (int64_t)cus * 5) launch_cfg<FORM, EPI, 1, 1, 1, 1, 4, 4>(g, batch, s);
-  else if (b32 <= cus) launch_cfg<FORM, EPI, 2, 1, 1, 1, 4, 4>(g, batch, s);
-  else if (blocks(64, 64) <= cus) launch_cfg<FORM, EPI, 2, 2, 1, 1, 4, 4>(g, batch, s);
-  else if (FORM == kTN || b128 <= 2 * (int64_t)cus) launch_cfg<FORM, EPI, 2, 2, 1, 2, 2, 4>(g, batch, s);
-  else launch_cfg<FORM, EPI, 2, 2, 1, 1, 4, 2>(g, batch, s);
+enum { kCfg32, kCfg64x32, kCfg64, kCfg64x128, kCfg64Light };
+int64_t count_blocks(const hdet_sgemm_args& g, int batch, int tm, int tn) {
+  return (int64_t)((g.m + tm - 1) / tm) * ((g.n + tn - 1) / tn) * batch;
+}
+template <typename F>
+int choose_cfg(F blocks, bool k_contiguous) {
+  const int64_t cus = hdet_compute_units();
+  if (blocks(64, 32) * 8 < cus * 5) return kCfg32;
+  if (blocks(64, 32) <= cus) return kCfg64x32;
+  if (blocks(64, 64) <= cus) return kCfg64;
+  if (!k_contiguous || blocks(64, 128) <= 2 * cus) return kCfg64x128;
+  return kCfg64Light;
+}
+#define HDET_SGEMM_SMALL(CALL)                     \
+  case kCfg32: CALL(1, 1, 1, 1, 4, 4); break;      \
+  case kCfg64x32: CALL(2, 1, 1, 1, 4, 4); break;
+#define HDET_SGEMM_LARGE(CALL)                     \
+  case kCfg64: CALL(2, 2, 1, 1, 4, 4); break;      \
+  case kCfg64x128: CALL(2, 2, 1, 2, 2, 4); break;  \
+  case kCfg64Light: CALL(2, 2, 1, 1, 4, 2); break;
+
+// Two products of few blocks and the loss reduction: blocks [0, wt) form the weight gradient, [wt, wt + ot) the other product
+// (the one with the longer contraction comes first), the rest reduce a replica's loss each.  Small layers' backward is bound by
+// launches and by CUs left idle, and its two products and the bias gradient need nothing of each other.  Each product keeps the
+// tile it would have alone.  Only the two small tiles share a launch: with the larger ones a launch fills the chip by itself,
+// and one kernel that holds them all needs 284 registers, a wavefront per SIMD (2-layer d = 256 transformer 962 to 993 us a
+// step with larger tiles in pairs, 830 without).
+// Per training step: MLP 64-128-10, batch 32, 4 replicas 39 -> 34 us; 2-layer d = 64 transformer 350 -> 261,
+// d = 256 890 -> 868 (bias gradients, GELU and residual sums without passes of their own).
+struct pair_grid { unsigned wx, wy, wt, ox, oy, ot; int wgrad_first, wcfg, ocfg; };
+template <bool NT>
+__global__ __launch_bounds__(kThreads) void sgemm_pair_kernel(const hdet_sgemm_args w, const hdet_sgemm_args o, int epi, const pair_grid pg,
+                                                             const hdet_loss_args loss) {
+  extern __shared__ float part[];
+  unsigned t = blockIdx.x;
+  if (t >= pg.wt + pg.ot) {
+    hdet_reduce_loss(loss.row_loss, loss.rows, loss.ctrl, (int)(t - pg.wt - pg.ot), reinterpret_cast<double*>(part));
+    return;
+  }
+  const unsigned first = pg.wgrad_first ? pg.wt : pg.ot;
+  const bool wgrad = (t < first) == (pg.wgrad_first != 0);
+  if (t >= first) t -= first;
+#define WGRAD(WTM, WTN, WM, WN, WK, U) sgemm_tile<false, false, WTM, WTN, WM, WN, WK, U>(w, HDET_SEPI_NONE, t, pg.wx, pg.wy, pg.wt, part)
+#define OTHER(WTM, WTN, WM, WN, WK, U) sgemm_tile<true, NT, WTM, WTN, WM, WN, WK, U>(o, epi, t, pg.ox, pg.oy, pg.ot, part)
+  if (wgrad) switch (pg.wcfg) { HDET_SGEMM_SMALL(WGRAD) }
+  else switch (pg.ocfg) { HDET_SGEMM_SMALL(OTHER) }
+#undef WGRAD
+#undef OTHER
+}
+
+template <int FORM>
+hipError_t launch_form(const hdet_sgemm_args& g, int epi, int batch, hipStream_t s) {
+  const int cfg = choose_cfg([&](int tm, int tn) { return count_blocks(g, batch, tm, tn); }, FORM != kTN);
+  if (count_blocks(g, batch, 64, 64) > kMaxBlocks) return hipErrorInvalidValue;
+#define CALL(WTM, WTN, WM, WN, WK, U)                                                                                            \
+  {                                                                                                                              \
+    const tiles t = tile_grid<WTM, WTN, WM, WN>(g, batch);                                                                       \
+    hipLaunchKernelGGL((sgemm_kernel<FORM, WTM, WTN, WM, WN, WK, U>), dim3(t.total), dim3(kThreads), 0, s, g, epi, t.x, t.y);    \
+  }
+  switch (cfg) { HDET_SGEMM_SMALL(CALL) HDET_SGEMM_LARGE(CALL) }
+#undef CALL
+  return hipGetLastError();
+}
+
+template <bool NT>
+hipError_t launch_pair(const hdet_sgemm_args& w, int wb, int wcfg, const hdet_sgemm_args& o, int epi, int ob, int ocfg,
+                       const hdet_loss_args& loss, hipStream_t s) {
+  tiles tw = {}, to = {};                                           // ob = 0: no other product, to.total stays 0
+  int lds = 64;                                                     // the loss reduction's
+#define WGRAD(WTM, WTN, WM, WN, WK, U) { tw = tile_grid<WTM, WTN, WM, WN>(w, wb); lds = std::max(lds, 4 * lds_floats<WTM, WTN, WM, WN, WK>()); }
+#define OTHER(WTM, WTN, WM, WN, WK, U) { to = tile_grid<WTM, WTN, WM, WN>(o, ob); lds = std::max(lds, 4 * lds_floats<WTM, WTN, WM, WN, WK>()); }
+  switch (wcfg) { HDET_SGEMM_SMALL(WGRAD) }
+  if (ob) switch (ocfg) { HDET_SGEMM_SMALL(OTHER) }
+#undef WGRAD
+#undef OTHER
+  const pair_grid pg = {tw.x, tw.y, tw.total, to.x, to.y, to.total, w.k >= o.k, wcfg, ocfg};
+  hipLaunchKernelGGL(sgemm_pair_kernel<NT>, dim3(tw.total + to.total + (unsigned)loss.n_replicas), dim3(kThreads), lds, s, w, o, epi, pg, loss);
+  return hipGetLastError();
+}
+
+hdet_sgemm_args with_batch(const hdet_sgemm_args& g_in) {
+  hdet_sgemm_args g = g_in;
+  if (g.n1 < 1) g.n1 = 1;
+  if (g.n2 < 1) g.n2 = 1;
+  return g;
 }
 
 }  // namespace
 
 hipError_t hdet_launch_sgemm(const hdet_sgemm_args& g_in, int epi, int batch, hipStream_t s) {
-  hdet_sgemm_args g = g_in;
-  if (g.n1 < 1) g.n1 = 1;
-  if (g.n2 < 1) g.n2 = 1;
+  const hdet_sgemm_args g = with_batch(g_in);
   // which axis of an operand is contiguous (an operand of one row or column may be read either way)
   const bool ak = g.a_cs == 1, bk = g.b_rs == 1 && (ak || g.b_cs != 1);
   if ((!ak && g.a_rs != 1) || (!bk && g.b_cs != 1) || (!ak && bk)) return hipErrorInvalidValue;
-  if (epi == HDET_SEPI_NONE) {
-    if (ak && bk) launch_form<kNT, HDET_SEPI_NONE>(g, batch, s);
-    else if (ak) launch_form<kNN, HDET_SEPI_NONE>(g, batch, s);
-    else launch_form<kTN, HDET_SEPI_NONE>(g, batch, s);
-  } else if (epi == HDET_SEPI_BIAS && ak && bk) {
-    launch_form<kNT, HDET_SEPI_BIAS>(g, batch, s);
-  } else if (epi == HDET_SEPI_BIAS_RELU && ak && bk) {
-    launch_form<kNT, HDET_SEPI_BIAS_RELU>(g, batch, s);
-  } else if (epi == HDET_SEPI_MASK && ak && g.b_cs == 1) {
-    launch_form<kNN, HDET_SEPI_MASK>(g, batch, s);
-  } else {
-    return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
+  const bool nt = epi == HDET_SEPI_BIAS || epi == HDET_SEPI_BIAS_RELU || epi == HDET_SEPI_BIAS_GELU || epi == HDET_SEPI_BIAS_RESID;
+  const bool nn = epi == HDET_SEPI_MASK || epi == HDET_SEPI_GELUGRAD;
+  if (!nt && !nn && epi != HDET_SEPI_NONE) return hipErrorInvalidValue;
+  if (nn) return ak && g.b_cs == 1 ? launch_form<kNN>(g, epi, batch, s) : hipErrorInvalidValue;
+  if (ak && bk) return launch_form<kNT>(g, epi, batch, s);
+  if (nt) return hipErrorInvalidValue;
+  return ak ? launch_form<kNN>(g, epi, batch, s) : launch_form<kTN>(g, epi, batch, s);
+}
+
+hipError_t hdet_launch_sgemm_pair(const hdet_sgemm_args& wgrad, int wgrad_batch, const hdet_sgemm_args* other, bool other_nt, int epi,
+                                  int other_batch, const hdet_loss_args* loss, hipStream_t s) {
+  const hdet_sgemm_args w = with_batch(wgrad), o = other ? with_batch(*other) : hdet_sgemm_args{};
+  const hdet_loss_args l = loss ? *loss : hdet_loss_args{nullptr, 0, nullptr, 0};
+  if (w.a_rs != 1 || w.b_cs != 1) return hipErrorInvalidValue;
+  if (other && (o.a_cs != 1 || (other_nt ? o.b_rs != 1 : o.b_cs != 1))) return hipErrorInvalidValue;
+  const bool fits = epi == HDET_SEPI_NONE || (!other_nt && (epi == HDET_SEPI_MASK || epi == HDET_SEPI_GELUGRAD));
+  if (!fits) return hipErrorInvalidValue;
+  const int ob = other ? other_batch : 0;
+  const int wcfg = choose_cfg([&](int tm, int tn) { return count_blocks(w, wgrad_batch, tm, tn); }, false);
+  const int ocfg = ob ? choose_cfg([&](int tm, int tn) { return count_blocks(o, ob, tm, tn); }, true) : kCfg32;
+  if (wcfg <= kCfg64x32 && ocfg <= kCfg64x32)
+    return other_nt ? launch_pair<true>(w, wgrad_batch, wcfg, o, epi, ob, ocfg, l, s) : launch_pair<false>(w, wgrad_batch, wcfg, o, epi, ob, ocfg, l, s);
+  if (hipError_t e = launch_form<kTN>(w, HDET_SEPI_NONE, wgrad_batch, s)) return e;
+  if (ob)
+    if (hipError_t e = other_nt ? launch_form<kNT>(o, epi, ob, s) : launch_form<kNN>(o, epi, ob, s)) return e;
+  return loss ? hdet_launch_loss_reduce(l.row_loss, l.rows, l.ctrl, l.n_replicas, s) : hipSuccess;
 }

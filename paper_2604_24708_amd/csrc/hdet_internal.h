@@ -131,9 +131,13 @@ __host__ __device__ __forceinline__ int64_t hdet_batch_offset(const hdet_batch_i
 }
 
 // fp32 GEMM with element strides (hdet_gemm_f32.hip): C(m,n) = sum_k A(m,k) B(k,n)
-enum { HDET_SEPI_NONE = 0, HDET_SEPI_BIAS = 1, HDET_SEPI_BIAS_RELU = 2, HDET_SEPI_MASK = 3 };
+enum { HDET_SEPI_NONE = 0, HDET_SEPI_BIAS = 1, HDET_SEPI_BIAS_RELU = 2, HDET_SEPI_MASK = 3,
+       HDET_SEPI_BIAS_GELU = 4,      // c = acc + bias, c2 = gelu(c)
+       HDET_SEPI_BIAS_RESID = 5,     // c = (acc + bias) + mask: a Linear layer added to its residual stream `mask`
+       HDET_SEPI_GELUGRAD = 6 };     // c = acc * gelu'(mask): gradient through the GELU at pre-activation `mask`
 struct hdet_sgemm_args {
   const float* a; const float* b; float* c;
+  float* c2;                    // second output in c's layout (HDET_SEPI_BIAS_GELU)
   int m, n, k;
   int n1, n2;                   // batch split (0 is read as 1)
   int64_t a_rs, a_cs, a_s[3];   // A(m,k) = a[batch + m*a_rs + k*a_cs]
@@ -141,8 +145,17 @@ struct hdet_sgemm_args {
   int64_t c_rs, c_s[3];         // C(m,n) = c[batch + m*c_rs + n]
   const float* bias; int64_t bias_bs;            // + bias[z0*bias_bs + n]
   const float* mask; int64_t mask_rs, mask_bs;   // * (mask[z0*mask_bs + m*mask_rs + n] > 0)
+  float* rowsum; int64_t rowsum_bs;              // weight gradients: rowsum[z0*rowsum_bs + m] = sum_k A(m,k), or null
 };
+// Per-replica mean of the row losses, for the launch that carries it (see hdet_launch_sgemm_pair)
+struct hdet_loss_args { const float* row_loss; int rows; hdet_ctrl* ctrl; int n_replicas; };
 hipError_t hdet_launch_sgemm(const hdet_sgemm_args& g, int epi, int batch, hipStream_t stream);
+hipError_t hdet_launch_loss_reduce(const float* row_loss, int rows, hdet_ctrl* ctrl, int n_replicas, hipStream_t s);
+// Two independent products, in one launch where both are small: a weight gradient (neither operand contiguous along k; its row sums are the bias
+// gradient) and, unless `other` is null, one whose A is contiguous along k -- and B too with other_nt --, with epilogue
+// `epi`; and, unless null, the loss reduction.
+hipError_t hdet_launch_sgemm_pair(const hdet_sgemm_args& wgrad, int wgrad_batch, const hdet_sgemm_args* other, bool other_nt, int epi,
+                                  int other_batch, const hdet_loss_args* loss, hipStream_t stream);
 
 // bf16 GEMM on the matrix cores (hdet_gemm_bf16.hip)
 enum { HDET_EPI_F32 = 0, HDET_EPI_BIAS_F32 = 1, HDET_EPI_BIAS_RELU_BF16 = 2, HDET_EPI_MASK_BF16 = 3,

@@ -234,21 +234,10 @@ __global__ __launch_bounds__(BS, SUMS ? 2 : 4) void xent_row_kernel(const float*
   }
 }
 
-// Per-replica mean of the row losses in a fixed tree order (one block per replica), the
-// step loss l(theta_r, B_r) of Algorithm 1, and its accumulation into L_acc (Sec. 3.4).
+// one block per replica (see hdet_reduce_loss)
 __global__ __launch_bounds__(256) void loss_reduce_kernel(const float* row_loss, int rows, hdet_ctrl* ctrl) {
   __shared__ double part[4];
-  const int r = blockIdx.x;
-  double s = 0.0;
-  for (int b = threadIdx.x; b < rows; b += 256) s += (double)row_loss[(int64_t)r * rows + b];
-  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const double mean = (part[0] + part[1] + part[2] + part[3]) / (double)rows;
-    ctrl->l_step[r] = (float)mean;
-    ctrl->l_acc[r] += mean;
-  }
+  hdet_reduce_loss(row_loss, rows, ctrl, blockIdx.x, part);
 }
 
 }  // namespace
@@ -390,29 +379,27 @@ static hipError_t forward_backward_f32(hdet_mlp_plan* p, const void* x, const in
   // loss and dlogits
   float* dz = (float*)p->dz_a; float* dz_next = (float*)p->dz_b;
   if (hipError_t e = hdet_launch_xent(false, p->logits, y, B, w[L], dz, p->row_loss, N, ctrl, p->ls_channel, s, nullptr, 0, B)) return e;
-  hipLaunchKernelGGL(loss_reduce_kernel, dim3(N), dim3(256), 0, s, p->row_loss, B, ctrl);
-  // backward
+  // backward: a layer's weight gradient, bias gradient and input gradient in one launch, the last layer's with the loss
+  const hdet_loss_args loss = {p->row_loss, B, ctrl, N};
   for (int i = L - 1; i >= 0; --i) {
-    // dW = dZ^T X
+    // dW = dZ^T X, db = column sums of dZ
     hdet_sgemm_args g = {};
     g.a = dz; g.a_rs = 1; g.a_cs = w[i + 1]; g.a_s[0] = (int64_t)B * w[i + 1];     // A(o,b) = dZ[b][o]
     g.b = (const float*)p->act[i]; g.b_rs = w[i]; g.b_cs = 1; g.b_s[0] = (int64_t)B * w[i];   // B(b,k) = X[b][k]
     g.c = grads + p->w_off[i]; g.c_rs = w[i]; g.c_s[0] = ps;
     g.m = w[i + 1]; g.n = w[i]; g.k = shared ? N * B : B;
-    if (hipError_t e = hdet_launch_sgemm(g, HDET_SEPI_NONE, shared ? 1 : N, s)) return e;
-    hipLaunchKernelGGL(bias_grad_kernel<float>, dim3((w[i + 1] + 63) / 64, shared ? 1 : N), dim3(1024), 0, s, dz, shared ? N * B : B, w[i + 1],
-                       (int64_t)B * w[i + 1], grads + p->b_off[i], ps);
+    g.rowsum = grads + p->b_off[i]; g.rowsum_bs = ps;
+    // dX = dZ W, masked by the ReLU of the layer below
+    hdet_sgemm_args d = {};
     if (i > 0) {
-      // dX = dZ W, masked by the ReLU of the layer below
-      hdet_sgemm_args d = {};
       d.a = dz; d.a_rs = w[i + 1]; d.a_cs = 1; d.a_s[0] = (int64_t)B * w[i + 1];
       d.b = theta + p->w_off[i]; d.b_rs = w[i]; d.b_cs = 1; d.b_s[0] = ps;         // B(o,k) = W[o][k]
       d.c = dz_next; d.c_rs = w[i]; d.c_s[0] = (int64_t)B * w[i];
       d.m = B; d.n = w[i]; d.k = w[i + 1];
       d.mask = (const float*)p->act[i]; d.mask_rs = w[i]; d.mask_bs = (int64_t)B * w[i];
-      if (hipError_t e = hdet_launch_sgemm(d, HDET_SEPI_MASK, N, s)) return e;
-      float* t = dz; dz = dz_next; dz_next = t;
     }
+    if (hipError_t e = hdet_launch_sgemm_pair(g, shared ? 1 : N, i > 0 ? &d : nullptr, false, HDET_SEPI_MASK, N, i == L - 1 ? &loss : nullptr, s)) return e;
+    float* t = dz; dz = dz_next; dz_next = t;
   }
   return hipGetLastError();
 }

@@ -808,7 +808,6 @@ hipError_t hdet_launch_xent(bool bf16, const float* logits, const int32_t* label
                             float* row_loss, int n_replicas, const hdet_ctrl* ctrl, int ls_channel, hipStream_t s,
                             float* colsum = nullptr, int rows_per_block = 0, int grad_rows = 0);
 bool hdet_xent_wide(int classes);
-hipError_t hdet_launch_loss_reduce(const float* row_loss, int rows, hdet_ctrl* ctrl, int n_replicas, hipStream_t s);
 
 // Rows per block of the wide-row loss kernel when it also forms stage 1 of the head bias gradient: enough rows
 // to make the partial sums few, as long as about four blocks per compute unit remain; 0 = a separate pass does it.
@@ -975,6 +974,7 @@ hdet_tf_plan* hdet_tf_create(const hdet_config& cfg, const hdet_buffers& buf, in
   // produces that bias gradient's input (and, when it is of the fused kind, stage 1 of its column sum); -1 otherwise
   auto add_job = [&](int cols, int mode, int64_t out_off, int64_t out2_off, int64_t producer_g = -1, int chunks = 0) {
     if (cols % 8 != 0) return;                       // such widths take the single-stage kernel
+    if (!p->bf16 && mode == 0) return;               // fp32 biases come with the weight gradients' products
     const bool by_ln = (mode == 1 && hdet_tf_ln_fused(p, out_off)) || (producer_g >= 0 && hdet_tf_ln_fused(p, producer_g));
     const int nchunks = chunks ? chunks : by_ln ? (p->M + kLnRows - 1) / kLnRows : p->nrc;
     colsum_job j = {part_off, out_off, out2_off, cols, mode, first_block, nchunks};
@@ -1157,6 +1157,17 @@ struct mat { const void* p; int64_t ld; int64_t s[3]; };
 // gradient, colsum_out receives stage 1 of the column sums of the result.  *fused tells the caller whether it happened.
 struct gelu_fusion { void* gelu_out; const void* gelu_pre; bool* fused; const void* resid; void* resid_out; const drop_args* drop; float* colsum_out; };
 
+hdet_sgemm_args sgemm_of(int form, mat A, mat B, float* c, int64_t ldc, const int64_t* c_s, int m, int n, int k, int n1, int n2) {
+  hdet_sgemm_args g = {};
+  g.a = (const float*)A.p; g.b = (const float*)B.p; g.c = c;
+  g.m = m; g.n = n; g.k = k; g.n1 = n1; g.n2 = n2;
+  if (form == TN) { g.a_rs = 1; g.a_cs = A.ld; } else { g.a_rs = A.ld; g.a_cs = 1; }
+  if (form == NT) { g.b_rs = 1; g.b_cs = B.ld; } else { g.b_rs = B.ld; g.b_cs = 1; }
+  g.c_rs = ldc;
+  for (int i = 0; i < 3; ++i) { g.a_s[i] = A.s[i]; g.b_s[i] = B.s[i]; g.c_s[i] = c_s[i]; }
+  return g;
+}
+
 template <typename T>
 hipError_t gemm(const hdet_tf_plan* pl, int form, mat A, mat B, void* c, int64_t ldc, const int64_t* c_s, bool act_out,
                 int m, int n, int k, int n1, int n2, const float* bias, int64_t bias_bs, hipStream_t s,
@@ -1194,15 +1205,17 @@ hipError_t gemm(const hdet_tf_plan* pl, int form, mat A, mat B, void* c, int64_t
     }
     return hdet_launch_bgemm(g, form != TN, form == NT, epi, batch, s);
   }
-  hdet_sgemm_args g = {};
-  g.a = (const float*)A.p; g.b = (const float*)B.p; g.c = (float*)c;
-  g.m = m; g.n = n; g.k = k; g.n1 = n1; g.n2 = n2;
-  if (form == TN) { g.a_rs = 1; g.a_cs = A.ld; } else { g.a_rs = A.ld; g.a_cs = 1; }
-  if (form == NT) { g.b_rs = 1; g.b_cs = B.ld; } else { g.b_rs = B.ld; g.b_cs = 1; }
-  g.c_rs = ldc;
-  for (int i = 0; i < 3; ++i) { g.a_s[i] = A.s[i]; g.b_s[i] = B.s[i]; g.c_s[i] = c_s[i]; }
+  hdet_sgemm_args g = sgemm_of(form, A, B, (float*)c, ldc, c_s, m, n, k, n1, n2);
   g.bias = bias; g.bias_bs = bias_bs;
-  return hdet_launch_sgemm(g, bias ? HDET_SEPI_BIAS : HDET_SEPI_NONE, batch, s);
+  int epi = bias ? HDET_SEPI_BIAS : HDET_SEPI_NONE;
+  if (gf && bias && gf->gelu_out) {
+    g.c2 = (float*)gf->gelu_out; epi = HDET_SEPI_BIAS_GELU;
+    *gf->fused = true;
+  } else if (gf && bias && gf->resid && !gf->drop) {
+    g.c = (float*)gf->resid_out; g.mask = (const float*)gf->resid; g.mask_rs = ldc; g.mask_bs = c_s[0]; epi = HDET_SEPI_BIAS_RESID;
+    *gf->fused = true;
+  }
+  return hdet_launch_sgemm(g, epi, batch, s);
 }
 
 #define TF_CHECK(expr) do { hipError_t e_ = (expr); if (e_ != hipSuccess) return e_; } while (0)
@@ -1301,12 +1314,13 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
   TF_CHECK(gemm<T>(p, NT, act(p->hf, d), wt(p->w_head, d), p->logits, V, act_v, false, M, V, d, 1, 1, theta + p->b_head, ps, s));
   // the loss kernel for wide rows also forms stage 1 of the head bias gradient, xr rows per chunk
   float* head_part = nullptr;
-  const int xr = xent_rows_per_block(M, N, V);
+  const int xr = sizeof(T) == 2 ? xent_rows_per_block(M, N, V) : 0;
   if (xr)
     for (const colsum_job& j : p->jobs)
       if (j.out_off == p->b_head && j.mode == 0 && j.cols == V && j.nchunks == (M + xr - 1) / xr) { head_part = p->part + j.part_off; break; }
   TF_CHECK(hdet_launch_xent(sizeof(T) == 2, p->logits, targets, M, V, p->dlogits, p->row_loss, N, ctrl, p->ls_channel, s, head_part, xr));
-  TF_CHECK(hdet_launch_loss_reduce(p->row_loss, M, ctrl, N, s));
+  constexpr bool f32 = sizeof(T) == 4;
+  if (!f32) TF_CHECK(hdet_launch_loss_reduce(p->row_loss, M, ctrl, N, s));
 
   // ---- backward -----------------------------------------------------------------------
   auto colsum = [&](const void* src, int cols, int64_t out_off) {
@@ -1353,9 +1367,31 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
                    nullptr, one);
   };
 
-  if (!head_part) TF_CHECK(colsum(p->dlogits, V, p->b_head));
-  TF_CHECK(gemm<T>(p, NN, act(p->dlogits, V), wt(p->w_head, d), p->dtmp, d, act_d, true, M, d, V, 1, 1, nullptr, 0, s));
-  TF_CHECK(wgrad(p->dlogits, V, p->hf, d, p->w_head));
+  // fp32: a layer's weight, bias and input gradients in one launch; gelu_pre: the input gradient goes through the GELU there
+  auto linear_bwd = [&](const void* dy, int wy, const void* x, int wx, int64_t w_off, int64_t b_off, void* dx, const void* gelu_pre,
+                        const hdet_loss_args* loss) -> hipError_t {
+    const bool one = shared && tf_wgrad_one_product(wy, wx);
+    hdet_sgemm_args g = sgemm_of(TN, act(dy, wy), act(x, wx), grads + w_off, wx, plane, wy, wx, one ? N * M : M, 1, 1);
+    if (one) {            // the product sums over the replicas, the bias gradients stay per replica
+      hipLaunchKernelGGL((colsum_kernel<T, 0>), dim3((wy + 63) / 64, N), dim3(1024), 0, s, (const T*)dy, (int64_t)wy, (int64_t)M * wy, M, wy,
+                         (const T*)nullptr, nullptr, nullptr, grads + b_off, grads, ps);
+    } else {
+      g.rowsum = grads + b_off; g.rowsum_bs = ps;
+    }
+    const int64_t dx_s[3] = {(int64_t)M * wx, 0, 0};
+    hdet_sgemm_args dg = sgemm_of(NN, act(dy, wy), wt(w_off, wx), (float*)dx, wx, dx_s, M, wx, wy, 1, 1);
+    dg.mask = (const float*)gelu_pre; dg.mask_rs = wx; dg.mask_bs = (int64_t)M * wx;
+    return hdet_launch_sgemm_pair(g, one ? 1 : N, &dg, false, gelu_pre ? HDET_SEPI_GELUGRAD : HDET_SEPI_NONE, N, loss, s);
+  };
+
+  if (f32) {
+    const hdet_loss_args loss = {p->row_loss, M, ctrl, N};
+    TF_CHECK(linear_bwd(p->dlogits, V, p->hf, d, p->w_head, p->b_head, p->dtmp, nullptr, &loss));
+  } else {
+    if (!head_part) TF_CHECK(colsum(p->dlogits, V, p->b_head));
+    TF_CHECK(gemm<T>(p, NN, act(p->dlogits, V), wt(p->w_head, d), p->dtmp, d, act_d, true, M, d, V, 1, 1, nullptr, 0, s));
+    TF_CHECK(wgrad(p->dlogits, V, p->hf, d, p->w_head));
+  }
   // With a dropout channel, the gradient that enters a residual branch is the stream's gradient passed
   // through that branch's dropout; the LayerNorm backward kernel that produces the stream's gradient
   // writes it as a second output where it can (dropped_done), else a separate pass does.
@@ -1374,24 +1410,29 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
         hipLaunchKernelGGL((dropout_kernel<T, false>), dim3(grid_for(nd / 4), N), dim3(256), 0, s, (const T*)nullptr, (const T*)p->dxa, (T*)p->dtmp2, nd, da);
       dy = p->dtmp2;
     }
-    if (!b2_done) TF_CHECK(colsum(dy, d, o.b_2));
-    bool b1_done = false;
-    {
-      bool fused = false;
-      // stage 1 of the first MLP layer's bias gradient comes with the product when its epilogue forms the GELU gradient
-      float* b1_part = nullptr;
-      for (const colsum_job& j : p->jobs)
-        if (j.out_off == o.b_1 && j.mode == 0 && j.cols == ff && j.nchunks == (M + 127) / 128) { b1_part = p->part + j.part_off; break; }
-      const gelu_fusion gf = {nullptr, p->z[l], &fused, nullptr, nullptr, nullptr, b1_part};
-      TF_CHECK(gemm<T>(p, NN, act(dy, d), wt(o.w_2, ff), p->dff, ff, act_ff, true, M, ff, d, 1, 1, nullptr, 0, s, &gf));
-      if (!fused)
-        hipLaunchKernelGGL(gelu_bwd_kernel<T>, dim3(grid_for((int64_t)N * nff)), dim3(256), 0, s, (const T*)p->dff, (const T*)p->z[l], (T*)p->dff, (int64_t)N * nff);
-      b1_done = fused && b1_part;
+    if (f32) {
+      TF_CHECK(linear_bwd(dy, d, p->f[l], ff, o.w_2, o.b_2, p->dff, p->z[l], nullptr));
+      TF_CHECK(linear_bwd(p->dff, ff, p->h2[l], d, o.w_1, o.b_1, p->dtmp, nullptr, nullptr));
+    } else {
+      if (!b2_done) TF_CHECK(colsum(dy, d, o.b_2));
+      bool b1_done = false;
+      {
+        bool fused = false;
+        // stage 1 of the first MLP layer's bias gradient comes with the product when its epilogue forms the GELU gradient
+        float* b1_part = nullptr;
+        for (const colsum_job& j : p->jobs)
+          if (j.out_off == o.b_1 && j.mode == 0 && j.cols == ff && j.nchunks == (M + 127) / 128) { b1_part = p->part + j.part_off; break; }
+        const gelu_fusion gf = {nullptr, p->z[l], &fused, nullptr, nullptr, nullptr, b1_part};
+        TF_CHECK(gemm<T>(p, NN, act(dy, d), wt(o.w_2, ff), p->dff, ff, act_ff, true, M, ff, d, 1, 1, nullptr, 0, s, &gf));
+        if (!fused)
+          hipLaunchKernelGGL(gelu_bwd_kernel<T>, dim3(grid_for((int64_t)N * nff)), dim3(256), 0, s, (const T*)p->dff, (const T*)p->z[l], (T*)p->dff, (int64_t)N * nff);
+        b1_done = fused && b1_part;
+      }
+      TF_CHECK(wgrad(dy, d, p->f[l], ff, o.w_2));
+      if (!b1_done) TF_CHECK(colsum(p->dff, ff, o.b_1));
+      TF_CHECK(gemm<T>(p, NN, act(p->dff, ff), wt(o.w_1, d), p->dtmp, d, act_d, true, M, d, ff, 1, 1, nullptr, 0, s));
+      TF_CHECK(wgrad(p->dff, ff, p->h2[l], d, o.w_1));
     }
-    TF_CHECK(wgrad(dy, d, p->f[l], ff, o.w_2));
-    if (!b1_done) TF_CHECK(colsum(p->dff, ff, o.b_1));
-    TF_CHECK(gemm<T>(p, NN, act(p->dff, ff), wt(o.w_1, d), p->dtmp, d, act_d, true, M, d, ff, 1, 1, nullptr, 0, s));
-    TF_CHECK(wgrad(p->dff, ff, p->h2[l], d, o.w_1));
     dropped_done = false;
     da.site = 2 * l;
     bo_done = false;
@@ -1405,27 +1446,46 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
         hipLaunchKernelGGL((dropout_kernel<T, false>), dim3(grid_for(nd / 4), N), dim3(256), 0, s, (const T*)nullptr, (const T*)p->dxb, (T*)p->dtmp2, nd, da);
       dob = p->dtmp2;
     }
-    if (!bo_done) TF_CHECK(colsum(dob, d, o.b_o));
-    TF_CHECK(gemm<T>(p, NN, act(dob, d), wt(o.w_o, d), p->dtmp, d, act_d, true, M, d, d, 1, 1, nullptr, 0, s));   // da
-    TF_CHECK(wgrad(dob, d, p->a[l], d, o.w_o));
+    if (f32) {
+      TF_CHECK(linear_bwd(dob, d, p->a[l], d, o.w_o, o.b_o, p->dtmp, nullptr, nullptr));
+    } else {
+      if (!bo_done) TF_CHECK(colsum(dob, d, o.b_o));
+      TF_CHECK(gemm<T>(p, NN, act(dob, d), wt(o.w_o, d), p->dtmp, d, act_d, true, M, d, d, 1, 1, nullptr, 0, s));   // da
+      TF_CHECK(wgrad(dob, d, p->a[l], d, o.w_o));
+    }
     if (p->fused_attn) {
       hdet_attn_desc ad = attn_desc(l);
       TF_CHECK(hdet_launch_attn_bwd(ad, s));
     } else {
       const mat sc = head_sq(p->scores);
       const mat dq = qkv_part(p->dqkv, 0), dk = qkv_part(p->dqkv, 1), dv = qkv_part(p->dqkv, 2);
-      // dp = da v^T
-      TF_CHECK(gemm<T>(p, NT, head_cols(p->dtmp), qkv_part(p->qkv[l], 2), p->scores, S, sc.s, false, S, S, dh, B, nh, nullptr, 0, s));
-      // dv = p^T da
-      TF_CHECK(gemm<T>(p, TN, head_sq(p->p[l]), head_cols(p->dtmp), (void*)dv.p, 3 * d, dv.s, true, S, dh, S, B, nh, nullptr, 0, s));
+      // dp = da v^T,  dv = p^T da
+      if (f32) {
+        const hdet_sgemm_args gv = sgemm_of(TN, head_sq(p->p[l]), head_cols(p->dtmp), (float*)dv.p, 3 * d, dv.s, S, dh, S, B, nh);
+        const hdet_sgemm_args gp = sgemm_of(NT, head_cols(p->dtmp), qkv_part(p->qkv[l], 2), (float*)p->scores, S, sc.s, S, S, dh, B, nh);
+        TF_CHECK(hdet_launch_sgemm_pair(gv, N * B * nh, &gp, true, HDET_SEPI_NONE, N * B * nh, nullptr, s));
+      } else {
+        TF_CHECK(gemm<T>(p, NT, head_cols(p->dtmp), qkv_part(p->qkv[l], 2), p->scores, S, sc.s, false, S, S, dh, B, nh, nullptr, 0, s));
+        TF_CHECK(gemm<T>(p, TN, head_sq(p->p[l]), head_cols(p->dtmp), (void*)dv.p, 3 * d, dv.s, true, S, dh, S, B, nh, nullptr, 0, s));
+      }
       launch_softmax_bwd<T>(p->scores, p->p[l], heads_rows, S, scale, ta, p->ds, s);
       // dq = ds k,  dk = ds^T q
-      TF_CHECK(gemm<T>(p, NN, head_sq(p->ds), qkv_part(p->qkv[l], 1), (void*)dq.p, 3 * d, dq.s, true, S, dh, S, B, nh, nullptr, 0, s));
-      TF_CHECK(gemm<T>(p, TN, head_sq(p->ds), qkv_part(p->qkv[l], 0), (void*)dk.p, 3 * d, dk.s, true, S, dh, S, B, nh, nullptr, 0, s));
+      if (f32) {
+        const hdet_sgemm_args gk = sgemm_of(TN, head_sq(p->ds), qkv_part(p->qkv[l], 0), (float*)dk.p, 3 * d, dk.s, S, dh, S, B, nh);
+        const hdet_sgemm_args gq = sgemm_of(NN, head_sq(p->ds), qkv_part(p->qkv[l], 1), (float*)dq.p, 3 * d, dq.s, S, dh, S, B, nh);
+        TF_CHECK(hdet_launch_sgemm_pair(gk, N * B * nh, &gq, false, HDET_SEPI_NONE, N * B * nh, nullptr, s));
+      } else {
+        TF_CHECK(gemm<T>(p, NN, head_sq(p->ds), qkv_part(p->qkv[l], 1), (void*)dq.p, 3 * d, dq.s, true, S, dh, S, B, nh, nullptr, 0, s));
+        TF_CHECK(gemm<T>(p, TN, head_sq(p->ds), qkv_part(p->qkv[l], 0), (void*)dk.p, 3 * d, dk.s, true, S, dh, S, B, nh, nullptr, 0, s));
+      }
     }
-    TF_CHECK(colsum(p->dqkv, 3 * d, o.b_qkv));
-    TF_CHECK(gemm<T>(p, NN, act(p->dqkv, 3 * d), wt(o.w_qkv, d), p->dtmp, d, act_d, true, M, d, 3 * d, 1, 1, nullptr, 0, s));
-    TF_CHECK(wgrad(p->dqkv, 3 * d, p->h1[l], d, o.w_qkv));
+    if (f32) {
+      TF_CHECK(linear_bwd(p->dqkv, 3 * d, p->h1[l], d, o.w_qkv, o.b_qkv, p->dtmp, nullptr, nullptr));
+    } else {
+      TF_CHECK(colsum(p->dqkv, 3 * d, o.b_qkv));
+      TF_CHECK(gemm<T>(p, NN, act(p->dqkv, 3 * d), wt(o.w_qkv, d), p->dtmp, d, act_d, true, M, d, 3 * d, 1, 1, nullptr, 0, s));
+      TF_CHECK(wgrad(p->dqkv, 3 * d, p->h1[l], d, o.w_qkv));
+    }
     dropped_done = false;
     da.site = 2 * (l - 1) + 1;                     // the MLP branch of the block below
     b2_done = false;

@@ -70,7 +70,9 @@ def mlp_grads(widths, batch, n, shared=False, bf16=False, seed=3):
 
 
 # (widths, batch, replicas): products with few tiles, up to one block of each tile size per compute unit, more, many
-FP32 = [([33, 31, 9], 7, 2), ([1, 3, 1, 2], 5, 3), ([1003, 250, 70], 500, 4), ([77, 1030, 130], 515, 4), ([41, 2050, 8], 1030, 4)]
+FP32 = [([33, 31, 9], 7, 2), ([1, 3, 1, 2], 5, 3), ([1003, 250, 70], 500, 4), ([77, 1030, 130], 515, 4), ([41, 2050, 8], 1030, 4),
+        # a layer's two products in one launch, with the same and with different tiles, and one of them too large for that
+        ([515, 130, 77], 130, 4), ([300, 260, 200, 8], 300, 4), ([2000, 24, 520], 40, 4)]
 
 
 @pytest.mark.parametrize("shared", [False, True])
