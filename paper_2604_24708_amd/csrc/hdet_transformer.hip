@@ -30,18 +30,80 @@ constexpr int kColsumRows = 128;                // rows per block in stage 1 of 
 // ------------------------------------------------------------------------------------------
 // elementwise / row kernels; blockIdx.y = replica
 // ------------------------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void embed_fwd_kernel(const float* theta, int64_t ps, int64_t tok_off, int64_t pos_off,
-                                                        const int32_t* ids, int M, int S, int d, T* x) {
-  const int r = blockIdx.y;
-  const float* tok = theta + (int64_t)r * ps + tok_off;
-  const float* pos = theta + (int64_t)r * ps + pos_off;
-  const int64_t n = (int64_t)M * d;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-    const int m = (int)(i / d), c = (int)(i % d);
-    const int id = ids[(int64_t)r * M + m];
-    hdet_st(x + (int64_t)r * n + i, tok[(int64_t)id * d + c] + pos[(int64_t)(m % S) * d + c]);
+// x[m] = tok[ids[m]] + pos[m mod S].  VEC: 8 elements a thread (d % 8 == 0, 16-byte aligned rows).
+template <typename T, bool VEC>
+__device__ __forceinline__ void embed_rows(const float* tok, const float* pos, const int32_t* ids, int M, int S, int d, T* x, int64_t first, int64_t step) {
+  constexpr int W = VEC ? 8 : 1;
+  const int dw = d / W;
+  const int64_t n = (int64_t)M * dw;
+  for (int64_t i = first; i < n; i += step) {
+    int m, c;
+    if (n <= 0xffffffffll) { m = (int)((uint32_t)i / (uint32_t)dw); c = (int)((uint32_t)i % (uint32_t)dw); }
+    else { m = (int)(i / dw); c = (int)(i % dw); }
+    const float* a = tok + (int64_t)ids[m] * d + W * c;
+    const float* b = pos + (int64_t)(m % S) * d + W * c;
+    if (VEC) {
+      hdet_f8 u = hdet_ld8(a);
+      const hdet_f8 v = hdet_ld8(b);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) u.v[j] += v.v[j];
+      hdet_st8(x + 8 * i, u);
+    } else {
+      hdet_st(x + i, *a + *b);
+    }
   }
+}
+
+// Position of 64 token ids in the order (id, row): the number of smaller ids plus that of equal ones in earlier rows.  The
+// block's four wavefronts count a quarter of the rows each; the ids counted against are uniform and come through the scalar
+// cache, so a comparison is two instructions and M^2 of them, spread over the chip, take less time than one block sorting
+// (M = 4096, 8 replicas: 8 us of the vector units against 50 us).
+__device__ __forceinline__ void rank_ids(const int32_t* __restrict__ ids, int M, int i0, unsigned long long* sorted, int (*cnt)[64]) {
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i = i0 + lane;
+  const uint32_t t = (uint32_t)ids[i < M ? i : M - 1];
+  const int quarter = (M + 3) / 4;
+  const int j0 = w * quarter, j1 = j0 + quarter < M ? j0 + quarter : M;
+  const int before = j1 < i0 ? j1 : i0;                              // rows before the block's 64, ...
+  const int from = j0 > i0 ? j0 : i0, to = j1 < i0 + 64 ? j1 : i0 + 64;        // ... among them ...
+  int n = 0;
+#pragma unroll 32
+  for (int j = j0; j < before; ++j) n += (uint32_t)ids[j] <= t;
+  for (int j = from; j < to; ++j) {
+    const uint32_t o = (uint32_t)ids[j];
+    n += o < t || (o == t && j < i);
+  }
+#pragma unroll 32
+  for (int j = j0 > i0 + 64 ? j0 : i0 + 64; j < j1; ++j) n += (uint32_t)ids[j] < t;      // ... and behind them
+  cnt[w][lane] = n;
+  __syncthreads();
+  if (w == 0 && i < M) sorted[cnt[0][lane] + cnt[1][lane] + cnt[2][lane] + cnt[3][lane]] = ((unsigned long long)t << 32) | (uint32_t)i;
+}
+
+// What a pass needs before its first layer, in one launch: blocks [0, rank_blocks) sort the token ids for the embedding
+// gradient (rank_ids), the next zero_blocks clear that gradient, the rest gather the embeddings.
+template <typename T, bool VEC>
+__global__ __launch_bounds__(256) void embed_fwd_kernel(const float* theta, int64_t ps, int64_t tok_off, int64_t pos_off,
+                                                        const int32_t* __restrict__ ids, int M, int S, int d, T* x, unsigned rank_blocks,
+                                                        unsigned long long* sorted, unsigned zero_blocks, float* grads, int64_t zero_len) {
+  __shared__ int cnt[4][64];
+  const int r = blockIdx.y;
+  if (blockIdx.x < rank_blocks) {
+    rank_ids(ids + (int64_t)r * M, M, (int)blockIdx.x * 64, sorted + (int64_t)r * M, cnt);
+    return;
+  }
+  unsigned b = blockIdx.x - rank_blocks;
+  if (b < zero_blocks) {
+    float* q = grads + (int64_t)r * ps + tok_off;
+    const int64_t n4 = ((tok_off | ps) & 3) == 0 ? zero_len >> 2 : 0;
+    for (int64_t i = (int64_t)b * 256 + threadIdx.x; i < n4; i += (int64_t)zero_blocks * 256)
+      *reinterpret_cast<hdet_f4v*>(q + 4 * i) = (hdet_f4v){0.f, 0.f, 0.f, 0.f};
+    for (int64_t i = 4 * n4 + (int64_t)b * 256 + threadIdx.x; i < zero_len; i += (int64_t)zero_blocks * 256) q[i] = 0.f;
+    return;
+  }
+  b -= zero_blocks;
+  embed_rows<T, VEC>(theta + (int64_t)r * ps + tok_off, theta + (int64_t)r * ps + pos_off, ids + (int64_t)r * M, M, S, d, x + (int64_t)r * M * d,
+                     (int64_t)b * 256 + threadIdx.x, (int64_t)(gridDim.x - rank_blocks - zero_blocks) * 256);
 }
 
 // dtok[ids[m]] += dx[m] with fp32 atomics (the region is zeroed first), for the shapes the ordered
@@ -58,33 +120,14 @@ __global__ __launch_bounds__(256) void embed_bwd_kernel(float* grads, int64_t ps
   }
 }
 // The same sum in a fixed order, for M up to 16384 rows per replica and d a multiple of 8 up to 2048:
-// (1) one block per replica sorts the keys (token id, row) in LDS (bitonic network over the next power
-// of two, padded with all-ones keys), so that the rows of a token id are adjacent and ascending;
+// (1) the rows are ordered by (token id, row) (rank_ids), so that the rows of a token id are adjacent and ascending;
 // (2) one wavefront per sorted position: where a new id starts, it adds that id's rows of dx in
 // ascending row order and writes the token's gradient row (the region is zeroed first for the ids
 // that do not occur).
-template <int P2>
-__global__ __launch_bounds__(1024) void tok_sort_kernel(const int32_t* ids, int M, unsigned long long* sorted) {
-  __shared__ unsigned long long keys[P2];
-  const int r = blockIdx.x, tid = threadIdx.x;
-  for (int i = tid; i < P2; i += 1024)
-    keys[i] = i < M ? ((unsigned long long)(uint32_t)ids[(int64_t)r * M + i] << 32) | (uint32_t)i : ~0ull;
-  __syncthreads();
-  for (int k = 2; k <= P2; k <<= 1)
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int t = tid; t < P2 / 2; t += 1024) {
-        const int i = 2 * j * (t / j) + (t % j);
-        const unsigned long long a = keys[i], b = keys[i + j];
-        if ((a > b) == ((i & k) == 0)) { keys[i] = b; keys[i + j] = a; }
-      }
-      __syncthreads();
-    }
-  for (int i = tid; i < M; i += 1024) sorted[(int64_t)r * M + i] = keys[i];
-}
 // Step (2) runs in two levels so that a frequent token does not serialise one wavefront: level 1
 // sums the rows of every segment -- a maximal run of one id inside a block of kTokChunk sorted
-// positions -- into seg[first position of the segment]; level 2 adds the segments of each id in
-// ascending order and writes the token's gradient row.
+// positions -- and writes the token's gradient row if the segment is all of the id, else
+// seg[first position of the segment]; level 2 adds the segments of the other ids in ascending order.
 constexpr int kTokChunk = 32;
 __device__ __forceinline__ uint32_t key_id(unsigned long long key) { return (uint32_t)(key >> 32); }
 template <int NCH>
@@ -97,10 +140,9 @@ __device__ __forceinline__ void add_row(hdet_f8 (&acc)[NCH], const hdet_f8 (&v)[
     }
 }
 template <typename T, int NCH>
-__global__ __launch_bounds__(256) void tok_segment_kernel(const unsigned long long* sorted, int M, int d, const T* dx, float* seg) {
+__device__ __forceinline__ void tok_segment(const unsigned long long* sorted, int M, int d, const T* dx, float* seg, float* tok_grads, int r, int j0) {
   constexpr int U = NCH == 1 ? 8 : 4;               // rows in flight, by register budget
-  const int r = blockIdx.y, lane = threadIdx.x & 63;
-  const int j0 = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
   if (j0 >= M) return;
   const unsigned long long* sk = sorted + (int64_t)r * M;
   const uint32_t id = key_id(sk[j0]);
@@ -135,7 +177,8 @@ __global__ __launch_bounds__(256) void tok_segment_kernel(const unsigned long lo
       if (u < n) add_row<NCH>(acc, v[u], lane, d8);
     if (n < U) break;
   }
-  float* dst = seg + ((int64_t)r * M + j0) * d;
+  const bool starts = j0 == 0 || key_id(sk[j0 - 1]) != id, ends = jend >= M || key_id(sk[jend]) != id;
+  float* dst = starts && ends ? tok_grads + (int64_t)id * d : seg + ((int64_t)r * M + j0) * d;
 #pragma unroll
   for (int i = 0; i < NCH; ++i)
     if (lane + 64 * i < d8) hdet_st8(dst + 8 * (lane + 64 * i), acc[i]);
@@ -150,6 +193,8 @@ __global__ __launch_bounds__(256) void tok_total_kernel(const unsigned long long
   const unsigned long long* sk = sorted + (int64_t)r * M;
   const uint32_t id = key_id(sk[j0]);
   if (j0 > 0 && key_id(sk[j0 - 1]) == id) return;                    // not the first row of its id
+  const int next = (j0 / kTokChunk + 1) * kTokChunk;
+  if (next >= M || key_id(sk[next]) != id) return;                   // one segment: level 1 has written it
   const int d8 = d >> 3;
   const float* src = seg + (int64_t)r * M * d;
   hdet_f8 acc[NCH];
@@ -183,18 +228,30 @@ __global__ __launch_bounds__(256) void tok_total_kernel(const unsigned long long
     if (lane + 64 * i < d8) hdet_st8(dst + 8 * (lane + 64 * i), acc[i]);
 }
 
-// dpos[s] = sum over the sequences b, in ascending order, of dx[b S + s]
-template <typename T>
-__global__ __launch_bounds__(256) void pos_bwd_kernel(float* grads, int64_t ps, int64_t pos_off, int B, int S, int d, const T* dx) {
-  const int r = blockIdx.y;
-  float* pos = grads + (int64_t)r * ps + pos_off;
-  const int64_t n = (int64_t)S * d;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-    float a = 0.f;
-    for (int b = 0; b < B; ++b) a += hdet_ld(dx + ((int64_t)r * B + b) * n + i);
-    pos[i] = a;
+// dpos[s] = sum over the sequences b, in ascending order, of dx[b S + s].  VEC: 8 elements a thread.
+template <typename T, bool VEC>
+__device__ __forceinline__ void pos_rows(float* pos, int B, int64_t n, const T* dx, int64_t first, int64_t step) {
+  constexpr int W = VEC ? 8 : 1;
+  for (int64_t i = first; i < n / W; i += step) {
+    float a[W];
+#pragma unroll
+    for (int j = 0; j < W; ++j) a[j] = 0.f;
+#pragma unroll 4
+    for (int b = 0; b < B; ++b) {
+      const T* q = dx + (int64_t)b * n + W * i;
+      if (VEC) {
+        const hdet_f8 v = hdet_ld8(q);
+#pragma unroll
+        for (int j = 0; j < W; ++j) a[j] += v.v[j];
+      } else {
+        a[0] += hdet_ld(q);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < W; ++j) pos[W * i + j] = a[j];
   }
 }
+
 
 // Weight gradient formed in `splits` pieces along the contraction (the rows of the batch): dW = sum of the pieces in
 // the order 0 .. splits-1.  part[(replica * splits + piece) * len + i], len a multiple of 4.
@@ -207,11 +264,6 @@ __global__ __launch_bounds__(256) void wgrad_sum_kernel(const float* part, int s
   f4 acc = *reinterpret_cast<const f4*>(src);
   for (int sidx = 1; sidx < splits; ++sidx) acc += *reinterpret_cast<const f4*>(src + sidx * len);
   *reinterpret_cast<f4*>(grads + (int64_t)r * ps + w_off + i) = acc;
-}
-
-__global__ __launch_bounds__(256) void zero_kernel(float* p, int64_t ps, int64_t off, int64_t n) {
-  float* q = p + (int64_t)blockIdx.y * ps + off;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) q[i] = 0.f;
 }
 
 // LayerNorm forward, one wavefront per row: two passes (mean, then variance about it).
@@ -568,26 +620,27 @@ struct colsum_job {
   int64_t out2_off;
   int32_t cols, mode, first_block, nchunks;   // nchunks: row chunks stage 1 produced
 };
-__global__ __launch_bounds__(256) void colsum_final_kernel(const colsum_job* jobs, int njobs, const float* part,
-                                                           int n_replicas, float* grads, int64_t ps) {
-  int lo = 0, hi = njobs - 1;                       // last job whose first block is <= blockIdx.x
+__device__ __forceinline__ void colsum_final(const colsum_job* jobs, int njobs, const float* part, int n_replicas, float* grads, int64_t ps,
+                                             int block, int r) {
+  int lo = 0, hi = njobs - 1;                       // last job whose first block is <= block
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
-    if (jobs[mid].first_block <= (int)blockIdx.x) lo = mid; else hi = mid - 1;
+    if (jobs[mid].first_block <= block) lo = mid; else hi = mid - 1;
   }
   const colsum_job j = jobs[lo];
   const int nchunks = j.nchunks;
-  const int r = blockIdx.y, c = (blockIdx.x - j.first_block) * 256 + threadIdx.x;
+  const int c = (block - j.first_block) * 256 + threadIdx.x;
   if (c >= j.cols) return;
-  // chunks added in ascending order, eight loads in flight
+  // chunks added in ascending order, 16 loads in flight
   auto total = [&](const float* q) {
+    constexpr int U = 16;
     float a = 0.f;
-    for (int k = 0; k < nchunks; k += 8) {
-      float v[8];
+    for (int k = 0; k < nchunks; k += U) {
+      float v[U];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = k + u < nchunks ? q[(int64_t)(k + u) * j.cols] : 0.f;
+      for (int u = 0; u < U; ++u) v[u] = k + u < nchunks ? q[(int64_t)(k + u) * j.cols] : 0.f;
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
+      for (int u = 0; u < U; ++u)
         if (k + u < nchunks) a += v[u];
     }
     return a;
@@ -595,6 +648,33 @@ __global__ __launch_bounds__(256) void colsum_final_kernel(const colsum_job* job
   const float* p1 = part + j.part_off + (int64_t)r * nchunks * j.cols + c;
   grads[(int64_t)r * ps + j.out_off + c] = total(p1);
   if (j.mode == 1) grads[(int64_t)r * ps + j.out2_off + c] = total(p1 + (int64_t)n_replicas * nchunks * j.cols);
+}
+
+// The end of a pass, in one launch, as nothing in it needs anything else of it: stage 2 of the column sums, the position
+// embedding's gradient and level 1 of the token embedding's (blocks in this order; seg_blocks = 0: the atomic form follows).
+struct tail_args {
+  const colsum_job* jobs; int njobs; const float* part; int n_replicas;
+  float* grads; int64_t ps, tok_off, pos_off;
+  unsigned final_blocks, pos_blocks;
+  int B, S, M, d;
+  const unsigned long long* sorted; float* seg;
+};
+template <typename T, int NCH, bool VEC>
+__global__ __launch_bounds__(256) void backward_tail_kernel(const tail_args a, const T* dx) {
+  const int r = blockIdx.y;
+  unsigned b = blockIdx.x;
+  if (b < a.final_blocks) {
+    colsum_final(a.jobs, a.njobs, a.part, a.n_replicas, a.grads, a.ps, (int)b, r);
+    return;
+  }
+  b -= a.final_blocks;
+  if (b < a.pos_blocks) {
+    const int64_t n = (int64_t)a.S * a.d;
+    pos_rows<T, VEC>(a.grads + (int64_t)r * a.ps + a.pos_off, a.B, n, dx + (int64_t)r * a.B * n, (int64_t)b * 256 + threadIdx.x, (int64_t)a.pos_blocks * 256);
+    return;
+  }
+  b -= a.pos_blocks;
+  tok_segment<T, NCH>(a.sorted, a.M, a.d, dx, a.seg, a.grads + (int64_t)r * a.ps + a.tok_off, r, (int)b * 4 + (int)(threadIdx.x >> 6));
 }
 
 // Column reductions over the M rows: block = 64 columns x 16 row phases; thread (c, q) adds
@@ -1112,7 +1192,7 @@ void launch_softmax_bwd(const float* dp, const void* prob, int64_t rows, int S, 
 }
 
 // Column reductions described at colsum_kernel into the gradient plane offsets out_off (and out2_off),
-// per replica.  Widths that are multiples of 8 only run stage 1 here; launch_colsum_final ends the pass.
+// per replica.  Widths that are multiples of 8 only run stage 1 here; the backward tail ends the pass.
 template <typename T, int MODE>
 hipError_t launch_colsum(const hdet_tf_plan* p, const void* src, int cols, const void* x, const float* mean, const float* rstd,
                          int64_t out_off, int64_t out2_off, hipStream_t s) {
@@ -1130,13 +1210,6 @@ hipError_t launch_colsum(const hdet_tf_plan* p, const void* src, int cols, const
     hipLaunchKernelGGL((colsum_kernel<T, MODE>), dim3((cols + 63) / 64, N), dim3(1024), 0, s, (const T*)src, (int64_t)cols, (int64_t)M * cols, M, cols,
                        (const T*)x, mean, rstd, grads + out_off, grads + out2_off, ps);
   }
-  return hipGetLastError();
-}
-
-hipError_t launch_colsum_final(const hdet_tf_plan* p, hipStream_t s) {
-  if (p->jobs.empty()) return hipSuccess;
-  hipLaunchKernelGGL(colsum_final_kernel, dim3(p->final_blocks, p->N), dim3(256), 0, s, p->jobs_dev, (int)p->jobs.size(), p->part,
-                     p->N, p->buf.grads_dev, p->buf.plane_stride);
   return hipGetLastError();
 }
 
@@ -1266,7 +1339,16 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
                 act_v[3] = {(int64_t)M * V, 0, 0}, plane[3] = {ps, 0, 0};
 
   // ---- forward ------------------------------------------------------------------------
-  hipLaunchKernelGGL(embed_fwd_kernel<T>, dim3(grid_for(nd), N), dim3(256), 0, s, theta, ps, p->tok, p->pos, ids, M, S, d, (T*)p->x_in[0]);
+  const bool aligned_rows = d % 8 == 0 && p->tok % 4 == 0 && p->pos % 4 == 0 && ps % 4 == 0;
+  const bool ordered_tok = M <= 16384 && aligned_rows && d <= 2048;       // token-embedding gradient in a fixed order
+  {
+    const int64_t tok_len = (int64_t)V * d;
+    const unsigned rb = ordered_tok ? (M + 63) / 64 : 0, zb = grid_for((tok_len + 15) / 16), eb = grid_for(aligned_rows ? nd / 8 : nd);
+#define EMBED(VEC) hipLaunchKernelGGL((embed_fwd_kernel<T, VEC>), dim3(rb + zb + eb, N), dim3(256), 0, s, theta, ps, p->tok, p->pos, ids, M, S, d, \
+                                      (T*)p->x_in[0], rb, p->tok_sorted, zb, grads, tok_len)
+    if (aligned_rows) EMBED(true); else EMBED(false);
+#undef EMBED
+  }
   for (int l = 0; l < L; ++l) {
     const tf_block_off& o = p->blk[l];
     launch_ln_fwd<T>(p, p->x_in[l], o.ln1_g, o.ln1_b, p->h1[l], p->st1_mean[l], p->st1_rstd[l], s);
@@ -1493,24 +1575,28 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
                              l > 0 ? p->blk[l - 1].b_2 : -1, &b2_done))
       TF_CHECK(ln_params(p->dtmp, p->x_in[l], p->st1_mean[l], p->st1_rstd[l], o.ln1_g, o.ln1_b));
   }
-  hipLaunchKernelGGL(zero_kernel, dim3(grid_for((int64_t)V * d), N), dim3(256), 0, s, grads, ps, p->tok, (int64_t)V * d);
-  if (M <= 16384 && d % 8 == 0 && d <= 2048 && p->tok % 4 == 0 && ps % 4 == 0) {
-#define SORT(P2) hipLaunchKernelGGL(tok_sort_kernel<P2>, dim3(N), dim3(1024), 0, s, ids, M, p->tok_sorted)
-    if (M <= 1024) SORT(1024); else if (M <= 2048) SORT(2048); else if (M <= 4096) SORT(4096); else if (M <= 8192) SORT(8192); else SORT(16384);
-#undef SORT
-    const int nch = (d / 8 + 63) / 64;
-    float* seg = p->tok_seg;
-#define CALL(K) hipLaunchKernelGGL((tok_segment_kernel<T, K>), dim3((M + 3) / 4, N), dim3(256), 0, s, p->tok_sorted, M, d, (const T*)p->dxa, seg)
+  {
+    tail_args tail = {};
+    tail.jobs = p->jobs_dev; tail.njobs = (int)p->jobs.size(); tail.part = p->part; tail.n_replicas = N;
+    tail.grads = grads; tail.ps = ps; tail.tok_off = p->tok; tail.pos_off = p->pos;
+    tail.B = B; tail.S = S; tail.M = M; tail.d = d; tail.sorted = p->tok_sorted; tail.seg = p->tok_seg;
+    tail.final_blocks = p->final_blocks;
+    tail.pos_blocks = grid_for(aligned_rows ? (int64_t)S * d / 8 : (int64_t)S * d);
+    const dim3 grid(tail.final_blocks + tail.pos_blocks + (ordered_tok ? (M + 3) / 4 : 0), N);
+    const int nch = ordered_tok ? (d / 8 + 63) / 64 : 1;
+#define CALL(K) \
+    if (aligned_rows) hipLaunchKernelGGL((backward_tail_kernel<T, K, true>), grid, dim3(256), 0, s, tail, (const T*)p->dxa); \
+    else hipLaunchKernelGGL((backward_tail_kernel<T, 1, false>), grid, dim3(256), 0, s, tail, (const T*)p->dxa)
     HDET_NCH_SWITCH(nch, CALL)
 #undef CALL
-#define CALL(K) hipLaunchKernelGGL((tok_total_kernel<K>), dim3((M + 3) / 4, N), dim3(256), 0, s, p->tok_sorted, M, d, seg, grads, ps, p->tok)
-    HDET_NCH_SWITCH(nch, CALL)
+    if (ordered_tok) {
+#define CALL(K) hipLaunchKernelGGL((tok_total_kernel<K>), dim3((M + 3) / 4, N), dim3(256), 0, s, p->tok_sorted, M, d, p->tok_seg, grads, ps, p->tok)
+      HDET_NCH_SWITCH(nch, CALL)
 #undef CALL
-  } else {
-    hipLaunchKernelGGL(embed_bwd_kernel<T>, dim3(grid_for(nd), N), dim3(256), 0, s, grads, ps, p->tok, ids, M, d, (const T*)p->dxa);
+    } else {
+      hipLaunchKernelGGL(embed_bwd_kernel<T>, dim3(grid_for(nd), N), dim3(256), 0, s, grads, ps, p->tok, ids, M, d, (const T*)p->dxa);
+    }
   }
-  hipLaunchKernelGGL(pos_bwd_kernel<T>, dim3(grid_for((int64_t)S * d), N), dim3(256), 0, s, grads, ps, p->pos, B, S, d, (const T*)p->dxa);
-  TF_CHECK(launch_colsum_final(p, s));
   return hipGetLastError();
 }
 
