@@ -436,15 +436,24 @@ static hipError_t forward_backward_bf16(hdet_mlp_plan* p, const void* x, const i
   if (hipError_t e = hdet_launch_xent(true, p->logits, y, B, w[L], dz, p->row_loss, N, ctrl, p->ls_channel, s, nullptr, 0, B)) return e;
   hipLaunchKernelGGL(loss_reduce_kernel, dim3(N), dim3(256), 0, s, p->row_loss, B, ctrl);
   for (int i = L - 1; i >= 0; --i) {
-    // db = column sums of dZ: from the 128-row partial sums when the product that formed dZ left them, else from dZ itself
-    if (have_part)
+    hdet_bgemm_args g = {};                          // dW = dZ^T X
+    g.a = dz; g.lda = w[i + 1]; g.a_s[0] = (int64_t)B * w[i + 1];           // A(o,b) = dZ[b][o]
+    g.b = (const uint16_t*)p->act[i]; g.ldb = w[i]; g.b_s[0] = (int64_t)B * w[i];   // B(b,k) = X[b][k]
+    g.c = grads + p->w_off[i]; g.ldc = w[i]; g.c_s[0] = ps;
+    g.m = w[i + 1]; g.n = w[i]; g.k = shared ? N * B : B;
+    g.n1 = g.n2 = 1;
+    const bool fast = hdet_bgemm_dma_eligible(g, false, false, HDET_EPI_F32);
+    // db = column sums of dZ: beside dW where a general kernel forms that, from the 128-row partial sums when the product that
+    // formed dZ left them, else from dZ itself
+    if (!fast) {
+      g.rowsum = grads + p->b_off[i]; g.rowsum_bs = ps;
+    } else if (have_part)
       hipLaunchKernelGGL(bias_grad_kernel<float>, dim3((w[i + 1] + 63) / 64, shared ? 1 : N), dim3(1024), 0, s, p->colsum_part,
                          shared ? N * nchunks : nchunks, w[i + 1], (int64_t)nchunks * w[i + 1], grads + p->b_off[i], ps);
     else
       hipLaunchKernelGGL(bias_grad_kernel<uint16_t>, dim3((w[i + 1] + 63) / 64, shared ? 1 : N), dim3(1024), 0, s, dz, shared ? N * B : B, w[i + 1],
                          (int64_t)B * w[i + 1], grads + p->b_off[i], ps);
     have_part = false;
-    const uint16_t* dz_cur = dz;
     if (i > 0) {                                     // dX = dZ W, through the ReLU below (before W is touched by a fused update)
       hdet_bgemm_args d = {};
       d.a = dz; d.lda = w[i + 1]; d.a_s[0] = (int64_t)B * w[i + 1];
@@ -461,12 +470,6 @@ static hipError_t forward_backward_bf16(hdet_mlp_plan* p, const void* x, const i
       if (e != hipSuccess) return e;
       uint16_t* t = dz; dz = dz_next; dz_next = t;
     }
-    hdet_bgemm_args g = {};                          // dW = dZ^T X
-    g.a = dz_cur; g.lda = w[i + 1]; g.a_s[0] = (int64_t)B * w[i + 1];           // A(o,b) = dZ[b][o]
-    g.b = (const uint16_t*)p->act[i]; g.ldb = w[i]; g.b_s[0] = (int64_t)B * w[i];   // B(b,k) = X[b][k]
-    g.c = grads + p->w_off[i]; g.ldc = w[i]; g.c_s[0] = ps;
-    g.m = w[i + 1]; g.n = w[i]; g.k = shared ? N * B : B;
-    g.n1 = g.n2 = 1;
     const int64_t wlen = (int64_t)w[i + 1] * w[i];
     // the update of W applied by the product that forms its gradient (Eq. 2): dW never goes to memory
     if (fuse && !shared && hdet_fuse_args_for(c, *fuse, p->w_off[i], w[i + 1], w[i], &g.upd) &&
