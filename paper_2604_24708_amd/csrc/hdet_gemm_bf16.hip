@@ -499,9 +499,10 @@ hipError_t launch_general(const hdet_bgemm_args& g, int batch, hipStream_t s) {
   hipLaunchKernelGGL((hdet_bgemm_kernel<AK, BK, EPI, WT, WT, 2>), dim3((g.n + 64 * WT - 1) / (64 * WT), (g.m + 64 * WT - 1) / (64 * WT), batch), dim3(256), 0, s, g)
   const int64_t cus = hdet_compute_units();
   if (few_tiles(g, batch)) HDET_FRAG(1, 1, 4, 4);
-  // less than one 64 x 64 block per CU and a long contraction: K in 8 (96 x 700, K = 1500, 6 items: 15.5 | LDS 64 x 64 26.6;
+  // less than one 64 x 64 block per CU and a long contraction: K in 8 (training step with 96 x 700, K = 1500, 6 items in it: 170 us,
+  // with 64 x 64 fragment tiles 173, LDS 64 x 64 185; alone, 64 x 64 fragment tiles 15.5 | LDS 64 x 64 26.6;
   // 111 x 3193, K = 1788, 2 items, odd rows: 24 | 51; at K = 842 10.7 | 10.9)
-  else if (g.k >= 1024 && tiles(g, batch, 64, 64) < cus) HDET_FRAG(2, 2, 8, 2);
+  else if (g.k >= 1024 && tiles(g, batch, 64, 64) < cus) HDET_FRAG(1, 1, 8, 4);
   // 128 x 128 tiles once there are several rounds of them (256 x 4095, K = 4095, 8 items: 337 | 64 x 64 441; 700 x 1500, K = 576:
   // 14.8 | 10.1; 1788 x 3193, K = 222: 18.4 | 14.7), unless they would be half empty
   else if (tiles(g, batch, 128, 128) >= 4 * cus && g.m > 64 && g.n > 64) HDET_LDS(2);
