@@ -10,7 +10,7 @@
 // Loads and stores are 128-bit, coalesced along the parameter axis and non-temporal (every
 // byte is touched exactly once per step, far beyond any cache).
 //
-// Three kernels:
+// Four kernels:
 //   plane  -- one thread per (replica, column), replica on blockIdx.y; steps that need no
 //             exchange along the replica axis.  One column per thread and a grid that covers
 //             the plane exactly streamed fastest on MI355X (about 6.4 TB/s, against 5.9 for
@@ -19,6 +19,7 @@
 //             up to four replicas a wavefront); gradients (shared mode) and updated parameters (fused converge) cross the
 //             replica axis through LDS, each wavefront then writes its own plane.  Keeps
 //             the register footprint of the plane kernel instead of N columns per thread.
+//   state  -- the wave kernel's form for one set of moments and whole columns.
 //   loop   -- one thread walks the replica axis of a column; on request (hdet_set_launch_shape) and
 //             for planes of more columns than a grid holds.
 // The P mod 4 trailing parameters are one more column in the plane and wave kernels, read and
@@ -238,6 +239,60 @@ __global__ __launch_bounds__(kMaxWaves * 64) void hdet_update_wave_kernel(const 
   }
 }
 
+// The wave kernel for one set of moments, 2 to 16 replicas and large planes: whole columns only, 16-byte accesses without a
+// mask of their own.  The order in which the streams reach the memory decides here: the general form, whose accesses are
+// masked one by one, is 1 to 4 % slower on planes of several hundred MB (and up to 10 % faster in the other forms), but has
+// the trailing parameters in the same launch: it is taken where there are any, up to 4 million parameters, where a launch of
+// their own would cost more than the rest gains.  us, this / general:  N = 8, P = 20e6 379 / 381;  N = 16, P = 5e6 184 / 192;
+// with a launch for three trailing parameters, N = 8, P = 2e6 47 / 40, P = 20e6 379 / 378.
+template <bool CONV>
+__global__ __launch_bounds__(kMaxWaves * 64) void hdet_update_state_kernel(const hdet_update_args a, const int groups) {
+  __shared__ exchange_buf<1> ex;
+  const int n = a.n_replicas;
+  const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int grp = wid / n, r = wid - grp * n;
+  const rep_scalars s = replica_scalars(a, r);
+  if (blockIdx.x == 0 && grp == 0 && lane == 0 && a.lr_channel == 0) a.ctrl_out->lr_used[r] = s.lr;
+  const int64_t i = ((int64_t)blockIdx.x * groups + grp) * 64 + lane;
+  const bool ok = i < (a.n_params >> 2);
+  const int64_t off = (int64_t)r * a.stride + (i << 2);
+  const int64_t moff = i << 2;
+  const bool mine = ok && r == 0;                     // this thread holds the moments
+  f4 th = splat<f4>(0.f), m = th, v = th;
+  f4 g[1] = {th};
+  if (ok) {
+    th = ld<f4>(a.theta + off);
+    g[0] = ld<f4>(a.grad + (int64_t)r * a.grad_stride + (i << 2));
+    if (a.grad_stride == 0) g[0] = g[0] * a.grad_scale;
+  }
+  if (mine) {
+    m = ld<f4>(a.m + moff);
+    v = ld<f4>(a.v + moff);
+  }
+  const f4 gbar = exchange_mean<1>(ex, g, grp, r, n, n, lane);
+  if (r == 0) {
+    const f4 ratio = adamw_moments<f4>(gbar, m, v, a);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) ex.mean[grp][c][lane] = ratio[c];
+  }
+  __syncthreads();
+  const f4 ratio = {ex.mean[grp][0][lane], ex.mean[grp][1][lane], ex.mean[grp][2][lane], ex.mean[grp][3][lane]};
+  adamw_apply<f4>(th, ratio, s);
+  if (CONV) __syncthreads();                          // ex.mean is written again below
+  if (mine) {
+    st<f4>(a.m + moff, m);
+    st<f4>(a.v + moff, v);
+  }
+  if (CONV) {
+    const f4 x[1] = {th};
+    th = exchange_mean<1>(ex, x, grp, r, n, n, lane);
+  }
+  if (ok) {
+    st<f4>(a.theta + off, th);
+    if (a.shadow) st_bf16(a.shadow + off, th);
+  }
+}
+
 // Standalone converge (Eq. 3) in the same shape: 4 B read + 4 B written per replica-element.
 template <int R>
 __global__ __launch_bounds__(kMaxWaves * 64) void hdet_converge_wave_kernel(const hdet_converge_args a,
@@ -396,6 +451,8 @@ int clamp_blocks(int64_t n_params, int blocks) {
   return (int)(need < blocks ? need : blocks);
 }
 
+constexpr int64_t kStateParams = 4000000;      // see hdet_update_state_kernel
+
 // Shape of a wave-kernel launch: R replicas per wavefront, 512-thread blocks of several column groups while R = 1.
 struct wave_shape {
   int r, groups, waves;
@@ -437,6 +494,19 @@ void launch_variant(const hdet_update_args& a, int variant, int blocks, hipStrea
     const wave_shape w = wave_launch(a.n_params, n);
     if (w.bx <= 0x7fffffff) {
       const dim3 grid((unsigned)w.bx), block(64 * w.groups * w.waves);
+      if constexpr (SSTATE) {
+        if (w.r == 1 && n > 1 && ((a.n_params & 3) == 0 || a.n_params >= kStateParams)) {
+          hipLaunchKernelGGL((hdet_update_state_kernel<CONV>), grid, block, 0, stream, a, w.groups);
+          const int64_t whole = a.n_params & ~(int64_t)3;
+          if (whole == a.n_params) return;
+          hdet_update_args t = a;                     // the trailing parameters, in the general form
+          t.theta += whole; t.grad += whole; t.m += whole; t.v += whole;
+          if (t.shadow) t.shadow += whole;
+          t.n_params -= whole;
+          hipLaunchKernelGGL((hdet_update_wave_kernel<OPT, SHARED, CONV, SSTATE, 1>), dim3(1), block, 0, stream, t, w.groups, w.waves);
+          return;
+        }
+      }
       if (w.r == 1) hipLaunchKernelGGL((hdet_update_wave_kernel<OPT, SHARED, CONV, SSTATE, 1>), grid, block, 0, stream, a, w.groups, w.waves);
       else if (w.r == 2) hipLaunchKernelGGL((hdet_update_wave_kernel<OPT, SHARED, CONV, SSTATE, 2>), grid, block, 0, stream, a, w.groups, w.waves);
       else if (w.r == 3) hipLaunchKernelGGL((hdet_update_wave_kernel<OPT, SHARED, CONV, SSTATE, 3>), grid, block, 0, stream, a, w.groups, w.waves);

@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("opt,mode,one_state", [(O.ADAMW, O.GRAD_SHARED, True), (O.SGDM, O.GRAD_SHARED, False),
                                                 (O.SGDM, O.GRAD_PER_REPLICA, False)])
-@pytest.mark.parametrize("n,P", [(1, 3), (2, 1), (5, 2), (16, 257), (17, 3), (18, 1022), (33, 259), (48, 5), (49, 256), (64, 1)])
+@pytest.mark.parametrize("n,P", [(1, 3), (2, 1), (5, 2), (16, 257), (17, 3), (18, 1022), (33, 259), (48, 5), (49, 256), (64, 1),
+                                 (2, 4), (3, 1024), (16, 516), (2, 4000002)])
 def test_default_kernels_equal_the_general_one(n, P, opt, mode, one_state):
     d = base_cfg(n_replicas=n, optimizer=opt, grad_mode=mode, shared_opt_state=one_state)
     a, b = FlatRun(d, P, stride=(P + 3) // 4 * 4 + 8, variant=1, blocks=3), FlatRun(d, P, stride=(P + 3) // 4 * 4 + 8)
