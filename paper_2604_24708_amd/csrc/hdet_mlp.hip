@@ -144,8 +144,13 @@ __device__ __forceinline__ void xent_block_reduce(float& a, float& b, float* red
   __syncthreads();
 }
 
-template <typename T, int BS, int NV, bool SUMS>
-__global__ __launch_bounds__(BS, SUMS ? 2 : 4) void xent_row_kernel(const float* logits, const int32_t* labels, int rows, int classes,
+// NV: chunks a thread may own, all but the last SLACK of which every thread owns (the host picks NV that closely), so that only
+// those are masked.  Bound by the issue slots per element as much as by memory: with NV for the widest rows, a mask on every
+// chunk and the next row's registers copied, rows of 2048 spent three quarters of theirs on chunks that do not exist.
+// 65536 rows of 2048 347 -> 176 us (4.6 TB/s), 16384 of 4096 117 -> 81 (5.0), 32768 of 32000 1295 -> 1150 (5.5); 1024 threads
+// a row instead of 512 for the widest: 6-layer step 4 % longer.
+template <typename T, int BS, int NV, int SLACK, bool SUMS>
+__global__ __launch_bounds__(BS, !SUMS || (BS == 256 && NV <= 6) ? 4 : 2) void xent_row_kernel(const float* logits, const int32_t* labels, int rows, int classes,
                                                       int rows_per_block, T* dlogits, float* row_loss, const hdet_ctrl* ctrl,
                                                       int ls_channel, float* colsum, int grad_rows) {
   constexpr int NW = BS / 64;
@@ -156,26 +161,25 @@ __global__ __launch_bounds__(BS, SUMS ? 2 : 4) void xent_row_kernel(const float*
   const float hitb = hit * invb, missb = miss * invb;
   const int row0 = blockIdx.x * rows_per_block;
   const int row1 = row0 + rows_per_block < rows ? row0 + rows_per_block : rows;
-  hdet_f4 cur[NV], nxt[SUMS ? NV : 1], acc[SUMS ? NV : 1];
+  hdet_f4 row_a[NV], row_b[SUMS ? NV : 1], acc[SUMS ? NV : 1];
+#define OWNED(i) ((i) < NV - SLACK || tid + BS * (i) < c4)
+  auto fetch = [&](hdet_f4* dst, int row) {
 #pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    if (SUMS) {
+    for (int i = 0; i < NV; ++i)
+      if (OWNED(i)) dst[i] = hdet_ld4_stream(logits + ((int64_t)r * rows + row) * classes + 4 * (tid + BS * i));
+  };
+  if (SUMS) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i].v[j] = 0.f;
-    }
-    if (tid + BS * i < c4 && row0 < row1) cur[i] = hdet_ld4_stream(logits + ((int64_t)r * rows + row0) * classes + 4 * (tid + BS * i));
+    for (int i = 0; i < NV; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[SUMS ? i : 0].v[j] = 0.f;
   }
-  for (int row = row0; row < row1; ++row) {
+  auto one_row = [&](int row, hdet_f4* cur) {
     const int64_t gr = (int64_t)r * rows + row;
-    if (SUMS && row + 1 < row1) {
-#pragma unroll
-      for (int i = 0; i < NV; ++i)
-        if (tid + BS * i < c4) nxt[i] = hdet_ld4_stream(logits + (gr + 1) * classes + 4 * (tid + BS * i));
-    }
     float mx = -INFINITY, sz = 0.f, unused = 0.f;
 #pragma unroll
     for (int i = 0; i < NV; ++i)
-      if (tid + BS * i < c4) {
+      if (OWNED(i)) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) { mx = fmaxf(mx, cur[i].v[j]); sz += cur[i].v[j]; }
       }
@@ -184,7 +188,7 @@ __global__ __launch_bounds__(BS, SUMS ? 2 : 4) void xent_row_kernel(const float*
     float se = 0.f;
 #pragma unroll
     for (int i = 0; i < NV; ++i)
-      if (tid + BS * i < c4) {
+      if (OWNED(i)) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) { cur[i].v[j] = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[i].v[j], kLog2e, -mxl)); se += cur[i].v[j]; }
       }
@@ -196,7 +200,7 @@ __global__ __launch_bounds__(BS, SUMS ? 2 : 4) void xent_row_kernel(const float*
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       const int ch = tid + BS * i;
-      if (ch < c4) {
+      if (OWNED(i)) {
         hdet_f4 o;
 #pragma unroll
         for (int j = 0; j < 4; ++j) o.v[j] = __builtin_fmaf(cur[i].v[j], a, -missb);
@@ -207,31 +211,40 @@ __global__ __launch_bounds__(BS, SUMS ? 2 : 4) void xent_row_kernel(const float*
         }
         hdet_st4_stream(dl + 4 * ch, o);
         if (SUMS) {
+          hdet_f4& t = acc[SUMS ? i : 0];
           if (sizeof(T) == 2) {
             const unsigned u0 = hdet_bf16_pack(o.v[0], o.v[1]), u1 = hdet_bf16_pack(o.v[2], o.v[3]);
-            acc[i].v[0] += __uint_as_float(u0 << 16);
-            acc[i].v[1] += __uint_as_float(u0 & 0xffff0000u);
-            acc[i].v[2] += __uint_as_float(u1 << 16);
-            acc[i].v[3] += __uint_as_float(u1 & 0xffff0000u);
+            t.v[0] += __uint_as_float(u0 << 16);
+            t.v[1] += __uint_as_float(u0 & 0xffff0000u);
+            t.v[2] += __uint_as_float(u1 << 16);
+            t.v[3] += __uint_as_float(u1 & 0xffff0000u);
           } else {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc[i].v[j] += o.v[j];
+            for (int j = 0; j < 4; ++j) t.v[j] += o.v[j];
           }
         }
       }
     }
     if (tid == 0) row_loss[gr] = logf(se) - hit * (logits[gr * classes + y] - mx) - eps * (sz / (float)classes - mx);
-    if (SUMS) {
-#pragma unroll
-      for (int i = 0; i < NV; ++i) cur[i] = nxt[i];
+  };
+  if (row0 < row1) fetch(row_a, row0);
+  if (!SUMS) {
+    if (row0 < row1) one_row(row0, row_a);                           // one row to a block
+    return;
+  }
+  for (int row = row0; row < row1; row += 2) {                      // the rows' registers take turns
+    if (row + 1 < row1) fetch(row_b, row + 1);
+    one_row(row, row_a);
+    if (row + 1 < row1) {
+      if (row + 2 < row1) fetch(row_a, row + 2);
+      one_row(row + 1, row_b);
     }
   }
-  if (SUMS) {
-    float* cs = colsum + ((int64_t)r * gridDim.x + blockIdx.x) * classes;
+  float* cs = colsum + ((int64_t)r * gridDim.x + blockIdx.x) * classes;
 #pragma unroll
-    for (int i = 0; i < NV; ++i)
-      if (tid + BS * i < c4) *reinterpret_cast<hdet_f4*>(cs + 4 * (tid + BS * i)) = acc[i];
-  }
+  for (int i = 0; i < NV; ++i)
+    if (OWNED(i)) *reinterpret_cast<hdet_f4*>(cs + 4 * (tid + BS * i)) = acc[SUMS ? i : 0];
+#undef OWNED
 }
 
 // one block per replica (see hdet_reduce_loss)
@@ -267,20 +280,24 @@ hipError_t hdet_launch_xent(bool bf16, const float* logits, const int32_t* label
     const bool sums = colsum != nullptr && rows_per_block > 0;
     if (!sums) rows_per_block = 1;
     const dim3 grid((rows + rows_per_block - 1) / rows_per_block, n_replicas);
-#define HDET_XENT_ROW(T, BS, NV, SUMS) \
-  hipLaunchKernelGGL((xent_row_kernel<T, BS, NV, SUMS>), grid, dim3(BS), 0, s, logits, labels, rows, classes, rows_per_block, (T*)dlogits, row_loss, ctrl, ls_channel, colsum, grad_rows)
-#define HDET_XENT_ROW_T(BS, NV, SUMS)        \
-  do {                                       \
-    if (bf16) HDET_XENT_ROW(uint16_t, BS, NV, SUMS); \
-    else HDET_XENT_ROW(float, BS, NV, SUMS); \
+    if (sums && !bf16) return hipErrorInvalidValue;          // full precision takes the sums elsewhere
+#define HDET_XENT_ROW(T, BS, NV, SLACK, SUMS) \
+  hipLaunchKernelGGL((xent_row_kernel<T, BS, NV, SLACK, SUMS>), grid, dim3(BS), 0, s, logits, labels, rows, classes, rows_per_block, (T*)dlogits, row_loss, ctrl, ls_channel, colsum, grad_rows)
+#define HDET_XENT_ROW_T(BS, NV, SLACK)                    \
+  do {                                                    \
+    if (sums) HDET_XENT_ROW(uint16_t, BS, NV, SLACK, true); \
+    else if (bf16) HDET_XENT_ROW(uint16_t, BS, NV, SLACK, false); \
+    else HDET_XENT_ROW(float, BS, NV, SLACK, false);      \
   } while (0)
-    if (classes <= 8192) {
-      if (sums) HDET_XENT_ROW_T(256, 8, true);
-      else HDET_XENT_ROW_T(256, 8, false);
-    } else {
-      if (sums) HDET_XENT_ROW_T(512, 16, true);
-      else HDET_XENT_ROW_T(512, 16, false);
-    }
+    const int per256 = (classes / 4 + 255) / 256, per512 = (classes / 4 + 511) / 512;
+    if (per256 <= 2) HDET_XENT_ROW_T(256, 2, 1);             // the narrowest rows have 512 chunks: a thread owns one at least
+    else if (per256 <= 4) HDET_XENT_ROW_T(256, 4, 2);
+    else if (per256 <= 6) HDET_XENT_ROW_T(256, 6, 2);
+    else if (per256 <= 8) HDET_XENT_ROW_T(256, 8, 2);
+    else if (per512 <= 8) HDET_XENT_ROW_T(512, 8, 4);
+    else if (per512 <= 12) HDET_XENT_ROW_T(512, 12, 4);
+    else if (per512 <= 14) HDET_XENT_ROW_T(512, 14, 2);
+    else HDET_XENT_ROW_T(512, 16, 2);
 #undef HDET_XENT_ROW_T
 #undef HDET_XENT_ROW
     return hipGetLastError();
