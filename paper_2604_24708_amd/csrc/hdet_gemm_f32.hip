@@ -15,7 +15,7 @@
 //    K = 1024 in 8 parts is 16 steps per wavefront instead of 128.
 // Loads are dword aligned only (odd leading dimensions are common here); rows beyond the matrix are clamped to its
 // last row (their results are not stored), the K mod 8 tail is a separate masked step.
-// Measured against a 64 x 64 tile staged through LDS on the vector units (us per launch, 4 replicas, same box):
+// Measured against a 64 x 64 tile staged through LDS on the vector units (us per launch, 4 replicas, same machine):
 //   512 x 256, K = 1024 (NT)  152 -> 17;   512 x 256, K = 4000 (NN)  270 -> 46;   4000 x 256, K = 512 (TN)  104 -> 46 (91 TFLOP/s);
 //   128 x 64, K = 64 (NT)     15 -> 4;     128 x 64, K = 512 (NN)    80 -> 6.
 
@@ -271,7 +271,7 @@ tiles tile_grid(const hdet_sgemm_args& g, int batch) {
 }
 
 // Tile and K split by the number of blocks a launch would have, b(tm x tn) = tiles over the whole batch, on 256 CUs
-// (microseconds over 8 replicas or as given, same box; chosen | other candidates):
+// (microseconds over 8 replicas or as given, same machine; chosen | other candidates):
 //   few tiles: 32 x 32, K in 4.        128 x 64, K = 64, 4 items: 3.9 | 64 x 32 4.3 | 64 x 64 5.2 (K in 8: 4.3, in 16: 4.1)
 //   up to one 64 x 32 block per CU (and at least 5/8 of them), K in 4:
 //                                      512 x 256, K = 1024, 4 items: 15.4 | 32 x 32 22.4 | 64 x 64 22.8
