@@ -10,8 +10,9 @@
 // epilogues.  bf16 precision (fp32 master weights): the matrix-core GEMM of
 // hdet_gemm_bf16.hip on the bf16 copy of the parameters; every activation and activation
 // gradient that goes to memory is bf16 except the logits; biases, loss and parameter
-// gradients are fp32.  Both: a column-sum for the bias gradients and a wavefront-per-row
-// softmax cross-entropy whose per-replica mean is reduced in a fixed order.
+// gradients are fp32.  Bias gradients come with the weight gradients' products, or from a
+// column sum where the LDS-direct kernel forms those.  Both precisions: a wavefront-per-row
+// softmax cross-entropy (a block per wide row) whose per-replica mean is reduced in a fixed order.
 
 #include <vector>
 
