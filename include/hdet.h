@@ -285,8 +285,8 @@ int hdet_set_state(hdet_handle* h, const hdet_state* in);
 
 /* Kernel selection, for measurements and tests.  variant 0 (default): the fastest update
  * kernel for the case (one thread per replica column, or -- when gradients or parameters
- * must cross the replica axis and N <= 16 -- one wavefront per replica with an LDS
- * exchange); variant 1: the general kernel in which one thread walks the replica axis (any
+ * must cross the replica axis -- a wavefront for each one to four replicas with an LDS
+ * exchange, or the general kernel where that is faster); variant 1: the general kernel in which one thread walks the replica axis (any
  * N).  `blocks` > 0 sets the grid of the grid-stride kernels (0: library default).
  * variant | 2: the transformer's attention runs as separate batched GEMMs and softmax
  * kernels (scores and probabilities in device memory) also where the fused kernels apply.

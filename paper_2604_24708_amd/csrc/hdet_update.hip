@@ -20,8 +20,9 @@
 //             replica axis through LDS, each wavefront then writes its own plane.  Keeps
 //             the register footprint of the plane kernel instead of N columns per thread.
 //   state  -- the wave kernel's form for one set of moments and whole columns.
-//   loop   -- one thread walks the replica axis of a column; on request (hdet_set_launch_shape) and
-//             for planes of more columns than a grid holds.
+//   loop   -- one thread walks the replica axis of a column; on request (hdet_set_launch_shape), for
+//             planes of more columns than a grid holds, and beyond 16 replicas at the sizes that
+//             loop_walks_better names.
 // The P mod 4 trailing parameters are one more column in the plane and wave kernels, read and
 // written element by element (ld_col / st_col): a launch of their own cost 3 to 6 us, as much as
 // the whole update of a small model.
@@ -325,7 +326,7 @@ __global__ __launch_bounds__(kMaxWaves * 64) void hdet_converge_wave_kernel(cons
 
 // ---------------------------------------------------------------------------------------
 // loop kernel: one thread walks the replica axis of a column of width T (f4 or float).  Bound by the loads in flight: a
-// column's replicas are a chain of memory latencies unless several are requested at once (kAhead).
+// column's replicas are a chain of memory latencies, which only many columns at a time hide.
 // ---------------------------------------------------------------------------------------
 
 template <int OPT, bool SHARED, bool CONV, bool SSTATE, typename T>
@@ -468,14 +469,32 @@ wave_shape wave_launch(int64_t n_params, int n) {
   return w;
 }
 
-// Beyond 16 replicas the loop kernel stays where its grid is resident in one piece and still fills the chip (2.5 to 4.5
-// blocks of 256 columns per CU, 0.65 to 1.2 million parameters): it then walks the planes one after the other, which the
-// memory side likes better than the wave kernel's N planes side by side.  us, one set of moments, loop / wave:
-//   N = 32:  P = 0.1e6 20 / 10,  0.3e6 64 / 26,  1e6 67 / 74,  2e6 161 / 145,  8e6 608 / 574
-//   N = 64:  P = 0.1e6 57 / 19,  0.3e6 125 / 52,  0.7e6 106 / 112,  2e6 333 / 311
-bool loop_walks_better(int64_t n_params, int n) {
-  const int64_t columns = n_params >> 2;
-  return n > kMaxWaves && 2 * columns >= 5 * 256 * kThreads && 2 * columns <= 9 * 256 * kThreads;
+// Beyond 16 replicas: whether the loop kernel takes a launch.  Up to a block or two of 256 columns per CU it is bound by the
+// latency of a thread's walk along the replicas, two to five times slower than the wave kernel; from there on it walks the
+// planes one after the other, which the memory side likes better than the wave kernel's N planes side by side, until its grid
+// no longer runs in one piece.  With one set of moments and 33 replicas or more it stays ahead for good: the wave kernel then
+// has a block of up to 16 wavefronts per CU and its exchanges stand alone.  The lines are in blocks per CU (a quarter each), by
+// what crosses the replica axis.  Single sizes scatter by 10 % with the planes' distance, so the figures are wave / loop, the
+// geometric mean over one to three sizes in each range of P (256 CUs):
+//                            0.12-0.2e6 0.3-0.4e6 0.4-0.5e6 0.5-0.62e6 0.8-1e6 1.2-1.5e6 1.5-1.9e6 1.9-2.5e6 3.5-5.5e6
+//   one set,       N = 32      0.40      0.65      0.82      0.85      1.12     1.11      1.11      0.94      0.97
+//   one set,       N = 48      0.42      0.74      0.92      1.05      1.23     1.19      1.35      1.09      1.10
+//   one set, conv, N = 48      0.72      0.97      1.15      1.13      1.28     1.26      1.30      1.25      1.21
+//   AdamW, mean,   N = 32      0.36      0.77      0.97      0.91      1.10     1.00      1.03      0.99      1.00
+//   SGD, mean,     N = 48      0.47      0.88      1.00      0.95      1.03     1.01      1.12      0.99      0.97
+//   AdamW, conv,   N = 48      0.78      1.06      1.20      1.01      1.01     0.94      1.01      0.97      0.96
+//   converge alone (with a plane update), N = 32  0.96  1.08  1.06  1.00  1.04  0.99      0.99      0.98      0.99
+struct crossing { bool mean, one_set, conv; };      // gradients; ... with one set of moments; parameters
+bool loop_walks_better(int64_t n_params, int n, const crossing& x) {
+  if (n <= kMaxWaves) return false;
+  const int64_t quarters = (n_params >> 2) * 4 / (kThreads * (int64_t)hdet_compute_units());
+  if (x.one_set && n > 2 * kMaxWaves) return quarters >= (x.conv ? 8 : 10);
+  if (x.mean) return quarters >= 10 && quarters < 28;
+  return quarters >= 6 && quarters < 12;
+}
+bool converge_loop_walks_better(int64_t n_params, int n) {
+  const int64_t quarters = (n_params >> 2) * 4 / (kThreads * (int64_t)hdet_compute_units());
+  return n > kMaxWaves && quarters >= 3 && quarters < 16;
 }
 
 template <int OPT, bool SHARED, bool CONV, bool SSTATE = false>
@@ -490,7 +509,7 @@ void launch_variant(const hdet_update_args& a, int variant, int blocks, hipStrea
       hipLaunchKernelGGL((hdet_update_plane_kernel<OPT>), dim3((unsigned)bx, n), dim3(kThreads), 0, stream, a);
       return;
     }
-  } else if (variant == 0 && !loop_walks_better(a.n_params, n)) {
+  } else if (variant == 0 && !loop_walks_better(a.n_params, n, {SHARED, SSTATE, CONV})) {
     const wave_shape w = wave_launch(a.n_params, n);
     if (w.bx <= 0x7fffffff) {
       const dim3 grid((unsigned)w.bx), block(64 * w.groups * w.waves);
@@ -544,7 +563,7 @@ hipError_t hdet_launch_update(const hdet_update_args& a, int optimizer, bool sha
 
 hipError_t hdet_launch_converge(const hdet_converge_args& a, int variant, int blocks, hipStream_t stream) {
   const wave_shape w = wave_launch(a.n_params, a.n_replicas);
-  if (variant == 0 && w.bx <= 0x7fffffff) {
+  if (variant == 0 && w.bx <= 0x7fffffff && !converge_loop_walks_better(a.n_params, a.n_replicas)) {
     const dim3 grid((unsigned)w.bx), block(64 * w.groups * w.waves);
     if (w.r == 1) hipLaunchKernelGGL(hdet_converge_wave_kernel<1>, grid, block, 0, stream, a, w.groups, w.waves);
     else if (w.r == 2) hipLaunchKernelGGL(hdet_converge_wave_kernel<2>, grid, block, 0, stream, a, w.groups, w.waves);

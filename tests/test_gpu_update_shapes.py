@@ -51,3 +51,61 @@ def test_bf16_copy_of_trailing_parameters(n):
         assert torch.all(sh[:, P:] == 3.0)
         assert (t % 2 == 1) or torch.equal(th[:, :P], th[:1, :P].expand(n, P))
     H.hdet_destroy(h)
+
+
+def _flat_handle(n, P, opt, shared, one_state, variant, seed):
+    """Planes of a run in its middle (not in the oracle: these sizes only have to agree between kernels)."""
+    g = torch.Generator(device="cuda:0").manual_seed(seed)
+    stride = (P + 3) // 4 * 4 + 8
+    theta = torch.randn((n, stride), device="cuda:0", generator=g)
+    planes = 1 if one_state else n
+    m = 1e-3 * torch.randn((planes, stride), device="cuda:0", generator=g)
+    v = torch.rand((planes, stride), device="cuda:0", generator=g) * 1e-6 if opt == H.HDET_ADAMW else None
+    grads = 1e-2 * torch.randn((n, stride), device="cuda:0", generator=g)
+    cfg = H.make_config(n_replicas=n, sync_interval=2, total_steps=1 << 20, warm_steps=0, lr_max=1e-3, alpha=0.1, model_kind=H.HDET_FLAT,
+                        n_params=P, optimizer=opt, grad_mode=H.HDET_GRAD_SHARED if shared else H.HDET_GRAD_PER_REPLICA,
+                        shared_opt_state=int(one_state), autolr_enabled=0, constant_lr=1)
+    h = H.hdet_create(cfg, theta, m, v, plane_stride=stride)
+    if variant:
+        H.hdet_set_launch_shape(h, variant, 0)
+    return h, theta, m, v, grads
+
+
+# blocks of 256 columns per compute unit at which a rule for more than 16 replicas changes kernel
+@pytest.mark.parametrize("blocks", [0.75, 1.5, 2.0, 2.5, 3.0, 4.0, 7.0])
+@pytest.mark.parametrize("n,opt,shared,one_state", [(17, "adamw", True, True), (33, "adamw", True, True), (18, "sgdm", True, False), (33, "sgdm", False, False)])
+def test_both_sides_of_each_line_give_the_same_bits(n, opt, shared, one_state, blocks):
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    opt = H.HDET_ADAMW if opt == "adamw" else H.HDET_SGDM
+    edge = int(blocks * 256 * cus) * 4
+    for P in (edge - 1, edge):
+        a, b = (_flat_handle(n, P, opt, shared, one_state, variant, 5) for variant in (1, 0))
+        for fuse in (0, H.HDET_FUSE_CONVERGE, 0, 0):          # steps 2 and 4 are sync steps: converge fused, then standing alone
+            for h, _, _, _, g in (a, b):
+                H.hdet_fanout_step(h, g, fuse)
+        for h in (a[0], b[0]):
+            H.hdet_converge(h)
+        torch.cuda.synchronize()
+        assert all(torch.equal(x, y) for x, y in zip(a[1:4], b[1:4]) if x is not None)
+        assert torch.equal(b[1][:, :P], b[1][:1, :P].expand(n, P))
+        H.hdet_destroy(a[0]); H.hdet_destroy(b[0])
+
+
+@pytest.mark.parametrize("n,P,fuse", [(48, 1_300_000, 0), (64, 1_700_000, 0), (64, 2_500_000, 1)])
+def test_the_default_kernel_keeps_pace_with_the_general_one(n, P, fuse):
+    """One set of moments and many replicas, where a wavefront's several replicas have been 20 to 35 % slower than one thread's walk."""
+    best = [1e30, 1e30]
+    runs = [_flat_handle(n, P, H.HDET_ADAMW, True, True, variant, 6) for variant in (1, 0)]
+    t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    for turn in range(6):
+        for i, (h, _, _, _, g) in enumerate(runs):
+            t0.record()
+            for _ in range(10):
+                H.hdet_fanout_step(h, g, H.HDET_FUSE_CONVERGE if fuse else 0)
+            t1.record()
+            torch.cuda.synchronize()
+            if turn:
+                best[i] = min(best[i], t0.elapsed_time(t1))
+    for h, *_ in runs:
+        H.hdet_destroy(h)
+    assert best[1] <= 1.08 * best[0]
