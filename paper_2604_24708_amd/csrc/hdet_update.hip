@@ -240,12 +240,14 @@ __global__ __launch_bounds__(kMaxWaves * 64) void hdet_update_wave_kernel(const 
   }
 }
 
-// The wave kernel for one set of moments, 2 to 16 replicas and large planes: whole columns only, 16-byte accesses without a
-// mask of their own.  The order in which the streams reach the memory decides here: the general form, whose accesses are
-// masked one by one, is 1 to 4 % slower on planes of several hundred MB (and up to 10 % faster in the other forms), but has
-// the trailing parameters in the same launch: it is taken where there are any, up to 4 million parameters, where a launch of
-// their own would cost more than the rest gains.  us, this / general:  N = 8, P = 20e6 379 / 381;  N = 16, P = 5e6 184 / 192;
-// with a launch for three trailing parameters, N = 8, P = 2e6 47 / 40, P = 20e6 379 / 378.
+// The wave kernel for one set of moments and 2 to 16 replicas: whole columns only, 16-byte accesses without a mask of their own.
+// The order in which the streams reach the memory decides here: the general form, whose accesses are masked one by one, is up
+// to 5 % slower (and up to 10 % faster in the other forms of update), but has the trailing parameters in the same launch.  With
+// some, a launch of their own (3 to 4 us) pays from 9 replicas and 4 million parameters on.  One kernel that holds both forms
+// needs more than 64 registers a lane: up to 50 % slower.  us, this / general:
+//   none trailing:   N = 5, P = 8e6 108 / 113;  N = 8, P = 20e6 370 / 368;  N = 12, P = 20e6 595 / 607;  N = 16, P = 4e6 146 / 154
+//   some, with their launch:  N = 2, P = 4e6 31 / 28;  N = 8, P = 4e6 79 / 75, P = 12e6 224 / 225, P = 90e6 1694 / 1698;
+//                             N = 9, P = 8e6 180 / 194;  N = 12, P = 3e6 99 / 93, P = 12e6 356 / 364;  N = 16, P = 30e6 1129 / 1166
 template <bool CONV>
 __global__ __launch_bounds__(kMaxWaves * 64) void hdet_update_state_kernel(const hdet_update_args a, const int groups) {
   __shared__ exchange_buf<1> ex;
@@ -452,7 +454,8 @@ int clamp_blocks(int64_t n_params, int blocks) {
   return (int)(need < blocks ? need : blocks);
 }
 
-constexpr int64_t kStateParams = 4000000;      // see hdet_update_state_kernel
+constexpr int kStateReplicas = 9;              // see hdet_update_state_kernel
+constexpr int64_t kStateParams = 4000000;
 
 // Shape of a wave-kernel launch: R replicas per wavefront, 512-thread blocks of several column groups while R = 1.
 struct wave_shape {
@@ -514,7 +517,7 @@ void launch_variant(const hdet_update_args& a, int variant, int blocks, hipStrea
     if (w.bx <= 0x7fffffff) {
       const dim3 grid((unsigned)w.bx), block(64 * w.groups * w.waves);
       if constexpr (SSTATE) {
-        if (w.r == 1 && n > 1 && ((a.n_params & 3) == 0 || a.n_params >= kStateParams)) {
+        if (w.r == 1 && n > 1 && ((a.n_params & 3) == 0 || (n >= kStateReplicas && a.n_params >= kStateParams))) {
           hipLaunchKernelGGL((hdet_update_state_kernel<CONV>), grid, block, 0, stream, a, w.groups);
           const int64_t whole = a.n_params & ~(int64_t)3;
           if (whole == a.n_params) return;

@@ -109,3 +109,34 @@ def test_the_default_kernel_keeps_pace_with_the_general_one(n, P, fuse):
     for h, *_ in runs:
         H.hdet_destroy(h)
     assert best[1] <= 1.08 * best[0]
+
+
+@pytest.mark.parametrize("n", [8, 9, 16])
+@pytest.mark.parametrize("P", [3_999_999, 4_000_000, 4_000_001, 4_000_003])
+def test_one_set_of_moments_with_and_without_trailing_parameters(n, P):
+    a, b = (_flat_handle(n, P, H.HDET_ADAMW, True, True, variant, 8) for variant in (1, 0))
+    for fuse in (0, H.HDET_FUSE_CONVERGE):
+        for h, _, _, _, g in (a, b):
+            H.hdet_fanout_step(h, g, fuse)
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, y) for x, y in zip(a[1:4], b[1:4]))
+    H.hdet_destroy(a[0]); H.hdet_destroy(b[0])
+
+
+def test_trailing_parameters_of_few_replicas_take_no_launch_of_their_own():
+    """Three parameters more are within the scatter of planes of 4 million, not a launch (3 to 4 us of 28) away."""
+    runs = [_flat_handle(2, P, H.HDET_ADAMW, True, True, 0, 9) for P in (4_000_000, 4_000_003)]
+    best = [1e30, 1e30]
+    t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    for turn in range(6):
+        for i, (h, _, _, _, g) in enumerate(runs):
+            t0.record()
+            for _ in range(30):
+                H.hdet_fanout_step(h, g, 0)
+            t1.record()
+            torch.cuda.synchronize()
+            if turn:
+                best[i] = min(best[i], t0.elapsed_time(t1))
+    for h, *_ in runs:
+        H.hdet_destroy(h)
+    assert best[1] <= 1.07 * best[0]
