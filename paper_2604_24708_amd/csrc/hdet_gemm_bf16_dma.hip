@@ -141,7 +141,8 @@ struct lds_tile {
 
 // Two blocks share a CU when their stages fit twice into the 160 KiB of LDS; the register budget
 // follows (second launch-bound argument: wavefronts per SIMD).
-template <bool A_KMAJOR, bool B_KMAJOR, int EPI, int TM, int TN, int WGM, int WGN, int NST, int TK>
+// STREAM: results are written past the L2 (stream_result).
+template <bool A_KMAJOR, bool B_KMAJOR, int EPI, int TM, int TN, int WGM, int WGN, int NST, int TK, bool STREAM>
 __global__ __launch_bounds__(64 * WGM * WGN, (NST * (TM + TN) * TK * 2 <= 80 * 1024 ? 2 : 1) * (WGM * WGN / 4))
 void hdet_bgemm_dma_kernel(const hdet_bgemm_args g) {
   constexpr int THREADS = 64 * WGM * WGN;
@@ -281,10 +282,10 @@ void hdet_bgemm_dma_kernel(const hdet_bgemm_args g) {
   static_assert(WGM * WGN * 32 * EP * 4 <= NST * STAGE * 2, "staging area exceeds the stage buffers");
   float* stg = reinterpret_cast<float*>(S) + wave * (32 * EP);
   const int lr = lane / LPR, lc = (lane % LPR) * 4;
-  // Results are written past the L2, where they would push out the operand tiles that the blocks of an XCD share:
-  // 8192 x 4096 x 8 at K = 1024 with both GELU outputs 622 -> 582 us alone; steps of the 6-layer transformer 1.6 %, of long
-  // sequences 2 % shorter, also where the next kernel reads the result at once.
-  auto put = [&](auto* p, auto v) { __builtin_nontemporal_store(v, p); };
+  auto put = [&](auto* p, auto v) {
+    if (STREAM) __builtin_nontemporal_store(v, p);
+    else *p = v;
+  };
   constexpr bool kBias = EPI == HDET_EPI_BIAS_RELU_BF16 || EPI == HDET_EPI_BIAS_F32 || EPI == HDET_EPI_BIAS_BF16 ||
                          EPI == HDET_EPI_BIAS_GELU_BF16 || EPI == HDET_EPI_BIAS_RESID_BF16 || EPI == HDET_EPI_BIAS_DROP_RESID_BF16;
   // the second operand of the gating epilogues (the activations a ReLU or GELU gradient looks at) is
@@ -488,6 +489,38 @@ int hdet_compute_units() {
 
 namespace {
 
+// Whether a launch writes its results past the L2, where they would push out the operand tiles that the blocks of an XCD share.
+// That wins while the rows are whole 128-byte lines, also where the next kernel reads the result at once.  Rows that begin inside
+// a line leave partial lines on either side of every tile, which the L2 puts together and the memory does not: such results go
+// through the L2 unless the product is long enough, by epilogue, to hide that.  us, past / through (M = 4096, 8 items; pitch mod 128):
+//   whole lines: logits 4096 wide K = 128 100 / 127, K = 512 178 / 211, 30016 wide K = 64 714 / 817;  both GELU outputs K = 512,
+//                4 items 98 / 109;  ReLU 4096 wide K = 256 109 / 132;  2048 x 2048 weight gradients K = 512 43 / 45, K = 64 27 / 25
+//   half lines (64): logits 30000 wide K = 256 956 / 1207, 10000 wide K = 64 292 / 260;  weight gradients K = 64 31 / 26, K = 1024 93 / 91
+//   others: logits 5000 wide (32) K = 64 207 / 143, K = 256 213 / 201, K = 1024 362 / 375, 29996 wide K = 128 1477 / 1113;
+//           both GELU outputs 2056 wide (16) K = 64 154 / 71, K = 512 150 / 127, 6168 wide K = 2048 843 / 918;
+//           input gradient 2056 wide K = 256 70 / 62, K = 1024 155 / 148;  weight gradients 2056 wide K = 256 49 / 37;
+//           bias 6168 wide (48) K = 128 188 / 151, K = 512 259 / 264, 2056 wide K = 512 104 / 96;  ReLU 4104 wide K = 128 104 / 112;
+//           ReLU gate 2056 wide K = 128 79 / 79, K = 512 106 / 131;  residual 2056 wide K = 512 117 / 133, 1000 wide K = 256 46 / 39;
+//           GELU gradient 2056 wide K = 64 83 / 87, K = 512 122 / 146
+// (the update epilogue writes no result)
+template <int EPI> constexpr bool kAlwaysStream = EPI == HDET_EPI_ADAMW || EPI == HDET_EPI_GELUGRAD_BF16;
+bool stream_result(const hdet_bgemm_args& g, int epi, int batch) {
+  const int64_t size = epi == HDET_EPI_F32 || epi == HDET_EPI_BIAS_F32 ? 4 : 2;
+  const uint64_t part = (reinterpret_cast<uintptr_t>(g.c) | (uint64_t)((g.ldc | g.c_s[0] | g.c_s[1] | g.c_s[2]) * size)) & 127;
+  if (part == 0) return true;
+  if (part == 64 && epi != HDET_EPI_F32) return epi != HDET_EPI_BIAS_F32 || g.k >= 128;
+  const bool large = (int64_t)batch * g.m * g.n * size > (int64_t)256 << 20;       // more than the memory-side cache holds
+  switch (epi) {
+    case HDET_EPI_MASK_BF16: return g.k >= 256;
+    case HDET_EPI_BIAS_RESID_BF16: case HDET_EPI_BIAS_DROP_RESID_BF16: return g.k >= 512;
+    case HDET_EPI_BIAS_F32: return large && g.k >= 512;
+    case HDET_EPI_BIAS_RELU_BF16: return large && g.k >= 128;
+    case HDET_EPI_BIAS_BF16: return large && g.k >= 256;
+    case HDET_EPI_BIAS_GELU_BF16: case HDET_EPI_BF16: return large && g.k >= 2048;
+  }
+  return false;
+}
+
 template <bool AK, bool BK, int EPI>
 hipError_t launch_shape(const hdet_bgemm_args& g, int batch, hipStream_t s) {
   auto blocks = [&](int tm, int tn) { return (int64_t)((g.m + tm - 1) / tm) * ((g.n + tn - 1) / tn) * batch; };
@@ -498,12 +531,16 @@ hipError_t launch_shape(const hdet_bgemm_args& g, int batch, hipStream_t s) {
   // Tile order inside a batch item: with many tile columns, the 32 blocks an XCD runs at a time would share one
   // operand tile of A and none of B; walking groups of 4 (2) tile rows column by column cuts the operand bytes its L2
   // has to fetch by up to two thirds (head product of the transformer, 125 tile columns: 9-11 % faster).
+  const bool stream = kAlwaysStream<EPI> || stream_result(g, EPI, batch);
+#define HDET_DMA_KERNEL(TM, TN, WGM, WGN, NST, TK, STREAM) \
+  hipLaunchKernelGGL((hdet_bgemm_dma_kernel<AK, BK, EPI, TM, TN, WGM, WGN, NST, TK, STREAM>), grid, dim3(64 * WGM * WGN), 0, s, ga)
 #define HDET_DMA_LAUNCH(TM, TN, WGM, WGN, NST, TK)                                                            \
   do {                                                                                                        \
     const dim3 grid((g.n + TN - 1) / TN, (g.m + TM - 1) / TM, batch);                                          \
     hdet_bgemm_args ga = g;                                                                                   \
     ga.tile_group = grid.x >= 64 ? 4 : grid.x >= 12 ? 2 : 1;                                                  \
-    hipLaunchKernelGGL((hdet_bgemm_dma_kernel<AK, BK, EPI, TM, TN, WGM, WGN, NST, TK>), grid, dim3(64 * WGM * WGN), 0, s, ga); \
+    if (stream) HDET_DMA_KERNEL(TM, TN, WGM, WGN, NST, TK, true);                                             \
+    else if constexpr (!kAlwaysStream<EPI>) HDET_DMA_KERNEL(TM, TN, WGM, WGN, NST, TK, false);                \
   } while (0)
   // short-K products with plenty of tiles also take the largest tile, unless the epilogue reads a second
   // operand: those do better with two blocks per CU, whose epilogues and main loops overlap
@@ -526,6 +563,7 @@ hipError_t launch_shape(const hdet_bgemm_args& g, int batch, hipStream_t s) {
     else if constexpr (EPI != HDET_EPI_ADAMW) HDET_DMA_LAUNCH(256, 128, 4, 2, 3, 32);   // two blocks per CU, 72 KiB each
   } else HDET_DMA_LAUNCH(128, 128, 2, 2, 2, 64);                                    // two blocks per CU, 64 KiB each
 #undef HDET_DMA_LAUNCH
+#undef HDET_DMA_KERNEL
   return hipGetLastError();
 }
 
