@@ -80,6 +80,32 @@ __device__ __forceinline__ void rank_ids(const int32_t* __restrict__ ids, int M,
   if (w == 0 && i < M) sorted[cnt[0][lane] + cnt[1][lane] + cnt[2][lane] + cnt[3][lane]] = ((unsigned long long)t << 32) | (uint32_t)i;
 }
 
+// The same order for many rows and replicas: one block per replica sorts the keys in LDS (bitonic network over the next power
+// of two, padded with all-ones keys).  Bound by its barriers, and the same for any number of replicas up to one per CU.
+template <int P2>
+__global__ __launch_bounds__(1024) void tok_sort_kernel(const int32_t* ids, int M, unsigned long long* sorted) {
+  __shared__ unsigned long long keys[P2];
+  const int r = blockIdx.x, tid = threadIdx.x;
+  for (int i = tid; i < P2; i += 1024)
+    keys[i] = i < M ? ((unsigned long long)(uint32_t)ids[(int64_t)r * M + i] << 32) | (uint32_t)i : ~0ull;
+  __syncthreads();
+  for (int k = 2; k <= P2; k <<= 1)
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      for (int t = tid; t < P2 / 2; t += 1024) {
+        const int i = 2 * j * (t / j) + (t % j);
+        const unsigned long long a = keys[i], b = keys[i + j];
+        if ((a > b) == ((i & k) == 0)) { keys[i] = b; keys[i + j] = a; }
+      }
+      __syncthreads();
+    }
+  for (int i = tid; i < M; i += 1024) sorted[(int64_t)r * M + i] = keys[i];
+}
+// Counting costs N M^2 comparisons spread over the chip, sorting grows with M alone: they meet at one N M.  us, counting beside the
+// clearing and the gather / sorting, clearing and gather one after the other (256 CUs): N = 8, M = 16384 170 / 217;  N = 32,
+// M = 4096 52 / 80, M = 8192 153 / 145, M = 16384 525 / 278;  N = 64, M = 4096 84 / 104, M = 8192 279 / 186, M = 16384 995 / 374.
+// Whole passes of a small model, counting / sorting: N M = 147456 982 / 1005, 196608 1379 / 1369, 262144 1810 / 1775.
+bool order_by_sort(int64_t M, int64_t N) { return N * M > 800 * (int64_t)hdet_compute_units(); }
+
 // What a pass needs before its first layer, in one launch: blocks [0, rank_blocks) sort the token ids for the embedding
 // gradient (rank_ids), the next zero_blocks clear that gradient, the rest gather the embeddings.
 template <typename T, bool VEC>
@@ -120,7 +146,8 @@ __global__ __launch_bounds__(256) void embed_bwd_kernel(float* grads, int64_t ps
   }
 }
 // The same sum in a fixed order, for M up to 16384 rows per replica and d a multiple of 8 up to 2048:
-// (1) the rows are ordered by (token id, row) (rank_ids), so that the rows of a token id are adjacent and ascending;
+// (1) the rows are ordered by (token id, row) (rank_ids, or tok_sort_kernel for many rows and replicas), so that the rows of a
+// token id are adjacent and ascending;
 // (2) one wavefront per sorted position: where a new id starts, it adds that id's rows of dx in
 // ascending row order and writes the token's gradient row (the region is zeroed first for the ids
 // that do not occur).
@@ -1367,7 +1394,13 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
   const bool ordered_tok = M <= 16384 && aligned_rows && d <= 2048;       // token-embedding gradient in a fixed order
   {
     const int64_t tok_len = (int64_t)V * d;
-    const unsigned rb = ordered_tok ? (M + 63) / 64 : 0, zb = grid_for((tok_len + 15) / 16), eb = grid_for(aligned_rows ? nd / 8 : nd);
+    const bool sort = ordered_tok && order_by_sort(M, N);
+    if (sort) {
+#define SORT(P2) hipLaunchKernelGGL(tok_sort_kernel<P2>, dim3(N), dim3(1024), 0, s, ids, M, p->tok_sorted)
+      if (M <= 4096) SORT(4096); else if (M <= 8192) SORT(8192); else SORT(16384);
+#undef SORT
+    }
+    const unsigned rb = ordered_tok && !sort ? (M + 63) / 64 : 0, zb = grid_for((tok_len + 15) / 16), eb = grid_for(aligned_rows ? nd / 8 : nd);
 #define EMBED(VEC) hipLaunchKernelGGL((embed_fwd_kernel<T, VEC>), dim3(rb + zb + eb, N), dim3(256), 0, s, theta, ps, p->tok, p->pos, ids, M, S, d, \
                                       (T*)p->x_in[0], rb, p->tok_sorted, zb, grads, tok_len)
     if (aligned_rows) EMBED(true); else EMBED(false);

@@ -1,11 +1,14 @@
 """The token-embedding gradient against the position-embedding gradient: with one sequence per replica the latter holds the
 gradient of every row, so that row sums by token id are the former.  Lengths around the 64 rows that a block orders and the 32
 sorted rows that a wavefront adds up; ids all alike, all different, alternating, and descending."""
+import numpy as np
 import pytest
 import torch
 
 import hdet_inputs as I
 import paper_2604_24708_amd as H
+from oracle import transformer_oracle as T
+from test_gpu_transformer import TfRun, base
 
 pytestmark = pytest.mark.gpu
 
@@ -43,3 +46,24 @@ def test_token_gradient_is_the_sum_of_its_rows(S, d, pattern, bf16):
         # an fp32 sum of k <= S terms in any order: at most k 2^-24 of their absolute sum
         assert torch.all((tok[r] - want).abs() <= S * 2.0 ** -24 * size)
         assert float(size.max()) > 0.0
+
+
+# rows times replicas on both sides of where counting the ids gives way to sorting them (800 rows a compute unit), each size of
+# the sort, and rows that are no power of two
+@pytest.mark.parametrize("n,S,B", [(3, 10, 13), (64, 64, 50), (64, 64, 51), (64, 25, 164), (26, 63, 127), (13, 64, 246), (13, 64, 256), (25, 61, 268)])
+def test_embedding_gradients_against_the_oracle(n, S, B):
+    cfg = dict(n_blocks=1, d_model=8, n_heads=1, d_ff=16, seq_len=S, vocab=150)
+    run = TfRun(base(n_replicas=n), cfg, B)
+    ids, tgt, losses = run.forward_backward(1)
+    run.forward_backward(1)                                  # the second pass finds the first one's gradients in place
+    got = run.g.double().cpu().numpy()
+    k, m = 150 * 8, 150 * 8 + S * 8
+    for r in {0, n // 2, n - 1}:
+        loss, ref = T.loss_and_grad(run.orc.theta[r], ids[r], tgt[r], cfg)
+        assert abs(losses[r] - loss) <= 1e-5 * loss
+        # per row, in norm: a sum of up to a third of the M rows, each off by the few 2^-24 of a chain of fp32 products, and summed
+        # in fp32 (a random walk of up to sqrt(5000) such roundings); one term more or less is 1 / 5000 of the largest sum at least
+        for a, b in ((got[r, :k], ref[:k]), (got[r, k:m], ref[k:m])):
+            a, b = a.reshape(-1, 8), b.reshape(-1, 8).astype(np.float64)
+            assert np.all(np.linalg.norm(a - b, axis=1) <= 4e-5 * np.linalg.norm(b, axis=1) + 1e-6 * np.linalg.norm(b) / np.sqrt(len(b)))
+    run.close()
