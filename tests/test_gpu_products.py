@@ -116,8 +116,8 @@ def test_results_of_no_whole_lines_cost_no_more_than_whole_ones():
         cfg = H.make_config(n_replicas=n, sync_interval=4, total_steps=10, lr_max=1e-3, alpha=0.1, widths=[64, classes], batch=batch,
                             model_kind=H.HDET_MLP, precision=H.HDET_BF16_GEMM_FP32_MASTER)
         ws = torch.empty(H.hdet_workspace_bytes(cfg, theta.shape[1])[2], dtype=torch.uint8, device=dev)
-        h = H.hdet_create(cfg, theta, m, v, grads=g, params_bf16=torch.zeros_like(theta, dtype=torch.bfloat16), workspace=ws,
-                          plane_stride=theta.shape[1])
+        copy = torch.zeros_like(theta, dtype=torch.bfloat16)
+        h = H.hdet_create(cfg, theta, m, v, grads=g, params_bf16=copy, workspace=ws, plane_stride=theta.shape[1])
         t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         times = []
         for _ in range(6):
