@@ -1090,14 +1090,17 @@ hdet_tf_plan* hdet_tf_create(const hdet_config& cfg, const hdet_buffers& buf, in
   }
   p->lnf_g = off; off += d; p->lnf_b = off; off += d;
   p->w_head = off; off += V * d; p->b_head = off; off += V;
-  // stage 2 of the column reductions: one job per bias vector and LayerNorm parameter pair
+  // stage 2 of the column reductions: one job per LayerNorm parameter pair and per bias vector (in fp32 a bias gradient comes with
+  // the weight gradient's product, unless that sums over the replicas)
+  const bool shared = cfg.grad_mode == HDET_GRAD_SHARED;
   int64_t part_off = 0;
   int first_block = 0;
   // producer_g: for the bias of an output projection, the gain offset of the LayerNorm whose backward kernel
-  // produces that bias gradient's input (and, when it is of the fused kind, stage 1 of its column sum); -1 otherwise
-  auto add_job = [&](int cols, int mode, int64_t out_off, int64_t out2_off, int64_t producer_g = -1, int chunks = 0) {
+  // produces that bias gradient's input (and, when it is of the fused kind, stage 1 of its column sum); -1 otherwise.
+  // inputs: columns of a bias's weight matrix
+  auto add_job = [&](int cols, int mode, int64_t out_off, int64_t out2_off, int64_t inputs, int64_t producer_g = -1, int chunks = 0) {
     if (cols % 8 != 0) return;                       // such widths take the single-stage kernel
-    if (!p->bf16 && mode == 0) return;               // fp32 biases come with the weight gradients' products
+    if (!p->bf16 && mode == 0 && !(shared && tf_wgrad_one_product(cols, inputs))) return;
     const bool by_ln = (mode == 1 && hdet_tf_ln_fused(p, out_off)) || (producer_g >= 0 && hdet_tf_ln_fused(p, producer_g));
     const int nchunks = chunks ? chunks : by_ln ? (p->M + kLnRows - 1) / kLnRows : p->nrc;
     colsum_job j = {part_off, out_off, out2_off, cols, mode, first_block, nchunks};
@@ -1106,19 +1109,19 @@ hdet_tf_plan* hdet_tf_create(const hdet_config& cfg, const hdet_buffers& buf, in
     first_block += (cols + 255) / 256;
   };
   const int xr = xent_rows_per_block(p->M, p->N, V);
-  add_job((int)V, 0, p->b_head, 0, -1, xr ? (p->M + xr - 1) / xr : 0);
-  add_job((int)d, 1, p->lnf_g, p->lnf_b);
+  add_job((int)V, 0, p->b_head, 0, d, -1, xr ? (p->M + xr - 1) / xr : 0);
+  add_job((int)d, 1, p->lnf_g, p->lnf_b, 0);
   for (int l = 0; l < p->L; ++l) {
     const tf_block_off& b = p->blk[l];
-    add_job((int)d, 0, b.b_2, 0, l + 1 < p->L ? p->blk[l + 1].ln1_g : p->lnf_g);
-    add_job((int)ff, 0, b.b_1, 0);
-    add_job((int)d, 1, b.ln2_g, b.ln2_b);
-    add_job((int)d, 0, b.b_o, 0, b.ln2_g);
-    add_job(3 * (int)d, 0, b.b_qkv, 0);
-    add_job((int)d, 1, b.ln1_g, b.ln1_b);
+    add_job((int)d, 0, b.b_2, 0, ff, l + 1 < p->L ? p->blk[l + 1].ln1_g : p->lnf_g);
+    add_job((int)ff, 0, b.b_1, 0, d);
+    add_job((int)d, 1, b.ln2_g, b.ln2_b, 0);
+    add_job((int)d, 0, b.b_o, 0, d, b.ln2_g);
+    add_job(3 * (int)d, 0, b.b_qkv, 0, d);
+    add_job((int)d, 1, b.ln1_g, b.ln1_b, 0);
   }
   p->final_blocks = first_block;
-  if (cfg.grad_mode == HDET_GRAD_SHARED) {
+  if (shared) {
     for (int l = 0; l < p->L; ++l) {
       const tf_block_off& o = p->blk[l];
       if (tf_wgrad_one_product(3 * d, d)) p->summed.push_back({o.w_qkv, 3 * d * d});
@@ -1453,7 +1456,7 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
   TF_CHECK(gemm<T>(p, NT, act(p->hf, d), wt(p->w_head, d), p->logits, V, act_v, false, M, V, d, 1, 1, theta + p->b_head, ps, s));
   // the loss kernel for wide rows also forms stage 1 of the head bias gradient, xr rows per chunk
   float* head_part = nullptr;
-  const int xr = sizeof(T) == 2 ? xent_rows_per_block(M, N, V) : 0;
+  const int xr = xent_rows_per_block(M, N, V);
   if (xr)
     for (const colsum_job& j : p->jobs)
       if (j.out_off == p->b_head && j.mode == 0 && j.cols == V && j.nchunks == (M + xr - 1) / xr) { head_part = p->part + j.part_off; break; }
@@ -1506,16 +1509,18 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
                    nullptr, one);
   };
 
-  // fp32: a layer's weight, bias and input gradients in one launch; gelu_pre: the input gradient goes through the GELU there
+  // fp32: a layer's weight, bias and input gradients in one launch; gelu_pre: the input gradient goes through the GELU there.  A
+  // product that sums over the replicas leaves the bias gradients, which stay per replica, to the column sums, unless the launch
+  // that formed dy has left stage 1 of them (bias_done): with N = 8, M = 1024 and 32000 classes the loss kernel and the launch
+  // with stage 2 take 384 + 36 us, without the sums and with one stage over all of dy 357 + 14 + 269.
   auto linear_bwd = [&](const void* dy, int wy, const void* x, int wx, int64_t w_off, int64_t b_off, void* dx, const void* gelu_pre,
-                        const hdet_loss_args* loss) -> hipError_t {
+                        const hdet_loss_args* loss, bool bias_done) -> hipError_t {
     const bool one = shared && tf_wgrad_one_product(wy, wx);
     hdet_sgemm_args g = sgemm_of(TN, act(dy, wy), act(x, wx), grads + w_off, wx, plane, wy, wx, one ? N * M : M, 1, 1);
-    if (one) {            // the product sums over the replicas, the bias gradients stay per replica
-      hipLaunchKernelGGL((colsum_kernel<T, 0>), dim3((wy + 63) / 64, N), dim3(1024), 0, s, (const T*)dy, (int64_t)wy, (int64_t)M * wy, M, wy,
-                         (const T*)nullptr, nullptr, nullptr, grads + b_off, grads, ps);
-    } else {
+    if (!one) {
       g.rowsum = grads + b_off; g.rowsum_bs = ps;
+    } else if (!bias_done) {
+      TF_CHECK(colsum(dy, wy, b_off));
     }
     const int64_t dx_s[3] = {(int64_t)M * wx, 0, 0};
     hdet_sgemm_args dg = sgemm_of(NN, act(dy, wy), wt(w_off, wx), (float*)dx, wx, dx_s, M, wx, wy, 1, 1);
@@ -1525,7 +1530,7 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
 
   if (f32) {
     const hdet_loss_args loss = {p->row_loss, M, ctrl, N};
-    TF_CHECK(linear_bwd(p->dlogits, V, p->hf, d, p->w_head, p->b_head, p->dtmp, nullptr, &loss));
+    TF_CHECK(linear_bwd(p->dlogits, V, p->hf, d, p->w_head, p->b_head, p->dtmp, nullptr, &loss, head_part != nullptr));
   } else {
     if (!head_part) TF_CHECK(colsum(p->dlogits, V, p->b_head));
     TF_CHECK(gemm<T>(p, NN, act(p->dlogits, V), wt(p->w_head, d), p->dtmp, d, act_d, true, M, d, V, 1, 1, nullptr, 0, s));
@@ -1550,8 +1555,8 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
       dy = p->dtmp2;
     }
     if (f32) {
-      TF_CHECK(linear_bwd(dy, d, p->f[l], ff, o.w_2, o.b_2, p->dff, p->z[l], nullptr));
-      TF_CHECK(linear_bwd(p->dff, ff, p->h2[l], d, o.w_1, o.b_1, p->dtmp, nullptr, nullptr));
+      TF_CHECK(linear_bwd(dy, d, p->f[l], ff, o.w_2, o.b_2, p->dff, p->z[l], nullptr, b2_done));
+      TF_CHECK(linear_bwd(p->dff, ff, p->h2[l], d, o.w_1, o.b_1, p->dtmp, nullptr, nullptr, false));
     } else {
       if (!b2_done) TF_CHECK(colsum(dy, d, o.b_2));
       bool b1_done = false;
@@ -1586,7 +1591,7 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
       dob = p->dtmp2;
     }
     if (f32) {
-      TF_CHECK(linear_bwd(dob, d, p->a[l], d, o.w_o, o.b_o, p->dtmp, nullptr, nullptr));
+      TF_CHECK(linear_bwd(dob, d, p->a[l], d, o.w_o, o.b_o, p->dtmp, nullptr, nullptr, bo_done));
     } else {
       if (!bo_done) TF_CHECK(colsum(dob, d, o.b_o));
       TF_CHECK(gemm<T>(p, NN, act(dob, d), wt(o.w_o, d), p->dtmp, d, act_d, true, M, d, d, 1, 1, nullptr, 0, s));   // da
@@ -1619,7 +1624,7 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
       }
     }
     if (f32) {
-      TF_CHECK(linear_bwd(p->dqkv, 3 * d, p->h1[l], d, o.w_qkv, o.b_qkv, p->dtmp, nullptr, nullptr));
+      TF_CHECK(linear_bwd(p->dqkv, 3 * d, p->h1[l], d, o.w_qkv, o.b_qkv, p->dtmp, nullptr, nullptr, false));
     } else {
       TF_CHECK(colsum(p->dqkv, 3 * d, o.b_qkv));
       TF_CHECK(gemm<T>(p, NN, act(p->dqkv, 3 * d), wt(o.w_qkv, d), p->dtmp, d, act_d, true, M, d, 3 * d, 1, 1, nullptr, 0, s));
