@@ -97,7 +97,7 @@ __device__ __forceinline__ us8 load8(const uint16_t* src, int64_t idx, int valid
   return r;
 }
 
-// One operand tile: ROWS (128 or 256) rows of the output dimension x 32 of the contraction.
+// One operand tile: ROWS (64 or 128) rows of the output dimension x 32 of the contraction.
 // KMAJOR: element (row, k) at src[row * ld + k], LDS tile[row][k];
 // otherwise at src[k * ld + row], LDS tile[k][row].
 template <bool KMAJOR, int ROWS, int THREADS>
@@ -190,11 +190,10 @@ __device__ __forceinline__ bf16x8 ones() {
   return __builtin_bit_cast(bf16x8, o);
 }
 
-// WMT x WNT: 32x32 MFMA blocks per wavefront in m and n; WGM x 2 wavefronts per block
-// (WGM = 2: 256 threads, WGM = 4: 512 threads), block tile (32 WMT WGM) x (64 WNT).
-template <bool A_KMAJOR, bool B_KMAJOR, int EPI, int WMT, int WNT, int WGM>
-__global__ __launch_bounds__(128 * WGM, WGM) void hdet_bgemm_kernel(const hdet_bgemm_args g) {
-  constexpr int TM = 32 * WMT * WGM, TN = 64 * WNT, THREADS = 128 * WGM;
+// WT x WT: 32x32 MFMA blocks per wavefront; 2 x 2 wavefronts per block, block tile (64 WT) x (64 WT).
+template <bool A_KMAJOR, bool B_KMAJOR, int EPI, int WT>
+__global__ __launch_bounds__(256, 2) void hdet_bgemm_kernel(const hdet_bgemm_args g) {
+  constexpr int TM = 64 * WT, TN = TM, THREADS = 256;
   __shared__ __attribute__((aligned(16))) uint16_t As[2][tile_elems(TM)];
   __shared__ __attribute__((aligned(16))) uint16_t Bs[2][tile_elems(TN)];
   // Workgroups are dealt round-robin to the 8 XCDs (each with its own L2) in launch order.
@@ -218,23 +217,23 @@ __global__ __launch_bounds__(128 * WGM, WGM) void hdet_bgemm_kernel(const hdet_b
   const int64_t c_base = hdet_batch_offset(bi, g.c_s);
   const int m0 = by * TM, n0 = bx * TN;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = (wave >> 1) * (32 * WMT), wn = (wave & 1) * (32 * WNT);
+  const int wm = (wave >> 1) * (32 * WT), wn = (wave & 1) * (32 * WT);
   const bool a_odd = (g.lda & 1) != 0 || (reinterpret_cast<uintptr_t>(A) & 3) != 0;
   const bool b_odd = (g.ldb & 1) != 0 || (reinterpret_cast<uintptr_t>(B) & 3) != 0;
 
-  f16v acc[WMT][WNT];
+  f16v acc[WT][WT];
 #pragma unroll
-  for (int i = 0; i < WMT; ++i)
+  for (int i = 0; i < WT; ++i)
 #pragma unroll
-    for (int j = 0; j < WNT; ++j)
+    for (int j = 0; j < WT; ++j)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
   constexpr bool SUMS = has_rowsum<A_KMAJOR, B_KMAJOR, EPI>();
   const bool sums = SUMS && g.rowsum && bx == 0 && wn == 0;         // uniform over the wavefront
-  f16v rsum[SUMS ? WMT : 1];
+  f16v rsum[SUMS ? WT : 1];
 #pragma unroll
-  for (int i = 0; i < (SUMS ? WMT : 1); ++i)
+  for (int i = 0; i < (SUMS ? WT : 1); ++i)
 #pragma unroll
     for (int e = 0; e < 16; ++e) rsum[i][e] = 0.f;
 
@@ -265,19 +264,19 @@ __global__ __launch_bounds__(128 * WGM, WGM) void hdet_bgemm_kernel(const hdet_b
     __builtin_amdgcn_sched_barrier(0);     // keep the loads ahead of the MFMAs ...
 #pragma unroll
     for (int ks = 0; ks < TK; ks += 16) {
-      bf16x8 af[WMT], bfr[WNT];
+      bf16x8 af[WT], bfr[WT];
 #pragma unroll
-      for (int i = 0; i < WMT; ++i) af[i] = operand<A_KMAJOR, TM, THREADS>::fragment(As[buf], wm + i * 32, ks, lane);
+      for (int i = 0; i < WT; ++i) af[i] = operand<A_KMAJOR, TM, THREADS>::fragment(As[buf], wm + i * 32, ks, lane);
 #pragma unroll
-      for (int j = 0; j < WNT; ++j) bfr[j] = operand<B_KMAJOR, TN, THREADS>::fragment(Bs[buf], wn + j * 32, ks, lane);
+      for (int j = 0; j < WT; ++j) bfr[j] = operand<B_KMAJOR, TN, THREADS>::fragment(Bs[buf], wn + j * 32, ks, lane);
 #pragma unroll
-      for (int i = 0; i < WMT; ++i)
+      for (int i = 0; i < WT; ++i)
 #pragma unroll
-        for (int j = 0; j < WNT; ++j)
+        for (int j = 0; j < WT; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
       if (SUMS && sums) {
 #pragma unroll
-        for (int i = 0; i < WMT; ++i) rsum[SUMS ? i : 0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], ones(), rsum[SUMS ? i : 0], 0, 0, 0);
+        for (int i = 0; i < WT; ++i) rsum[SUMS ? i : 0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], ones(), rsum[SUMS ? i : 0], 0, 0, 0);
       }
     }
     __builtin_amdgcn_sched_barrier(0);     // ... and every use of the loaded data behind them
@@ -289,15 +288,15 @@ __global__ __launch_bounds__(128 * WGM, WGM) void hdet_bgemm_kernel(const hdet_b
   // epilogue: accumulator element e of lane l is C(row, col) with
   //   row = (e / 4) * 8 + (l / 32) * 4 + e % 4,  col = l % 32   inside its 32x32 block
 #pragma unroll
-  for (int i = 0; i < WMT; ++i)
+  for (int i = 0; i < WT; ++i)
 #pragma unroll
-    for (int j = 0; j < WNT; ++j)
+    for (int j = 0; j < WT; ++j)
 #pragma unroll
       for (int e = 0; e < 16; ++e)
         put_element<EPI>(g, z, c_base, m0 + wm + i * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3), n0 + wn + j * 32 + (lane & 31), acc[i][j][e]);
   if (SUMS && sums && (lane & 31) == 0) {                           // every column holds the sum
 #pragma unroll
-    for (int i = 0; i < WMT; ++i)
+    for (int i = 0; i < WT; ++i)
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const int row = m0 + wm + i * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
@@ -307,8 +306,8 @@ __global__ __launch_bounds__(128 * WGM, WGM) void hdet_bgemm_kernel(const hdet_b
 }
 
 // Products with few output tiles: what counts there is the length of a block's K loop and the wavefronts in flight, as for
-// the fp32 products (hdet_gemm_f32.hip), and the kernel is built the same way.  A wavefront loads the fragments of its
-// (32 WTM) x (32 WTN) tile straight from global memory, U steps of 16 k ahead, without LDS and without a barrier; WK wavefronts
+// the fp32 products (hdet_gemm_f32.hip), and the kernel is built the same way.  A wavefront loads the fragments of the block's
+// 32 x 32 tile straight from global memory, four steps of 16 k ahead, without LDS and without a barrier; WK wavefronts
 // share the contraction and add their partial tiles through LDS in ascending order of k.  An operand contiguous along k is one
 // 16-byte load per lane and fragment (with the funnel shift where chunks start at odd elements); one contiguous along its
 // output axis is eight 2-byte loads, 32 consecutive elements at a time, so that no alignment is needed at all.
@@ -329,11 +328,11 @@ __device__ __forceinline__ us8 frag_load_tail(const uint16_t* src, int64_t lane_
   return r;
 }
 
-template <bool A_KMAJOR, bool B_KMAJOR, int EPI, int WTM, int WTN, int WK, int U>
+template <bool A_KMAJOR, bool B_KMAJOR, int EPI, int WK>
 __global__ __launch_bounds__(64 * WK) void hdet_bgemm_frag_kernel(const hdet_bgemm_args g) {
-  constexpr int NW = WTM * WTN * 16;                                // accumulator registers
-  static_assert(NW % WK == 0, "the wavefronts of a K split share the tile's registers evenly");
-  __shared__ float part[WK > 1 ? WK * NW * 64 : 1];
+  constexpr int U = 4;                                              // steps in flight
+  static_assert(WK > 1 && 16 % WK == 0, "the wavefronts of a K split share the tile's 16 registers evenly");
+  __shared__ float part[WK * 16 * 64];
   unsigned bx, by, bz;
   {   // launch order -> tile: XCD x (launch index mod 8) takes the x-th of eight contiguous ranges of tiles
     const unsigned total = gridDim.x * gridDim.y * gridDim.z;
@@ -351,66 +350,36 @@ __global__ __launch_bounds__(64 * WK) void hdet_bgemm_frag_kernel(const hdet_bge
   const int64_t c_base = hdet_batch_offset(bi, g.c_s);
   const int lane = threadIdx.x & 63, half = lane >> 5;
   const int wk = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int m0 = by * (32 * WTM), n0 = bx * (32 * WTN);
+  const int m0 = by * 32, n0 = bx * 32;
   const bool a_odd = (g.lda & 1) != 0 || (reinterpret_cast<uintptr_t>(A) & 3) != 0;
   const bool b_odd = (g.ldb & 1) != 0 || (reinterpret_cast<uintptr_t>(B) & 3) != 0;
 
-  f16v acc[WTM][WTN];
-#pragma unroll
-  for (int i = 0; i < WTM; ++i)
-#pragma unroll
-    for (int j = 0; j < WTN; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
   constexpr bool SUMS = has_rowsum<A_KMAJOR, B_KMAJOR, EPI>();
   const bool sums = SUMS && g.rowsum && bx == 0;                    // uniform over the block
-  f16v rsum[SUMS ? WTM : 1];
+  f16v acc, rsum;
 #pragma unroll
-  for (int i = 0; i < (SUMS ? WTM : 1); ++i)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) rsum[i][e] = 0.f;
+  for (int e = 0; e < 16; ++e) { acc[e] = 0.f; rsum[e] = 0.f; }
 
-  // lane l: row r0 + l % 32 (the matrix's last row again beyond it; a 32-row group beyond the matrix repeats the first one), k = 8 (l / 32) + 0..7
-  int64_t aoff[WTM], boff[WTN];
-#pragma unroll
-  for (int i = 0; i < WTM; ++i) {
-    int row = (m0 + 32 * i < g.m ? m0 + 32 * i : m0) + (lane & 31);
-    if (row >= g.m) row = g.m - 1;
-    aoff[i] = A_KMAJOR ? row * g.lda + half * 8 : half * 8 * g.lda + row;
-  }
-#pragma unroll
-  for (int j = 0; j < WTN; ++j) {
-    int row = (n0 + 32 * j < g.n ? n0 + 32 * j : n0) + (lane & 31);
-    if (row >= g.n) row = g.n - 1;
-    boff[j] = B_KMAJOR ? row * g.ldb + half * 8 : half * 8 * g.ldb + row;
-  }
+  // lane l: row r0 + l % 32 (the matrix's last row again beyond it), k = 8 (l / 32) + 0..7
+  const int arow = m0 + (lane & 31) < g.m ? m0 + (lane & 31) : g.m - 1, brow = n0 + (lane & 31) < g.n ? n0 + (lane & 31) : g.n - 1;
+  const int64_t aoff = A_KMAJOR ? arow * g.lda + half * 8 : half * 8 * g.lda + arow;
+  const int64_t boff = B_KMAJOR ? brow * g.ldb + half * 8 : half * 8 * g.ldb + brow;
   const int64_t astep = A_KMAJOR ? 16 : 16 * g.lda, bstep = B_KMAJOR ? 16 : 16 * g.ldb;
   const int nfull = g.k >> 4, per = (nfull + WK - 1) / WK;
   const int c0 = wk * per < nfull ? wk * per : nfull, c1 = c0 + per < nfull ? c0 + per : nfull;
 
-  us8 a[2][U][WTM], b[2][U][WTN];
+  us8 a[2][U], b[2][U];
   auto fetch = [&](int buf, int c) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int cc = c + u < c1 ? c + u : c1 - 1;                   // past the end: the last step again, not used
-#pragma unroll
-      for (int i = 0; i < WTM; ++i) a[buf][u][i] = frag_load<A_KMAJOR>(A + cc * astep, aoff[i], g.lda, a_odd);
-#pragma unroll
-      for (int j = 0; j < WTN; ++j) b[buf][u][j] = frag_load<B_KMAJOR>(B + cc * bstep, boff[j], g.ldb, b_odd);
+      a[buf][u] = frag_load<A_KMAJOR>(A + cc * astep, aoff, g.lda, a_odd);
+      b[buf][u] = frag_load<B_KMAJOR>(B + cc * bstep, boff, g.ldb, b_odd);
     }
   };
-  auto step = [&](us8 (&av)[WTM], us8 (&bv)[WTN]) {
-#pragma unroll
-    for (int i = 0; i < WTM; ++i)
-#pragma unroll
-      for (int j = 0; j < WTN; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av[i]), __builtin_bit_cast(bf16x8, bv[j]), acc[i][j], 0, 0, 0);
-    if (SUMS && sums) {
-#pragma unroll
-      for (int i = 0; i < WTM; ++i)
-        rsum[SUMS ? i : 0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av[i]), ones(), rsum[SUMS ? i : 0], 0, 0, 0);
-    }
+  auto step = [&](us8 av, us8 bv) {
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av), __builtin_bit_cast(bf16x8, bv), acc, 0, 0, 0);
+    if (SUMS && sums) rsum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av), ones(), rsum, 0, 0, 0);
   };
   if (c0 < c1) {
     fetch(0, c0);
@@ -428,50 +397,33 @@ __global__ __launch_bounds__(64 * WK) void hdet_bgemm_frag_kernel(const hdet_bge
     }
   }
   const int kleft = g.k & 15;
-  if (kleft && wk == WK - 1) {
-    us8 av[WTM], bv[WTN];
-#pragma unroll
-    for (int i = 0; i < WTM; ++i) av[i] = frag_load_tail<A_KMAJOR>(A + nfull * astep, aoff[i], g.lda, kleft - half * 8);
-#pragma unroll
-    for (int j = 0; j < WTN; ++j) bv[j] = frag_load_tail<B_KMAJOR>(B + nfull * bstep, boff[j], g.ldb, kleft - half * 8);
-    step(av, bv);
-  }
+  if (kleft && wk == WK - 1)
+    step(frag_load_tail<A_KMAJOR>(A + nfull * astep, aoff, g.lda, kleft - half * 8), frag_load_tail<B_KMAJOR>(B + nfull * bstep, boff, g.ldb, kleft - half * 8));
 
-  auto put = [&](int q, float v) {                                  // q: accumulator register of the tile
-    const int e = q % 16, i = q / (16 * WTN), j = (q / 16) % WTN;
-    put_element<EPI>(g, z, c_base, m0 + 32 * i + (e >> 2) * 8 + half * 4 + (e & 3), n0 + 32 * j + (lane & 31), v);
-  };
-  if (WK == 1) {
+  float* mine = part + wk * (16 * 64) + lane;                       // [register][lane] of this wavefront's partial tile
 #pragma unroll
-    for (int q = 0; q < NW; ++q) put(q, acc[q / (16 * WTN)][(q / 16) % WTN][q % 16]);
-  } else {
-    float* mine = part + wk * (NW * 64) + lane;                     // [register][lane] of this wavefront's partial tile
+  for (int e = 0; e < 16; ++e) mine[e * 64] = acc[e];
+  __syncthreads();
 #pragma unroll
-    for (int q = 0; q < NW; ++q) mine[q * 64] = acc[q / (16 * WTN)][(q / 16) % WTN][q % 16];
-    __syncthreads();
+  for (int t = 0; t < 16 / WK; ++t) {
+    const int e = wk * (16 / WK) + t;
+    float v = part[e * 64 + lane];
 #pragma unroll
-    for (int t = 0; t < NW / WK; ++t) {
-      const int q = wk * (NW / WK) + t;
-      float v = part[q * 64 + lane];
-#pragma unroll
-      for (int p = 1; p < WK; ++p) v += part[(p * NW + q) * 64 + lane];
-      put(q, v);
-    }
+    for (int p = 1; p < WK; ++p) v += part[(p * 16 + e) * 64 + lane];
+    put_element<EPI>(g, z, c_base, m0 + (e >> 2) * 8 + half * 4 + (e & 3), n0 + (lane & 31), v);
   }
   if (SUMS && sums) {
-    static_assert(!SUMS || WK > 1, "the row sums meet in the tile's LDS");
     __syncthreads();                                                // the tile's partial sums have been read
     if ((lane & 31) == 0) {                                         // every column holds the sum: [K part][row]
 #pragma unroll
-      for (int i = 0; i < WTM; ++i)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) part[wk * (WTM * 32) + i * 32 + (e >> 2) * 8 + half * 4 + (e & 3)] = rsum[SUMS ? i : 0][e];
+      for (int e = 0; e < 16; ++e) part[wk * 32 + (e >> 2) * 8 + half * 4 + (e & 3)] = rsum[e];
     }
     __syncthreads();
-    for (int r = threadIdx.x; r < WTM * 32; r += 64 * WK) {
+    const int r = threadIdx.x;
+    if (r < 32) {
       float v = part[r];
 #pragma unroll
-      for (int p = 1; p < WK; ++p) v += part[p * (WTM * 32) + r];
+      for (int p = 1; p < WK; ++p) v += part[p * 32 + r];
       if (m0 + r < g.m) g.rowsum[(int64_t)z * g.rowsum_bs + m0 + r] = v;
     }
   }
@@ -492,17 +444,16 @@ bool few_tiles(const hdet_bgemm_args& g, int batch) { return tiles(g, batch, 64,
 
 template <bool AK, bool BK, int EPI>
 hipError_t launch_general(const hdet_bgemm_args& g, int batch, hipStream_t s) {
-#define HDET_FRAG(WTM, WTN, WK, U)                                                                    \
-  hipLaunchKernelGGL((hdet_bgemm_frag_kernel<AK, BK, EPI, WTM, WTN, WK, U>),                          \
-                     dim3((g.n + 32 * WTN - 1) / (32 * WTN), (g.m + 32 * WTM - 1) / (32 * WTM), batch), dim3(64 * WK), 0, s, g)
+#define HDET_FRAG(WK)                                                                                 \
+  hipLaunchKernelGGL((hdet_bgemm_frag_kernel<AK, BK, EPI, WK>), dim3((g.n + 31) / 32, (g.m + 31) / 32, batch), dim3(64 * WK), 0, s, g)
 #define HDET_LDS(WT)                                                                                  \
-  hipLaunchKernelGGL((hdet_bgemm_kernel<AK, BK, EPI, WT, WT, 2>), dim3((g.n + 64 * WT - 1) / (64 * WT), (g.m + 64 * WT - 1) / (64 * WT), batch), dim3(256), 0, s, g)
+  hipLaunchKernelGGL((hdet_bgemm_kernel<AK, BK, EPI, WT>), dim3((g.n + 64 * WT - 1) / (64 * WT), (g.m + 64 * WT - 1) / (64 * WT), batch), dim3(256), 0, s, g)
   const int64_t cus = hdet_compute_units();
-  if (few_tiles(g, batch)) HDET_FRAG(1, 1, 4, 4);
+  if (few_tiles(g, batch)) HDET_FRAG(4);
   // less than one 64 x 64 block per CU and a long contraction: K in 8 (training step with 96 x 700, K = 1500, 6 items in it: 170 us,
   // with 64 x 64 fragment tiles 173, LDS 64 x 64 185; alone, 64 x 64 fragment tiles 15.5 | LDS 64 x 64 26.6;
   // 111 x 3193, K = 1788, 2 items, odd rows: 24 | 51; at K = 842 10.7 | 10.9)
-  else if (g.k >= 1024 && tiles(g, batch, 64, 64) < cus) HDET_FRAG(1, 1, 8, 4);
+  else if (g.k >= 1024 && tiles(g, batch, 64, 64) < cus) HDET_FRAG(8);
   // 128 x 128 tiles once there are several rounds of them (256 x 4095, K = 4095, 8 items: 337 | 64 x 64 441; 700 x 1500, K = 576:
   // 14.8 | 10.1; 1788 x 3193, K = 222: 18.4 | 14.7), unless they would be half empty
   else if (tiles(g, batch, 128, 128) >= 4 * cus && g.m > 64 && g.n > 64) HDET_LDS(2);

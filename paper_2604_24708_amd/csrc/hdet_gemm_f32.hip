@@ -12,7 +12,7 @@
 //    four loads of whole 128-byte lines.
 //  * The wavefronts of a block may split K (WK > 1): each walks its own contiguous part, the partial tiles meet in
 //    LDS and are added in ascending order of k, every wavefront finishing 1 / WK of the tile.  A 32 x 32 tile with
-//    K = 1024 in 8 parts is 16 steps per wavefront instead of 128.
+//    K = 1024 in 4 parts is 32 steps per wavefront instead of 128.
 // Loads are dword aligned only (odd leading dimensions are common here); rows beyond the matrix are clamped to its
 // last row (their results are not stored), the K mod 8 tail is a separate masked step.
 // Measured against a 64 x 64 tile staged through LDS on the vector units (us per launch, 4 replicas, same machine):

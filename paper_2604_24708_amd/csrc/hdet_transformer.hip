@@ -1274,14 +1274,13 @@ struct mat { const void* p; int64_t ld; int64_t s[3]; };
 // C = A B in the given operand order; the output is of the activation type (act_out) or
 // fp32; bias (fp32, per replica) is optional.  Element offsets inside `p` are in elements of
 // the operand's own type.
-// GELU fused into the bf16 GEMMs around it.  gelu_out: the product is the pre-activation z
-// (written to c) and f = gelu(z) goes to gelu_out; gelu_pre: the product is the gradient at f and
-// c receives the gradient at z = that * gelu'(gelu_pre).  `*fused` tells whether the GEMM took
-// them (it does on the LDS-direct path); otherwise the caller runs the element-wise kernel.
-// What a GEMM may fold into its epilogue when the fast bf16 kernel takes the product: the GELU after
-// it (second output), the GELU gradient at the pre-activation, or the residual stream it is added to
-// (the sum then goes to resid_out instead of c; with `drop`, the layer's output is dropped out first); with the GELU
-// gradient, colsum_out receives stage 1 of the column sums of the result.  *fused tells the caller whether it happened.
+// What a GEMM may fold into its epilogue, where the LDS-direct bf16 kernel or the fp32 kernel takes the product:
+//   gelu_out: the product is the pre-activation z (written to c) and f = gelu(z) goes to gelu_out;
+//   gelu_pre: the product is the gradient at f and c receives the gradient at z = that * gelu'(gelu_pre) (bf16; the fp32 path
+//     forms it in the launch it shares with the weight gradient); colsum_out then receives stage 1 of the column sums of c;
+//   resid: the product is added to its residual stream and the sum goes to resid_out instead of c; with `drop` (bf16) the
+//     layer's output is dropped out first.
+// *fused tells the caller whether it happened; otherwise the caller runs the element-wise kernel.
 struct gelu_fusion { void* gelu_out; const void* gelu_pre; bool* fused; const void* resid; void* resid_out; const drop_args* drop; float* colsum_out; };
 
 hdet_sgemm_args sgemm_of(int form, mat A, mat B, float* c, int64_t ldc, const int64_t* c_s, int m, int n, int k, int n1, int n2) {
@@ -1392,6 +1391,7 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
   const int64_t act_d[3] = {(int64_t)M * d, 0, 0}, act_3d[3] = {(int64_t)M * 3 * d, 0, 0}, act_ff[3] = {(int64_t)M * ff, 0, 0},
                 act_v[3] = {(int64_t)M * V, 0, 0}, plane[3] = {ps, 0, 0};
 
+  constexpr bool f32 = sizeof(T) == 4;
   // ---- forward ------------------------------------------------------------------------
   const bool aligned_rows = d % 8 == 0 && p->tok % 4 == 0 && p->pos % 4 == 0 && ps % 4 == 0;
   const bool ordered_tok = M <= 16384 && aligned_rows && d <= 2048;       // token-embedding gradient in a fixed order
@@ -1440,8 +1440,9 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
       bool fused = false;
       const gelu_fusion gf = {p->f[l], nullptr, &fused, nullptr, nullptr, nullptr, nullptr};
       TF_CHECK(gemm<T>(p, NT, act(p->h2[l], d), wt(o.w_1, d), p->z[l], ff, act_ff, true, M, ff, d, 1, 1, theta + o.b_1, ps, s, &gf));
-      if (!fused)
-        hipLaunchKernelGGL(gelu_fwd_kernel<T>, dim3(grid_for((int64_t)N * nff)), dim3(256), 0, s, (const T*)p->z[l], (T*)p->f[l], (int64_t)N * nff);
+      if constexpr (!f32)                            // fp32 products always carry it
+        if (!fused)
+          hipLaunchKernelGGL(gelu_fwd_kernel<T>, dim3(grid_for((int64_t)N * nff)), dim3(256), 0, s, (const T*)p->z[l], (T*)p->f[l], (int64_t)N * nff);
     }
     {
       bool fused = false;
@@ -1461,7 +1462,6 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
     for (const colsum_job& j : p->jobs)
       if (j.out_off == p->b_head && j.mode == 0 && j.cols == V && j.nchunks == (M + xr - 1) / xr) { head_part = p->part + j.part_off; break; }
   TF_CHECK(hdet_launch_xent(sizeof(T) == 2, p->logits, targets, M, V, p->dlogits, p->row_loss, N, ctrl, p->ls_channel, s, head_part, xr));
-  constexpr bool f32 = sizeof(T) == 4;
   if (!f32) TF_CHECK(hdet_launch_loss_reduce(p->row_loss, M, ctrl, N, s));
 
   // ---- backward -----------------------------------------------------------------------
@@ -1528,7 +1528,7 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
     return hdet_launch_sgemm_pair(g, one ? 1 : N, &dg, false, gelu_pre ? HDET_SEPI_GELUGRAD : HDET_SEPI_NONE, N, loss, s);
   };
 
-  if (f32) {
+  if constexpr (f32) {
     const hdet_loss_args loss = {p->row_loss, M, ctrl, N};
     TF_CHECK(linear_bwd(p->dlogits, V, p->hf, d, p->w_head, p->b_head, p->dtmp, nullptr, &loss, head_part != nullptr));
   } else {
@@ -1554,7 +1554,7 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
         hipLaunchKernelGGL((dropout_kernel<T, false>), dim3(grid_for(nd / 4), N), dim3(256), 0, s, (const T*)nullptr, (const T*)p->dxa, (T*)p->dtmp2, nd, da);
       dy = p->dtmp2;
     }
-    if (f32) {
+    if constexpr (f32) {
       TF_CHECK(linear_bwd(dy, d, p->f[l], ff, o.w_2, o.b_2, p->dff, p->z[l], nullptr, b2_done));
       TF_CHECK(linear_bwd(p->dff, ff, p->h2[l], d, o.w_1, o.b_1, p->dtmp, nullptr, nullptr, false));
     } else {
@@ -1590,7 +1590,7 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
         hipLaunchKernelGGL((dropout_kernel<T, false>), dim3(grid_for(nd / 4), N), dim3(256), 0, s, (const T*)nullptr, (const T*)p->dxb, (T*)p->dtmp2, nd, da);
       dob = p->dtmp2;
     }
-    if (f32) {
+    if constexpr (f32) {
       TF_CHECK(linear_bwd(dob, d, p->a[l], d, o.w_o, o.b_o, p->dtmp, nullptr, nullptr, bo_done));
     } else {
       if (!bo_done) TF_CHECK(colsum(dob, d, o.b_o));
@@ -1604,7 +1604,7 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
       const mat sc = head_sq(p->scores);
       const mat dq = qkv_part(p->dqkv, 0), dk = qkv_part(p->dqkv, 1), dv = qkv_part(p->dqkv, 2);
       // dp = da v^T,  dv = p^T da
-      if (f32) {
+      if constexpr (f32) {
         const hdet_sgemm_args gv = sgemm_of(TN, head_sq(p->p[l]), head_cols(p->dtmp), (float*)dv.p, 3 * d, dv.s, S, dh, S, B, nh);
         const hdet_sgemm_args gp = sgemm_of(NT, head_cols(p->dtmp), qkv_part(p->qkv[l], 2), (float*)p->scores, S, sc.s, S, S, dh, B, nh);
         TF_CHECK(hdet_launch_sgemm_pair(gv, N * B * nh, &gp, true, HDET_SEPI_NONE, N * B * nh, nullptr, s));
@@ -1614,7 +1614,7 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
       }
       launch_softmax_bwd<T>(p->scores, p->p[l], heads_rows, S, scale, ta, p->ds, s);
       // dq = ds k,  dk = ds^T q
-      if (f32) {
+      if constexpr (f32) {
         const hdet_sgemm_args gk = sgemm_of(TN, head_sq(p->ds), qkv_part(p->qkv[l], 0), (float*)dk.p, 3 * d, dk.s, S, dh, S, B, nh);
         const hdet_sgemm_args gq = sgemm_of(NN, head_sq(p->ds), qkv_part(p->qkv[l], 1), (float*)dq.p, 3 * d, dq.s, S, dh, S, B, nh);
         TF_CHECK(hdet_launch_sgemm_pair(gk, N * B * nh, &gq, false, HDET_SEPI_NONE, N * B * nh, nullptr, s));
@@ -1623,7 +1623,7 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
         TF_CHECK(gemm<T>(p, TN, head_sq(p->ds), qkv_part(p->qkv[l], 0), (void*)dk.p, 3 * d, dk.s, true, S, dh, S, B, nh, nullptr, 0, s));
       }
     }
-    if (f32) {
+    if constexpr (f32) {
       TF_CHECK(linear_bwd(p->dqkv, 3 * d, p->h1[l], d, o.w_qkv, o.b_qkv, p->dtmp, nullptr, nullptr, false));
     } else {
       TF_CHECK(colsum(p->dqkv, 3 * d, o.b_qkv));
