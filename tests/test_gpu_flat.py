@@ -124,8 +124,8 @@ def test_update_converge_controller_parity(opt, mode, n, P):
 @pytest.mark.parametrize("mode", [O.GRAD_SHARED, O.GRAD_PER_REPLICA])
 @pytest.mark.parametrize("n", [3, 8, 16, 17, 64])
 def test_kernel_variants_agree_bit_for_bit(n, mode):
-    """The general loop kernel (forced, small grid) and the default kernels (plane / wave for
-    N <= 16, loop beyond) must give identical bits, and both match the oracle."""
+    """The general loop kernel (forced, small grid) and the default kernels (plane or wave, the
+    latter with several replicas a wavefront beyond 16) must give identical bits, and both match the oracle."""
     d = base_cfg(n_replicas=n, grad_mode=mode)
     a = FlatRun(d, 50003, stride=50176, variant=1, blocks=7)
     b = FlatRun(d, 50003, stride=50176)
