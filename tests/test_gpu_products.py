@@ -102,31 +102,31 @@ def test_bf16_products_of_every_alignment(widths, batch, n, shared):
         assert np.linalg.norm(got[:, s] - ref[:, s]) <= 1e-2 * np.linalg.norm(ref[:, s]) + 1e-30, s
 
 
+def _classifier_step_ms(classes, n=8, batch=8192, dev="cuda:0"):
+    P = I.mlp_param_count([64, classes])
+    theta = torch.randn((n, (P + 63) // 64 * 64), device=dev) * 0.1
+    m, v, g = (torch.zeros_like(theta) for _ in range(3))
+    x = torch.randn((n, batch, 64), device=dev)
+    y = torch.randint(0, classes, (n, batch), device=dev, dtype=torch.int32)
+    cfg = H.make_config(n_replicas=n, sync_interval=4, total_steps=10, lr_max=1e-3, alpha=0.1, widths=[64, classes], batch=batch,
+                        model_kind=H.HDET_MLP, precision=H.HDET_BF16_GEMM_FP32_MASTER)
+    ws = torch.empty(H.hdet_workspace_bytes(cfg, theta.shape[1])[2], dtype=torch.uint8, device=dev)
+    copy = torch.zeros_like(theta, dtype=torch.bfloat16)
+    h = H.hdet_create(cfg, theta, m, v, grads=g, params_bf16=copy, workspace=ws, plane_stride=theta.shape[1])
+    t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    times = []
+    for _ in range(6):
+        t0.record()
+        for _ in range(5):
+            H.hdet_forward_backward(h, x, y)
+        t1.record()
+        torch.cuda.synchronize()
+        times.append(t0.elapsed_time(t1) / 5)
+    H.hdet_destroy(h)
+    return min(times[1:])
+
+
 def test_results_of_no_whole_lines_cost_no_more_than_whole_ones():
     """Logits of 5000 columns begin inside a 128-byte line, those of 5024 on one: the step of a one-layer classifier, whose
-    product is little more than its result, has been 16 % slower with the former."""
-    best = []
-    for classes in (5000, 5024):
-        n, batch, dev = 8, 8192, "cuda:0"
-        P = I.mlp_param_count([64, classes])
-        theta = torch.randn((n, (P + 63) // 64 * 64), device=dev) * 0.1
-        m, v, g = (torch.zeros_like(theta) for _ in range(3))
-        x = torch.randn((n, batch, 64), device=dev)
-        y = torch.randint(0, classes, (n, batch), device=dev, dtype=torch.int32)
-        cfg = H.make_config(n_replicas=n, sync_interval=4, total_steps=10, lr_max=1e-3, alpha=0.1, widths=[64, classes], batch=batch,
-                            model_kind=H.HDET_MLP, precision=H.HDET_BF16_GEMM_FP32_MASTER)
-        ws = torch.empty(H.hdet_workspace_bytes(cfg, theta.shape[1])[2], dtype=torch.uint8, device=dev)
-        copy = torch.zeros_like(theta, dtype=torch.bfloat16)
-        h = H.hdet_create(cfg, theta, m, v, grads=g, params_bf16=copy, workspace=ws, plane_stride=theta.shape[1])
-        t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        times = []
-        for _ in range(6):
-            t0.record()
-            for _ in range(5):
-                H.hdet_forward_backward(h, x, y)
-            t1.record()
-            torch.cuda.synchronize()
-            times.append(t0.elapsed_time(t1))
-        best.append(min(times[1:]))
-        H.hdet_destroy(h)
-    assert best[0] <= 1.1 * best[1]
+    product is little more than its result, has been 16 % slower with the former.  A disturbed measurement is repeated."""
+    assert any(_classifier_step_ms(5000) <= 1.1 * _classifier_step_ms(5024) for _ in range(3))

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 import hdet_inputs as I
+import paper_2604_24708_amd as H
 from oracle import hdet_oracle as O
 from oracle import transformer_oracle as T
 from test_gpu_transformer import TfRun, base, norm_err
@@ -21,15 +22,19 @@ CASES = [(32, 8, dict(n_blocks=1, d_model=8, n_heads=1, d_ff=16, seq_len=33, voc
          (2, 2, dict(n_blocks=2, d_model=1024, n_heads=4, d_ff=8192, seq_len=35, vocab=19))]
 
 
-@pytest.mark.parametrize("n,batch,cfg", CASES)
-def test_bias_gradients_of_one_product_matrices(n, batch, cfg):
-    run = TfRun(base(n_replicas=n, grad_mode=O.GRAD_SHARED), cfg, batch)
+@pytest.mark.parametrize("n,batch,cfg,drop", [(*c, False) for c in CASES] + [(*CASES[-1], True)])
+def test_bias_gradients_of_one_product_matrices(n, batch, cfg, drop):
+    """drop: with a dropout channel, the bias gradients of the branches below are those of the dropped-out gradient."""
+    extra = [(H.HDET_CH_DROPOUT, 0.2, 0.5, 1e-3, 0.0, 0.5)] if drop else []
+    run = TfRun(base(n_replicas=n, grad_mode=O.GRAD_SHARED, extra=extra), cfg, batch)
     run.forward_backward(1)
     ids, tgt, losses = run.forward_backward(2)
     got = run.g.double().cpu().numpy()
+    p = run.orc.dropout_table()
     summed = {}
     for r in range(n) if n <= 3 else (0, n - 1):
-        loss, ref = T.loss_and_grad(run.orc.theta[r], ids[r], tgt[r], cfg)
+        dropout = dict(p=float(p[r]), seed=run.d["seed"], step=1, replica=r) if drop else None
+        loss, ref = T.loss_and_grad(run.orc.theta[r], ids[r], tgt[r], cfg, dropout=dropout)
         assert abs(losses[r] - loss) <= 1e-5 * loss
         off = 0
         for name, shape in I.transformer_shapes(cfg):
