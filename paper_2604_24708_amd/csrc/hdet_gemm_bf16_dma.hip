@@ -10,14 +10,16 @@
 // or absent and C can be written 4 columns at a time; everything else takes the other kernel.
 //
 // Design
-//  * Block tile TM x TN, WGM x WGN wavefronts, each owning (TM/WGM) x (TN/WGN) as 32x32 blocks of
-//    v_mfma_f32_32x32x16_bf16.  K step TK = 32 or 64, NST LDS stages of one K step each.
+//  * Block tile TM x TN, WGM x WGN wavefronts, each owning (TM/WGM) x 64 as 16x16 blocks of v_mfma_f32_16x16x32_bf16.  On random
+//    data the chip holds 2.03 PFLOP/s of these from registers, 1.82 of the 32x32x16 form, at whose larger blocks every accumulator
+//    is read and written twice as often per operation; the sums of a product are the same to the bit.  K step TK = 32 or 64, NST LDS
+//    stages of one K step each.
 //  * LDS-direct loads: one instruction moves 64 lanes x 16 bytes into 1 KiB of consecutive LDS.
 //    Which global chunk a lane fetches is chosen so that the tile lands already swizzled:
 //      - operand contiguous along k: tile [row][TK], the 16-byte chunks of a row XOR-permuted by
 //        a function of the row, so that the 128-bit fragment reads hit disjoint banks;
 //      - operand contiguous along the output axis: tile [k][ROWS], chunks XOR-permuted by
-//        4 (k mod 4), so that the four k-rows a 16-lane group of the transposing LDS read
+//        a function of k, so that the eight k-rows that half a wavefront of the transposing LDS read
 //        (ds_read_b64_tr_b16) touches fall on disjoint banks.  No padding anywhere.
 //    The loads go through a buffer descriptor whose extent is the operand of this batch item:
 //    chunks outside it (ragged m, n, k edges) are given an out-of-range offset and arrive as
@@ -25,10 +27,11 @@
 //  * Pipeline: the stage NST K steps ahead is requested as soon as its buffer is free.  One
 //    barrier per K step, placed before the last MFMA sub-step: by then every wavefront has read
 //    the whole current stage into registers, so the stage is refilled at once, and the next
-//    stage has landed (s_waitcnt vmcnt leaves the younger stages in flight).  Fragments are
+//    stage has landed (s_waitcnt vmcnt leaves the younger stages in flight).  With K steps of 64, fragments are
 //    double-buffered in registers across sub-steps, LDS reads and load issue are dealt out
-//    between the MFMAs, and the order is pinned with sched_barrier.
-//  * Epilogue through LDS: accumulators (lane = column, 4 consecutive rows) are transposed via a
+//    between the MFMAs, and the order is pinned with sched_barrier; with K steps of 32 the second block of the CU
+//    runs while one reads its fragments.  The 256 x 256 tile has a kernel of its own (hdet_bgemm_alt_kernel).
+//  * Epilogue through LDS: accumulators (lane = row, 4 consecutive columns) go through a
 //    per-wavefront staging strip so that every global store writes whole rows, 4 columns per
 //    lane; bias / ReLU / ReLU-gate / bf16 rounding (hardware round-to-nearest-even) fused.
 //  * Launch order is remapped so that each XCD (own L2) works on a contiguous range of tiles, walked in groups
@@ -41,7 +44,6 @@
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f16v __attribute__((ext_vector_type(16)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef short s4 __attribute__((ext_vector_type(4)));
 typedef short s8 __attribute__((ext_vector_type(8)));
@@ -91,7 +93,10 @@ struct lds_tile {
   static_assert(KMAJOR || ROWS >= 128, "the chunk permutation of a [k][ROWS] tile needs at least 16 chunks per k-row");
   static_assert(TK == 32 || TK == 64, "K step");
   // chunk permutation inside a [row][TK] row: 64-byte rows by row / 4, 128-byte rows by row / 2
-  static __device__ __forceinline__ int swz(int r) { return TK == 32 ? (r >> 2) & 3 : (r >> 1) & 7; }
+  // (four times two bits: 0, 2, 3, 1 -- a 128-bit read serves lanes 0-3, 12-15 and 20-27 together, then the others)
+  static __device__ __forceinline__ int swz(int r) { return TK == 32 ? (0x78 >> ((r >> 1) & 6)) & 3 : (r >> 1) & 7; }
+  // ... of a [k][ROWS] row: a 32-lane half of the transposing read takes 32 bytes of each of 8 k-rows (k mod 4 and k / 8 differ)
+  static __device__ __forceinline__ int swz_k(int k) { return ((k & 3) << 2) | (((k >> 3) & 1) << 1); }
   uint32_t off[NI];     // byte offset of this lane's chunk at K step 0, or kAbsent
   int kofs[NI];         // k index of the chunk inside a K step
   uint32_t kstep;       // bytes per K step
@@ -106,7 +111,7 @@ struct lds_tile {
         kofs[i] = cg * 8;
         off[i] = row < rows ? (uint32_t)((row * ld + cg * 8) * 2) : kAbsent;
       } else {
-        const int kk = c / RCH, cg = (c % RCH) ^ ((kk & 3) << 2);
+        const int kk = c / RCH, cg = (c % RCH) ^ swz_k(kk);
         const int row = row0 + cg * 8;
         kofs[i] = kk;
         off[i] = row < rows ? (uint32_t)((kk * ld + row) * 2) : kAbsent;
@@ -117,19 +122,19 @@ struct lds_tile {
     const uint32_t v = (kt * TK + kofs[i] < kdim) ? off[i] + (uint32_t)kt * kstep : kAbsent;
     lds_load16(rsrc, tile_addr + (i * THREADS + wave * 64) * 16, v);
   }
-  // MFMA 32x32x16 operand fragment: lane l gets (row = r0 + l % 32, k = ks + 8 * (l / 32) + 0..7).
+  // MFMA 16x16x32 operand fragment: lane l gets (row = r0 + l % 16, k = ks + 8 * (l / 16) + 0..7).
   static __device__ __forceinline__ bf16x8 fragment(const uint16_t* tile, int r0, int ks, int lane) {
     if (KMAJOR) {
-      const int row = r0 + (lane & 31);
-      const int chunk = ((ks >> 3) + (lane >> 5)) ^ swz(row);
+      const int row = r0 + (lane & 15);
+      const int chunk = ((ks >> 3) + (lane >> 4)) ^ swz(row);
       return *reinterpret_cast<const bf16x8*>(tile + row * TK + (chunk << 3));
     }
     // Transposing read: within a 16-lane group, lane p points at the 4 elements
-    // (k = kb + p / 4, rows rb + 4 * (p % 4) .. + 3) and lane i receives (k = kb .. kb + 3, row rb + i).
+    // (k = kb + p / 4, rows r0 + 4 * (p % 4) .. + 3) and lane i receives (k = kb .. kb + 3, row r0 + i).
     const int p = lane & 15;
-    const int row = r0 + (((lane >> 4) & 1) << 4) + ((p & 3) << 2);
-    const int k = ks + ((lane >> 5) << 3) + (p >> 2);
-    const uint16_t* q = tile + k * ROWS + (((row >> 3) ^ ((k & 3) << 2)) << 3) + (row & 7);
+    const int row = r0 + ((p & 3) << 2);
+    const int k = ks + ((lane >> 4) << 3) + (p >> 2);
+    const uint16_t* q = tile + k * ROWS + (((row >> 3) ^ swz_k(k)) << 3) + (row & 7);
     const s4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s4 __attribute__((address_space(3)))*)(q));
     const s4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s4 __attribute__((address_space(3)))*)(q + 4 * ROWS));
     const s8 both = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
@@ -137,13 +142,219 @@ struct lds_tile {
   }
 };
 
+// Launch order -> tile: each XCD (own L2; blocks are dealt to the XCDs round-robin) works through a contiguous
+// range of tiles, and inside a batch item consecutive tiles walk groups of tile_group tile rows column by column,
+// so that the blocks an XCD runs at one time share operand tiles of both kinds in its L2.
+struct tile_id { int bx, by, bz; };
+__device__ __forceinline__ tile_id tile_of_block(int tile_group) {
+  const unsigned total = gridDim.x * gridDim.y * gridDim.z;
+  unsigned t = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
+  {   // XCD x = launch index mod 8 takes the x-th of eight contiguous ranges (the first total mod 8 ranges one tile longer)
+    const unsigned x = t & 7u, rem = total & 7u;
+    t = x * (total >> 3) + (x < rem ? x : rem) + (t >> 3);
+  }
+  tile_id id;
+  const unsigned per = gridDim.x * gridDim.y;
+  id.bz = t / per;
+  const unsigned r = t - id.bz * per;
+  const unsigned gm = tile_group > 1 ? (unsigned)tile_group : 1u;
+  const unsigned gsz = gm * gridDim.x;
+  const unsigned grp = r / gsz, first = grp * gm;
+  const unsigned rows = gridDim.y - first < gm ? gridDim.y - first : gm;
+  const unsigned q = r - grp * gsz;
+  id.by = first + q % rows;
+  id.bx = q / rows;
+  return id;
+}
+
+// The block's TM x TN tile to memory.  Accumulators go through LDS as fp32, the wavefront's own 32 rows x 64 columns at a time, and are read
+// back with 4 consecutive columns a lane, so that every global access is made of whole rows of the strip.  (Strips of 16 rows x 256 columns
+// shared by four wavefronts, whose accesses are whole 1 KiB rows, measured the same or, with the update, 6 % slower.)
+// LDS serves one wavefront's accesses in order, so a strip needs no barrier.
+// STREAM: results are written past the L2 (stream_result).  `S`: the stage buffers, which no wavefront reads or loads into any more.
+template <int EPI, int TM, int TN, int WGM, int WGN, bool STREAM, int LDS_BYTES>
+__device__ __forceinline__ void store_tile(const hdet_bgemm_args& g, const f4 (&acc)[TM / WGM / 16][TN / WGN / 16], uint16_t* S, int bx, int by, int z,
+                                           int64_t c_base, int tid) {
+  constexpr int THREADS = 64 * WGM * WGN;
+  constexpr int SR = 32, CW = 64, EP = CW + 4, LPR = CW / 4, RPI = 64 / LPR;      // pitch EP: both sides free of bank conflicts
+  constexpr int NIT = SR / RPI, NSTRIP = TM / WGM / SR;
+  static_assert(TN / WGN == CW, "a wavefront owns 64 columns");
+  static_assert(WGM * WGN * SR * EP * 4 <= LDS_BYTES, "staging area exceeds the stage buffers");
+  const int m0 = by * TM, n0 = bx * TN, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = (wave / WGN) * (TM / WGM), wn = (wave % WGN) * 64;
+  float* const stg = reinterpret_cast<float*>(S) + wave * (SR * EP);
+  const int lr = lane / LPR, lc = (lane % LPR) * 4;
+  const int col = n0 + wn + lc;
+  const bool col_ok = col < g.n;                             // n is a multiple of 4: the 4 columns exist together
+  auto put = [&](auto* p, auto v) {
+    if (STREAM) __builtin_nontemporal_store(v, p);
+    else *p = v;
+  };
+  constexpr bool kBias = EPI == HDET_EPI_BIAS_RELU_BF16 || EPI == HDET_EPI_BIAS_F32 || EPI == HDET_EPI_BIAS_BF16 ||
+                         EPI == HDET_EPI_BIAS_GELU_BF16 || EPI == HDET_EPI_BIAS_RESID_BF16 || EPI == HDET_EPI_BIAS_DROP_RESID_BF16;
+  // the second operand of the gating epilogues (the activations a ReLU or GELU gradient looks at) is
+  // fetched one strip ahead, so that its latency hides behind the previous strip's pass through LDS
+  constexpr bool kGate = EPI == HDET_EPI_MASK_BF16 || EPI == HDET_EPI_GELUGRAD_BF16 || EPI == HDET_EPI_BIAS_RESID_BF16 ||
+                         EPI == HDET_EPI_BIAS_DROP_RESID_BF16;
+  us4 gate[2][NIT];
+  auto fetch_gate = [&](int strip, us4 (&dst)[NIT]) {
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+      const int row = m0 + wm + strip * SR + it * RPI + lr;
+      dst[it] = us4{0, 0, 0, 0};
+      if (row < g.m && col_ok)
+        dst[it] = *reinterpret_cast<const us4*>(g.mask + (int64_t)z * g.mask_bs + (int64_t)row * g.mask_ld + col);
+    }
+  };
+  uint32_t drop_thresh = 0u;
+  float drop_scale = 1.f;
+  if (EPI == HDET_EPI_BIAS_DROP_RESID_BF16) {
+    const float p = (float)hdet_channel_value(g.drop_ctrl, g.drop_channel, z, 0.0);
+    drop_thresh = (uint32_t)floor((double)p * 4294967296.0);
+    drop_scale = 1.f / (1.f - p);
+  }
+  // HDET_EPI_ADAMW: the tile is the replica's gradient of a weight matrix and is applied at once (Eq. 2 with the
+  // replica's rate); the matrix's parameters and moments of a strip are requested before the strip goes through LDS
+  constexpr bool kUpd = EPI == HDET_EPI_ADAMW;
+  hdet_um::rep_scalars us = {0.f, 0.f, 0.f, 0.f};
+  if (kUpd) {
+    us = hdet_um::replica_scalars(g.upd, z);
+    if (bx == 0 && by == 0 && tid == 0 && g.upd.lr_channel == 0) g.upd.ctrl_out->lr_used[z] = us.lr;
+  }
+  f4 uth[kUpd ? NIT : 1], um[kUpd ? NIT : 1], uv[kUpd ? NIT : 1];
+  auto fetch_upd = [&](int strip) {
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+      const int row = m0 + wm + strip * SR + it * RPI + lr;
+      if (row < g.m && col_ok) {
+        const int64_t off = c_base + (int64_t)row * g.ldc + col;
+        uth[it] = __builtin_nontemporal_load(reinterpret_cast<const f4*>(g.upd.theta + off));
+        um[it] = __builtin_nontemporal_load(reinterpret_cast<const f4*>(g.upd.m + off));
+        uv[it] = __builtin_nontemporal_load(reinterpret_cast<const f4*>(g.upd.v + off));
+      }
+    }
+  };
+  // column sums of the stored result over the rows this lane stores, for its 4 columns
+  constexpr bool kColsum = EPI == HDET_EPI_GELUGRAD_BF16 || EPI == HDET_EPI_MASK_BF16;
+  f4 csum = {0.f, 0.f, 0.f, 0.f};
+  if (kGate) fetch_gate(0, gate[0]);
+  f4 bias = {0.f, 0.f, 0.f, 0.f};
+  if (kBias && col_ok) bias = *reinterpret_cast<const f4*>(g.bias + (int64_t)z * g.bias_bs + col);
+#pragma unroll
+  for (int strip = 0; strip < NSTRIP; ++strip) {
+    if (kGate && strip + 1 < NSTRIP) fetch_gate(strip + 1, gate[(strip + 1) & 1]);
+    if (kUpd) fetch_upd(strip);
+    // accumulator element e of lane l is C(row, col) with row = l % 16, col = (l / 16) * 4 + e inside its 16 x 16 block
+#pragma unroll
+    for (int ib = 0; ib < SR / 16; ++ib)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        *reinterpret_cast<f4*>(stg + (ib * 16 + (lane & 15)) * EP + j * 16 + (lane >> 4) * 4) = acc[strip * (SR / 16) + ib][j];
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+      f4 v = *reinterpret_cast<const f4*>(stg + (it * RPI + lr) * EP + lc);
+      const int row = m0 + wm + strip * SR + it * RPI + lr;
+      if (row < g.m && col_ok) {
+        const int64_t off = c_base + (int64_t)row * g.ldc + col;
+                  if (kBias) v += bias;
+                  if (EPI == HDET_EPI_BIAS_RELU_BF16) {
+        #pragma unroll
+                    for (int q = 0; q < 4; ++q) v[q] = v[q] > 0.f ? v[q] : 0.f;
+                  }
+                  if (EPI == HDET_EPI_MASK_BF16) {    // gradient through the ReLU of the layer below
+                    const us4 a = gate[strip & 1][it];
+        #pragma unroll
+                    for (int q = 0; q < 4; ++q) v[q] = bf2f(a[q]) > 0.f ? v[q] : 0.f;
+                  }
+                  if (EPI == HDET_EPI_BIAS_RESID_BF16) {  // the layer's output is rounded as the unfused path stores it, then added
+                    const us4 a = gate[strip & 1][it];
+        #pragma unroll
+                    for (int q = 0; q < 4; ++q) v[q] = bf2f(a[q]) + bf2f(f2bf(v[q]));
+                  }
+                  if (EPI == HDET_EPI_BIAS_DROP_RESID_BF16) {   // ... dropped out (one Philox block per 4 elements), then added
+                    const us4 a = gate[strip & 1][it];
+                    hdet_philox4 w = {{0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu}};
+                    if (drop_thresh != 0u)
+                      w = hdet_philox4x32_10((uint32_t)(((int64_t)row * g.ldc + col) >> 2), g.drop_step, (uint32_t)z * 65536u + g.drop_site,
+                                             g.drop_stream, g.drop_seed_lo, g.drop_seed_hi);
+        #pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                      float y = bf2f(f2bf(v[q]));
+                      if (drop_thresh != 0u) y = w.x[q] >= drop_thresh ? y * drop_scale : 0.f;
+                      v[q] = bf2f(a[q]) + y;
+                    }
+                  }
+                  if (EPI == HDET_EPI_GELUGRAD_BF16) {  // the incoming gradient is rounded as the unfused path stores it
+                    const us4 a = gate[strip & 1][it];
+        #pragma unroll
+                    for (int q = 0; q < 4; ++q) v[q] = bf2f(f2bf(v[q])) * hdet_gelu_tanh_grad_fast(bf2f(a[q]));
+                  }
+                  if (EPI == HDET_EPI_ADAMW) {
+                    f4 th = uth[it], mm = um[it], vv = uv[it];
+                    hdet_um::update_one<HDET_ADAMW, f4>(th, v, mm, vv, g.upd, us);
+                    __builtin_nontemporal_store(mm, reinterpret_cast<f4*>(g.upd.m + off));
+                    __builtin_nontemporal_store(vv, reinterpret_cast<f4*>(g.upd.v + off));
+                    __builtin_nontemporal_store(th, reinterpret_cast<f4*>(g.upd.theta + off));
+                    if (g.upd.shadow) {
+                      const us4 o = {hdet_um::to_bf16(th[0]), hdet_um::to_bf16(th[1]), hdet_um::to_bf16(th[2]), hdet_um::to_bf16(th[3])};
+                      __builtin_nontemporal_store(o, reinterpret_cast<us4*>(g.upd.shadow + off));
+                    }
+                  } else if (EPI == HDET_EPI_F32 || EPI == HDET_EPI_BIAS_F32) {
+                    put(reinterpret_cast<f4*>(reinterpret_cast<float*>(g.c) + off), v);
+                  } else if (EPI == HDET_EPI_BIAS_GELU_BF16) {
+                    const us4 pre = {f2bf(v[0]), f2bf(v[1]), f2bf(v[2]), f2bf(v[3])};
+                    put(reinterpret_cast<us4*>(reinterpret_cast<uint16_t*>(g.c) + off), pre);
+                    const us4 o = {f2bf(hdet_gelu_tanh_fast(bf2f(pre[0]))), f2bf(hdet_gelu_tanh_fast(bf2f(pre[1]))),
+                                   f2bf(hdet_gelu_tanh_fast(bf2f(pre[2]))), f2bf(hdet_gelu_tanh_fast(bf2f(pre[3])))};
+                    put(reinterpret_cast<us4*>(reinterpret_cast<uint16_t*>(g.c2) + off), o);
+                  } else {
+                    const us4 o = {f2bf(v[0]), f2bf(v[1]), f2bf(v[2]), f2bf(v[3])};
+                    put(reinterpret_cast<us4*>(reinterpret_cast<uint16_t*>(g.c) + off), o);
+                    if (kColsum) {
+        #pragma unroll
+                      for (int q = 0; q < 4; ++q) csum[q] += bf2f(o[q]);
+                    }
+                  }
+      }
+    }
+  }
+  // Stage 1 of the column sums: a lane has added its rows in ascending order; the RPI lanes that hold the same
+  // columns are added by exchanges (a fixed tree), then the wavefronts that share a 128-row block in the order of
+  // their rows.  Every (128-row block, column) of C is written by exactly one block of the grid.
+  if (kColsum && g.colsum) {
+    static_assert(TM % 128 == 0 && TM / WGM <= 128 && 128 % (TM / WGM) == 0, "wavefronts must tile 128-row blocks");
+    float* cbuf = reinterpret_cast<float*>(S);         // [WGM * WGN wavefronts][CW columns]
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      float x = csum[q];
+#pragma unroll
+      for (int o = LPR; o < 64; o <<= 1) x += __shfl_xor(x, o);
+      csum[q] = x;
+    }
+    __syncthreads();                                   // the strips are no longer in use
+    if (lane < LPR) *reinterpret_cast<f4*>(cbuf + wave * CW + lc) = csum;
+    __syncthreads();
+    constexpr int WPC = 128 / (TM / WGM),              // wavefronts (along m) per 128-row block
+                  CHUNKS = TM / 128;
+    const int nchunks = (g.m + 127) / 128;
+    for (int t = tid; t < CHUNKS * TN; t += THREADS) {
+      const int ch = t / TN, cn = t % TN;              // 128-row block of the tile, column of the tile
+      float a = 0.f;
+#pragma unroll
+      for (int u = 0; u < WPC; ++u) a += cbuf[((ch * WPC + u) * WGN + cn / CW) * CW + cn % CW];
+      const int chunk = m0 / 128 + ch, c = n0 + cn;
+      if (chunk < nchunks && c < g.n) g.colsum[((int64_t)z * nchunks + chunk) * g.n + c] = a;
+    }
+  }
+}
+
 }  // namespace
 
 // Two blocks share a CU when their stages fit twice into the 160 KiB of LDS; the register budget
 // follows (second launch-bound argument: wavefronts per SIMD).
-// STREAM: results are written past the L2 (stream_result).
 template <bool A_KMAJOR, bool B_KMAJOR, int EPI, int TM, int TN, int WGM, int WGN, int NST, int TK, bool STREAM>
-__global__ __launch_bounds__(64 * WGM * WGN, (NST * (TM + TN) * TK * 2 <= 80 * 1024 ? 2 : 1) * (WGM * WGN / 4))
+__global__ __launch_bounds__(64 * WGM * WGN, 160 * 1024 / (NST * (TM + TN) * TK * 2) * (WGM * WGN / 4))
 void hdet_bgemm_dma_kernel(const hdet_bgemm_args g) {
   constexpr int THREADS = 64 * WGM * WGN;
   constexpr int WMT = TM / WGM / 32, WNT = TN / WGN / 32;
@@ -153,28 +364,8 @@ void hdet_bgemm_dma_kernel(const hdet_bgemm_args g) {
   typedef lds_tile<B_KMAJOR, TN, THREADS, TK> tb;
   constexpr int LPT = ta::NI + tb::NI;            // load instructions per thread and stage
 
-  int bx, by, bz;
-  {
-    // Launch order -> tile: each XCD (own L2; blocks are dealt to the XCDs round-robin) works through a contiguous
-    // range of tiles, and inside a batch item consecutive tiles walk groups of tile_group tile rows column by column,
-    // so that the blocks an XCD runs at one time share operand tiles of both kinds in its L2.
-    const unsigned total = gridDim.x * gridDim.y * gridDim.z;
-    unsigned t = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
-    {   // XCD x = launch index mod 8 takes the x-th of eight contiguous ranges (the first total mod 8 ranges one tile longer)
-      const unsigned x = t & 7u, rem = total & 7u;
-      t = x * (total >> 3) + (x < rem ? x : rem) + (t >> 3);
-    }
-    const unsigned per = gridDim.x * gridDim.y;
-    bz = t / per;
-    const unsigned r = t - bz * per;
-    const unsigned gm = g.tile_group > 1 ? (unsigned)g.tile_group : 1u;
-    const unsigned gsz = gm * gridDim.x;
-    const unsigned grp = r / gsz, first = grp * gm;
-    const unsigned rows = gridDim.y - first < gm ? gridDim.y - first : gm;
-    const unsigned q = r - grp * gsz;
-    by = first + q % rows;
-    bx = q / rows;
-  }
+  const tile_id id = tile_of_block(g.tile_group);
+  const int bx = id.bx, by = id.by, bz = id.bz;
   const hdet_batch_index bi = hdet_split_batch(bz, g.n1, g.n2);
   const int z = bi.z0;            // replica: bias and mask are per replica
   const uint16_t* A = g.a + hdet_batch_offset(bi, g.a_s);
@@ -195,74 +386,97 @@ void hdet_bgemm_dma_kernel(const hdet_bgemm_args g) {
   la.init(m0, g.m, g.lda, tid);
   lb.init(n0, g.n, g.ldb, tid);
 
-  f16v acc[WMT][WNT];
+  constexpr int MB = TM / WGM / 16, NB = TN / WGN / 16;
+  f4 acc[MB][NB];
 #pragma unroll
-  for (int i = 0; i < WMT; ++i)
+  for (int i = 0; i < MB; ++i)
 #pragma unroll
-    for (int j = 0; j < WNT; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    for (int j = 0; j < NB; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
 
   const int nk = (g.k + TK - 1) / TK;
 #define STAGE_PTR(s) (S + (s) * STAGE)
 #define STAGE_ADDR(s) (s_addr + (s) * STAGE * 2)
-  // K steps 0 .. NST-1 are requested up front; steps past the end load nothing (all chunks absent)
+  auto request = [&](int s, int kt) {
 #pragma unroll
-  for (int s = 0; s < NST; ++s) {
+    for (int i = 0; i < ta::NI; ++i) la.issue_one(i, ra, STAGE_ADDR(s), kt, g.k, wave);
 #pragma unroll
-    for (int i = 0; i < ta::NI; ++i) la.issue_one(i, ra, STAGE_ADDR(s), s, g.k, wave);
-#pragma unroll
-    for (int i = 0; i < tb::NI; ++i) lb.issue_one(i, rb, STAGE_ADDR(s) + TM * TK * 2, s, g.k, wave);
-  }
-  wait_and_barrier<(NST - 1) * LPT>();
-
-  // Fragments are double-buffered in registers over the NSS = TK / 16 MFMA sub-steps of a K step:
-  // while the MFMAs of sub-step ss run on fa/fb[ss & 1], the fragments of the next sub-step (of
-  // the next stage after the last one) are read into the other set.
-  constexpr int NSS = TK / 16, NM = WMT * WNT, NR = WMT + WNT;
-  constexpr int IPA = (NR + NM - 1) / NM, IPB = (NR + LPT + NM - 1) / NM;
-  bf16x8 fa[2][WMT], fb[2][WNT];
-  auto read_frag = [&](bf16x8* a, bf16x8* b, const uint16_t* st, int ks, int idx) {
-    // order: a[0], b[0..WNT-1], a[1..WMT-1] -- what the first MFMAs of the next sub-step need first
-    if (idx == 0) a[0] = ta::fragment(st, wm, ks, lane);
-    else if (idx <= WNT) b[idx - 1] = tb::fragment(st + TM * TK, wn + (idx - 1) * 32, ks, lane);
-    else if (idx < NR) a[idx - WNT] = ta::fragment(st, wm + (idx - WNT) * 32, ks, lane);
+    for (int i = 0; i < tb::NI; ++i) lb.issue_one(i, rb, STAGE_ADDR(s) + TM * TK * 2, kt, g.k, wave);
   };
+  // rows of C are the second operand's, so that a lane's four accumulators are consecutive columns
+  auto multiply = [&](const bf16x8* a, const bf16x8* b, int q) {
+    acc[q / NB][q % NB] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[q % NB], a[q / NB], acc[q / NB][q % NB], 0, 0, 0);
+  };
+  if constexpr (TK == 32) {
+    bf16x8 fa[MB], fb[NB];
 #pragma unroll
-  for (int idx = 0; idx < NR; ++idx) read_frag(fa[0], fb[0], S, 0, idx);
+    for (int s = 0; s < NST - 1; ++s) request(s, s);
+    for (int kt0 = 0; kt0 < nk; kt0 += NST) {
+#pragma unroll
+      for (int s = 0; s < NST; ++s) {
+        const int kt = kt0 + s;
+        if (kt >= nk) break;
+        wait_and_barrier<(NST - 2) * LPT>();
+#pragma unroll
+        for (int i = 0; i < MB; ++i) fa[i] = ta::fragment(STAGE_PTR(s), wm + i * 16, 0, lane);
+#pragma unroll
+        for (int j = 0; j < NB; ++j) fb[j] = tb::fragment(STAGE_PTR(s) + TM * TK, wn + j * 16, 0, lane);
+        request((s + NST - 1) % NST, kt + NST - 1);
+#pragma unroll
+        for (int q = 0; q < MB * NB; ++q) multiply(fa, fb, q);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int s = 0; s < NST; ++s) request(s, s);
+    wait_and_barrier<(NST - 1) * LPT>();
 
-  for (int kt0 = 0; kt0 < nk; kt0 += NST) {
+    // Fragments are double-buffered in registers over the NSS = TK / 32 MFMA sub-steps of a K step:
+    // while the MFMAs of sub-step ss run on fa/fb[ss & 1], the fragments of the next sub-step (of
+    // the next stage after the last one) are read into the other set.
+    constexpr int NSS = TK / 32, NM = MB * NB, NR = MB + NB;
+    constexpr int IPA = (NR + NM - 1) / NM, IPB = (NR + LPT + NM - 1) / NM;
+    bf16x8 fa[2][MB], fb[2][NB];
+    auto read_frag = [&](bf16x8* a, bf16x8* b, const uint16_t* st, int ks, int idx) {
+      // order: a[0], b[0..], a[1..] -- what the first MFMAs of the next sub-step need first
+      if (idx == 0) a[0] = ta::fragment(st, wm, ks, lane);
+      else if (idx <= NB) b[idx - 1] = tb::fragment(st + TM * TK, wn + (idx - 1) * 16, ks, lane);
+      else if (idx < NR) a[idx - NB] = ta::fragment(st, wm + (idx - NB) * 16, ks, lane);
+    };
 #pragma unroll
-    for (int s = 0; s < NST; ++s) {
-      const int kt = kt0 + s;
-      if (kt >= nk) break;
-      const uint16_t* cur = STAGE_PTR(s);
-      const uint16_t* nxt = STAGE_PTR((s + 1) % NST);
+    for (int idx = 0; idx < NR; ++idx) read_frag(fa[0], fb[0], S, 0, idx);
+
+    for (int kt0 = 0; kt0 < nk; kt0 += NST) {
 #pragma unroll
-      for (int ss = 0; ss < NSS - 1; ++ss) {
+      for (int s = 0; s < NST; ++s) {
+        const int kt = kt0 + s;
+        if (kt >= nk) break;
+        const uint16_t* cur = STAGE_PTR(s);
+        const uint16_t* nxt = STAGE_PTR((s + 1) % NST);
+#pragma unroll
+        for (int ss = 0; ss < NSS - 1; ++ss) {
+#pragma unroll
+          for (int q = 0; q < NM; ++q) {
+            multiply(fa[ss & 1], fb[ss & 1], q);
+#pragma unroll
+            for (int u = 0; u < IPA; ++u) read_frag(fa[(ss + 1) & 1], fb[(ss + 1) & 1], cur, (ss + 1) * 32, q * IPA + u);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+        // every wavefront has read all of stage `cur`; stage `nxt` (K step kt + 1) has landed
+        wait_and_barrier<(NST - 2) * LPT>();
 #pragma unroll
         for (int q = 0; q < NM; ++q) {
-          acc[q / WNT][q % WNT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ss & 1][q / WNT], fb[ss & 1][q % WNT],
-                                                                          acc[q / WNT][q % WNT], 0, 0, 0);
+          multiply(fa[(NSS - 1) & 1], fb[(NSS - 1) & 1], q);
 #pragma unroll
-          for (int u = 0; u < IPA; ++u) read_frag(fa[(ss + 1) & 1], fb[(ss + 1) & 1], cur, (ss + 1) * 16, q * IPA + u);
+          for (int u = 0; u < IPB; ++u) {
+            const int it = q * IPB + u;
+            if (it < ta::NI) la.issue_one(it, ra, STAGE_ADDR(s), kt + NST, g.k, wave);
+            else if (it < LPT) lb.issue_one(it - ta::NI, rb, STAGE_ADDR(s) + TM * TK * 2, kt + NST, g.k, wave);
+            else read_frag(fa[0], fb[0], nxt, 0, it - LPT);
+          }
           __builtin_amdgcn_sched_barrier(0);
         }
-      }
-      // every wavefront has read all of stage `cur`; stage `nxt` (K step kt + 1) has landed
-      wait_and_barrier<(NST - 2) * LPT>();
-#pragma unroll
-      for (int q = 0; q < NM; ++q) {
-        acc[q / WNT][q % WNT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[(NSS - 1) & 1][q / WNT], fb[(NSS - 1) & 1][q % WNT],
-                                                                        acc[q / WNT][q % WNT], 0, 0, 0);
-#pragma unroll
-        for (int u = 0; u < IPB; ++u) {
-          const int it = q * IPB + u;
-          if (it < ta::NI) la.issue_one(it, ra, STAGE_ADDR(s), kt + NST, g.k, wave);
-          else if (it < LPT) lb.issue_one(it - ta::NI, rb, STAGE_ADDR(s) + TM * TK * 2, kt + NST, g.k, wave);
-          else read_frag(fa[0], fb[0], nxt, 0, it - LPT);
-        }
-        __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
@@ -272,196 +486,154 @@ void hdet_bgemm_dma_kernel(const hdet_bgemm_args g) {
   // they become the staging area of the epilogue
   wait_and_barrier<0>();
 
-  // Epilogue through LDS, one 32-row strip of at most 64 columns at a time: the accumulators
-  // (lane = column, 4 consecutive rows per 4 elements) are written as fp32 [32][CW] with a pitch
-  // that keeps the two half-wavefronts on disjoint banks, and read back with 4 consecutive
-  // columns per lane, so that every global store instruction writes whole rows of the strip.
-  // The strip is private to the wavefront and LDS serves one wavefront's accesses in order.
-  constexpr int JG = WNT < 2 ? WNT : 2;       // 32-column blocks per strip
-  constexpr int CW = JG * 32, EP = CW + 8, LPR = CW / 4, RPI = 64 / LPR;
-  static_assert(WGM * WGN * 32 * EP * 4 <= NST * STAGE * 2, "staging area exceeds the stage buffers");
-  float* stg = reinterpret_cast<float*>(S) + wave * (32 * EP);
-  const int lr = lane / LPR, lc = (lane % LPR) * 4;
-  auto put = [&](auto* p, auto v) {
-    if (STREAM) __builtin_nontemporal_store(v, p);
-    else *p = v;
-  };
-  constexpr bool kBias = EPI == HDET_EPI_BIAS_RELU_BF16 || EPI == HDET_EPI_BIAS_F32 || EPI == HDET_EPI_BIAS_BF16 ||
-                         EPI == HDET_EPI_BIAS_GELU_BF16 || EPI == HDET_EPI_BIAS_RESID_BF16 || EPI == HDET_EPI_BIAS_DROP_RESID_BF16;
-  // the second operand of the gating epilogues (the activations a ReLU or GELU gradient looks at) is
-  // fetched one strip ahead, so that its latency hides behind the previous strip's pass through LDS
-  constexpr bool kGate = EPI == HDET_EPI_MASK_BF16 || EPI == HDET_EPI_GELUGRAD_BF16 || EPI == HDET_EPI_BIAS_RESID_BF16 ||
-                         EPI == HDET_EPI_BIAS_DROP_RESID_BF16;
-  constexpr int NIT = 32 / RPI, NSTRIP = (WNT / JG) * WMT;
-  us4 gate[2][NIT];
-  auto fetch_gate = [&](int strip, us4 (&dst)[NIT]) {
-    const int col = n0 + wn + (strip / WMT) * CW + lc;
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-      const int row = m0 + wm + (strip % WMT) * 32 + it * RPI + lr;
-      dst[it] = us4{0, 0, 0, 0};
-      if (row < g.m && col < g.n)
-        dst[it] = *reinterpret_cast<const us4*>(g.mask + (int64_t)z * g.mask_bs + (int64_t)row * g.mask_ld + col);
+  store_tile<EPI, TM, TN, WGM, WGN, STREAM, NST * STAGE * 2>(g, acc, S, bx, by, z, c_base, tid);
+}
+
+namespace {
+
+// A tile of the kernel below: ROWS rows of the output dimension x 64 of the contraction, loaded by 512 threads.
+// KMAJOR: LDS [row][64], otherwise [k][ROWS], chunks permuted as in lds_tile.  SPLIT: LDS rows 64 .. 127 are the operand's rows 128 .. 191.
+// Rows (KMAJOR) or k (otherwise) past the operand's end lie past its extent as they are; the other edge is masked.  One offset a
+// lane: what the loads of a tile differ by is uniform (an offset and a k index for each load, as in lds_tile, spill).
+template <bool KMAJOR, int ROWS, bool SPLIT>
+struct half_tile {
+  static constexpr int NI = ROWS / 64, RCH = ROWS / 8;
+  typedef lds_tile<KMAJOR, ROWS, 512, 64> tile;
+  uint32_t off;          // byte offset of this lane's first chunk at K step 0, or kAbsent
+  __device__ __forceinline__ void init(int row0, int rows, int64_t ld, int tid) {
+    if (KMAJOR) off = (uint32_t)(((row0 + (tid >> 3)) * ld + chunk_k(tid)) * 2);
+    else {
+      const int kk = tid / RCH, r = ((tid % RCH) ^ tile::swz_k(kk)) * 8, row = row0 + (SPLIT ? r + (r & 64) : r);
+      off = row < rows ? (uint32_t)((kk * ld + row) * 2) : kAbsent;
     }
+  }
+  // k index of a thread's chunk inside a K step (KMAJOR)
+  static __device__ __forceinline__ int chunk_k(int tid) { return ((tid & 7) ^ tile::swz(tid >> 3)) * 8; }
+  // load instruction i: 64 further rows (KMAJOR), 4096 / ROWS further k (otherwise)
+  __device__ __forceinline__ void load(int i, i4 rsrc, uint32_t addr, int kt, int64_t ld, bool k_ok, int wave) const {
+    const uint32_t step = KMAJOR ? (uint32_t)(kt * 128 + (int64_t)(SPLIT ? 128 * i : 64 * i) * ld * 2) : (uint32_t)((kt * 64 + i * (4096 / ROWS)) * ld * 2);
+    lds_load16(rsrc, addr + (i * 512 + wave * 64) * 16, !KMAJOR || k_ok ? off + step : kAbsent);
+  }
+};
+
+}  // namespace
+
+// The 256 x 256 tile.  What bounds the long products is the power that the chip may draw, then the cycles in which no MFMA runs.
+//  * Eight wavefronts of 128 x 64 in two groups of four, one of each group on every SIMD: while one group multiplies (32 MFMAs, 512 cycles), the
+//    other reads its next fragments from LDS and requests a later stage; the block's barriers hand the matrix cores from one to the other, and
+//    s_setprio keeps the reading wavefront from delaying the multiplying one.  A K step of 64 is two such turns: rows 0-63 of the wavefront
+//    with all of its columns, then rows 64-127 with the column fragments still in registers.
+//  * Two stages of 64 KiB.  The half of A that the first turn reads, and B, are free for K step kt + 2 from the second turn of kt on, the other half
+//    from the first turn of kt + 1 on, so every load has five or six turns (2500-3000 cycles) to land and each turn waits for all
+//    but the newest eight of the wavefront's loads.  A turn's LDS reads are complete before its first barrier, which is what lets the other
+//    group (one turn behind) and this one request into what they read.
+// Per replica 8192 x 1024, K = 4096, 8 replicas: input gradients 454 -> 391 us (1.41 PFLOP/s), with bias and residual 472 -> 412; weight gradients
+// 4096 x 1024, K = 8192: 439 -> 390 (all eight wavefronts in step before, as in the kernel above: matrix cores busy 59 % of the cycles at
+// 1.94 GHz, now 70 % at 1.9; the weight gradients 69 % at 1.76 and 73 % at 1.87).  Measured and not kept: loads requested between the MFMAs with the
+// barrier's wait on LDS left out, 1-6 % slower; handing over 2 or 4 MFMAs before the end of a turn, 8-12 % slower; 256 x 128 tiles
+// in three stages, 5 % faster than kLong on long products and no faster where the weights are streamed.
+template <bool A_KMAJOR, bool B_KMAJOR, int EPI, bool STREAM>
+__global__ __launch_bounds__(512, 2) void hdet_bgemm_alt_kernel(const hdet_bgemm_args g) {
+  constexpr int TM = 256, TN = 256, TK = 64, HALF = 128 * TK, WGM = 2, WGN = 4, MB = TM / WGM / 16;
+  __shared__ __attribute__((aligned(1024))) uint16_t S[8 * HALF];
+  typedef half_tile<A_KMAJOR, 128, true> ta;
+  typedef half_tile<B_KMAJOR, TN, false> tb;
+  const tile_id id = tile_of_block(g.tile_group);
+  const hdet_batch_index bi = hdet_split_batch(id.bz, g.n1, g.n2);
+  const uint16_t* A = g.a + hdet_batch_offset(bi, g.a_s);
+  const uint16_t* B = g.b + hdet_batch_offset(bi, g.b_s);
+  const int64_t c_base = hdet_batch_offset(bi, g.c_s);
+  const int m0 = id.by * TM, n0 = id.bx * TN;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wn = (wave % WGN) * 64, hr = (wave / WGN) * 64;
+  const uint32_t a_bytes = (uint32_t)(((int64_t)((A_KMAJOR ? g.m : g.k) - 1) * g.lda + (A_KMAJOR ? g.k : g.m)) * 2);
+  const uint32_t b_bytes = (uint32_t)(((int64_t)((B_KMAJOR ? g.n : g.k) - 1) * g.ldb + (B_KMAJOR ? g.k : g.n)) * 2);
+  const i4 ra = make_rsrc(A, a_bytes), rb = make_rsrc(B, b_bytes);
+  const uint32_t s_addr = lds_addr_of(S);
+
+  ta la[2]; tb lb;
+  la[0].init(m0, g.m, g.lda, tid);
+  la[1].init(m0 + 64, g.m, g.lda, tid);
+  lb.init(n0, g.n, g.ldb, tid);
+  const int ck = ta::chunk_k(tid);
+
+  f4 acc[MB][4];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+
+  // LDS, in units of 128 rows x 64: half h of A of stage s at 2 h + s, B at 4 + 2 s
+  const int nk = (g.k + TK - 1) / TK;
+  auto load_a = [&](int h, int s, int kt) {
+    const uint32_t at = s_addr + (2 * h + s) * HALF * 2;
+#pragma unroll
+    for (int i = 0; i < ta::NI; ++i) la[h].load(i, ra, at, kt, g.lda, ck + kt * TK < g.k, wave);
   };
-  uint32_t drop_thresh = 0u;
-  float drop_scale = 1.f;
-  if (EPI == HDET_EPI_BIAS_DROP_RESID_BF16) {
-    const float p = (float)hdet_channel_value(g.drop_ctrl, g.drop_channel, z, 0.0);
-    drop_thresh = (uint32_t)floor((double)p * 4294967296.0);
-    drop_scale = 1.f / (1.f - p);
-  }
-  // HDET_EPI_ADAMW: the tile is the replica's gradient of a weight matrix and is applied at once (Eq. 2 with the
-  // replica's rate); the matrix's parameters and moments of a strip are requested before the strip goes through LDS
-  constexpr bool kUpd = EPI == HDET_EPI_ADAMW;
-  hdet_um::rep_scalars us = {0.f, 0.f, 0.f, 0.f};
-  if (kUpd) {
-    us = hdet_um::replica_scalars(g.upd, z);
-    if (bx == 0 && by == 0 && tid == 0 && g.upd.lr_channel == 0) g.upd.ctrl_out->lr_used[z] = us.lr;
-  }
-  f4 uth[kUpd ? NIT : 1], um[kUpd ? NIT : 1], uv[kUpd ? NIT : 1];
-  // column sums of the stored result over the wavefront's rows, for the columns this lane stores (per strip column group)
-  constexpr bool kColsum = EPI == HDET_EPI_GELUGRAD_BF16 || EPI == HDET_EPI_MASK_BF16;
-  f4 csum[WNT / JG];
+  auto load_b = [&](int s, int kt) {
+    const uint32_t at = s_addr + (4 + 2 * s) * HALF * 2;
 #pragma unroll
-  for (int jg = 0; jg < WNT / JG; ++jg) csum[jg] = f4{0.f, 0.f, 0.f, 0.f};
-  if (kGate) fetch_gate(0, gate[0]);
+    for (int i = 0; i < tb::NI; ++i) lb.load(i, rb, at, kt, g.ldb, ck + kt * TK < g.k, wave);
+  };
+  bf16x8 fa[2][4], fb[2][4];
+  auto read_a = [&](int h, int s) {
 #pragma unroll
-  for (int jg = 0; jg < WNT / JG; ++jg) {
-    const int col = n0 + wn + jg * CW + lc;
-    const bool col_ok = col < g.n;             // n is a multiple of 4: the 4 columns exist together
-    f4 bias = {0.f, 0.f, 0.f, 0.f};
-    if (kBias && col_ok) bias = *reinterpret_cast<const f4*>(g.bias + (int64_t)z * g.bias_bs + col);
+    for (int ss = 0; ss < 2; ++ss)
 #pragma unroll
-    for (int i = 0; i < WMT; ++i) {
-      const int strip = jg * WMT + i;
-      if (kGate && strip + 1 < NSTRIP) fetch_gate(strip + 1, gate[(strip + 1) & 1]);
-      if (kUpd) {
+      for (int i = 0; i < 4; ++i) fa[ss][i] = ta::tile::fragment(S + (2 * h + s) * HALF, hr + i * 16, ss * 32, lane);
+  };
+  auto read_b = [&](int s) {
 #pragma unroll
-        for (int it = 0; it < NIT; ++it) {
-          const int row = m0 + wm + i * 32 + it * RPI + lr;
-          if (row < g.m && col_ok) {
-            const int64_t off = c_base + (int64_t)row * g.ldc + col;
-            uth[it] = __builtin_nontemporal_load(reinterpret_cast<const f4*>(g.upd.theta + off));
-            um[it] = __builtin_nontemporal_load(reinterpret_cast<const f4*>(g.upd.m + off));
-            uv[it] = __builtin_nontemporal_load(reinterpret_cast<const f4*>(g.upd.v + off));
-          }
+    for (int ss = 0; ss < 2; ++ss)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) fb[ss][j] = tb::tile::fragment(S + (4 + 2 * s) * HALF, wn + j * 16, ss * 32, lane);
+  };
+  auto multiply = [&](int h) {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int ss = 0; ss < 2; ++ss)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          acc[4 * h + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[ss][j], fa[ss][i], acc[4 * h + i][j], 0, 0, 0);
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto meet = [] {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+      load_a(0, 0, 0); load_b(0, 0); load_a(1, 0, 0);
+      load_a(0, 1, 1); load_b(1, 1);
+      wait_and_barrier<8>();
+      if (wave >= 4) meet();
+      for (int kt0 = 0; kt0 < nk; kt0 += 2) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          const int kt = kt0 + s;
+          if (kt >= nk) break;
+          read_a(0, s);
+          read_b(s);
+          load_a(1, s ^ 1, kt + 1);
+          wait_and_barrier<8>();
+          multiply(0);
+          meet();
+          read_a(1, s);
+          load_a(0, s, kt + 2);
+          load_b(s, kt + 2);
+          wait_and_barrier<8>();
+          multiply(1);
+          meet();
         }
       }
-      // accumulator element e of lane l is C(row, col) with row = (e / 4) * 8 + (l / 32) * 4 + e % 4,
-      // col = l % 32 inside its 32x32 block
-#pragma unroll
-      for (int j = 0; j < JG; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e)
-          stg[((e >> 2) * 8 + (lane >> 5) * 4 + (e & 3)) * EP + j * 32 + (lane & 31)] = acc[i][jg * JG + j][e];
-#pragma unroll
-      for (int it = 0; it < 32 / RPI; ++it) {
-        const int rl = it * RPI + lr;
-        f4 v = *reinterpret_cast<const f4*>(stg + rl * EP + lc);
-        const int row = m0 + wm + i * 32 + rl;
-        if (row < g.m && col_ok) {
-          const int64_t off = c_base + (int64_t)row * g.ldc + col;
-          if (kBias) v += bias;
-          if (EPI == HDET_EPI_BIAS_RELU_BF16) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = v[q] > 0.f ? v[q] : 0.f;
-          }
-          if (EPI == HDET_EPI_MASK_BF16) {    // gradient through the ReLU of the layer below
-            const us4 a = gate[strip & 1][it];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = bf2f(a[q]) > 0.f ? v[q] : 0.f;
-          }
-          if (EPI == HDET_EPI_BIAS_RESID_BF16) {  // the layer's output is rounded as the unfused path stores it, then added
-            const us4 a = gate[strip & 1][it];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = bf2f(a[q]) + bf2f(f2bf(v[q]));
-          }
-          if (EPI == HDET_EPI_BIAS_DROP_RESID_BF16) {   // ... dropped out (one Philox block per 4 elements), then added
-            const us4 a = gate[strip & 1][it];
-            hdet_philox4 w = {{0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu}};
-            if (drop_thresh != 0u)
-              w = hdet_philox4x32_10((uint32_t)(((int64_t)row * g.ldc + col) >> 2), g.drop_step, (uint32_t)z * 65536u + g.drop_site,
-                                     g.drop_stream, g.drop_seed_lo, g.drop_seed_hi);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              float y = bf2f(f2bf(v[q]));
-              if (drop_thresh != 0u) y = w.x[q] >= drop_thresh ? y * drop_scale : 0.f;
-              v[q] = bf2f(a[q]) + y;
-            }
-          }
-          if (EPI == HDET_EPI_GELUGRAD_BF16) {  // the incoming gradient is rounded as the unfused path stores it
-            const us4 a = gate[strip & 1][it];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = bf2f(f2bf(v[q])) * hdet_gelu_tanh_grad_fast(bf2f(a[q]));
-          }
-          if (EPI == HDET_EPI_ADAMW) {
-            f4 th = uth[it], mm = um[it], vv = uv[it];
-            hdet_um::update_one<HDET_ADAMW, f4>(th, v, mm, vv, g.upd, us);
-            __builtin_nontemporal_store(mm, reinterpret_cast<f4*>(g.upd.m + off));
-            __builtin_nontemporal_store(vv, reinterpret_cast<f4*>(g.upd.v + off));
-            __builtin_nontemporal_store(th, reinterpret_cast<f4*>(g.upd.theta + off));
-            if (g.upd.shadow) {
-              const us4 o = {hdet_um::to_bf16(th[0]), hdet_um::to_bf16(th[1]), hdet_um::to_bf16(th[2]), hdet_um::to_bf16(th[3])};
-              __builtin_nontemporal_store(o, reinterpret_cast<us4*>(g.upd.shadow + off));
-            }
-          } else if (EPI == HDET_EPI_F32 || EPI == HDET_EPI_BIAS_F32) {
-            put(reinterpret_cast<f4*>(reinterpret_cast<float*>(g.c) + off), v);
-          } else if (EPI == HDET_EPI_BIAS_GELU_BF16) {
-            const us4 pre = {f2bf(v[0]), f2bf(v[1]), f2bf(v[2]), f2bf(v[3])};
-            put(reinterpret_cast<us4*>(reinterpret_cast<uint16_t*>(g.c) + off), pre);
-            const us4 o = {f2bf(hdet_gelu_tanh_fast(bf2f(pre[0]))), f2bf(hdet_gelu_tanh_fast(bf2f(pre[1]))),
-                           f2bf(hdet_gelu_tanh_fast(bf2f(pre[2]))), f2bf(hdet_gelu_tanh_fast(bf2f(pre[3])))};
-            put(reinterpret_cast<us4*>(reinterpret_cast<uint16_t*>(g.c2) + off), o);
-          } else {
-            const us4 o = {f2bf(v[0]), f2bf(v[1]), f2bf(v[2]), f2bf(v[3])};
-            put(reinterpret_cast<us4*>(reinterpret_cast<uint16_t*>(g.c) + off), o);
-            if (kColsum) {
-#pragma unroll
-              for (int q = 0; q < 4; ++q) csum[jg][q] += bf2f(o[q]);
-            }
-          }
-        }
-      }
-    }
-  }
-  // Stage 1 of the column sums: a lane has added its rows in ascending order; the RPI lanes that hold the same
-  // columns are added by exchanges (a fixed tree), then the wavefronts that share a 128-row block in the order of
-  // their rows.  Every (128-row block, column) of C is written by exactly one block of the grid.
-  if (kColsum && g.colsum) {
-    constexpr int RW = TM / WGM;                      // rows per wavefront
-    static_assert(TM % 128 == 0 && RW <= 128 && 128 % RW == 0, "wavefronts must tile 128-row blocks");
-    float* cbuf = reinterpret_cast<float*>(S);        // [WGM * WGN wavefronts][TN / WGN columns]
-#pragma unroll
-    for (int jg = 0; jg < WNT / JG; ++jg)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        float x = csum[jg][q];
-#pragma unroll
-        for (int o = LPR; o < 64; o <<= 1) x += __shfl_xor(x, o);
-        csum[jg][q] = x;
-      }
-    __syncthreads();                                   // the strips are no longer in use
-    if (lane < LPR) {
-#pragma unroll
-      for (int jg = 0; jg < WNT / JG; ++jg)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) cbuf[wave * (TN / WGN) + jg * CW + lc + q] = csum[jg][q];
-    }
-    __syncthreads();
-    constexpr int WPC = RW >= 128 ? 1 : 128 / RW;      // wavefronts (along m) per 128-row block
-    constexpr int CHUNKS = TM >= 128 ? TM / 128 : 1;
-    const int nchunks = (g.m + 127) / 128;
-    for (int t = tid; t < CHUNKS * TN; t += THREADS) {
-      const int ch = t / TN, cn = t % TN;              // chunk of the tile, column of the tile
-      const int wcol = cn / (TN / WGN), ccol = cn % (TN / WGN);
-      float a = 0.f;
-#pragma unroll
-      for (int u = 0; u < WPC; ++u) a += cbuf[((ch * WPC + u) * WGN + wcol) * (TN / WGN) + ccol];
-      const int chunk = m0 / 128 + ch, col = n0 + cn;
-      if (chunk < nchunks && col < g.n) g.colsum[((int64_t)z * nchunks + chunk) * g.n + col] = a;
-    }
-  }
+  if (wave < 4) meet();
+  wait_and_barrier<0>();
+  store_tile<EPI, TM, TN, WGM, WGN, STREAM, 8 * HALF * 2>(g, acc, S, id.bx, id.by, bi.z0, c_base, tid);
 }
 
 namespace {
@@ -521,49 +693,68 @@ bool stream_result(const hdet_bgemm_args& g, int epi, int batch) {
   return false;
 }
 
+// Which tile a product takes: the one whose time by
+//   base + rounds (epi share + slope K / 1000)  us,     rounds = ceil(tiles / CUs) / (blocks per CU), at least `least`
+// is the lowest.  `epi` is what the epilogue of a 256 x 256 tile takes where nothing hides it; a smaller tile takes `share` of it, less where a
+// second block of the CU multiplies meanwhile.  The constants come from sweeps of every tile over 18 grids of 72 to 1536 tiles of
+// 256 x 256, K = 64 .. 4096, with ten epilogues, the operands cold (another gigabyte of them each launch: with warm ones the smaller tiles, which
+// read their operands more often, look 10 to 30 % better than they are in a training step).  Against the fastest tile of each product this
+// choice loses 0.2 to 1 % on average by epilogue, 21 % at most (384 tiles at K = 1024 with both GELU outputs); lines by K and tile count
+// lost up to 34 %.  The alternating kernel is left out below K = 512 (1024 for weight gradients, 2048 for the GELU gradient, whose
+// epilogue takes as long as 1024 of K: 719 against 690 us for 8192 x 4096 x 8 in a step), where the model flatters it.
+struct tile_shape { int tm, tn, per_cu; float base, share, slope, least; };
+constexpr tile_shape kAlternating = {256, 256, 1, 1.6f, 1.f, 19.f, 1.f};       // hdet_bgemm_alt_kernel
+constexpr tile_shape kPair = {256, 128, 2, 3.6f, 0.53f, 32.f, 0.52f};          // K step 32, three stages, two blocks a CU
+constexpr tile_shape kPairWgrad = {256, 128, 2, 3.6f, 0.53f, 27.3f, 0.52f};
+constexpr tile_shape kLong = {256, 128, 1, 2.35f, 0.51f, 13.6f, 1.f};          // K step 64, three stages
+constexpr tile_shape kSmall = {128, 128, 2, 3.1f, 0.44f, 18.1f, 0.8f};         // K step 64, two stages, two blocks a CU
+template <int EPI> constexpr float kEpiTime =
+    EPI == HDET_EPI_ADAMW ? 80.f : EPI == HDET_EPI_GELUGRAD_BF16 || EPI == HDET_EPI_BIAS_DROP_RESID_BF16 ? 20.f
+    : EPI == HDET_EPI_MASK_BF16 || EPI == HDET_EPI_BIAS_RESID_BF16 || EPI == HDET_EPI_BIAS_GELU_BF16 ? 15.f
+    : EPI == HDET_EPI_F32 || EPI == HDET_EPI_BIAS_F32 ? 12.f : EPI == HDET_EPI_BIAS_RELU_BF16 ? 9.f : 8.f;
+
 template <bool AK, bool BK, int EPI>
 hipError_t launch_shape(const hdet_bgemm_args& g, int batch, hipStream_t s) {
-  auto blocks = [&](int tm, int tn) { return (int64_t)((g.m + tm - 1) / tm) * ((g.n + tn - 1) / tn) * batch; };
-  const int kCus = compute_units();
-  // a gating epilogue is long enough to want a second block on the CU up to K = 1024
-  constexpr bool gating = EPI == HDET_EPI_MASK_BF16 || EPI == HDET_EPI_GELUGRAD_BF16;
-  const bool long_k = g.k >= (gating ? 2048 : 1024);
-  // Tile order inside a batch item: with many tile columns, the 32 blocks an XCD runs at a time would share one
-  // operand tile of A and none of B; walking groups of 4 (2) tile rows column by column cuts the operand bytes its L2
-  // has to fetch by up to two thirds (head product of the transformer, 125 tile columns: 9-11 % faster).
+  constexpr bool wgrad = !AK && !BK, update = EPI == HDET_EPI_ADAMW;
+  const int cus = compute_units();
+  const float epi = kEpiTime<EPI>;
+  auto time_of = [&](const tile_shape& t) {
+    const int64_t tiles = (int64_t)((g.m + t.tm - 1) / t.tm) * ((g.n + t.tn - 1) / t.tn) * batch;
+    const float rounds = (float)((tiles + cus - 1) / cus) / t.per_cu;
+    return t.base + (rounds > t.least ? rounds : t.least) * (epi * t.share + t.slope * 1e-3f * g.k);
+  };
+  // the alternating kernel leaves the far edge of its tiles to the bounds of the buffer: no offset of a tile may wrap
+  const int64_t a_ext = ((int64_t)(AK ? g.m : g.k) + 256) * g.lda * 2, b_ext = ((int64_t)(BK ? g.n : g.k) + 256) * g.ldb * 2;
+  const bool alternating = g.k >= (update ? 1 : EPI == HDET_EPI_GELUGRAD_BF16 ? 2048 : wgrad ? 1024 : 512) && a_ext < (int64_t)1 << 31 && b_ext < (int64_t)1 << 31;
+  const float t_alt = alternating ? time_of(kAlternating) : 3e38f;
   const bool stream = kAlwaysStream<EPI> || stream_result(g, EPI, batch);
-#define HDET_DMA_KERNEL(TM, TN, WGM, WGN, NST, TK, STREAM) \
-  hipLaunchKernelGGL((hdet_bgemm_dma_kernel<AK, BK, EPI, TM, TN, WGM, WGN, NST, TK, STREAM>), grid, dim3(64 * WGM * WGN), 0, s, ga)
-#define HDET_DMA_LAUNCH(TM, TN, WGM, WGN, NST, TK)                                                            \
-  do {                                                                                                        \
-    const dim3 grid((g.n + TN - 1) / TN, (g.m + TM - 1) / TM, batch);                                          \
-    hdet_bgemm_args ga = g;                                                                                   \
-    ga.tile_group = grid.x >= 64 ? 4 : grid.x >= 12 ? 2 : 1;                                                  \
-    if (stream) HDET_DMA_KERNEL(TM, TN, WGM, WGN, NST, TK, true);                                             \
-    else if constexpr (!kAlwaysStream<EPI>) HDET_DMA_KERNEL(TM, TN, WGM, WGN, NST, TK, false);                \
+  auto launch = [&](auto kernel, const tile_shape& t, int threads) {
+    const dim3 grid((g.n + t.tn - 1) / t.tn, (g.m + t.tm - 1) / t.tm, batch);
+    hdet_bgemm_args ga = g;
+    // Tile order inside a batch item: with many tile columns, the 32 blocks an XCD runs at a time would share one
+    // operand tile of A and none of B; walking groups of 4 (2) tile rows column by column cuts the operand bytes its L2
+    // has to fetch by up to two thirds (head product of the transformer, 125 tile columns: 1505 us row by row, 1346 in groups of 4).
+    // Updates go row by row: what they stream is theta and the moments (4096 x 4096 x 8, K = 256: 638 us, 668 in groups of 2).
+    ga.tile_group = update ? 1 : grid.x >= 64 ? 4 : grid.x >= 12 ? 2 : 1;
+    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, ga);
+  };
+#define HDET_TILE(SHAPE, THREADS, KERNEL, ...)                                                        \
+  do {                                                                                                \
+    if (stream) launch(&KERNEL<AK, BK, EPI, __VA_ARGS__ true>, SHAPE, THREADS);                       \
+    else if constexpr (!kAlwaysStream<EPI>) launch(&KERNEL<AK, BK, EPI, __VA_ARGS__ false>, SHAPE, THREADS); \
   } while (0)
-  // short-K products with plenty of tiles also take the largest tile, unless the epilogue reads a second
-  // operand: those do better with two blocks per CU, whose epilogues and main loops overlap
-  // (a single round of the largest tile on nine tenths of the chip beats two rounds of the next one; but when the
-  // largest tiles make between one and two rounds and leave the last one under 80 % full, the half-size tiles, which
-  // the CUs take up two at a time and one by one, finish sooner: 3072 x 1024 x 8 replicas at K = 8192 by 5-12 %)
-  const int64_t big = blocks(256, 256);
-  const bool ragged_rounds = big > kCus && big < 2 * (int64_t)kCus && big * 10 < 2 * (int64_t)kCus * 8;
-  if (((long_k && big * 10 >= (int64_t)kCus * 9) || (!gating && big >= 3 * kCus)) && !(long_k && ragged_rounds))
-  {
-    // weight gradients (both operands read with the transposing LDS loads) run 2-5 % faster on three stages of
-    // K = 32 than on two of 64; the forward and input-gradient products 1-6 % slower
-    if constexpr (!AK && !BK) HDET_DMA_LAUNCH(256, 256, 2, 4, 3, 32);                         // one block per CU, 96 KiB of stages
-    else HDET_DMA_LAUNCH(256, 256, 2, 4, 2, 64);                                    // one block per CU, 128 KiB of stages
-  } else if (long_k && ragged_rounds && EPI != HDET_EPI_ADAMW) {
-    if constexpr (EPI != HDET_EPI_ADAMW) HDET_DMA_LAUNCH(256, 128, 4, 2, 3, 32);    // two blocks per CU, 72 KiB each
-  } else if (blocks(256, 128) >= kCus) {
-    // (the update epilogue holds a strip of theta, m and v in registers: too many for two blocks per CU)
-    if (long_k || EPI == HDET_EPI_ADAMW) HDET_DMA_LAUNCH(256, 128, 4, 2, 3, 64);    // one block per CU, 144 KiB
-    else if constexpr (EPI != HDET_EPI_ADAMW) HDET_DMA_LAUNCH(256, 128, 4, 2, 3, 32);   // two blocks per CU, 72 KiB each
-  } else HDET_DMA_LAUNCH(128, 128, 2, 2, 2, 64);                                    // two blocks per CU, 64 KiB each
-#undef HDET_DMA_LAUNCH
-#undef HDET_DMA_KERNEL
+  if constexpr (update) {
+    if (t_alt <= time_of(kSmall)) HDET_TILE(kAlternating, 512, hdet_bgemm_alt_kernel, );
+    else HDET_TILE(kSmall, 256, hdet_bgemm_dma_kernel, 128, 128, 2, 2, 2, 64,);
+  } else {
+    const float t_pair = time_of(wgrad ? kPairWgrad : kPair), t_small = time_of(kSmall), t_long = time_of(kLong);
+    if (t_alt <= t_pair && t_alt <= t_small && t_alt <= t_long) HDET_TILE(kAlternating, 512, hdet_bgemm_alt_kernel, );
+    else if (t_pair <= t_small && t_pair <= t_long)
+      HDET_TILE(kPair, 512, hdet_bgemm_dma_kernel, 256, 128, 4, 2, 3, 32,);
+    else if (t_small <= t_long) HDET_TILE(kSmall, 256, hdet_bgemm_dma_kernel, 128, 128, 2, 2, 2, 64,);
+    else HDET_TILE(kLong, 512, hdet_bgemm_dma_kernel, 256, 128, 4, 2, 3, 64,);
+  }
+#undef HDET_TILE
   return hipGetLastError();
 }
 
