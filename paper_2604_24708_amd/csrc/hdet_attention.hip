@@ -4,25 +4,35 @@
 // batched GEMMs, two softmax kernels and the [S][S] score and probability tensors in HBM by
 // three kernels that stream 64-row tiles of k, v (or q and the output gradient) through LDS.
 //
-// Arithmetic follows the unfused path operation by operation, so both agree to the rounding
-// of the bf16 tensors they share:
-//   forward   s = (q k^T) * scale (fp32), causal mask, p = bf16(exp(s - max) / sum), a = bf16(p v)
-//   backward  dp = da v^T, dot = sum_j dp_j p_j, ds = bf16(p (dp - dot) scale),
-//             dq = bf16(ds k), dk = bf16(ds^T q), dv = bf16(p^T da)
+// Arithmetic: products and sums as the unfused path forms them, with bf16 operands and fp32 accumulation:
+//   forward   s = (q k^T) * scale (fp32), causal mask, p = exp(s - log sum exp s), a = bf16(p) v
+//   backward  dot = sum_c da_c a_c, dp = da v^T - dot,
+//             ds = bf16(bf16(p) dp), dq = (ds k) scale, dk = (ds^T q) scale, dv = bf16(p)^T da
 // with scale = 1 / (sqrt(d_head) tau_r), tau_r the replica's attention temperature when that is
-// an explored channel (Remark 1).  Because p is rounded after the normalisation, every kernel
-// that needs a row-wide quantity first (max and sum in the forward, dot in the backward) walks
-// its tiles twice: once for the quantity, once for the product.  The exponential is the
-// hardware's exp2 of fma(s, scale * log2 e, -max); the row maximum (in that scaled form) and
-// 1/sum of the forward are kept ([rows] fp32 each) and the backward rebuilds p from them with
-// the same expression, hence bit for bit.
+// an explored channel (Remark 1).  Because p is rounded after the normalisation, as the unfused path does it, the forward
+// walks its tiles twice: for the row sums, then for the product (rounding exp(s - max) instead, in one walk, moves the loss
+// of a small model by 5e-4).  It leaves the logarithm of each row's sum ([rows] fp32, base 2), from which all three kernels form p as one
+// hardware exp2 of one fma, hence bit for bit alike, and what rounding took off a (a_rest, bf16), so that dot
+// comes from 16 bits of a and the backward kernels walk their tiles once.  The dp accumulators start at minus dot.
+//
+// What bounds them: neither pipe is full (matrix cores busy 29 to 42 % of the cycles, VALU 39 to 60 %); a wavefront's chain from its LDS reads
+// over the products and the exponentials to the next products, with the 2 to 4 wavefronts a SIMD holds, and below S = 512 what a block does before
+// and after its few tiles.  us, forward / dq / dk and dv:
+//   8 replicas x 16 sequences x 16 heads, S = 512   199 / 338 / 305 -> 195 / 234 / 265
+//   4 x 2 x 8, S = 2048                             112 / 187 / 143 -> 79 / 79 / 91
+//   8 x 16 x 8, S = 256                             43 / 67 / 55 -> 44 / 56 / 51
+// (before: dq walked its tiles twice, tiles went through registers into LDS, results of the paths of a tile were copied together, p was formed from
+// maximum and sum, and every grid had the first order of remap_block.)  Measured and not kept: both 32 x 32 blocks of a
+// tile in one basic block, 211 to 256 registers, 20 to 30 % slower in the backward kernels; dk and dv with 3 wavefronts
+// a SIMD, 313 us (registers spill); launches of 1 to 4 replicas at a time, so that dk and dv find in the memory-side cache what dq read, 5 to 50 %
+// slower; ds from the unrounded p, which moves the gradients of a small model by 5e-3.
 //
 // Layout: qkv [N][B][S][3d] bf16 (q | k | v, head h in columns h*64..), a and da [N][B][S][d],
 // dqkv like qkv.  A block is 4 wavefronts; a wavefront owns 32 rows (queries in the forward and
 // in the dq kernel, keys in the dk/dv kernel) whose operand fragments it loads once from global
-// memory into registers, and walks the 64-row tiles of the other side, which the block stages
-// in LDS (pitch 72 elements: the 128-bit fragment reads are free of bank conflicts) one tile
-// ahead, with one barrier per tile.  Tiles are v_mfma_f32_32x32x16_bf16 blocks.  The first
+// memory into registers, and walks the 64-row tiles of the other side, which go from global memory straight into
+// LDS one or two tiles ahead (three in the forward's first walk), with one barrier per tile.  The tiles at the diagonal have a loop of their own,
+// a 32 x 32 block at a time; the others need no tests.  Products are v_mfma_f32_32x32x16_bf16 blocks.  The first
 // product is formed with the wavefront's own rows as the accumulator's COLUMNS, so that a lane
 // holds one of its rows and 16 entries of the other side per block: row reductions stay inside
 // a lane (plus one exchange between the half-wavefronts at the very end), and the accumulator
@@ -35,8 +45,9 @@
 
 #include "hdet_internal.h"
 #include "hdet_elem.h"
+#include "hdet_lds.h"
 
-// the forward and the two backward kernels must evaluate the exponent identically: one explicit fma, nothing contracted
+// the exponent is one explicit fma in all three kernels, nothing else is contracted
 #pragma clang fp contract(off)
 
 namespace {
@@ -51,12 +62,12 @@ typedef unsigned short us4 __attribute__((ext_vector_type(4)));
 
 constexpr int DH = 64;            // head size
 constexpr int TB = 64;            // rows of a streamed LDS tile
-constexpr int PT = DH + 8;        // pitch of a [rows][64] tile
+constexpr int PT = DH + 8;        // pitch of a strip of results
 constexpr int WR = 32;            // rows a wavefront owns
 constexpr int NWV = 4;            // wavefronts per block
 constexpr int RB = WR * NWV;      // rows a block owns
 constexpr int THREADS = 64 * NWV;
-constexpr int TILE = TB * PT;     // elements of one LDS tile
+constexpr int TILE = TB * DH;     // elements of one LDS tile
 constexpr int SMAX = 16384;       // longest sequence accepted
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -64,41 +75,54 @@ __device__ __forceinline__ unsigned short f2bf(float x) { return __builtin_bit_c
 __device__ __forceinline__ float bf2f(unsigned short h) { return __uint_as_float((unsigned)h << 16); }
 __device__ __forceinline__ float bf16_round(float x) { return bf2f(f2bf(x)); }
 
-// MFMA 32x32x16 operand fragment of lane l: (row = r0 + l % 32, k = ks + 8 * (l / 32) + 0..7).
-// Tile stored [row][k] with `pitch` elements per row (pitch a multiple of 8).
-__device__ __forceinline__ bf16x8 frag_k(const uint16_t* t, int pitch, int r0, int ks, int lane) {
-  return *reinterpret_cast<const bf16x8*>(t + (r0 + (lane & 31)) * pitch + ks + ((lane >> 5) << 3));
-}
-// The same kind of fragment from global memory (row pitch ld elements)
+// Tiles lie in LDS as [64][64], the eight 16-byte chunks of row r permuted by XOR with swz(r): the 32 rows of a k-contiguous fragment
+// and the 4 rows x 64 bytes that half a wavefront of the transposing read touches both fall on disjoint banks.
+__device__ __forceinline__ int swz(int r) { return ((r & 2) << 1) | ((r >> 2) & 3); }
+// Where a lane's fragments begin inside a tile (elements)
+struct frag_address {
+  int k[4], t[2][2];
+  __device__ __forceinline__ explicit frag_address(int lane) {
+    const int row = lane & 31, p = lane & 15;
+#pragma unroll
+    for (int k4 = 0; k4 < 4; ++k4) k[k4] = row * DH + (((2 * k4 + (lane >> 5)) ^ swz(row)) << 3);
+#pragma unroll
+    for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int kr = ((lane >> 5) << 2) + (p >> 2) + 8 * u;
+        t[dt][u] = kr * DH + (((4 * dt + ((lane >> 4) & 1) * 2 + ((p & 3) >> 1)) ^ swz(kr)) << 3) + ((p & 1) << 2);
+      }
+  }
+  // MFMA 32x32x16 operand fragment of lane l: (row = l % 32, k = 16 k4 + 8 * (l / 32) + 0..7) of a tile's 32 rows from `tile` on
+  __device__ __forceinline__ bf16x8 rows(const uint16_t* tile, int k4) const { return *reinterpret_cast<const bf16x8*>(tile + k[k4]); }
+  // Fragment of an operand that is contracted along its tile's ROW index (its rows are the tile's columns 32 dt ..),
+  // with the 16 k of the step in accumulator order: half-wavefront h holds k = ks + 4h + 0..3 and
+  // ks + 8 + 4h + 0..3.  Within a 16-lane group, lane p points at the 4 elements
+  // (k = kb + p / 4, columns cb + 4 * (p % 4) .. + 3) and lane i receives (k = kb .. kb + 3, column cb + i)
+  // from the transposing read.
+  __device__ __forceinline__ bf16x8 cols(const uint16_t* tile, int dt, int ks) const {
+    const s4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s4 __attribute__((address_space(3)))*)(tile + ks * DH + t[dt][0]));
+    const s4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s4 __attribute__((address_space(3)))*)(tile + ks * DH + t[dt][1]));
+    const s8 both = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(bf16x8, both);
+  }
+};
+// Fragment (row = l % 32, k = ks + 8 * (l / 32) + 0..7) from global memory (row pitch ld elements)
 __device__ __forceinline__ bf16x8 frag_g(const uint16_t* src, int64_t ld, int ks, int lane) {
   return *reinterpret_cast<const bf16x8*>(src + (int64_t)(lane & 31) * ld + ks + ((lane >> 5) << 3));
 }
-// Fragment of an operand that is contracted along its tile's ROW index (tile stored [k][row]),
-// with the 16 k of the step in accumulator order: half-wavefront h holds k = ks + 4h + 0..3 and
-// ks + 8 + 4h + 0..3.  Within a 16-lane group, lane p points at the 4 elements
-// (k = kb + p / 4, rows rb + 4 * (p % 4) .. + 3) and lane i receives (k = kb .. kb + 3, row rb + i)
-// from the transposing read.
-__device__ __forceinline__ bf16x8 frag_tp(const uint16_t* t, int pitch, int r0, int ks, int lane) {
-  const int p = lane & 15;
-  const int row = r0 + (((lane >> 4) & 1) << 4) + ((p & 3) << 2);
-  const int k = ks + ((lane >> 5) << 2) + (p >> 2);
-  const uint16_t* q = t + k * pitch + row;
-  const s4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s4 __attribute__((address_space(3)))*)(q));
-  const s4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s4 __attribute__((address_space(3)))*)(q + 8 * pitch));
-  const s8 both = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-  return __builtin_bit_cast(bf16x8, both);
-}
 __device__ __forceinline__ f16v mfma(bf16x8 a, bf16x8 b, f16v c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
-__device__ __forceinline__ f16v zero16() {
+__device__ __forceinline__ f16v all16(float x) {
   f16v z;
 #pragma unroll
-  for (int e = 0; e < 16; ++e) z[e] = 0.f;
+  for (int e = 0; e < 16; ++e) z[e] = x;
   return z;
 }
+__device__ __forceinline__ f16v zero16() { return all16(0.f); }
 // accumulator element e of lane l sits at (row = (e / 4) * 8 + (l / 32) * 4 + e % 4, col = l % 32) of its 32x32 block
 __device__ __forceinline__ int acc_row(int e, int lane) { return ((e >> 2) << 3) + ((lane >> 5) << 2) + (e & 3); }
 // elements 8 j .. 8 j + 7 of an accumulator block as the B fragment of contraction step j
-__device__ __forceinline__ bf16x8 acc_frag(const float (&x)[16], int j) {
+__device__ __forceinline__ bf16x8 acc_frag(const f16v& x, int j) {
   bf16x8 f;
 #pragma unroll
   for (int t = 0; t < 8; ++t) f[t] = (__bf16)x[8 * j + t];
@@ -106,53 +130,50 @@ __device__ __forceinline__ bf16x8 acc_frag(const float (&x)[16], int j) {
 }
 __device__ __forceinline__ float other_half(float x) { return __shfl_xor(x, 32); }
 __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
-// The probability as the unfused path stores it (bf16), from the raw score s, c = scale log2 e,
-// the row's maximum of s c and 1 / (row sum)
-__device__ __forceinline__ float prob(float s, float c, float mx, float inv) { return bf16_round(exp2_fast(__builtin_fmaf(s, c, -mx)) * inv); }
 
 // entries of an accumulator block whose row index (row0 + row in block) exceeds `limit` become `fill`
-__device__ __forceinline__ void fill_above(float (&x)[16], int row0, int limit, int lane, float fill) {
+__device__ __forceinline__ void fill_above(f16v& x, int row0, int limit, int lane, float fill) {
+  const int last = limit - row0 - acc_row(0, lane);
 #pragma unroll
-  for (int e = 0; e < 16; ++e) x[e] = row0 + acc_row(e, lane) > limit ? fill : x[e];
+  for (int e = 0; e < 16; ++e) x[e] = acc_row(e, 0) > last ? fill : x[e];
 }
 // ... whose row index is below `limit`
-__device__ __forceinline__ void fill_below(float (&x)[16], int row0, int limit, int lane, float fill) {
+__device__ __forceinline__ void fill_below(f16v& x, int row0, int limit, int lane, float fill) {
+  const int first = limit - row0 - acc_row(0, lane);
 #pragma unroll
-  for (int e = 0; e < 16; ++e) x[e] = row0 + acc_row(e, lane) < limit ? fill : x[e];
+  for (int e = 0; e < 16; ++e) x[e] = acc_row(e, 0) < first ? fill : x[e];
 }
 
-// One 64 x 64 bf16 tile from global memory (row pitch ld) to LDS (pitch PT) by the block's 256
-// threads, in two phases so that the loads are in flight while the previous tile is worked on.
-struct tile64 {
-  us8 v[2];
-  __device__ __forceinline__ void fetch(const uint16_t* src, int64_t ld, int tid) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int c = tid + i * THREADS;
-      v[i] = *reinterpret_cast<const us8*>(src + (int64_t)(c >> 3) * ld + ((c & 7) << 3));
-    }
+// The 64 x 64 bf16 tiles of a matrix (row pitch ld), from global memory straight to LDS: two instructions a wavefront and tile
+struct tile_stream {
+  const uint16_t* src;
+  int64_t ld;
+  uint32_t off;            // byte offset of this lane's first chunk inside a tile
+  int wave;
+  __device__ __forceinline__ tile_stream(const uint16_t* src_, int64_t ld_, int tid, int wave_) : src(src_), ld(ld_), wave(wave_) {
+    off = (uint32_t)(((tid >> 3) * ld + (((tid & 7) ^ swz(tid >> 3)) << 3)) * 2);
   }
-  __device__ __forceinline__ void commit(uint16_t* dst, int tid) const {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int c = tid + i * THREADS;
-      *reinterpret_cast<us8*>(dst + (c >> 3) * PT + ((c & 7) << 3)) = v[i];
-    }
+  // tile t to the LDS bytes [at, at + 8192); zeros if it does not exist
+  __device__ __forceinline__ void load(int t, bool exists, uint32_t at) const {
+    const hdet_rsrc rs = make_rsrc(src + (int64_t)t * TB * ld, exists ? (uint32_t)(((TB - 1) * ld + DH) * 2) : 0u);
+    lds_load16(rs, at + wave * 1024, off);
+    lds_load16(rs, at + 4096 + wave * 1024, off + (uint32_t)(64 * ld));
   }
 };
 
 struct attn_args {
   const uint16_t* qkv;      // [N][B][S][3d]
   uint16_t* a;              // forward: [N][B][S][d] output
+  uint16_t* a_rest;         // ... and what rounding took off it
   const uint16_t* da;       // backward: gradient at a
   uint16_t* dqkv;           // backward: [N][B][S][3d]
-  float* row_max;           // [N][B][heads][S]
-  float* row_inv;
-  float* row_dot;
+  float* row_lse;           // [N][B][heads][S] log2 of the row's sum of exponentials
+  float* row_ndot;          // minus the row's dot
   const hdet_ctrl* ctrl;
   int temp_channel;
   float scale;              // 1 / sqrt(d_head)
   int B, S, heads, d;
+  bool heavy_first;         // order of the blocks (remap_block)
 };
 
 __device__ __forceinline__ float replica_scale(const attn_args& g, int r) {
@@ -161,19 +182,34 @@ __device__ __forceinline__ float replica_scale(const attn_args& g, int r) {
 
 // Blocks reach the chip's 8 XCDs round-robin in launch order, and with causal masking the work of
 // a block grows with its position in the sequence: left alone, an XCD would always receive the
-// same position.  Launch index -> (row block, sequence and head, replica) such that every XCD
-// works through a contiguous range of (replica, sequence, head) with all row blocks of each,
-// which also keeps the tiles those share in one L2.
+// same position.  Launch index -> (row block counted from the longest, sequence and head, replica) such that every XCD
+// works through a contiguous range of (replica, sequence, head), in one of two orders:
+//  * all row blocks of each together, which keeps the tiles they share in one L2;
+//  * heavy_first: the longest row blocks of all of them, then the next ones.  In the first order the blocks of the last
+//    round are of any length (S = 2048, 1024 blocks: the CUs are busy 60 to 65 % of the kernel's time).
+// heavy_first_order says when.
 struct block_id { int x, bh, r; };
-__device__ __forceinline__ block_id remap_block() {
-  const unsigned nx = gridDim.x, ny = gridDim.y, total = nx * ny * gridDim.z;
+__device__ __forceinline__ block_id remap_block(bool heavy_first) {
+  const unsigned nx = gridDim.x, ny = gridDim.y, heads = ny * gridDim.z, total = nx * heads;
   unsigned lin = blockIdx.x + nx * (blockIdx.y + ny * blockIdx.z);
-  if ((total & 7u) == 0u) lin = (lin & 7u) * (total >> 3) + (lin >> 3);
   block_id b;
-  const unsigned grp = lin / nx;
-  // within an XCD the blocks go round-robin over shader engines and their CUs as well: rotate the
-  // row block from one (sequence, head) to the next so that no unit keeps seeing the same one
-  b.x = (lin % nx + grp + (grp >> 3) + (grp >> 6)) % nx;
+  unsigned grp;
+  if (heavy_first) {
+    if ((heads & 7u) == 0u) {
+      const unsigned own = heads >> 3, j = lin >> 3;
+      b.x = j / own;
+      grp = (lin & 7u) * own + j % own;
+    } else {
+      b.x = lin / heads;
+      grp = lin % heads;
+    }
+  } else {
+    if ((total & 7u) == 0u) lin = (lin & 7u) * (total >> 3) + (lin >> 3);
+    grp = lin / nx;
+    // within an XCD the blocks go round-robin over shader engines and their CUs as well: rotate the
+    // row block from one (sequence, head) to the next so that no unit keeps seeing the same one
+    b.x = (lin % nx + grp + (grp >> 3) + (grp >> 6)) % nx;
+  }
   b.bh = grp % ny;
   b.r = grp / ny;
   return b;
@@ -204,8 +240,8 @@ __device__ __forceinline__ void store_rows(const f16v (&o)[2], uint16_t* stg, ui
 // forward: block = 128 queries of one (replica, sequence, head)
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(THREADS, 4) void attn_fwd_kernel(const attn_args g) {
-  __shared__ __attribute__((aligned(16))) uint16_t smem[4 * TILE];        // keys x 2, values x 2
-  const block_id blk = remap_block();
+  __shared__ __attribute__((aligned(1024))) uint16_t smem[4 * TILE];      // a ring of tiles: the keys, then keys and values in turn
+  const block_id blk = remap_block(g.heavy_first);
   const int qblk = gridDim.x - 1 - blk.x, bh = blk.bh, r = blk.r;         // longest blocks first
   const int b = bh / g.heads, h = bh - b * g.heads;
   const int tid = threadIdx.x, lane = tid & 63, qi = lane & 31;
@@ -213,107 +249,134 @@ __global__ __launch_bounds__(THREADS, 4) void attn_fwd_kernel(const attn_args g)
   const int64_t ld = 3 * (int64_t)g.d;
   const int64_t tok0 = ((int64_t)r * g.B + b) * g.S;
   const uint16_t* base = g.qkv + tok0 * ld + h * DH;
-  const uint16_t* ksrc = base + g.d;
-  const uint16_t* vsrc = base + 2 * g.d;
   const int q0 = qblk * RB, wq0 = q0 + w * WR;
   const bool on = wq0 < g.S;                                               // S is a multiple of 64, not of 128
-  const int nkb = (q0 + RB < g.S ? q0 + RB : g.S) / TB;                    // key tiles the block walks
-  const int nkw = on ? (wq0 + WR - 1) / TB + 1 : 0;                        // ... and this wavefront
-  const float c = replica_scale(g, r) * kLog2e;
+  const int nfull = q0 / TB;                                               // key tiles below the diagonal for all wavefronts
+  const int nkb = (q0 + RB < g.S ? q0 + RB : g.S) / TB;                    // ... that the block walks
 
+  const tile_stream keys(base + g.d, ld, tid, w), vals(base + 2 * g.d, ld, tid, w);
+  const uint32_t s_addr = lds_addr_of(smem);
+  // entry j of the ring: key tiles 0 .. nkb - 1, then key and value tiles 0, 0, 1, 1, ..; past the end zeros
+  auto request = [&](int j) {
+    const uint32_t at = s_addr + (j & 3) * (TILE * 2);
+    const int u = j - nkb;
+    if (u < 0) keys.load(j, true, at);
+    else if (u & 1) vals.load(u >> 1, u < 2 * nkb, at);
+    else keys.load(u >> 1, u < 2 * nkb, at);
+  };
+  request(0); request(1); request(2);
+  const float c = replica_scale(g, r) * kLog2e;
   bf16x8 fq[4];
 #pragma unroll
   for (int k4 = 0; k4 < 4; ++k4) fq[k4] = frag_g(base + (int64_t)(on ? wq0 : 0) * ld, ld, k4 * 16, lane);
+  const frag_address fa(lane);
 
-  // Raw scores of 32-key block i of key tile kb, [key][query], -inf above the diagonal
-  auto scores = [&](const uint16_t* kt, int kb, int i, float (&x)[16]) {
+  // raw scores of a 32-key block, [key][query]
+  auto scores = [&](const uint16_t* kt) {
     f16v s = zero16();
 #pragma unroll
-    for (int k4 = 0; k4 < 4; ++k4) s = mfma(frag_k(kt, PT, 32 * i, k4 * 16, lane), fq[k4], s);
-#pragma unroll
-    for (int e = 0; e < 16; ++e) x[e] = s[e];
-    const int key0 = kb * TB + 32 * i;
-    if (key0 + 31 > wq0) fill_above(x, key0, wq0 + qi, lane, -INFINITY);
+    for (int k4 = 0; k4 < 4; ++k4) s = mfma(fa.rows(kt, k4), fq[k4], s);
+    return s;
   };
-  // the second block of a tile is left out when it lies above the diagonal altogether
-  auto blocks_of = [&](int kb) { return kb * TB + 32 > wq0 + WR - 1 ? 1 : 2; };
+  // the wavefront's 32-key blocks of a tile at the diagonal: f(block, first key, across the diagonal)
+  auto at_diagonal = [&](int kb, auto&& f) {
+#pragma unroll 1
+    for (int i = 0; i < 2; ++i) {
+      const int key0 = kb * TB + 32 * i;
+      if (on && key0 <= wq0) f(i, key0, key0 == wq0);
+    }
+  };
 
   // pass 1: row maximum (of the raw scores) and sum, each half-wavefront over its own keys
-  tile64 lk, lv;
   float m = -1e30f, l = 0.f;
-  lk.fetch(ksrc, ld, tid);
-  lk.commit(smem, tid);
-  if (nkb > 1) lk.fetch(ksrc + (int64_t)TB * ld, ld, tid);
-  __syncthreads();
-  for (int kb = 0; kb < nkb; ++kb) {
-    if (kb + 1 < nkb) lk.commit(smem + ((kb + 1) & 1) * TILE, tid);
-    if (kb + 2 < nkb) lk.fetch(ksrc + (int64_t)(kb + 2) * TB * ld, ld, tid);
-    if (kb < nkw) {
-      const int nb = blocks_of(kb);
-      for (int i = 0; i < nb; ++i) {
-        float x[16];
-        scores(smem + (kb & 1) * TILE, kb, i, x);
-        float top = m;
+  auto sum_block = [&](f16v& x) {
+    float top = m, sum = 0.f;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) top = fmaxf(top, x[e]);
-        const float tc = top * c;
-        float sum = 0.f;
+    for (int e = 0; e < 16; ++e) top = fmaxf(top, x[e]);
+    const float tc = top * c;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) sum += exp2_fast(__builtin_fmaf(x[e], c, -tc));
-        l = l * exp2_fast((m - top) * c) + sum;
-        m = top;
-      }
-    }
-    __syncthreads();
+    for (int e = 0; e < 16; ++e) sum += exp2_fast(__builtin_fmaf(x[e], c, -tc));
+    l = l * exp2_fast((m - top) * c) + sum;
+    m = top;
+  };
+  for (int kb = 0; kb < nfull; ++kb) {
+    wait_and_barrier<4>();
+    request(kb + 3);
+    const uint16_t* kt = smem + (kb & 3) * TILE;
+    f16v x0 = scores(kt), x1 = scores(kt + 32 * DH);
+    sum_block(x0);
+    sum_block(x1);
   }
-  const float mo = other_half(m), lo = other_half(l);
-  const float top = fmaxf(m, mo);
-  const float mx = top * c;
-  const float inv = 1.f / (l * exp2_fast((m - top) * c) + lo * exp2_fast((mo - top) * c));
-  if (on && lane < 32) {
-    const int64_t gr = (((int64_t)r * g.B + b) * g.heads + h) * g.S + wq0 + qi;
-    g.row_max[gr] = mx;
-    g.row_inv[gr] = inv;
+  for (int kb = nfull; kb < nkb; ++kb) {
+    wait_and_barrier<4>();
+    request(kb + 3);
+    at_diagonal(kb, [&](int i, int key0, bool across) {
+      f16v x = scores(smem + (kb & 3) * TILE + 32 * i * DH);
+      if (across) fill_above(x, key0, wq0 + qi, lane, -INFINITY);
+      sum_block(x);
+    });
   }
+  const float mo = other_half(m), lo = other_half(l), top = fmaxf(m, mo);
+  const float lse = __builtin_fmaf(top, c, __builtin_amdgcn_logf(l * exp2_fast((m - top) * c) + lo * exp2_fast((mo - top) * c)));
 
   // pass 2: a^T = v^T p^T, [column][query]
   f16v o[2] = {zero16(), zero16()};
-  lk.fetch(ksrc, ld, tid);
-  lv.fetch(vsrc, ld, tid);
-  lk.commit(smem, tid);
-  lv.commit(smem + 2 * TILE, tid);
-  if (nkb > 1) { lk.fetch(ksrc + (int64_t)TB * ld, ld, tid); lv.fetch(vsrc + (int64_t)TB * ld, ld, tid); }
-  __syncthreads();
-  for (int kb = 0; kb < nkb; ++kb) {
-    if (kb + 1 < nkb) { lk.commit(smem + ((kb + 1) & 1) * TILE, tid); lv.commit(smem + (2 + ((kb + 1) & 1)) * TILE, tid); }
-    if (kb + 2 < nkb) { lk.fetch(ksrc + (int64_t)(kb + 2) * TB * ld, ld, tid); lv.fetch(vsrc + (int64_t)(kb + 2) * TB * ld, ld, tid); }
-    if (kb < nkw) {
-      const uint16_t* vt = smem + (2 + (kb & 1)) * TILE;
-      const int nb = blocks_of(kb);
-      for (int i = 0; i < nb; ++i) {
-        float x[16];
-        scores(smem + (kb & 1) * TILE, kb, i, x);
+  auto add_block = [&](f16v& x, const uint16_t* vt) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) x[e] = exp2_fast(__builtin_fmaf(x[e], c, -mx)) * inv;
+    for (int e = 0; e < 16; ++e) x[e] = exp2_fast(__builtin_fmaf(x[e], c, -lse));
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const bf16x8 pf = acc_frag(x, j);
+    for (int j = 0; j < 2; ++j) {
+      const bf16x8 pf = acc_frag(x, j);
 #pragma unroll
-          for (int dt = 0; dt < 2; ++dt) o[dt] = mfma(frag_tp(vt, PT, 32 * dt, 32 * i + 16 * j, lane), pf, o[dt]);
-        }
-      }
+      for (int dt = 0; dt < 2; ++dt) o[dt] = mfma(fa.cols(vt, dt, 16 * j), pf, o[dt]);
     }
-    __syncthreads();
+  };
+  const uint16_t *kt, *vt;
+  auto next = [&](int kb) {
+    const int j = nkb + 2 * kb;
+    if (kb == 0) {
+      wait_and_barrier<2>();
+    } else {
+      wait_and_barrier<0>();
+      request(j + 2);
+    }
+    request(j + 3);
+    kt = smem + (j & 3) * TILE;
+    vt = smem + ((j + 1) & 3) * TILE;
+  };
+  for (int kb = 0; kb < nfull; ++kb) {
+    next(kb);
+    f16v x0 = scores(kt);
+    add_block(x0, vt);
+    f16v x1 = scores(kt + 32 * DH);
+    add_block(x1, vt + 32 * DH);
   }
-  store_rows(o, smem + w * WR * PT, g.a + (tok0 + (on ? wq0 : 0)) * g.d + h * DH, g.d, on, lane);
+  for (int kb = nfull; kb < nkb; ++kb) {
+    next(kb);
+    at_diagonal(kb, [&](int i, int key0, bool across) {
+      f16v x = scores(kt + 32 * i * DH);
+      if (across) fill_above(x, key0, wq0 + qi, lane, -INFINITY);
+      add_block(x, vt + 32 * i * DH);
+    });
+  }
+  wait_and_barrier<0>();
+  if (on && lane < 32) g.row_lse[(((int64_t)r * g.B + b) * g.heads + h) * g.S + wq0 + qi] = lse;
+  f16v rest[2];                            // what rounding takes off a
+#pragma unroll
+  for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) rest[dt][e] = o[dt][e] - bf16_round(o[dt][e]);
+  const int64_t out = (tok0 + (on ? wq0 : 0)) * g.d + h * DH;
+  store_rows(o, smem + w * WR * PT, g.a + out, g.d, on, lane);
+  store_rows(rest, smem + w * WR * PT, g.a_rest + out, g.d, on, lane);
 }
 
 // ---------------------------------------------------------------------------------------------
 // backward, step 1: the row dots and dq; block = 128 queries
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(THREADS, 2) void attn_bwd_dq_kernel(const attn_args g) {
-  __shared__ __attribute__((aligned(16))) uint16_t smem[4 * TILE];        // keys x 2, values x 2
-  const block_id blk = remap_block();
+__global__ __launch_bounds__(THREADS, 3) void attn_bwd_dq_kernel(const attn_args g) {
+  __shared__ __attribute__((aligned(1024))) uint16_t smem[3 * 2 * TILE];  // keys and values, three stages
+  const block_id blk = remap_block(g.heavy_first);
   const int qblk = gridDim.x - 1 - blk.x, bh = blk.bh, r = blk.r;
   const int b = bh / g.heads, h = bh - b * g.heads;
   const int tid = threadIdx.x, lane = tid & 63, qi = lane & 31;
@@ -321,99 +384,98 @@ __global__ __launch_bounds__(THREADS, 2) void attn_bwd_dq_kernel(const attn_args
   const int64_t ld = 3 * (int64_t)g.d;
   const int64_t tok0 = ((int64_t)r * g.B + b) * g.S;
   const uint16_t* base = g.qkv + tok0 * ld + h * DH;
-  const uint16_t* ksrc = base + g.d;
-  const uint16_t* vsrc = base + 2 * g.d;
   const int q0 = qblk * RB, wq0 = q0 + w * WR;
   const bool on = wq0 < g.S;
+  const int nfull = q0 / TB;
   const int nkb = (q0 + RB < g.S ? q0 + RB : g.S) / TB;
-  const int nkw = on ? (wq0 + WR - 1) / TB + 1 : 0;
-  const float scale = replica_scale(g, r);
-  const float c = scale * kLog2e;
   const int64_t gr = (((int64_t)r * g.B + b) * g.heads + h) * g.S + (on ? wq0 : 0) + qi;
-  const float mx = g.row_max[gr], inv = g.row_inv[gr];
 
+  const tile_stream keys(base + g.d, ld, tid, w), vals(base + 2 * g.d, ld, tid, w);
+  const uint32_t s_addr = lds_addr_of(smem);
+  auto request = [&](int t, int stage) {
+    keys.load(t, t < nkb, s_addr + stage * (4 * TILE));
+    vals.load(t, t < nkb, s_addr + stage * (4 * TILE) + 2 * TILE);
+  };
   bf16x8 fq[4], fda[4];
-#pragma unroll
-  for (int k4 = 0; k4 < 4; ++k4) {
-    fq[k4] = frag_g(base + (int64_t)(on ? wq0 : 0) * ld, ld, k4 * 16, lane);
-    fda[k4] = frag_g(g.da + (tok0 + (on ? wq0 : 0)) * g.d + h * DH, g.d, k4 * 16, lane);
-  }
-
-  // p and dp = v da^T of key block i of tile kb, both [key][query]; false above the diagonal
-  auto p_and_dp = [&](const uint16_t* kt, const uint16_t* vt, int kb, int i, float (&p)[16], f16v& dp) -> bool {
-    const int key0 = kb * TB + 32 * i;
-    if (key0 > wq0 + WR - 1) return false;
-    f16v s = zero16();
-    dp = zero16();
+  // minus the row's dot = sum over the columns of da a: the diagonal of a product of 32 rows each
+  float ndot = 0.f;
+  {
+    const int64_t row = (tok0 + (on ? wq0 : 0)) * g.d + h * DH;
+    bf16x8 hi[4], lo[4];
 #pragma unroll
     for (int k4 = 0; k4 < 4; ++k4) {
-      s = mfma(frag_k(kt, PT, 32 * i, k4 * 16, lane), fq[k4], s);
-      dp = mfma(frag_k(vt, PT, 32 * i, k4 * 16, lane), fda[k4], dp);
+      fda[k4] = frag_g(g.da + row, g.d, k4 * 16, lane);
+      hi[k4] = frag_g(g.a + row, g.d, k4 * 16, lane);
+      lo[k4] = frag_g(g.a_rest + row, g.d, k4 * 16, lane);
     }
+    f16v x = zero16();
 #pragma unroll
-    for (int e = 0; e < 16; ++e) p[e] = prob(s[e], c, mx, inv);
-    if (key0 + 31 > wq0) fill_above(p, key0, wq0 + qi, lane, 0.f);
-    return true;
-  };
-
-  tile64 lk, lv;
-  auto prologue = [&]() {
-    lk.fetch(ksrc, ld, tid);
-    lv.fetch(vsrc, ld, tid);
-    lk.commit(smem, tid);
-    lv.commit(smem + 2 * TILE, tid);
-    if (nkb > 1) { lk.fetch(ksrc + (int64_t)TB * ld, ld, tid); lv.fetch(vsrc + (int64_t)TB * ld, ld, tid); }
-    __syncthreads();
-  };
-  auto advance = [&](int kb) {
-    if (kb + 1 < nkb) { lk.commit(smem + ((kb + 1) & 1) * TILE, tid); lv.commit(smem + (2 + ((kb + 1) & 1)) * TILE, tid); }
-    if (kb + 2 < nkb) { lk.fetch(ksrc + (int64_t)(kb + 2) * TB * ld, ld, tid); lv.fetch(vsrc + (int64_t)(kb + 2) * TB * ld, ld, tid); }
-  };
-
-  // pass 1: dot = sum over the keys of dp p
-  float dot = 0.f;
-  prologue();
-  for (int kb = 0; kb < nkb; ++kb) {
-    advance(kb);
-    if (kb < nkw) {
+    for (int k4 = 0; k4 < 4; ++k4) x = mfma(lo[k4], fda[k4], x);
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        float p[16];
-        f16v dp;
-        if (!p_and_dp(smem + (kb & 1) * TILE, smem + (2 + (kb & 1)) * TILE, kb, i, p, dp)) continue;
+    for (int k4 = 0; k4 < 4; ++k4) x = mfma(hi[k4], fda[k4], x);
+    const int d = qi - ((lane >> 5) << 2);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) dot = __builtin_fmaf(dp[e], p[e], dot);
-      }
-    }
-    __syncthreads();
+    for (int e = 0; e < 16; ++e) ndot = d == acc_row(e, 0) ? -x[e] : ndot;
   }
-  dot += other_half(dot);
-  if (on && lane < 32) g.row_dot[gr] = dot;
+  request(0, 0);
+  request(1, 1);
+#pragma unroll
+  for (int k4 = 0; k4 < 4; ++k4) fq[k4] = frag_g(base + (int64_t)(on ? wq0 : 0) * ld, ld, k4 * 16, lane);
+  const float lse = g.row_lse[gr];
+  const float scale = replica_scale(g, r);
+  const float c = scale * kLog2e;
+  ndot += other_half(ndot);
+  const frag_address fa(lane);
 
-  // pass 2: dq^T = k^T ds^T, [column][query]
-  f16v o[2] = {zero16(), zero16()};
-  prologue();
-  for (int kb = 0; kb < nkb; ++kb) {
-    advance(kb);
-    if (kb < nkw) {
-      const uint16_t* kt = smem + (kb & 1) * TILE;
+  f16v o[2] = {zero16(), zero16()};        // dq^T = k^T ds^T, [column][query]
+  auto block = [&](const uint16_t* kt, int key0, bool across) {
+    const uint16_t* vt = kt + TILE;
+    f16v s = zero16(), dp = all16(ndot);   // [key][query]; dp = v da^T - dot
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        float p[16];
-        f16v dp;
-        if (!p_and_dp(kt, smem + (2 + (kb & 1)) * TILE, kb, i, p, dp)) continue;
+    for (int k4 = 0; k4 < 4; ++k4) s = mfma(fa.rows(kt, k4), fq[k4], s);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) p[e] = p[e] * (dp[e] - dot) * scale;
+    for (int k4 = 0; k4 < 4; ++k4) dp = mfma(fa.rows(vt, k4), fda[k4], dp);
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const bf16x8 dsf = acc_frag(p, j);
+    for (int e = 0; e < 16; ++e) s[e] = exp2_fast(__builtin_fmaf(s[e], c, -lse));
+    if (across) fill_above(s, key0, wq0 + qi, lane, 0.f);
 #pragma unroll
-          for (int dt = 0; dt < 2; ++dt) o[dt] = mfma(frag_tp(kt, PT, 32 * dt, 32 * i + 16 * j, lane), dsf, o[dt]);
-        }
-      }
+    for (int j = 0; j < 2; ++j) {
+      const bf16x8 pf = acc_frag(s, j);
+#pragma unroll
+      for (int t = 0; t < 8; ++t) dp[8 * j + t] *= (float)pf[t];
+      const bf16x8 dsf = acc_frag(dp, j);
+#pragma unroll
+      for (int dt = 0; dt < 2; ++dt) o[dt] = mfma(fa.cols(kt, dt, 16 * j), dsf, o[dt]);
     }
-    __syncthreads();
+  };
+  int stage = 0, ahead = 2;
+  auto next = [&](int kb) {                // waits for tile kb, requests kb + 2
+    wait_and_barrier<4>();
+    request(kb + 2, ahead);
+    const uint16_t* kt = smem + stage * (2 * TILE);
+    ahead = stage;
+    stage = stage == 2 ? 0 : stage + 1;
+    return kt;
+  };
+  for (int kb = 0; kb < nfull; ++kb) {
+    const uint16_t* kt = next(kb);
+#pragma unroll 1
+    for (int i = 0; i < 2; ++i) block(kt + 32 * i * DH, 0, false);
   }
+  for (int kb = nfull; kb < nkb; ++kb) {
+    const uint16_t* kt = next(kb);
+#pragma unroll 1
+    for (int i = 0; i < 2; ++i) {
+      const int key0 = kb * TB + 32 * i;
+      if (on && key0 <= wq0) block(kt + 32 * i * DH, key0, key0 == wq0);
+    }
+  }
+  wait_and_barrier<0>();
+  if (on && lane < 32) g.row_ndot[gr] = ndot;
+#pragma unroll
+  for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) o[dt][e] *= scale;
   store_rows(o, smem + w * WR * PT, g.dqkv + (tok0 + (on ? wq0 : 0)) * ld + h * DH, ld, on, lane);
 }
 
@@ -421,9 +483,10 @@ __global__ __launch_bounds__(THREADS, 2) void attn_bwd_dq_kernel(const attn_args
 // backward, step 2: dk and dv; block = 128 keys, walks the query tiles at or below the diagonal
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(THREADS, 2) void attn_bwd_dkv_kernel(const attn_args g) {
-  __shared__ __attribute__((aligned(16))) uint16_t smem[4 * TILE];        // queries x 2, output gradients x 2
-  __shared__ __attribute__((aligned(16))) float st[2][3][TB];             // row max, 1 / row sum, row dot of the tile's queries
-  const block_id blk = remap_block();
+  // queries, output gradients and the queries' two row statistics (one for each wavefront, each twice): three stages
+  constexpr int STAGE = 2 * TILE + NWV * TB * 2;
+  __shared__ __attribute__((aligned(1024))) uint16_t smem[3 * STAGE];
+  const block_id blk = remap_block(g.heavy_first);
   const int kblk = blk.x, bh = blk.bh, r = blk.r;                          // the first blocks walk the most tiles
   const int b = bh / g.heads, h = bh - b * g.heads;
   const int tid = threadIdx.x, lane = tid & 63, ki = lane & 31;
@@ -431,102 +494,125 @@ __global__ __launch_bounds__(THREADS, 2) void attn_bwd_dkv_kernel(const attn_arg
   const int64_t ld = 3 * (int64_t)g.d;
   const int64_t tok0 = ((int64_t)r * g.B + b) * g.S;
   const uint16_t* base = g.qkv + tok0 * ld + h * DH;
-  const uint16_t* dasrc = g.da + tok0 * g.d + h * DH;
   const int64_t gr0 = (((int64_t)r * g.B + b) * g.heads + h) * g.S;
   const int k0 = kblk * RB, wk0 = k0 + w * WR;
   const bool on = wk0 < g.S;
   const int qb0 = k0 / TB, nqb = g.S / TB;
-  const float scale = replica_scale(g, r);
-  const float c = scale * kLog2e;
 
+  const tile_stream qs(base, ld, tid, w), das(g.da + tok0 * g.d + h * DH, g.d, tid, w);
+  const float* const stats = ((w & 1) ? g.row_ndot : g.row_lse) + gr0;
+  const uint32_t s_addr = lds_addr_of(smem);
+  auto request = [&](int t, int stage) {
+    const uint32_t at = s_addr + stage * (2 * STAGE);
+    qs.load(t, t < nqb, at);
+    das.load(t, t < nqb, at + 2 * TILE);
+    lds_load4(make_rsrc(stats + (int64_t)t * TB, t < nqb ? TB * 4 : 0), at + 4 * TILE + w * (TB * 4), lane * 4);
+  };
   bf16x8 fk[4], fv[4];
 #pragma unroll
   for (int k4 = 0; k4 < 4; ++k4) {
     fk[k4] = frag_g(base + g.d + (int64_t)(on ? wk0 : 0) * ld, ld, k4 * 16, lane);
     fv[k4] = frag_g(base + 2 * g.d + (int64_t)(on ? wk0 : 0) * ld, ld, k4 * 16, lane);
   }
-
-  tile64 lq, la;
-  float sv = 0.f;                                                          // one row statistic per thread < 192
-  const float* ssrc = tid < TB ? g.row_max : tid < 2 * TB ? g.row_inv : g.row_dot;
-  auto fetch = [&](int qb) {
-    lq.fetch(base + (int64_t)qb * TB * ld, ld, tid);
-    la.fetch(dasrc + (int64_t)qb * TB * g.d, g.d, tid);
-    if (tid < 3 * TB) sv = ssrc[gr0 + qb * TB + (tid & (TB - 1))];
-  };
-  auto commit = [&](int buf) {
-    lq.commit(smem + buf * TILE, tid);
-    la.commit(smem + (2 + buf) * TILE, tid);
-    if (tid < 3 * TB) st[buf][tid >> 6][tid & (TB - 1)] = sv;
-  };
+  request(qb0, 0);
+  request(qb0 + 1, 1);
+  const float scale = replica_scale(g, r);
+  const float c = scale * kLog2e;
+  const frag_address fa(lane);
 
   f16v dk[2] = {zero16(), zero16()}, dv[2] = {zero16(), zero16()};        // [column][key]
-  fetch(qb0);
-  commit(0);
-  if (qb0 + 1 < nqb) fetch(qb0 + 1);
-  __syncthreads();
-  for (int qb = qb0; qb < nqb; ++qb) {
-    const int buf = (qb - qb0) & 1;
-    if (qb + 1 < nqb) commit(buf ^ 1);
-    if (qb + 2 < nqb) fetch(qb + 2);
-    if (on && qb * TB + TB - 1 >= wk0) {
-      const uint16_t* qt = smem + buf * TILE;
-      const uint16_t* dat = smem + (2 + buf) * TILE;
+  // a 32-query block: its tile rows, its statistics
+  auto block = [&](const uint16_t* qt, const float* st, int qr0, bool across) {
+    const uint16_t* dat = qt + TILE;
+    f16v s = zero16(), dp;                                                 // [query][key]; dp = da v^T - dot
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int qr0 = qb * TB + 32 * i;                                  // first query of the block
-        if (qr0 + 31 < wk0) continue;                                      // all its queries precede the keys
-        f16v s = zero16(), dp = zero16();                                  // [query][key]
+    for (int e4 = 0; e4 < 4; ++e4) {                                       // 4 consecutive queries at a time
+      const f4 nd = *reinterpret_cast<const f4*>(st + TB + acc_row(4 * e4, lane));
 #pragma unroll
-        for (int k4 = 0; k4 < 4; ++k4) {
-          s = mfma(frag_k(qt, PT, 32 * i, k4 * 16, lane), fk[k4], s);
-          dp = mfma(frag_k(dat, PT, 32 * i, k4 * 16, lane), fv[k4], dp);
-        }
-        float p[16], ds[16];
+      for (int u = 0; u < 4; ++u) dp[4 * e4 + u] = nd[u];
+    }
 #pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4) {
-          const int row = 32 * i + acc_row(4 * e4, lane);                  // 4 consecutive queries of the tile
-          const f4 mx = *reinterpret_cast<const f4*>(&st[buf][0][row]);
-          const f4 inv = *reinterpret_cast<const f4*>(&st[buf][1][row]);
+    for (int k4 = 0; k4 < 4; ++k4) s = mfma(fa.rows(qt, k4), fk[k4], s);
 #pragma unroll
-          for (int u = 0; u < 4; ++u) p[4 * e4 + u] = prob(s[4 * e4 + u], c, mx[u], inv[u]);
-        }
-        if (qr0 < wk0 + WR - 1) fill_below(p, qr0, wk0 + ki, lane, 0.f);   // causal: query >= key
+    for (int k4 = 0; k4 < 4; ++k4) dp = mfma(fa.rows(dat, k4), fv[k4], dp);
 #pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4) {
-          const f4 dot = *reinterpret_cast<const f4*>(&st[buf][2][32 * i + acc_row(4 * e4, lane)]);
+    for (int e4 = 0; e4 < 4; ++e4) {
+      const f4 lse = *reinterpret_cast<const f4*>(st + acc_row(4 * e4, lane));
 #pragma unroll
-          for (int u = 0; u < 4; ++u) ds[4 * e4 + u] = p[4 * e4 + u] * (dp[4 * e4 + u] - dot[u]) * scale;
-        }
+      for (int u = 0; u < 4; ++u) s[4 * e4 + u] = exp2_fast(__builtin_fmaf(s[4 * e4 + u], c, -lse[u]));
+    }
+    if (across) fill_below(s, qr0, wk0 + ki, lane, 0.f);                   // causal: query >= key
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const bf16x8 pf = acc_frag(p, j), dsf = acc_frag(ds, j);
+    for (int j = 0; j < 2; ++j) {
+      const bf16x8 pf = acc_frag(s, j);
 #pragma unroll
-          for (int dt = 0; dt < 2; ++dt) {
-            dv[dt] = mfma(frag_tp(dat, PT, 32 * dt, 32 * i + 16 * j, lane), pf, dv[dt]);
-            dk[dt] = mfma(frag_tp(qt, PT, 32 * dt, 32 * i + 16 * j, lane), dsf, dk[dt]);
-          }
-        }
+      for (int t = 0; t < 8; ++t) dp[8 * j + t] *= (float)pf[t];
+      const bf16x8 dsf = acc_frag(dp, j);
+#pragma unroll
+      for (int dt = 0; dt < 2; ++dt) {
+        dv[dt] = mfma(fa.cols(dat, dt, 16 * j), pf, dv[dt]);
+        dk[dt] = mfma(fa.cols(qt, dt, 16 * j), dsf, dk[dt]);
       }
     }
-    __syncthreads();
+  };
+  int stage = 0, ahead = 2;
+  auto next = [&](int qb) {                // waits for tile qb, requests qb + 2
+    wait_and_barrier<5>();
+    request(qb + 2, ahead);
+    const uint16_t* qt = smem + stage * STAGE;
+    ahead = stage;
+    stage = stage == 2 ? 0 : stage + 1;
+    return qt;
+  };
+  int qb = qb0;
+  for (; qb < qb0 + RB / TB && qb < nqb; ++qb) {
+    const uint16_t* qt = next(qb);
+    const float* st = reinterpret_cast<const float*>(qt + 2 * TILE);
+#pragma unroll 1
+    for (int i = 0; i < 2; ++i) {
+      const int qr0 = qb * TB + 32 * i;
+      if (on && qr0 >= wk0) block(qt + 32 * i * DH, st + 32 * i, qr0, qr0 == wk0);
+    }
   }
+  for (; qb < nqb; ++qb) {
+    const uint16_t* qt = next(qb);
+    const float* st = reinterpret_cast<const float*>(qt + 2 * TILE);
+#pragma unroll 1
+    for (int i = 0; i < 2; ++i) block(qt + 32 * i * DH, st + 32 * i, 0, false);
+  }
+  wait_and_barrier<0>();
+#pragma unroll
+  for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) dk[dt][e] *= scale;
   uint16_t* dst = g.dqkv + (tok0 + (on ? wk0 : 0)) * ld + h * DH;
   store_rows(dk, smem + w * WR * PT, dst + g.d, ld, on, lane);
-  __syncthreads();
   store_rows(dv, smem + w * WR * PT, dst + 2 * g.d, ld, on, lane);
+}
+
+dim3 attn_grid(const hdet_attn_desc& a) { return dim3((a.seq_len + RB - 1) / RB, a.batch * a.heads, a.n_replicas); }
+
+// Longest row blocks first: while the grid has few rounds, so that the length of the last one counts for more than the tiles that
+// the blocks of a head find in the L2.  Forward / dq / dk and dv, time in this order over time in the other:
+//   S = 2048, 1024 blocks 0.84 / 0.83 / 0.81, 4096 blocks 0.93 / 0.97 / 0.96, 8192 blocks 1.00 / 1.03 / 1.03;
+//   S = 1024, 1024 blocks 0.90 / 1.00 / 0.85, 4096 blocks 0.97 / 1.00 / 0.99, 8192 blocks 1.05 / 1.10 / 1.04;
+//   S = 512,  1024 blocks 0.92 / 1.00 / 0.92, 2048 blocks 0.94 / 1.02 / 0.98, 4096 blocks 1.02 / 1.06 / 0.98;
+//   S = 256,  512 blocks 0.90 / 0.91 / 0.84, 2048 blocks 1.00 / 1.00 / 0.98;  S = 4096, 1152 blocks 0.76 / 0.89 / 0.84
+bool heavy_first_order(const hdet_attn_desc& a) {
+  const dim3 g = attn_grid(a);
+  const int64_t blocks = (int64_t)g.x * g.y * g.z;
+  return blocks <= (int64_t)(g.x >= 8 ? 16 : 8) * hdet_compute_units();
 }
 
 attn_args make_args(const hdet_attn_desc& a) {
   attn_args g;
-  g.qkv = a.qkv; g.a = a.a; g.da = a.da; g.dqkv = a.dqkv;
-  g.row_max = a.row_max; g.row_inv = a.row_inv; g.row_dot = a.row_dot;
+  g.qkv = a.qkv; g.a = a.a; g.a_rest = a.a_rest; g.da = a.da; g.dqkv = a.dqkv;
+  g.row_lse = a.row_lse; g.row_ndot = a.row_ndot;
   g.ctrl = a.ctrl; g.temp_channel = a.temp_channel; g.scale = a.scale;
   g.B = a.batch; g.S = a.seq_len; g.heads = a.heads; g.d = a.d_model;
+  g.heavy_first = heavy_first_order(a);
   return g;
 }
-
-dim3 attn_grid(const hdet_attn_desc& a) { return dim3((a.seq_len + RB - 1) / RB, a.batch * a.heads, a.n_replicas); }
 
 }  // namespace
 

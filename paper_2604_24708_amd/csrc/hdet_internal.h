@@ -276,11 +276,11 @@ hipError_t hdet_tf_forward_backward(hdet_tf_plan* p, const int32_t* ids, const i
 struct hdet_attn_desc {
   const uint16_t* qkv;      // [N][B][S][3 d_model]: q | k | v, head h in columns h*64..
   uint16_t* a;              // forward output [N][B][S][d_model]
+  uint16_t* a_rest;         // what rounding took off a, same shape: written by the forward, read by the backward
   const uint16_t* da;       // backward: gradient at a
   uint16_t* dqkv;           // backward output, layout of qkv
-  float* row_max;           // [N][B][heads][S] row statistics, written by the forward
-  float* row_inv;
-  float* row_dot;           // scratch of the backward, same shape
+  float* row_lse;           // [N][B][heads][S] row statistic, written by the forward
+  float* row_ndot;          // scratch of the backward, same shape
   const hdet_ctrl* ctrl;
   int temp_channel;         // attention-temperature channel or -1
   float scale;              // 1 / sqrt(d_head)

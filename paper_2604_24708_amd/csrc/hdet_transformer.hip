@@ -957,8 +957,8 @@ struct hdet_tf_plan {
   std::vector<float*> st1_mean, st1_rstd, st2_mean, st2_rstd;
   char *hf, *tmp_d, *dxa, *dxb, *dtmp, *dtmp2, *dff, *dqkv, *ds, *dlogits;
   float *stf_mean, *stf_rstd, *scores, *logits, *row_loss;
-  std::vector<float*> att_max, att_inv;      // [L] row statistics of the fused attention
-  float* att_dot;
+  std::vector<float*> att_lse;               // [L] row statistic of the fused attention
+  float* att_ndot;
   unsigned long long* tok_sorted;            // [N][M] keys (token id, row) in ascending order
   float* tok_seg;                            // [N][M][d] partial rows of the token-embedding gradient
   bool fused_attn;                           // bf16, head size 64, S a multiple of 64
@@ -990,7 +990,7 @@ static size_t tf_carve(hdet_tf_plan* p, char* base) {
   p->x_in.assign(L + 1, nullptr); p->x_mid.assign(L, nullptr); p->h1.assign(L, nullptr); p->h2.assign(L, nullptr);
   p->qkv.assign(L, nullptr); p->p.assign(L, nullptr); p->a.assign(L, nullptr); p->z.assign(L, nullptr); p->f.assign(L, nullptr);
   p->st1_mean.assign(L, nullptr); p->st1_rstd.assign(L, nullptr); p->st2_mean.assign(L, nullptr); p->st2_rstd.assign(L, nullptr);
-  p->att_max.assign(L, nullptr); p->att_inv.assign(L, nullptr);
+  p->att_lse.assign(L, nullptr);
   for (int l = 0; l <= L; ++l) p->x_in[l] = take(N * M * d * e);
   for (int l = 0; l < L; ++l) {
     p->x_mid[l] = take(N * M * d * e); p->h1[l] = take(N * M * d * e); p->h2[l] = take(N * M * d * e);
@@ -998,7 +998,7 @@ static size_t tf_carve(hdet_tf_plan* p, char* base) {
     p->z[l] = take(N * M * ff * e); p->f[l] = take(N * M * ff * e);
     p->st1_mean[l] = (float*)take(N * M * 4); p->st1_rstd[l] = (float*)take(N * M * 4);
     p->st2_mean[l] = (float*)take(N * M * 4); p->st2_rstd[l] = (float*)take(N * M * 4);
-    p->att_max[l] = (float*)take(N * heads * S * 4); p->att_inv[l] = (float*)take(N * heads * S * 4);
+    p->att_lse[l] = (float*)take(N * heads * S * 4);
   }
   p->hf = take(N * M * d * e); p->tmp_d = take(N * M * d * e);
   p->dxa = take(N * M * d * e); p->dxb = take(N * M * d * e); p->dtmp = take(N * M * d * e); p->dtmp2 = take(N * M * d * e);
@@ -1007,7 +1007,7 @@ static size_t tf_carve(hdet_tf_plan* p, char* base) {
   p->stf_mean = (float*)take(N * M * 4); p->stf_rstd = (float*)take(N * M * 4);
   p->scores = (float*)take(N * heads * S * S * 4); p->logits = (float*)take(N * M * V * 4);
   p->row_loss = (float*)take(N * M * 4);
-  p->att_dot = (float*)take(N * heads * S * 4);
+  p->att_ndot = (float*)take(N * heads * S * 4);
   p->tok_sorted = (unsigned long long*)take(N * M * 8);
   p->tok_seg = (float*)take(N * M * d * 4);
   p->nrc = (int)((M + kColsumRows - 1) / kColsumRows);
@@ -1383,7 +1383,8 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
   auto attn_desc = [&](int l) {
     hdet_attn_desc ad;
     ad.qkv = (const uint16_t*)p->qkv[l]; ad.a = (uint16_t*)p->a[l]; ad.da = (const uint16_t*)p->dtmp; ad.dqkv = (uint16_t*)p->dqkv;
-    ad.row_max = p->att_max[l]; ad.row_inv = p->att_inv[l]; ad.row_dot = p->att_dot;
+    ad.a_rest = (uint16_t*)p->p[l];          // the probabilities' place: unused here, and as large from S = 64 on
+    ad.row_lse = p->att_lse[l]; ad.row_ndot = p->att_ndot;
     ad.ctrl = ctrl; ad.temp_channel = p->temp_channel; ad.scale = scale;
     ad.n_replicas = N; ad.batch = B; ad.seq_len = S; ad.heads = nh; ad.d_model = d;
     return ad;
