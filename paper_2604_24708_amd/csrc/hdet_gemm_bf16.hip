@@ -22,8 +22,10 @@
 //
 // Tiling: each wavefront owns a 64x64 (or 32x32) output tile (2x2 blocks or one of v_mfma_f32_32x32x16_bf16);
 // a block is 2x2 wavefronts (128x128 or 64x64 tile).  K step 32, LDS double-buffered (one barrier per K
-// step), the next step's global loads in flight during the MFMAs; launch indices are remapped so
-// that each XCD's L2 serves a contiguous range of tiles.
+// step), the global loads of the next four steps in flight in registers; launch indices are remapped so
+// that each XCD's L2 serves a contiguous range of tiles.  What bounds it is the latency of those loads: with one step in flight, and the
+// funnel shift waiting for its data at once, 0.9 us a step.  96 x 1500, K = 700 gradient, 6 items 20.1 -> 15.9 us, 1500 x 784, K = 576
+// 13.4 -> 10.6, odd rows 96 x 1501, K = 703, 4 items 23.0 -> 14.1.
 //
 // Loads of operands that are not made of aligned chunks: memory is read in aligned dwords (16 bytes per
 // lane; global loads need no more than dword alignment) and, where a chunk starts at an odd element, one
@@ -34,6 +36,8 @@
 // tiles) 282 -> 28.6 us, 700 x 1500, K = 576 77 -> 14.8 us; 256 x 4095, K = 4095, 8 replicas: 337 us (204 TFLOP/s).
 //
 // Products with few output tiles take a second kernel (hdet_bgemm_frag_kernel below).
+
+#include <type_traits>
 
 #include "hdet_internal.h"
 
@@ -105,20 +109,6 @@ struct operand {
   static constexpr int NCH = ROWS * 4 / THREADS;   // 8-element chunks per thread and K step
   static constexpr int RCH = ROWS / 8;         // chunks per k-row of a [k][row] tile
   us8 reg[NCH];
-  // K step that lies inside the matrix and is not its last one: rows beyond `rows` repeat others
-  __device__ __forceinline__ void fetch(const uint16_t* src, int64_t ld, int row0, int rows, int k0, bool odd, int tid) {
-#pragma unroll
-    for (int i = 0; i < NCH; ++i) {
-      const int c = tid + i * THREADS;
-      if (KMAJOR) {
-        const int row = row0 + (c >> 2), k = k0 + ((c & 3) << 3);
-        reg[i] = load8_any(src, (int64_t)(row < rows ? row : rows - 1) * ld + k, odd);
-      } else {
-        const int k = k0 + c / RCH, row = row0 + ((c % RCH) << 3);
-        reg[i] = load8_any(src, (int64_t)k * ld + (row < rows ? row : row0), odd);
-      }
-    }
-  }
   // last K step: zeros beyond the contraction, nothing beyond the operand's extent is read
   __device__ __forceinline__ void fetch_last(const uint16_t* src, int64_t ld, int row0, int rows, int k0, int kdim, bool odd, int tid) {
     const int64_t extent = (int64_t)((KMAJOR ? rows : kdim) - 1) * ld + (KMAJOR ? kdim : rows);
@@ -163,6 +153,58 @@ struct operand {
   }
 };
 
+// The chunks of an operand that one thread loads, in K steps that lie inside the matrix and are not its last one: rows beyond `rows`
+// repeat others.  ODD: some chunk may start at an odd element; then a fifth dword is loaded, and the funnel shift waits until the chunk
+// goes to LDS.
+template <bool KMAJOR, int ROWS, int THREADS, bool ODD>
+struct chunk_stream {
+  typedef operand<KMAJOR, ROWS, THREADS> op;
+  static constexpr int NCH = op::NCH;
+  const char* p[NCH];           // dword at or before the chunk of K step 0
+  unsigned odd[NCH];            // the same in every K step: TK is even
+  int64_t step;                 // bytes between K steps
+  struct stage { u4 d[NCH]; unsigned e[ODD ? NCH : 1]; };
+  __device__ __forceinline__ void init(const uint16_t* src, int64_t ld, int row0, int rows, int tid) {
+    step = (KMAJOR ? TK : TK * ld) * 2;
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) {
+      const int c = tid + i * THREADS;
+      int64_t at;
+      if (KMAJOR) {
+        const int row = row0 + (c >> 2);
+        at = (int64_t)(row < rows ? row : rows - 1) * ld + ((c & 3) << 3);
+      } else {
+        const int row = row0 + ((c % op::RCH) << 3);
+        at = (int64_t)(c / op::RCH) * ld + (row < rows ? row : row0);
+      }
+      odd[i] = ODD ? ((unsigned)(uintptr_t)(src + at) >> 1) & 1u : 0u;
+      p[i] = reinterpret_cast<const char*>(src + at - odd[i]);
+    }
+  }
+  __device__ __forceinline__ void request(stage& x, int kt) const {
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) {
+      const unsigned int* q = reinterpret_cast<const unsigned int*>(p[i] + kt * step);
+      x.d[i] = *reinterpret_cast<const u4a*>(q);
+      if (ODD) x.e[ODD ? i : 0] = q[3 + odd[i]];
+    }
+  }
+  __device__ __forceinline__ void commit(const stage& x, uint16_t* tile, int tid) const {
+    op o;
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) {
+      u4 r = x.d[i];
+      if (ODD) {
+        const unsigned sh = odd[i] << 4, e = x.e[ODD ? i : 0];
+        r = u4{__builtin_amdgcn_alignbit(r[1], r[0], sh), __builtin_amdgcn_alignbit(r[2], r[1], sh), __builtin_amdgcn_alignbit(r[3], r[2], sh),
+               __builtin_amdgcn_alignbit(e, r[3], sh)};
+      }
+      o.reg[i] = __builtin_bit_cast(us8, r);
+    }
+    o.commit(tile, tid);
+  }
+};
+
 // one element of C with the epilogue EPI
 template <int EPI>
 __device__ __forceinline__ void put_element(const hdet_bgemm_args& g, int z, int64_t c_base, int row, int col, float v) {
@@ -193,7 +235,7 @@ __device__ __forceinline__ bf16x8 ones() {
 // WT x WT: 32x32 MFMA blocks per wavefront; 2 x 2 wavefronts per block, block tile (64 WT) x (64 WT).
 template <bool A_KMAJOR, bool B_KMAJOR, int EPI, int WT>
 __global__ __launch_bounds__(256, 2) void hdet_bgemm_kernel(const hdet_bgemm_args g) {
-  constexpr int TM = 64 * WT, TN = TM, THREADS = 256;
+  constexpr int TM = 64 * WT, TN = TM, THREADS = 256, DEPTH = 4;
   __shared__ __attribute__((aligned(16))) uint16_t As[2][tile_elems(TM)];
   __shared__ __attribute__((aligned(16))) uint16_t Bs[2][tile_elems(TN)];
   // Workgroups are dealt round-robin to the 8 XCDs (each with its own L2) in launch order.
@@ -237,38 +279,17 @@ __global__ __launch_bounds__(256, 2) void hdet_bgemm_kernel(const hdet_bgemm_arg
 #pragma unroll
     for (int e = 0; e < 16; ++e) rsum[i][e] = 0.f;
 
-  // One register stage: the global loads of K step kt + 1 are issued before the MFMAs of step
-  // kt and written to the other LDS buffer after them (one barrier per step); other blocks
-  // on the same CU cover the rest of the memory latency.
-  operand<A_KMAJOR, TM, THREADS> oa;
-  operand<B_KMAJOR, TN, THREADS> ob;
+  typedef operand<A_KMAJOR, TM, THREADS> ta;
+  typedef operand<B_KMAJOR, TN, THREADS> tb;
   const int nk = (g.k + TK - 1) / TK;
-  // a chunk at the end of a k-row reads on into the next one, which has to be long enough for that
-  const bool roomy = (A_KMAJOR || g.lda >= 8) && (B_KMAJOR || g.ldb >= 8);
-  auto request = [&](int kt) {
-    if (kt + 1 < nk && roomy) {
-      oa.fetch(A, g.lda, m0, g.m, kt * TK, a_odd, tid);
-      ob.fetch(B, g.ldb, n0, g.n, kt * TK, b_odd, tid);
-    } else {
-      oa.fetch_last(A, g.lda, m0, g.m, kt * TK, g.k, a_odd, tid);
-      ob.fetch_last(B, g.ldb, n0, g.n, kt * TK, g.k, b_odd, tid);
-    }
-  };
-  request(0);
-  oa.commit(As[0], tid);
-  ob.commit(Bs[0], tid);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int buf = kt & 1;
-    if (kt + 1 < nk) request(kt + 1);
-    __builtin_amdgcn_sched_barrier(0);     // keep the loads ahead of the MFMAs ...
+  auto multiply = [&](int buf) {
 #pragma unroll
     for (int ks = 0; ks < TK; ks += 16) {
       bf16x8 af[WT], bfr[WT];
 #pragma unroll
-      for (int i = 0; i < WT; ++i) af[i] = operand<A_KMAJOR, TM, THREADS>::fragment(As[buf], wm + i * 32, ks, lane);
+      for (int i = 0; i < WT; ++i) af[i] = ta::fragment(As[buf], wm + i * 32, ks, lane);
 #pragma unroll
-      for (int j = 0; j < WT; ++j) bfr[j] = operand<B_KMAJOR, TN, THREADS>::fragment(Bs[buf], wn + j * 32, ks, lane);
+      for (int j = 0; j < WT; ++j) bfr[j] = tb::fragment(Bs[buf], wn + j * 32, ks, lane);
 #pragma unroll
       for (int i = 0; i < WT; ++i)
 #pragma unroll
@@ -279,10 +300,82 @@ __global__ __launch_bounds__(256, 2) void hdet_bgemm_kernel(const hdet_bgemm_arg
         for (int i = 0; i < WT; ++i) rsum[SUMS ? i : 0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], ones(), rsum[SUMS ? i : 0], 0, 0, 0);
       }
     }
-    __builtin_amdgcn_sched_barrier(0);     // ... and every use of the loaded data behind them
-    oa.commit(As[buf ^ 1], tid);      // last read before the previous barrier
-    ob.commit(Bs[buf ^ 1], tid);
+  };
+  // The last K step, which alone looks at the extent of anything, is requested first and stays in registers until its turn.
+  ta la;
+  tb lb;
+  la.fetch_last(A, g.lda, m0, g.m, (nk - 1) * TK, g.k, a_odd, tid);
+  lb.fetch_last(B, g.ldb, n0, g.n, (nk - 1) * TK, g.k, b_odd, tid);
+  // a chunk at the end of a k-row reads on into the next one, which has to be long enough for that
+  const bool roomy = (A_KMAJOR || g.lda >= 8) && (B_KMAJOR || g.ldb >= 8);
+  // DEPTH register stages: the loads of a K step are requested DEPTH steps before it is written to LDS, one step before its
+  // MFMAs; two LDS buffers, one barrier a step.
+  auto pipelined = [&](auto odd_) {
+    constexpr bool ODD = decltype(odd_)::value;
+    const int nf = nk - 1;
+    chunk_stream<A_KMAJOR, TM, THREADS, ODD> ca;
+    chunk_stream<B_KMAJOR, TN, THREADS, ODD> cb;
+    ca.init(A, g.lda, m0, g.m, tid);
+    cb.init(B, g.ldb, n0, g.n, tid);
+    typename decltype(ca)::stage ra[DEPTH];
+    typename decltype(cb)::stage rb[DEPTH];
+    auto request = [&](int s, int kt) {            // past the end: the last whole step again, not used
+      const int k = kt < nf ? kt : nf - 1;
+      ca.request(ra[s], k);
+      cb.request(rb[s], k);
+    };
+    auto commit = [&](int s) {
+      ca.commit(ra[s], As[s & 1], tid);
+      cb.commit(rb[s], Bs[s & 1], tid);
+    };
+    auto commit_last = [&](int s) {
+      la.commit(As[s & 1], tid);
+      lb.commit(Bs[s & 1], tid);
+    };
+    if (nf > 0) {
+#pragma unroll
+      for (int s = 0; s < DEPTH; ++s) request(s, s);
+      commit(0);
+      request(0, DEPTH);
+    } else {
+      commit_last(0);
+    }
     __syncthreads();
+    int kt0 = 0;
+    for (; kt0 + DEPTH < nf; kt0 += DEPTH) {        // no branch inside: it would have the compiler wait for every load
+#pragma unroll
+      for (int s = 0; s < DEPTH; ++s) {
+        multiply(s & 1);
+        commit((s + 1) % DEPTH);                    // last read before the previous barrier
+        request((s + 1) % DEPTH, kt0 + s + 1 + DEPTH);
+        __syncthreads();
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < DEPTH; ++s) {
+      if (kt0 + s >= nf) break;
+      multiply(s & 1);
+      if (kt0 + s + 1 < nf) commit((s + 1) % DEPTH);
+      else commit_last((s + 1) % DEPTH);
+      __syncthreads();
+    }
+    multiply(nf & 1);
+  };
+  if (roomy) {
+    if (a_odd || b_odd) pipelined(std::true_type{});
+    else pipelined(std::false_type{});
+  } else {
+    for (int kt = 0; kt < nk; ++kt) {
+      ta xa;
+      tb xb;
+      xa.fetch_last(A, g.lda, m0, g.m, kt * TK, g.k, a_odd, tid);
+      xb.fetch_last(B, g.ldb, n0, g.n, kt * TK, g.k, b_odd, tid);
+      if (kt) __syncthreads();
+      xa.commit(As[0], tid);
+      xb.commit(Bs[0], tid);
+      __syncthreads();
+      multiply(0);
+    }
   }
 
   // epilogue: accumulator element e of lane l is C(row, col) with
@@ -435,11 +528,10 @@ namespace {
 int64_t tiles(const hdet_bgemm_args& g, int batch, int tm, int tn) {
   return (int64_t)((g.m + tm - 1) / tm) * ((g.n + tn - 1) / tn) * batch;
 }
-// A product that leaves most of the chip idle in 64 x 64 tiles takes the fragment kernel with 32 x 32 tiles and K in 4, whatever its
-// K: that kernel reaches 50-65 TFLOP/s, the LDS kernels need about 0.5 us per 32 k and block, and the two meet at about 100
-// tiles of 64 x 64 on 256 CUs.  Measured (us, 256 CUs): 96 x 700, K = 100, 6 items (132 tiles) 4.3 | LDS 64 x 64 4.9; 96 x 100,
-// K = 700, 6 items 5.7 | 9.6; 64 x 512, K = 512, 8 items 4.7 | 7.8, LDS-direct 7.0; 96 x 1500, K = 784, 6 items (288 tiles)
-// 18.4 | 13.5, LDS-direct 9.4.
+// A product that leaves most of the chip idle in 64 x 64 tiles takes the fragment kernel with 32 x 32 tiles, K in 8 from K = 512 on and in 4
+// below.  us, operands cold, K in 8 / in 4 / LDS 64 x 64:  96 x 703, K = 1501, 4 items (88 tiles, odd rows) 22.4 / 25.4 / 23.5;
+// 100 x 300, K = 3001, 3 items 27.2 / 40.9 / 37.0;  64 x 1024, K = 2048, 4 items 17.9 / 18.4 / 20;  96 x 100, K = 700, 6 items 8.5 / 9.3 / 10.8;
+// 100 x 576 gradient, K = 576 6.5 / 7.0 / 8.6.  Beyond: 96 x 700, K = 1500, 6 items (132 tiles) 24.5 / - / 19.2.
 bool few_tiles(const hdet_bgemm_args& g, int batch) { return tiles(g, batch, 64, 64) * 5 < 2 * (int64_t)hdet_compute_units(); }
 
 template <bool AK, bool BK, int EPI>
@@ -449,11 +541,10 @@ hipError_t launch_general(const hdet_bgemm_args& g, int batch, hipStream_t s) {
 #define HDET_LDS(WT)                                                                                  \
   hipLaunchKernelGGL((hdet_bgemm_kernel<AK, BK, EPI, WT>), dim3((g.n + 64 * WT - 1) / (64 * WT), (g.m + 64 * WT - 1) / (64 * WT), batch), dim3(256), 0, s, g)
   const int64_t cus = hdet_compute_units();
-  if (few_tiles(g, batch)) HDET_FRAG(4);
-  // less than one 64 x 64 block per CU and a long contraction: K in 8 (training step with 96 x 700, K = 1500, 6 items in it: 170 us,
-  // with 64 x 64 fragment tiles 173, LDS 64 x 64 185; alone, 64 x 64 fragment tiles 15.5 | LDS 64 x 64 26.6;
-  // 111 x 3193, K = 1788, 2 items, odd rows: 24 | 51; at K = 842 10.7 | 10.9)
-  else if (g.k >= 1024 && tiles(g, batch, 64, 64) < cus) HDET_FRAG(8);
+  if (few_tiles(g, batch)) {
+    if (g.k >= 512) HDET_FRAG(8);
+    else HDET_FRAG(4);
+  }
   // 128 x 128 tiles once there are several rounds of them (256 x 4095, K = 4095, 8 items: 337 | 64 x 64 441; 700 x 1500, K = 576:
   // 14.8 | 10.1; 1788 x 3193, K = 222: 18.4 | 14.7), unless they would be half empty
   else if (tiles(g, batch, 128, 128) >= 4 * cus && g.m > 64 && g.n > 64) HDET_LDS(2);
@@ -473,7 +564,13 @@ hipError_t hdet_launch_bgemm(const hdet_bgemm_args& g_in, bool a_kmajor, bool b_
   // The LDS-direct kernel where the operands allow it, except for products of few tiles in the epilogues that the general kernels
   // have.  Weight gradients stay: the update that the LDS-direct kernel can apply to them (HDET_EPI_ADAMW) has to see the same sums.
   const bool plain = epi <= HDET_EPI_BIAS_BF16 && !g.colsum && a_kmajor;
-  if (hdet_bgemm_dma_eligible(g, a_kmajor, b_kmajor, epi) && !(plain && few_tiles(g, batch)))
+  // Forward products of up to two 64 x 64 tiles a CU: their time is the chain of one block, and four times the blocks of 128 x 128
+  // count for more than loads that pass the registers by.  us, this file's kernel / LDS-direct, operands cold: 200 x 1000, K = 3000, 2 items
+  // 23.5 / 42.7;  96 x 704, K = 1504, 6 items 16.8 / 25.4;  96 x 1504, K = 784 16.0 / 19.0;  128 x 1024, K = 1024, 8 items 16.4 / 19.5;
+  // 256 x 640, K = 640, 5 items 11.5 / 14.0;  200 x 512, K = 512, 6 items 9.9 / 12.4;  32 x 2048, K = 512, 4 items 10.2 / 9.8;
+  // 256 x 2048, K = 256, 3 items 9.8 / 9.8.  (Gradients of such layers stay: 96 x 1500, K = 700 16.4 / 14.5.)
+  const bool small_grid = plain && b_kmajor && tiles(g, batch, 64, 64) <= 2 * (int64_t)hdet_compute_units();
+  if (hdet_bgemm_dma_eligible(g, a_kmajor, b_kmajor, epi) && !small_grid && !(plain && few_tiles(g, batch)))
     return hdet_launch_bgemm_dma(g, a_kmajor, b_kmajor, epi, batch, s);
   if (a_kmajor && b_kmajor) {            // forward
     switch (epi) {

@@ -233,65 +233,65 @@ __device__ __forceinline__ void store_tile(const hdet_bgemm_args& g, const f4 (&
       const int row = m0 + wm + strip * SR + it * RPI + lr;
       if (row < g.m && col_ok) {
         const int64_t off = c_base + (int64_t)row * g.ldc + col;
-                  if (kBias) v += bias;
-                  if (EPI == HDET_EPI_BIAS_RELU_BF16) {
-        #pragma unroll
-                    for (int q = 0; q < 4; ++q) v[q] = v[q] > 0.f ? v[q] : 0.f;
-                  }
-                  if (EPI == HDET_EPI_MASK_BF16) {    // gradient through the ReLU of the layer below
-                    const us4 a = gate[strip & 1][it];
-        #pragma unroll
-                    for (int q = 0; q < 4; ++q) v[q] = bf2f(a[q]) > 0.f ? v[q] : 0.f;
-                  }
-                  if (EPI == HDET_EPI_BIAS_RESID_BF16) {  // the layer's output is rounded as the unfused path stores it, then added
-                    const us4 a = gate[strip & 1][it];
-        #pragma unroll
-                    for (int q = 0; q < 4; ++q) v[q] = bf2f(a[q]) + bf2f(f2bf(v[q]));
-                  }
-                  if (EPI == HDET_EPI_BIAS_DROP_RESID_BF16) {   // ... dropped out (one Philox block per 4 elements), then added
-                    const us4 a = gate[strip & 1][it];
-                    hdet_philox4 w = {{0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu}};
-                    if (drop_thresh != 0u)
-                      w = hdet_philox4x32_10((uint32_t)(((int64_t)row * g.ldc + col) >> 2), g.drop_step, (uint32_t)z * 65536u + g.drop_site,
-                                             g.drop_stream, g.drop_seed_lo, g.drop_seed_hi);
-        #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                      float y = bf2f(f2bf(v[q]));
-                      if (drop_thresh != 0u) y = w.x[q] >= drop_thresh ? y * drop_scale : 0.f;
-                      v[q] = bf2f(a[q]) + y;
-                    }
-                  }
-                  if (EPI == HDET_EPI_GELUGRAD_BF16) {  // the incoming gradient is rounded as the unfused path stores it
-                    const us4 a = gate[strip & 1][it];
-        #pragma unroll
-                    for (int q = 0; q < 4; ++q) v[q] = bf2f(f2bf(v[q])) * hdet_gelu_tanh_grad_fast(bf2f(a[q]));
-                  }
-                  if (EPI == HDET_EPI_ADAMW) {
-                    f4 th = uth[it], mm = um[it], vv = uv[it];
-                    hdet_um::update_one<HDET_ADAMW, f4>(th, v, mm, vv, g.upd, us);
-                    __builtin_nontemporal_store(mm, reinterpret_cast<f4*>(g.upd.m + off));
-                    __builtin_nontemporal_store(vv, reinterpret_cast<f4*>(g.upd.v + off));
-                    __builtin_nontemporal_store(th, reinterpret_cast<f4*>(g.upd.theta + off));
-                    if (g.upd.shadow) {
-                      const us4 o = {hdet_um::to_bf16(th[0]), hdet_um::to_bf16(th[1]), hdet_um::to_bf16(th[2]), hdet_um::to_bf16(th[3])};
-                      __builtin_nontemporal_store(o, reinterpret_cast<us4*>(g.upd.shadow + off));
-                    }
-                  } else if (EPI == HDET_EPI_F32 || EPI == HDET_EPI_BIAS_F32) {
-                    put(reinterpret_cast<f4*>(reinterpret_cast<float*>(g.c) + off), v);
-                  } else if (EPI == HDET_EPI_BIAS_GELU_BF16) {
-                    const us4 pre = {f2bf(v[0]), f2bf(v[1]), f2bf(v[2]), f2bf(v[3])};
-                    put(reinterpret_cast<us4*>(reinterpret_cast<uint16_t*>(g.c) + off), pre);
-                    const us4 o = {f2bf(hdet_gelu_tanh_fast(bf2f(pre[0]))), f2bf(hdet_gelu_tanh_fast(bf2f(pre[1]))),
-                                   f2bf(hdet_gelu_tanh_fast(bf2f(pre[2]))), f2bf(hdet_gelu_tanh_fast(bf2f(pre[3])))};
-                    put(reinterpret_cast<us4*>(reinterpret_cast<uint16_t*>(g.c2) + off), o);
-                  } else {
-                    const us4 o = {f2bf(v[0]), f2bf(v[1]), f2bf(v[2]), f2bf(v[3])};
-                    put(reinterpret_cast<us4*>(reinterpret_cast<uint16_t*>(g.c) + off), o);
-                    if (kColsum) {
-        #pragma unroll
-                      for (int q = 0; q < 4; ++q) csum[q] += bf2f(o[q]);
-                    }
-                  }
+        if (kBias) v += bias;
+        if (EPI == HDET_EPI_BIAS_RELU_BF16) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) v[q] = v[q] > 0.f ? v[q] : 0.f;
+        }
+        if (EPI == HDET_EPI_MASK_BF16) {    // gradient through the ReLU of the layer below
+          const us4 a = gate[strip & 1][it];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) v[q] = bf2f(a[q]) > 0.f ? v[q] : 0.f;
+        }
+        if (EPI == HDET_EPI_BIAS_RESID_BF16) {  // the layer's output is rounded as the unfused path stores it, then added
+          const us4 a = gate[strip & 1][it];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) v[q] = bf2f(a[q]) + bf2f(f2bf(v[q]));
+        }
+        if (EPI == HDET_EPI_BIAS_DROP_RESID_BF16) {   // ... dropped out (one Philox block per 4 elements), then added
+          const us4 a = gate[strip & 1][it];
+          hdet_philox4 w = {{0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu}};
+          if (drop_thresh != 0u)
+            w = hdet_philox4x32_10((uint32_t)(((int64_t)row * g.ldc + col) >> 2), g.drop_step, (uint32_t)z * 65536u + g.drop_site,
+                                   g.drop_stream, g.drop_seed_lo, g.drop_seed_hi);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            float y = bf2f(f2bf(v[q]));
+            if (drop_thresh != 0u) y = w.x[q] >= drop_thresh ? y * drop_scale : 0.f;
+            v[q] = bf2f(a[q]) + y;
+          }
+        }
+        if (EPI == HDET_EPI_GELUGRAD_BF16) {  // the incoming gradient is rounded as the unfused path stores it
+          const us4 a = gate[strip & 1][it];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) v[q] = bf2f(f2bf(v[q])) * hdet_gelu_tanh_grad_fast(bf2f(a[q]));
+        }
+        if (EPI == HDET_EPI_ADAMW) {
+          f4 th = uth[it], mm = um[it], vv = uv[it];
+          hdet_um::update_one<HDET_ADAMW, f4>(th, v, mm, vv, g.upd, us);
+          __builtin_nontemporal_store(mm, reinterpret_cast<f4*>(g.upd.m + off));
+          __builtin_nontemporal_store(vv, reinterpret_cast<f4*>(g.upd.v + off));
+          __builtin_nontemporal_store(th, reinterpret_cast<f4*>(g.upd.theta + off));
+          if (g.upd.shadow) {
+            const us4 o = {hdet_um::to_bf16(th[0]), hdet_um::to_bf16(th[1]), hdet_um::to_bf16(th[2]), hdet_um::to_bf16(th[3])};
+            __builtin_nontemporal_store(o, reinterpret_cast<us4*>(g.upd.shadow + off));
+          }
+        } else if (EPI == HDET_EPI_F32 || EPI == HDET_EPI_BIAS_F32) {
+          put(reinterpret_cast<f4*>(reinterpret_cast<float*>(g.c) + off), v);
+        } else if (EPI == HDET_EPI_BIAS_GELU_BF16) {
+          const us4 pre = {f2bf(v[0]), f2bf(v[1]), f2bf(v[2]), f2bf(v[3])};
+          put(reinterpret_cast<us4*>(reinterpret_cast<uint16_t*>(g.c) + off), pre);
+          const us4 o = {f2bf(hdet_gelu_tanh_fast(bf2f(pre[0]))), f2bf(hdet_gelu_tanh_fast(bf2f(pre[1]))),
+                         f2bf(hdet_gelu_tanh_fast(bf2f(pre[2]))), f2bf(hdet_gelu_tanh_fast(bf2f(pre[3])))};
+          put(reinterpret_cast<us4*>(reinterpret_cast<uint16_t*>(g.c2) + off), o);
+        } else {
+          const us4 o = {f2bf(v[0]), f2bf(v[1]), f2bf(v[2]), f2bf(v[3])};
+          put(reinterpret_cast<us4*>(reinterpret_cast<uint16_t*>(g.c) + off), o);
+          if (kColsum) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) csum[q] += bf2f(o[q]);
+          }
+        }
       }
     }
   }
@@ -584,29 +584,29 @@ __global__ __launch_bounds__(512, 2) void hdet_bgemm_alt_kernel(const hdet_bgemm
     __builtin_amdgcn_sched_barrier(0);
   };
 
-      load_a(0, 0, 0); load_b(0, 0); load_a(1, 0, 0);
-      load_a(0, 1, 1); load_b(1, 1);
-      wait_and_barrier<8>();
-      if (wave >= 4) meet();
-      for (int kt0 = 0; kt0 < nk; kt0 += 2) {
+  load_a(0, 0, 0); load_b(0, 0); load_a(1, 0, 0);
+  load_a(0, 1, 1); load_b(1, 1);
+  wait_and_barrier<8>();
+  if (wave >= 4) meet();
+  for (int kt0 = 0; kt0 < nk; kt0 += 2) {
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-          const int kt = kt0 + s;
-          if (kt >= nk) break;
-          read_a(0, s);
-          read_b(s);
-          load_a(1, s ^ 1, kt + 1);
-          wait_and_barrier<8>();
-          multiply(0);
-          meet();
-          read_a(1, s);
-          load_a(0, s, kt + 2);
-          load_b(s, kt + 2);
-          wait_and_barrier<8>();
-          multiply(1);
-          meet();
-        }
-      }
+    for (int s = 0; s < 2; ++s) {
+      const int kt = kt0 + s;
+      if (kt >= nk) break;
+      read_a(0, s);
+      read_b(s);
+      load_a(1, s ^ 1, kt + 1);
+      wait_and_barrier<8>();
+      multiply(0);
+      meet();
+      read_a(1, s);
+      load_a(0, s, kt + 2);
+      load_b(s, kt + 2);
+      wait_and_barrier<8>();
+      multiply(1);
+      meet();
+    }
+  }
   if (wave < 4) meet();
   wait_and_barrier<0>();
   store_tile<EPI, TM, TN, WGM, WGN, STREAM, 8 * HALF * 2>(g, acc, S, id.bx, id.by, bi.z0, c_base, tid);
@@ -684,6 +684,12 @@ constexpr tile_shape kPair = {256, 128, 2, 3.6f, 0.53f, 32.f, 0.52f};          /
 constexpr tile_shape kPairWgrad = {256, 128, 2, 3.6f, 0.53f, 27.3f, 0.52f};
 constexpr tile_shape kLong = {256, 128, 1, 2.35f, 0.51f, 13.6f, 1.f};          // K step 64, three stages
 constexpr tile_shape kSmall = {128, 128, 2, 3.1f, 0.44f, 18.1f, 0.8f};         // K step 64, two stages, two blocks a CU
+// Up to one 128 x 128 tile a CU (below the sweeps' range) nothing but the length of a block's own chain counts: such tiles, from K = 512 on with
+// four stages of K = 64 in flight instead of two, whose longer start costs 1 us.  us, four stages / two / what the cost would choose, operands cold:
+//   32 x 1024, K = 2048, 4 items, ReLU gate at K = 1024 14.7 / 17.0 / 17.7;  64 x 512, K = 4096, 3 items 38.6 / 54.1 / 48.4;
+//   96 x 704, K = 1504, 6 items 25.0 / 30.3 / 26.8;  200 x 1000, K = 3000, 2 items 42.8 / 51.6 / 61.2;  96 x 1504, K = 784 19.0 / 19.5 / 19.8;
+//   32 x 2048, K = 512, 4 items 10.1 / 11.6 / 12.2;  128 x 1024, K = 256, 8 items 10.1 / 9.3 / 9.9;  gradients of K = 32 to 256 7 to 15 % slower
+constexpr tile_shape kDeep = {128, 128, 1, 0.f, 0.f, 0.f, 0.f};                // K step 64, four stages
 template <int EPI> constexpr float kEpiTime =
     EPI == HDET_EPI_ADAMW ? 80.f : EPI == HDET_EPI_GELUGRAD_BF16 || EPI == HDET_EPI_BIAS_DROP_RESID_BF16 ? 20.f
     : EPI == HDET_EPI_MASK_BF16 || EPI == HDET_EPI_BIAS_RESID_BF16 || EPI == HDET_EPI_BIAS_GELU_BF16 ? 15.f
@@ -724,7 +730,11 @@ hipError_t launch_shape(const hdet_bgemm_args& g, int batch, hipStream_t s) {
     else HDET_TILE(kSmall, 256, hdet_bgemm_dma_kernel, 128, 128, 2, 2, 2, 64,);
   } else {
     const float t_pair = time_of(wgrad ? kPairWgrad : kPair), t_small = time_of(kSmall), t_long = time_of(kLong);
-    if (t_alt <= t_pair && t_alt <= t_small && t_alt <= t_long) HDET_TILE(kAlternating, 512, hdet_bgemm_alt_kernel, );
+    if ((int64_t)((g.m + 127) / 128) * ((g.n + 127) / 128) * batch <= cus) {
+      if (g.k >= 512) HDET_TILE(kDeep, 256, hdet_bgemm_dma_kernel, 128, 128, 2, 2, 4, 64,);
+      else HDET_TILE(kSmall, 256, hdet_bgemm_dma_kernel, 128, 128, 2, 2, 2, 64,);
+    }
+    else if (t_alt <= t_pair && t_alt <= t_small && t_alt <= t_long) HDET_TILE(kAlternating, 512, hdet_bgemm_alt_kernel, );
     else if (t_pair <= t_small && t_pair <= t_long)
       HDET_TILE(kPair, 512, hdet_bgemm_dma_kernel, 256, 128, 4, 2, 3, 32,);
     else if (t_small <= t_long) HDET_TILE(kSmall, 256, hdet_bgemm_dma_kernel, 128, 128, 2, 2, 2, 64,);
