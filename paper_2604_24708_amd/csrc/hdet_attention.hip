@@ -21,6 +21,7 @@
 //   8 replicas x 16 sequences x 16 heads, S = 512   199 / 338 / 305 -> 195 / 234 / 265
 //   4 x 2 x 8, S = 2048                             112 / 187 / 143 -> 79 / 79 / 91
 //   8 x 16 x 8, S = 256                             43 / 67 / 55 -> 44 / 56 / 51
+// (with the column sums of sum_columns dq and dk, dv take 2 to 7 % longer)
 // (before: dq walked its tiles twice, tiles went through registers into LDS, results of the paths of a tile were copied together, p was formed from
 // maximum and sum, and every grid had the first order of remap_block.)  Measured and not kept: both 32 x 32 blocks of a
 // tile in one basic block, 211 to 256 registers, 20 to 30 % slower in the backward kernels; dk and dv with 3 wavefronts
@@ -169,6 +170,7 @@ struct attn_args {
   uint16_t* dqkv;           // backward: [N][B][S][3d]
   float* row_lse;           // [N][B][heads][S] log2 of the row's sum of exponentials
   float* row_ndot;          // minus the row's dot
+  float* colsum;            // backward: sums of dqkv over the rows of a block, [N][B][S / 128][3d], or null
   const hdet_ctrl* ctrl;
   int temp_channel;
   float scale;              // 1 / sqrt(d_head)
@@ -234,6 +236,30 @@ __device__ __forceinline__ void store_rows(const f16v (&o)[2], uint16_t* stg, ui
       *reinterpret_cast<us8*>(dst + (int64_t)row * ld + col) = *reinterpret_cast<const us8*>(stg + row * PT + col);
     }
   }
+}
+
+// The block's 64 column sums over its 128 rows, as stored, from the wavefronts' strips (stage 1 of the qkv bias gradient, which was a pass
+// over dqkv of 75 us at S = 512, where the two kernels grow by 19; 21 against 7 at S = 256): one product of each strip against ones, then the four wavefronts in the order of their rows.
+// Every thread calls it; all 128 rows exist.
+__device__ __forceinline__ void sum_columns(const uint16_t* strips, float* sums, float* dst, int tid) {
+  const int lane = tid & 63, w = tid >> 6, p = lane & 15;
+  const us8 o = {0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80};
+  const uint16_t* from = strips + w * WR * PT + (((lane >> 5) << 2) + (p >> 2)) * PT + ((lane >> 4) & 1) * 16 + ((p & 3) << 2);
+#pragma unroll
+  for (int dt = 0; dt < 2; ++dt) {
+    f16v x = zero16();
+#pragma unroll
+    for (int ks = 0; ks < WR; ks += 16) {
+      const uint16_t* q = from + ks * PT + 32 * dt;
+      const s4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s4 __attribute__((address_space(3)))*)(q));
+      const s4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s4 __attribute__((address_space(3)))*)(q + 8 * PT));
+      const s8 both = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+      x = mfma(__builtin_bit_cast(bf16x8, o), __builtin_bit_cast(bf16x8, both), x);
+    }
+    if (lane < 32) sums[w * DH + 32 * dt + lane] = x[0];
+  }
+  __syncthreads();
+  if (tid < DH) dst[tid] = (sums[tid] + sums[DH + tid]) + (sums[2 * DH + tid] + sums[3 * DH + tid]);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -477,6 +503,7 @@ __global__ __launch_bounds__(THREADS, 3) void attn_bwd_dq_kernel(const attn_args
 #pragma unroll
     for (int e = 0; e < 16; ++e) o[dt][e] *= scale;
   store_rows(o, smem + w * WR * PT, g.dqkv + (tok0 + (on ? wq0 : 0)) * ld + h * DH, ld, on, lane);
+  if (g.colsum) sum_columns(smem, reinterpret_cast<float*>(smem + RB * PT), g.colsum + (tok0 + q0) / RB * ld + h * DH, tid);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -587,7 +614,13 @@ __global__ __launch_bounds__(THREADS, 2) void attn_bwd_dkv_kernel(const attn_arg
     for (int e = 0; e < 16; ++e) dk[dt][e] *= scale;
   uint16_t* dst = g.dqkv + (tok0 + (on ? wk0 : 0)) * ld + h * DH;
   store_rows(dk, smem + w * WR * PT, dst + g.d, ld, on, lane);
-  store_rows(dv, smem + w * WR * PT, dst + 2 * g.d, ld, on, lane);
+  store_rows(dv, smem + (NWV + w) * WR * PT, dst + 2 * g.d, ld, on, lane);
+  if (g.colsum) {
+    float* const sums = reinterpret_cast<float*>(smem + 2 * RB * PT);
+    float* const at = g.colsum + (tok0 + k0) / RB * ld + h * DH;
+    sum_columns(smem, sums, at + g.d, tid);
+    sum_columns(smem + RB * PT, sums + NWV * DH, at + 2 * g.d, tid);
+  }
 }
 
 dim3 attn_grid(const hdet_attn_desc& a) { return dim3((a.seq_len + RB - 1) / RB, a.batch * a.heads, a.n_replicas); }
@@ -607,7 +640,7 @@ bool heavy_first_order(const hdet_attn_desc& a) {
 attn_args make_args(const hdet_attn_desc& a) {
   attn_args g;
   g.qkv = a.qkv; g.a = a.a; g.a_rest = a.a_rest; g.da = a.da; g.dqkv = a.dqkv;
-  g.row_lse = a.row_lse; g.row_ndot = a.row_ndot;
+  g.row_lse = a.row_lse; g.row_ndot = a.row_ndot; g.colsum = a.colsum;
   g.ctrl = a.ctrl; g.temp_channel = a.temp_channel; g.scale = a.scale;
   g.B = a.batch; g.S = a.seq_len; g.heads = a.heads; g.d = a.d_model;
   g.heavy_first = heavy_first_order(a);
@@ -628,7 +661,7 @@ hipError_t hdet_launch_attn_fwd(const hdet_attn_desc& a, hipStream_t s) {
 }
 
 hipError_t hdet_launch_attn_bwd(const hdet_attn_desc& a, hipStream_t s) {
-  if (!hdet_attn_fusable(a.seq_len, a.d_model, a.heads, a.batch)) return hipErrorInvalidValue;
+  if (!hdet_attn_fusable(a.seq_len, a.d_model, a.heads, a.batch) || (a.colsum && a.seq_len % RB)) return hipErrorInvalidValue;
   hipLaunchKernelGGL(attn_bwd_dq_kernel, attn_grid(a), dim3(THREADS), 0, s, make_args(a));
   hipLaunchKernelGGL(attn_bwd_dkv_kernel, attn_grid(a), dim3(THREADS), 0, s, make_args(a));
   return hipGetLastError();

@@ -281,6 +281,7 @@ struct hdet_attn_desc {
   uint16_t* dqkv;           // backward output, layout of qkv
   float* row_lse;           // [N][B][heads][S] row statistic, written by the forward
   float* row_ndot;          // scratch of the backward, same shape
+  float* colsum;            // backward: sums of dqkv over each 128 rows, [N][batch * seq_len / 128][3 d_model]; seq_len a multiple of 128, or null
   const hdet_ctrl* ctrl;
   int temp_channel;         // attention-temperature channel or -1
   float scale;              // 1 / sqrt(d_head)

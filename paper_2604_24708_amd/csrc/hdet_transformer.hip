@@ -1384,7 +1384,7 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
     hdet_attn_desc ad;
     ad.qkv = (const uint16_t*)p->qkv[l]; ad.a = (uint16_t*)p->a[l]; ad.da = (const uint16_t*)p->dtmp; ad.dqkv = (uint16_t*)p->dqkv;
     ad.a_rest = (uint16_t*)p->p[l];          // the probabilities' place: unused here, and as large from S = 64 on
-    ad.row_lse = p->att_lse[l]; ad.row_ndot = p->att_ndot;
+    ad.row_lse = p->att_lse[l]; ad.row_ndot = p->att_ndot; ad.colsum = nullptr;
     ad.ctrl = ctrl; ad.temp_channel = p->temp_channel; ad.scale = scale;
     ad.n_replicas = N; ad.batch = B; ad.seq_len = S; ad.heads = nh; ad.d_model = d;
     return ad;
@@ -1598,8 +1598,12 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
       TF_CHECK(gemm<T>(p, NN, act(dob, d), wt(o.w_o, d), p->dtmp, d, act_d, true, M, d, d, 1, 1, nullptr, 0, s));   // da
       TF_CHECK(wgrad(dob, d, p->a[l], d, o.w_o));
     }
+    bool bqkv_done = false;                        // stage 1 of the qkv bias gradient comes from the attention's backward kernels
     if (p->fused_attn) {
       hdet_attn_desc ad = attn_desc(l);
+      if (S % kColsumRows == 0)
+        for (const colsum_job& j : p->jobs)
+          if (j.out_off == o.b_qkv && j.mode == 0 && j.cols == 3 * d && j.nchunks == M / kColsumRows) { ad.colsum = p->part + j.part_off; bqkv_done = true; break; }
       TF_CHECK(hdet_launch_attn_bwd(ad, s));
     } else {
       const mat sc = head_sq(p->scores);
@@ -1627,7 +1631,7 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
     if constexpr (f32) {
       TF_CHECK(linear_bwd(p->dqkv, 3 * d, p->h1[l], d, o.w_qkv, o.b_qkv, p->dtmp, nullptr, nullptr, false));
     } else {
-      TF_CHECK(colsum(p->dqkv, 3 * d, o.b_qkv));
+      if (!bqkv_done) TF_CHECK(colsum(p->dqkv, 3 * d, o.b_qkv));
       TF_CHECK(gemm<T>(p, NN, act(p->dqkv, 3 * d), wt(o.w_qkv, d), p->dtmp, d, act_d, true, M, d, 3 * d, 1, 1, nullptr, 0, s));
       TF_CHECK(wgrad(p->dqkv, 3 * d, p->h1[l], d, o.w_qkv));
     }
