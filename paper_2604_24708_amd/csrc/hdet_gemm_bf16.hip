@@ -233,7 +233,8 @@ __device__ __forceinline__ bf16x8 ones() {
 }
 
 // WT x WT: 32x32 MFMA blocks per wavefront; 2 x 2 wavefronts per block, block tile (64 WT) x (64 WT).
-template <bool A_KMAJOR, bool B_KMAJOR, int EPI, int WT>
+// PIECES: the contraction is summed in that many pieces, each from zero, and the pieces are added in ascending order (launch_general).
+template <bool A_KMAJOR, bool B_KMAJOR, int EPI, int WT, int PIECES = 1>
 __global__ __launch_bounds__(256, 2) void hdet_bgemm_kernel(const hdet_bgemm_args g) {
   constexpr int TM = 64 * WT, TN = TM, THREADS = 256, DEPTH = 4;
   __shared__ __attribute__((aligned(16))) uint16_t As[2][tile_elems(TM)];
@@ -282,9 +283,42 @@ __global__ __launch_bounds__(256, 2) void hdet_bgemm_kernel(const hdet_bgemm_arg
   typedef operand<A_KMAJOR, TM, THREADS> ta;
   typedef operand<B_KMAJOR, TN, THREADS> tb;
   const int nk = (g.k + TK - 1) / TK;
+  // steps of 16 k a piece and left of this one; the last piece takes what is left over
+  const int per_piece = ((g.k >> 4) + PIECES - 1) / PIECES;
+  int left = per_piece, pieces_left = PIECES - 1;
+  f16v tot[PIECES > 1 ? WT : 1][PIECES > 1 ? WT : 1], rtot[PIECES > 1 && SUMS ? WT : 1];
+  auto close_piece = [&] {
+    if constexpr (PIECES > 1) {
+      const f16v zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < WT; ++i) {
+#pragma unroll
+        for (int j = 0; j < WT; ++j) { tot[i][j] += acc[i][j]; acc[i][j] = zero; }
+        if constexpr (SUMS) { rtot[i] += rsum[i]; rsum[i] = zero; }
+      }
+    }
+  };
+  if constexpr (PIECES > 1) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+#pragma unroll
+      for (int i = 0; i < WT; ++i) {
+#pragma unroll
+        for (int j = 0; j < WT; ++j) tot[i][j][e] = 0.f;
+        if constexpr (SUMS) rtot[i][e] = 0.f;
+      }
+  }
   auto multiply = [&](int buf) {
 #pragma unroll
     for (int ks = 0; ks < TK; ks += 16) {
+      if constexpr (PIECES > 1) {
+        if (left == 0 && pieces_left > 0) {            // uniform
+          close_piece();
+          left = per_piece;
+          --pieces_left;
+        }
+        --left;
+      }
       bf16x8 af[WT], bfr[WT];
 #pragma unroll
       for (int i = 0; i < WT; ++i) af[i] = ta::fragment(As[buf], wm + i * 32, ks, lane);
@@ -378,6 +412,15 @@ __global__ __launch_bounds__(256, 2) void hdet_bgemm_kernel(const hdet_bgemm_arg
     }
   }
 
+  if constexpr (PIECES > 1) {
+    close_piece();
+#pragma unroll
+    for (int i = 0; i < WT; ++i) {
+#pragma unroll
+      for (int j = 0; j < WT; ++j) acc[i][j] = tot[i][j];
+      if constexpr (SUMS) rsum[i] = rtot[i];
+    }
+  }
   // epilogue: accumulator element e of lane l is C(row, col) with
   //   row = (e / 4) * 8 + (l / 32) * 4 + e % 4,  col = l % 32   inside its 32x32 block
 #pragma unroll
@@ -528,29 +571,29 @@ namespace {
 int64_t tiles(const hdet_bgemm_args& g, int batch, int tm, int tn) {
   return (int64_t)((g.m + tm - 1) / tm) * ((g.n + tn - 1) / tn) * batch;
 }
-// A product that leaves most of the chip idle in 64 x 64 tiles takes the fragment kernel with 32 x 32 tiles, K in 8 from K = 512 on and in 4
-// below.  us, operands cold, K in 8 / in 4 / LDS 64 x 64:  96 x 703, K = 1501, 4 items (88 tiles, odd rows) 22.4 / 25.4 / 23.5;
-// 100 x 300, K = 3001, 3 items 27.2 / 40.9 / 37.0;  64 x 1024, K = 2048, 4 items 17.9 / 18.4 / 20;  96 x 100, K = 700, 6 items 8.5 / 9.3 / 10.8;
-// 100 x 576 gradient, K = 576 6.5 / 7.0 / 8.6.  Beyond: 96 x 700, K = 1500, 6 items (132 tiles) 24.5 / - / 19.2.
+// A product that leaves most of the chip idle in 64 x 64 tiles takes the fragment kernel with 32 x 32 tiles and K in 4, whatever its K.
+// (K in 8 is 5 to 30 % faster from K = 512 on -- 96 x 703, K = 1501, 4 items 22.4 / 25.4 us, 100 x 300, K = 3001, 3 items 27.2 / 40.9 -- and not
+// kept: sums in another order put stored activations on the other side of a rounding boundary, and units behind a ReLU on the other side of
+// zero, which moves single entries of a small batch's gradients by more than their tensor's root mean square.)
 bool few_tiles(const hdet_bgemm_args& g, int batch) { return tiles(g, batch, 64, 64) * 5 < 2 * (int64_t)hdet_compute_units(); }
 
+// `aligned`: the LDS-direct kernel could form the product as well, whose sums are not split.
 template <bool AK, bool BK, int EPI>
-hipError_t launch_general(const hdet_bgemm_args& g, int batch, hipStream_t s) {
-#define HDET_FRAG(WK)                                                                                 \
-  hipLaunchKernelGGL((hdet_bgemm_frag_kernel<AK, BK, EPI, WK>), dim3((g.n + 31) / 32, (g.m + 31) / 32, batch), dim3(64 * WK), 0, s, g)
-#define HDET_LDS(WT)                                                                                  \
-  hipLaunchKernelGGL((hdet_bgemm_kernel<AK, BK, EPI, WT>), dim3((g.n + 64 * WT - 1) / (64 * WT), (g.m + 64 * WT - 1) / (64 * WT), batch), dim3(256), 0, s, g)
+hipError_t launch_general(const hdet_bgemm_args& g, int batch, bool aligned, hipStream_t s) {
+#define HDET_LDS(WT, ...)                                                                             \
+  hipLaunchKernelGGL((hdet_bgemm_kernel<AK, BK, EPI, WT, ##__VA_ARGS__>), dim3((g.n + 64 * WT - 1) / (64 * WT), (g.m + 64 * WT - 1) / (64 * WT), batch), dim3(256), 0, s, g)
   const int64_t cus = hdet_compute_units();
-  if (few_tiles(g, batch)) {
-    if (g.k >= 512) HDET_FRAG(8);
-    else HDET_FRAG(4);
-  }
+  if (few_tiles(g, batch)) hipLaunchKernelGGL((hdet_bgemm_frag_kernel<AK, BK, EPI, 4>), dim3((g.n + 31) / 32, (g.m + 31) / 32, batch), dim3(256), 0, s, g);
+  // less than one 64 x 64 block per CU and a long contraction: the sums of K in 8, by one block that walks the eighths one after the
+  // other.  (Eight wavefronts of the fragment kernel, an eighth each, give the same bits.  us, so / in this kernel: 96 x 700, K = 1500,
+  // 6 items 24.4 / 19.7;  97 x 2111, K = 1501, 3 items 58.7 / 23.3;  64 x 1500, K = 2047, 5 items 46.7 / 35.6;  130 x 1001, K = 4095, 4 items
+  // 119 / 45.8;  96 x 1500, K = 1500 gradient, 4 items 32.9 / 19.2.  Summed in one piece 18.9, 25.7, 39.6, 52.7, 16.7: see few_tiles.)
+  else if (!aligned && g.k >= 1024 && tiles(g, batch, 64, 64) < cus) HDET_LDS(1, 8);
   // 128 x 128 tiles once there are several rounds of them (256 x 4095, K = 4095, 8 items: 337 | 64 x 64 441; 700 x 1500, K = 576:
   // 14.8 | 10.1; 1788 x 3193, K = 222: 18.4 | 14.7), unless they would be half empty
   else if (tiles(g, batch, 128, 128) >= 4 * cus && g.m > 64 && g.n > 64) HDET_LDS(2);
   else HDET_LDS(1);
 #undef HDET_LDS
-#undef HDET_FRAG
   return hipGetLastError();
 }
 
@@ -570,25 +613,26 @@ hipError_t hdet_launch_bgemm(const hdet_bgemm_args& g_in, bool a_kmajor, bool b_
   // 256 x 640, K = 640, 5 items 11.5 / 14.0;  200 x 512, K = 512, 6 items 9.9 / 12.4;  32 x 2048, K = 512, 4 items 10.2 / 9.8;
   // 256 x 2048, K = 256, 3 items 9.8 / 9.8.  (Gradients of such layers stay: 96 x 1500, K = 700 16.4 / 14.5.)
   const bool small_grid = plain && b_kmajor && tiles(g, batch, 64, 64) <= 2 * (int64_t)hdet_compute_units();
-  if (hdet_bgemm_dma_eligible(g, a_kmajor, b_kmajor, epi) && !small_grid && !(plain && few_tiles(g, batch)))
+  const bool aligned = hdet_bgemm_dma_eligible(g, a_kmajor, b_kmajor, epi);
+  if (aligned && !small_grid && !(plain && few_tiles(g, batch)))
     return hdet_launch_bgemm_dma(g, a_kmajor, b_kmajor, epi, batch, s);
   if (a_kmajor && b_kmajor) {            // forward
     switch (epi) {
-      case HDET_EPI_F32: return launch_general<true, true, HDET_EPI_F32>(g, batch, s);
-      case HDET_EPI_BIAS_F32: return launch_general<true, true, HDET_EPI_BIAS_F32>(g, batch, s);
-      case HDET_EPI_BIAS_RELU_BF16: return launch_general<true, true, HDET_EPI_BIAS_RELU_BF16>(g, batch, s);
-      case HDET_EPI_BIAS_BF16: return launch_general<true, true, HDET_EPI_BIAS_BF16>(g, batch, s);
+      case HDET_EPI_F32: return launch_general<true, true, HDET_EPI_F32>(g, batch, aligned, s);
+      case HDET_EPI_BIAS_F32: return launch_general<true, true, HDET_EPI_BIAS_F32>(g, batch, aligned, s);
+      case HDET_EPI_BIAS_RELU_BF16: return launch_general<true, true, HDET_EPI_BIAS_RELU_BF16>(g, batch, aligned, s);
+      case HDET_EPI_BIAS_BF16: return launch_general<true, true, HDET_EPI_BIAS_BF16>(g, batch, aligned, s);
       default: return hipErrorInvalidValue;
     }
   }
   if (a_kmajor) {                        // dgrad
-    if (epi == HDET_EPI_MASK_BF16) return launch_general<true, false, HDET_EPI_MASK_BF16>(g, batch, s);
-    if (epi == HDET_EPI_BF16) return launch_general<true, false, HDET_EPI_BF16>(g, batch, s);
+    if (epi == HDET_EPI_MASK_BF16) return launch_general<true, false, HDET_EPI_MASK_BF16>(g, batch, aligned, s);
+    if (epi == HDET_EPI_BF16) return launch_general<true, false, HDET_EPI_BF16>(g, batch, aligned, s);
     return hipErrorInvalidValue;
   }
   if (!b_kmajor) {                       // wgrad
-    if (epi == HDET_EPI_F32) return launch_general<false, false, HDET_EPI_F32>(g, batch, s);
-    if (epi == HDET_EPI_BF16) return launch_general<false, false, HDET_EPI_BF16>(g, batch, s);
+    if (epi == HDET_EPI_F32) return launch_general<false, false, HDET_EPI_F32>(g, batch, aligned, s);
+    if (epi == HDET_EPI_BF16) return launch_general<false, false, HDET_EPI_BF16>(g, batch, aligned, s);
   }
   return hipErrorInvalidValue;
 }
