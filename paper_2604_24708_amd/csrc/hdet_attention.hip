@@ -11,8 +11,8 @@
 // with scale = 1 / (sqrt(d_head) tau_r), tau_r the replica's attention temperature when that is
 // an explored channel (Remark 1).  Because p is rounded after the normalisation, as the unfused path does it, the forward
 // walks its tiles twice: for the row sums, then for the product (rounding exp(s - max) instead, in one walk, moves the loss
-// of a small model by 5e-4).  It leaves the logarithm of each row's sum ([rows] fp32, base 2), from which all three kernels form p as one
-// hardware exp2 of one fma, hence bit for bit alike, and what rounding took off a (a_rest, bf16), so that dot
+// of a small model by 5e-4).  It leaves each row's maximum and the reciprocal of its sum ([rows] fp32 each), from which all three kernels
+// form p by the same operations, hence bit for bit alike, and what rounding took off a (a_rest, bf16), so that dot
 // comes from 16 bits of a and the backward kernels walk their tiles once.  The dp accumulators start at minus dot.
 //
 // What bounds them: neither pipe is full (matrix cores busy 29 to 42 % of the cycles, VALU 39 to 60 %); a wavefront's chain from its LDS reads
@@ -131,6 +131,9 @@ __device__ __forceinline__ bf16x8 acc_frag(const f16v& x, int j) {
 }
 __device__ __forceinline__ float other_half(float x) { return __shfl_xor(x, 32); }
 __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
+// The probability, before it is rounded to bf16, from the raw score s, the row's maximum of s c and 1 / (row sum).  The maximum's rounding
+// cancels in the normalisation; that of one statistic for both, maximum plus log2 sum, does not: half an ulp of a number as large as the scores.
+__device__ __forceinline__ float prob(float s, float c, float mx, float inv) { return exp2_fast(__builtin_fmaf(s, c, -mx)) * inv; }
 
 // entries of an accumulator block whose row index (row0 + row in block) exceeds `limit` become `fill`
 __device__ __forceinline__ void fill_above(f16v& x, int row0, int limit, int lane, float fill) {
@@ -168,7 +171,8 @@ struct attn_args {
   uint16_t* a_rest;         // ... and what rounding took off it
   const uint16_t* da;       // backward: gradient at a
   uint16_t* dqkv;           // backward: [N][B][S][3d]
-  float* row_lse;           // [N][B][heads][S] log2 of the row's sum of exponentials
+  float* row_max;           // [N][B][heads][S] the row's maximum of s c, c = scale log2 e
+  float* row_inv;           // 1 / the row's sum of exp2(s c - maximum)
   float* row_ndot;          // minus the row's dot
   float* colsum;            // backward: sums of dqkv over the rows of a block, [N][B][S / 128][3d], or null
   const hdet_ctrl* ctrl;
@@ -343,13 +347,14 @@ __global__ __launch_bounds__(THREADS, 4) void attn_fwd_kernel(const attn_args g)
     });
   }
   const float mo = other_half(m), lo = other_half(l), top = fmaxf(m, mo);
-  const float lse = __builtin_fmaf(top, c, __builtin_amdgcn_logf(l * exp2_fast((m - top) * c) + lo * exp2_fast((mo - top) * c)));
+  const float mx = top * c;
+  const float inv = 1.f / (l * exp2_fast((m - top) * c) + lo * exp2_fast((mo - top) * c));
 
   // pass 2: a^T = v^T p^T, [column][query]
   f16v o[2] = {zero16(), zero16()};
   auto add_block = [&](f16v& x, const uint16_t* vt) {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) x[e] = exp2_fast(__builtin_fmaf(x[e], c, -lse));
+    for (int e = 0; e < 16; ++e) x[e] = prob(x[e], c, mx, inv);
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const bf16x8 pf = acc_frag(x, j);
@@ -386,7 +391,11 @@ __global__ __launch_bounds__(THREADS, 4) void attn_fwd_kernel(const attn_args g)
     });
   }
   wait_and_barrier<0>();
-  if (on && lane < 32) g.row_lse[(((int64_t)r * g.B + b) * g.heads + h) * g.S + wq0 + qi] = lse;
+  if (on && lane < 32) {
+    const int64_t gr = (((int64_t)r * g.B + b) * g.heads + h) * g.S + wq0 + qi;
+    g.row_max[gr] = mx;
+    g.row_inv[gr] = inv;
+  }
   f16v rest[2];                            // what rounding takes off a
 #pragma unroll
   for (int dt = 0; dt < 2; ++dt)
@@ -447,7 +456,7 @@ __global__ __launch_bounds__(THREADS, 3) void attn_bwd_dq_kernel(const attn_args
   request(1, 1);
 #pragma unroll
   for (int k4 = 0; k4 < 4; ++k4) fq[k4] = frag_g(base + (int64_t)(on ? wq0 : 0) * ld, ld, k4 * 16, lane);
-  const float lse = g.row_lse[gr];
+  const float mx = g.row_max[gr], inv = g.row_inv[gr];
   const float scale = replica_scale(g, r);
   const float c = scale * kLog2e;
   ndot += other_half(ndot);
@@ -462,7 +471,7 @@ __global__ __launch_bounds__(THREADS, 3) void attn_bwd_dq_kernel(const attn_args
 #pragma unroll
     for (int k4 = 0; k4 < 4; ++k4) dp = mfma(fa.rows(vt, k4), fda[k4], dp);
 #pragma unroll
-    for (int e = 0; e < 16; ++e) s[e] = exp2_fast(__builtin_fmaf(s[e], c, -lse));
+    for (int e = 0; e < 16; ++e) s[e] = prob(s[e], c, mx, inv);
     if (across) fill_above(s, key0, wq0 + qi, lane, 0.f);
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
@@ -510,7 +519,7 @@ __global__ __launch_bounds__(THREADS, 3) void attn_bwd_dq_kernel(const attn_args
 // backward, step 2: dk and dv; block = 128 keys, walks the query tiles at or below the diagonal
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(THREADS, 2) void attn_bwd_dkv_kernel(const attn_args g) {
-  // queries, output gradients and the queries' two row statistics (one for each wavefront, each twice): three stages
+  // queries, output gradients and the queries' three row statistics (a wavefront each, the last one twice): three stages
   constexpr int STAGE = 2 * TILE + NWV * TB * 2;
   __shared__ __attribute__((aligned(1024))) uint16_t smem[3 * STAGE];
   const block_id blk = remap_block(g.heavy_first);
@@ -527,7 +536,7 @@ __global__ __launch_bounds__(THREADS, 2) void attn_bwd_dkv_kernel(const attn_arg
   const int qb0 = k0 / TB, nqb = g.S / TB;
 
   const tile_stream qs(base, ld, tid, w), das(g.da + tok0 * g.d + h * DH, g.d, tid, w);
-  const float* const stats = ((w & 1) ? g.row_ndot : g.row_lse) + gr0;
+  const float* const stats = (w == 0 ? g.row_max : w == 1 ? g.row_inv : g.row_ndot) + gr0;
   const uint32_t s_addr = lds_addr_of(smem);
   auto request = [&](int t, int stage) {
     const uint32_t at = s_addr + stage * (2 * STAGE);
@@ -554,7 +563,7 @@ __global__ __launch_bounds__(THREADS, 2) void attn_bwd_dkv_kernel(const attn_arg
     f16v s = zero16(), dp;                                                 // [query][key]; dp = da v^T - dot
 #pragma unroll
     for (int e4 = 0; e4 < 4; ++e4) {                                       // 4 consecutive queries at a time
-      const f4 nd = *reinterpret_cast<const f4*>(st + TB + acc_row(4 * e4, lane));
+      const f4 nd = *reinterpret_cast<const f4*>(st + 2 * TB + acc_row(4 * e4, lane));
 #pragma unroll
       for (int u = 0; u < 4; ++u) dp[4 * e4 + u] = nd[u];
     }
@@ -564,9 +573,10 @@ __global__ __launch_bounds__(THREADS, 2) void attn_bwd_dkv_kernel(const attn_arg
     for (int k4 = 0; k4 < 4; ++k4) dp = mfma(fa.rows(dat, k4), fv[k4], dp);
 #pragma unroll
     for (int e4 = 0; e4 < 4; ++e4) {
-      const f4 lse = *reinterpret_cast<const f4*>(st + acc_row(4 * e4, lane));
+      const f4 mx = *reinterpret_cast<const f4*>(st + acc_row(4 * e4, lane));
+      const f4 inv = *reinterpret_cast<const f4*>(st + TB + acc_row(4 * e4, lane));
 #pragma unroll
-      for (int u = 0; u < 4; ++u) s[4 * e4 + u] = exp2_fast(__builtin_fmaf(s[4 * e4 + u], c, -lse[u]));
+      for (int u = 0; u < 4; ++u) s[4 * e4 + u] = prob(s[4 * e4 + u], c, mx[u], inv[u]);
     }
     if (across) fill_below(s, qr0, wk0 + ki, lane, 0.f);                   // causal: query >= key
 #pragma unroll
@@ -640,7 +650,7 @@ bool heavy_first_order(const hdet_attn_desc& a) {
 attn_args make_args(const hdet_attn_desc& a) {
   attn_args g;
   g.qkv = a.qkv; g.a = a.a; g.a_rest = a.a_rest; g.da = a.da; g.dqkv = a.dqkv;
-  g.row_lse = a.row_lse; g.row_ndot = a.row_ndot; g.colsum = a.colsum;
+  g.row_max = a.row_max; g.row_inv = a.row_inv; g.row_ndot = a.row_ndot; g.colsum = a.colsum;
   g.ctrl = a.ctrl; g.temp_channel = a.temp_channel; g.scale = a.scale;
   g.B = a.batch; g.S = a.seq_len; g.heads = a.heads; g.d = a.d_model;
   g.heavy_first = heavy_first_order(a);

@@ -279,7 +279,8 @@ struct hdet_attn_desc {
   uint16_t* a_rest;         // what rounding took off a, same shape: written by the forward, read by the backward
   const uint16_t* da;       // backward: gradient at a
   uint16_t* dqkv;           // backward output, layout of qkv
-  float* row_lse;           // [N][B][heads][S] row statistic, written by the forward
+  float* row_max;           // [N][B][heads][S] row statistics, written by the forward
+  float* row_inv;
   float* row_ndot;          // scratch of the backward, same shape
   float* colsum;            // backward: sums of dqkv over each 128 rows, [N][batch * seq_len / 128][3 d_model]; seq_len a multiple of 128, or null
   const hdet_ctrl* ctrl;

@@ -957,7 +957,7 @@ struct hdet_tf_plan {
   std::vector<float*> st1_mean, st1_rstd, st2_mean, st2_rstd;
   char *hf, *tmp_d, *dxa, *dxb, *dtmp, *dtmp2, *dff, *dqkv, *ds, *dlogits;
   float *stf_mean, *stf_rstd, *scores, *logits, *row_loss;
-  std::vector<float*> att_lse;               // [L] row statistic of the fused attention
+  std::vector<float*> att_max, att_inv;      // [L] row statistics of the fused attention
   float* att_ndot;
   unsigned long long* tok_sorted;            // [N][M] keys (token id, row) in ascending order
   float* tok_seg;                            // [N][M][d] partial rows of the token-embedding gradient
@@ -990,7 +990,7 @@ static size_t tf_carve(hdet_tf_plan* p, char* base) {
   p->x_in.assign(L + 1, nullptr); p->x_mid.assign(L, nullptr); p->h1.assign(L, nullptr); p->h2.assign(L, nullptr);
   p->qkv.assign(L, nullptr); p->p.assign(L, nullptr); p->a.assign(L, nullptr); p->z.assign(L, nullptr); p->f.assign(L, nullptr);
   p->st1_mean.assign(L, nullptr); p->st1_rstd.assign(L, nullptr); p->st2_mean.assign(L, nullptr); p->st2_rstd.assign(L, nullptr);
-  p->att_lse.assign(L, nullptr);
+  p->att_max.assign(L, nullptr); p->att_inv.assign(L, nullptr);
   for (int l = 0; l <= L; ++l) p->x_in[l] = take(N * M * d * e);
   for (int l = 0; l < L; ++l) {
     p->x_mid[l] = take(N * M * d * e); p->h1[l] = take(N * M * d * e); p->h2[l] = take(N * M * d * e);
@@ -998,7 +998,7 @@ static size_t tf_carve(hdet_tf_plan* p, char* base) {
     p->z[l] = take(N * M * ff * e); p->f[l] = take(N * M * ff * e);
     p->st1_mean[l] = (float*)take(N * M * 4); p->st1_rstd[l] = (float*)take(N * M * 4);
     p->st2_mean[l] = (float*)take(N * M * 4); p->st2_rstd[l] = (float*)take(N * M * 4);
-    p->att_lse[l] = (float*)take(N * heads * S * 4);
+    p->att_max[l] = (float*)take(N * heads * S * 4); p->att_inv[l] = (float*)take(N * heads * S * 4);
   }
   p->hf = take(N * M * d * e); p->tmp_d = take(N * M * d * e);
   p->dxa = take(N * M * d * e); p->dxb = take(N * M * d * e); p->dtmp = take(N * M * d * e); p->dtmp2 = take(N * M * d * e);
@@ -1384,7 +1384,7 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
     hdet_attn_desc ad;
     ad.qkv = (const uint16_t*)p->qkv[l]; ad.a = (uint16_t*)p->a[l]; ad.da = (const uint16_t*)p->dtmp; ad.dqkv = (uint16_t*)p->dqkv;
     ad.a_rest = (uint16_t*)p->p[l];          // the probabilities' place: unused here, and as large from S = 64 on
-    ad.row_lse = p->att_lse[l]; ad.row_ndot = p->att_ndot; ad.colsum = nullptr;
+    ad.row_max = p->att_max[l]; ad.row_inv = p->att_inv[l]; ad.row_ndot = p->att_ndot; ad.colsum = nullptr;
     ad.ctrl = ctrl; ad.temp_channel = p->temp_channel; ad.scale = scale;
     ad.n_replicas = N; ad.batch = B; ad.seq_len = S; ad.heads = nh; ad.d_model = d;
     return ad;
