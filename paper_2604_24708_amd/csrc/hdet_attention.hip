@@ -6,14 +6,14 @@
 //
 // Arithmetic: products and sums as the unfused path forms them, with bf16 operands and fp32 accumulation:
 //   forward   s = (q k^T) * scale (fp32), causal mask, p = exp(s - log sum exp s), a = bf16(p) v
-//   backward  dot = sum_c da_c a_c, dp = da v^T - dot,
+//   backward  dot = sum_c da_c a_c (fp32, a before it was rounded), dp = da v^T - dot,
 //             ds = bf16(bf16(p) dp), dq = (ds k) scale, dk = (ds^T q) scale, dv = bf16(p)^T da
 // with scale = 1 / (sqrt(d_head) tau_r), tau_r the replica's attention temperature when that is
 // an explored channel (Remark 1).  Because p is rounded after the normalisation, as the unfused path does it, the forward
 // walks its tiles twice: for the row sums, then for the product (rounding exp(s - max) instead, in one walk, moves the loss
 // of a small model by 5e-4).  It leaves each row's maximum and the reciprocal of its sum ([rows] fp32 each), from which all three kernels
-// form p by the same operations, hence bit for bit alike, and what rounding took off a (a_rest, bf16), so that dot
-// comes from 16 bits of a and the backward kernels walk their tiles once.  The dp accumulators start at minus dot.
+// form p by the same operations, hence bit for bit alike, and what rounding took off a (a_rest), so that dot
+// comes from the fp32 a and the backward kernels walk their tiles once.  The dp accumulators start at minus dot.
 //
 // What bounds them: neither pipe is full (matrix cores busy 29 to 42 % of the cycles, VALU 39 to 60 %); a wavefront's chain from its LDS reads
 // over the products and the exponentials to the next products, with the 2 to 4 wavefronts a SIMD holds, and below S = 512 what a block does before
@@ -74,7 +74,14 @@ constexpr float kLog2e = 1.4426950408889634f;
 
 __device__ __forceinline__ unsigned short f2bf(float x) { return __builtin_bit_cast(unsigned short, (__bf16)x); }
 __device__ __forceinline__ float bf2f(unsigned short h) { return __uint_as_float((unsigned)h << 16); }
-__device__ __forceinline__ float bf16_round(float x) { return bf2f(f2bf(x)); }
+// What rounding to bf16 took off an fp32 number, in 16 bits: the difference of the two as integers, in units of fp32's last place.  Only a
+// number halfway between two bf16 may have been 2^15 such units above its bf16 and is kept as 2^15 - 1.
+__device__ __forceinline__ unsigned short rest_of(float x) {
+  const int d = (int)(__float_as_uint(x) - ((unsigned)f2bf(x) << 16));
+  return (unsigned short)(d > 32767 ? 32767 : d < -32768 ? -32768 : d);
+}
+// the fp32 number from its bf16 and rest
+__device__ __forceinline__ float with_rest(unsigned short hi, unsigned short rest) { return __uint_as_float(((unsigned)hi << 16) + (unsigned)(int)(short)rest); }
 
 // Tiles lie in LDS as [64][64], the eight 16-byte chunks of row r permuted by XOR with swz(r): the 32 rows of a k-contiguous fragment
 // and the 4 rows x 64 bytes that half a wavefront of the transposing read touches both fall on disjoint banks.
@@ -168,7 +175,7 @@ struct tile_stream {
 struct attn_args {
   const uint16_t* qkv;      // [N][B][S][3d]
   uint16_t* a;              // forward: [N][B][S][d] output
-  uint16_t* a_rest;         // ... and what rounding took off it
+  uint16_t* a_rest;         // ... and what rounding took off it (rest_of)
   const uint16_t* da;       // backward: gradient at a
   uint16_t* dqkv;           // backward: [N][B][S][3d]
   float* row_max;           // [N][B][heads][S] the row's maximum of s c, c = scale log2 e
@@ -222,14 +229,15 @@ __device__ __forceinline__ block_id remap_block(bool heavy_first) {
 }
 
 // The wavefront's [32 rows][64] result, held transposed in two accumulator blocks (block dt:
-// columns 32 dt .., lane = row), goes to `dst` (row pitch ld) through the wavefront's LDS strip
+// columns 32 dt .., lane = row), goes to `dst` (row pitch ld) as to16(value) through the wavefront's LDS strip
 // so that every global store writes 16 bytes of a row.
-__device__ __forceinline__ void store_rows(const f16v (&o)[2], uint16_t* stg, uint16_t* dst, int64_t ld, bool on, int lane) {
+template <typename F>
+__device__ __forceinline__ void store_rows(const f16v (&o)[2], F&& to16, uint16_t* stg, uint16_t* dst, int64_t ld, bool on, int lane) {
 #pragma unroll
   for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
     for (int e4 = 0; e4 < 4; ++e4) {
-      const us4 x = {f2bf(o[dt][4 * e4]), f2bf(o[dt][4 * e4 + 1]), f2bf(o[dt][4 * e4 + 2]), f2bf(o[dt][4 * e4 + 3])};
+      const us4 x = {to16(o[dt][4 * e4]), to16(o[dt][4 * e4 + 1]), to16(o[dt][4 * e4 + 2]), to16(o[dt][4 * e4 + 3])};
       *reinterpret_cast<us4*>(stg + (lane & 31) * PT + dt * 32 + acc_row(4 * e4, lane)) = x;
     }
   __syncthreads();
@@ -396,14 +404,9 @@ __global__ __launch_bounds__(THREADS, 4) void attn_fwd_kernel(const attn_args g)
     g.row_max[gr] = mx;
     g.row_inv[gr] = inv;
   }
-  f16v rest[2];                            // what rounding takes off a
-#pragma unroll
-  for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) rest[dt][e] = o[dt][e] - bf16_round(o[dt][e]);
   const int64_t out = (tok0 + (on ? wq0 : 0)) * g.d + h * DH;
-  store_rows(o, smem + w * WR * PT, g.a + out, g.d, on, lane);
-  store_rows(rest, smem + w * WR * PT, g.a_rest + out, g.d, on, lane);
+  store_rows(o, f2bf, smem + w * WR * PT, g.a + out, g.d, on, lane);
+  store_rows(o, rest_of, smem + w * WR * PT, g.a_rest + out, g.d, on, lane);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -432,25 +435,20 @@ __global__ __launch_bounds__(THREADS, 3) void attn_bwd_dq_kernel(const attn_args
     vals.load(t, t < nkb, s_addr + stage * (4 * TILE) + 2 * TILE);
   };
   bf16x8 fq[4], fda[4];
-  // minus the row's dot = sum over the columns of da a: the diagonal of a product of 32 rows each
-  float ndot = 0.f;
+  float ndot = 0.f;                        // minus the row's dot = sum over the columns of da a, in fp32: 32 columns a half-wavefront
   {
     const int64_t row = (tok0 + (on ? wq0 : 0)) * g.d + h * DH;
-    bf16x8 hi[4], lo[4];
+    us8 hi[4], rest[4];
 #pragma unroll
     for (int k4 = 0; k4 < 4; ++k4) {
       fda[k4] = frag_g(g.da + row, g.d, k4 * 16, lane);
-      hi[k4] = frag_g(g.a + row, g.d, k4 * 16, lane);
-      lo[k4] = frag_g(g.a_rest + row, g.d, k4 * 16, lane);
+      hi[k4] = __builtin_bit_cast(us8, frag_g(g.a + row, g.d, k4 * 16, lane));
+      rest[k4] = __builtin_bit_cast(us8, frag_g(g.a_rest + row, g.d, k4 * 16, lane));
     }
-    f16v x = zero16();
 #pragma unroll
-    for (int k4 = 0; k4 < 4; ++k4) x = mfma(lo[k4], fda[k4], x);
+    for (int k4 = 0; k4 < 4; ++k4)
 #pragma unroll
-    for (int k4 = 0; k4 < 4; ++k4) x = mfma(hi[k4], fda[k4], x);
-    const int d = qi - ((lane >> 5) << 2);
-#pragma unroll
-    for (int e = 0; e < 16; ++e) ndot = d == acc_row(e, 0) ? -x[e] : ndot;
+      for (int t = 0; t < 8; ++t) ndot = __builtin_fmaf(-(float)fda[k4][t], with_rest(hi[k4][t], rest[k4][t]), ndot);
   }
   request(0, 0);
   request(1, 1);
@@ -511,7 +509,7 @@ __global__ __launch_bounds__(THREADS, 3) void attn_bwd_dq_kernel(const attn_args
   for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
     for (int e = 0; e < 16; ++e) o[dt][e] *= scale;
-  store_rows(o, smem + w * WR * PT, g.dqkv + (tok0 + (on ? wq0 : 0)) * ld + h * DH, ld, on, lane);
+  store_rows(o, f2bf, smem + w * WR * PT, g.dqkv + (tok0 + (on ? wq0 : 0)) * ld + h * DH, ld, on, lane);
   if (g.colsum) sum_columns(smem, reinterpret_cast<float*>(smem + RB * PT), g.colsum + (tok0 + q0) / RB * ld + h * DH, tid);
 }
 
@@ -623,8 +621,8 @@ __global__ __launch_bounds__(THREADS, 2) void attn_bwd_dkv_kernel(const attn_arg
 #pragma unroll
     for (int e = 0; e < 16; ++e) dk[dt][e] *= scale;
   uint16_t* dst = g.dqkv + (tok0 + (on ? wk0 : 0)) * ld + h * DH;
-  store_rows(dk, smem + w * WR * PT, dst + g.d, ld, on, lane);
-  store_rows(dv, smem + (NWV + w) * WR * PT, dst + 2 * g.d, ld, on, lane);
+  store_rows(dk, f2bf, smem + w * WR * PT, dst + g.d, ld, on, lane);
+  store_rows(dv, f2bf, smem + (NWV + w) * WR * PT, dst + 2 * g.d, ld, on, lane);
   if (g.colsum) {
     float* const sums = reinterpret_cast<float*>(smem + 2 * RB * PT);
     float* const at = g.colsum + (tok0 + k0) / RB * ld + h * DH;

@@ -1,10 +1,10 @@
-"""What the fused attention keeps in 32 bits: probabilities that sum to one however large the scores are."""
+"""What the fused attention keeps in 32 bits: probabilities that sum to one however large the scores are, and the row dots of its backward."""
 import numpy as np
 import pytest
 import torch
 
 import hdet_inputs as I
-from harness import check_bf16_tensor
+from harness import check_bf16_tensor, norm_err
 from oracle import hdet_oracle as O
 from test_gpu_transformer import TfRun, base
 
@@ -59,4 +59,31 @@ def test_probabilities_sum_to_one_at_large_scores(seq, size):
         for name in want:                                   # (the gradients of the queries and keys are sums that cancel)
             rows = slice(2 * d, None) if name in ("w_qkv.0", "b_qkv.0") else slice(None)
             check_bf16_tensor(got[name][rows], want[name][rows], 4e-2, ("large scores", seq, size, r, name))
+    run.close()
+
+
+@pytest.mark.parametrize("seq", [128, 448, 512])
+def test_row_dots_keep_32_bits_of_the_output(seq):
+    """All scores zero and all keys one vector: the gradient of the queries is that vector times the sum of ds over the row's keys, which is zero but for
+    what p, ds and the row's dot were rounded to.  Values of +-8 and a hundredth of that, in pairs that the output projection sees as one: the dots are
+    sums of large terms that cancel, and one from 16 bits of the attention's output makes that gradient several times what the rounding of ds does."""
+    d = 64
+    cfg = dict(n_blocks=1, d_model=d, n_heads=1, d_ff=64, seq_len=seq, vocab=40)
+
+    def large_values(par):
+        par["w_qkv.0"][:2 * d] = 0.0
+        par["b_qkv.0"][:d] = 0.0
+        par["b_qkv.0"][d:2 * d] = 1.0
+        par["b_qkv.0"][2 * d:] = np.where(np.arange(d) % 2 == 0, 8.0, -8.0)
+        par["w_qkv.0"][2 * d:] *= 0.1
+        par["w_o.0"][:, 1::2] = par["w_o.0"][:, 0::2]
+
+    run = run_with(cfg, 2, large_values)
+    ids, tgt, gl = run.forward_backward(1)
+    losses, grads = run.oracle_grads(run.orc.theta, ids, tgt, 1)
+    assert np.max(np.abs(gl - losses)) <= 1e-2
+    g_dev = run.g.cpu().numpy()[:, :run.P]
+    for r in range(2):
+        got, want = (gradients(cfg, g)["w_qkv.0"][:d] for g in (g_dev[r], grads[r]))
+        assert norm_err(got, want) <= 0.3
     run.close()
