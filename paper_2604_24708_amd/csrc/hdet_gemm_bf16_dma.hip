@@ -10,10 +10,12 @@
 // or absent and C can be written 4 columns at a time; everything else takes the other kernel.
 //
 // Design
-//  * Block tile TM x TN, WGM x WGN wavefronts, each owning (TM/WGM) x 64 as 16x16 blocks of v_mfma_f32_16x16x32_bf16.  On random
+//  * Block tile TM x TN, WGM x WGN wavefronts, each owning (TM/WGM) x 64.  K step TK = 32 or 64, NST LDS stages of one K step each.
+//    Kernels with K steps of 64 work on 16x16 blocks of v_mfma_f32_16x16x32_bf16: on random
 //    data the chip holds 2.03 PFLOP/s of these from registers, 1.82 of the 32x32x16 form, at whose larger blocks every accumulator
-//    is read and written twice as often per operation; the sums of a product are the same to the bit.  K step TK = 32 or 64, NST LDS
-//    stages of one K step each.
+//    is read and written twice as often per operation.  With K steps of 32 a 16x16x32 block is the whole step, and its fragments are not read
+//    while others multiply: those kernels keep 32x32x16, two sub-steps (weight gradients 3072 x 1024, K = 4096, 8 items 185 us, 205 with
+//    16x16x32; K = 2048 94 and 101; gradients through GELU 4096 x 8192, K = 1024, 8 items 691 and 698).  The sums are the same to the bit.
 //  * LDS-direct loads: one instruction moves 64 lanes x 16 bytes into 1 KiB of consecutive LDS.
 //    Which global chunk a lane fetches is chosen so that the tile lands already swizzled:
 //      - operand contiguous along k: tile [row][TK], the 16-byte chunks of a row XOR-permuted by
@@ -27,10 +29,9 @@
 //  * Pipeline: the stage NST K steps ahead is requested as soon as its buffer is free.  One
 //    barrier per K step, placed before the last MFMA sub-step: by then every wavefront has read
 //    the whole current stage into registers, so the stage is refilled at once, and the next
-//    stage has landed (s_waitcnt vmcnt leaves the younger stages in flight).  With K steps of 64, fragments are
+//    stage has landed (s_waitcnt vmcnt leaves the younger stages in flight).  Fragments are
 //    double-buffered in registers across sub-steps, LDS reads and load issue are dealt out
-//    between the MFMAs, and the order is pinned with sched_barrier; with K steps of 32 the second block of the CU
-//    runs while one reads its fragments.  The 256 x 256 tile has a kernel of its own (hdet_bgemm_alt_kernel).
+//    between the MFMAs, and the order is pinned with sched_barrier.  The 256 x 256 tile has a kernel of its own (hdet_bgemm_alt_kernel).
 //  * Epilogue through LDS: accumulators (lane = row, 4 consecutive columns) go through a
 //    per-wavefront staging strip so that every global store writes whole rows, 4 columns per
 //    lane; bias / ReLU / ReLU-gate / bf16 rounding (hardware round-to-nearest-even) fused.
@@ -46,6 +47,7 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float f16v __attribute__((ext_vector_type(16)));
 typedef short s4 __attribute__((ext_vector_type(4)));
 typedef short s8 __attribute__((ext_vector_type(8)));
 typedef hdet_rsrc i4;
@@ -58,6 +60,22 @@ __device__ __forceinline__ unsigned short f2bf(float x) {      // round to neare
 }
 __device__ __forceinline__ float bf2f(unsigned short h) { return __uint_as_float((unsigned)h << 16); }
 
+// The MFMA of a tile kernel, BLK x BLK with SK of the contraction.  Rows of C are the second operand's, so that a lane's accumulators come in
+// fours of consecutive columns of one row.
+template <int BLK> struct block;
+template <> struct block<16> {
+  static constexpr int SK = 32;
+  typedef f4 acc;
+  static __device__ __forceinline__ acc multiply(bf16x8 a, bf16x8 b, acc c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, a, c, 0, 0, 0); }
+};
+template <> struct block<32> {
+  static constexpr int SK = 16;
+  typedef f16v acc;
+  static __device__ __forceinline__ acc multiply(bf16x8 a, bf16x8 b, acc c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, c, 0, 0, 0); }
+};
+// ... by K step (see the top of the file)
+template <int TK> constexpr int kBlock = TK == 32 ? 32 : 16;
+
 // One operand tile: ROWS rows of the output dimension x TK of the contraction.
 // KMAJOR: element (row, k) at src[row * ld + k], LDS tile [row][TK];
 // otherwise at src[k * ld + row], LDS tile [k][ROWS].
@@ -69,10 +87,10 @@ struct lds_tile {
   static_assert(KMAJOR || ROWS >= 128, "the chunk permutation of a [k][ROWS] tile needs at least 16 chunks per k-row");
   static_assert(TK == 32 || TK == 64, "K step");
   // chunk permutation inside a [row][TK] row: 64-byte rows by row / 4, 128-byte rows by row / 2
-  // (four times two bits: 0, 2, 3, 1 -- a 128-bit read serves lanes 0-3, 12-15 and 20-27 together, then the others)
-  static __device__ __forceinline__ int swz(int r) { return TK == 32 ? (0x78 >> ((r >> 1) & 6)) & 3 : (r >> 1) & 7; }
-  // ... of a [k][ROWS] row: a 32-lane half of the transposing read takes 32 bytes of each of 8 k-rows (k mod 4 and k / 8 differ)
-  static __device__ __forceinline__ int swz_k(int k) { return ((k & 3) << 2) | (((k >> 3) & 1) << 1); }
+  static __device__ __forceinline__ int swz(int r) { return TK == 32 ? (r >> 2) & 3 : (r >> 1) & 7; }
+  // ... of a [k][ROWS] row: a 32-lane half of the transposing read takes 64 bytes of each of 4 k-rows, or (16 x 16 blocks) 32 bytes of
+  // each of 8 (k mod 4 and k / 8 differ)
+  static __device__ __forceinline__ int swz_k(int k) { return ((k & 3) << 2) | (kBlock<TK> == 16 ? ((k >> 3) & 1) << 1 : 0); }
   uint32_t off[NI];     // byte offset of this lane's chunk at K step 0, or kAbsent
   int kofs[NI];         // k index of the chunk inside a K step
   uint32_t kstep;       // bytes per K step
@@ -98,18 +116,19 @@ struct lds_tile {
     const uint32_t v = (kt * TK + kofs[i] < kdim) ? off[i] + (uint32_t)kt * kstep : kAbsent;
     lds_load16(rsrc, tile_addr + (i * THREADS + wave * 64) * 16, v);
   }
-  // MFMA 16x16x32 operand fragment: lane l gets (row = r0 + l % 16, k = ks + 8 * (l / 16) + 0..7).
+  // MFMA operand fragment: lane l gets (row = r0 + l % BLK, k = ks + 8 * (l / BLK) + 0..7).
   static __device__ __forceinline__ bf16x8 fragment(const uint16_t* tile, int r0, int ks, int lane) {
+    constexpr int BLK = kBlock<TK>;
     if (KMAJOR) {
-      const int row = r0 + (lane & 15);
-      const int chunk = ((ks >> 3) + (lane >> 4)) ^ swz(row);
+      const int row = r0 + lane % BLK;
+      const int chunk = ((ks >> 3) + lane / BLK) ^ swz(row);
       return *reinterpret_cast<const bf16x8*>(tile + row * TK + (chunk << 3));
     }
     // Transposing read: within a 16-lane group, lane p points at the 4 elements
     // (k = kb + p / 4, rows r0 + 4 * (p % 4) .. + 3) and lane i receives (k = kb .. kb + 3, row r0 + i).
     const int p = lane & 15;
-    const int row = r0 + ((p & 3) << 2);
-    const int k = ks + ((lane >> 4) << 3) + (p >> 2);
+    const int row = r0 + (lane & (BLK - 16)) + ((p & 3) << 2);
+    const int k = ks + ((lane / BLK) << 3) + (p >> 2);
     const uint16_t* q = tile + k * ROWS + (((row >> 3) ^ swz_k(k)) << 3) + (row & 7);
     const s4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s4 __attribute__((address_space(3)))*)(q));
     const s4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s4 __attribute__((address_space(3)))*)(q + 4 * ROWS));
@@ -148,9 +167,9 @@ __device__ __forceinline__ tile_id tile_of_block(int tile_group) {
 // shared by four wavefronts, whose accesses are whole 1 KiB rows, measured the same or, with the update, 6 % slower.)
 // LDS serves one wavefront's accesses in order, so a strip needs no barrier.
 // STREAM: results are written past the L2 (stream_result).  `S`: the stage buffers, which no wavefront reads or loads into any more.
-template <int EPI, int TM, int TN, int WGM, int WGN, bool STREAM, int LDS_BYTES>
-__device__ __forceinline__ void store_tile(const hdet_bgemm_args& g, const f4 (&acc)[TM / WGM / 16][TN / WGN / 16], uint16_t* S, int bx, int by, int z,
-                                           int64_t c_base, int tid) {
+template <int EPI, int TM, int TN, int WGM, int WGN, int BLK, bool STREAM, int LDS_BYTES>
+__device__ __forceinline__ void store_tile(const hdet_bgemm_args& g, const typename block<BLK>::acc (&acc)[TM / WGM / BLK][TN / WGN / BLK], uint16_t* S,
+                                           int bx, int by, int z, int64_t c_base, int tid) {
   constexpr int THREADS = 64 * WGM * WGN;
   constexpr int SR = 32, CW = 64, EP = CW + 4, LPR = CW / 4, RPI = 64 / LPR;      // pitch EP: both sides free of bank conflicts
   constexpr int NIT = SR / RPI, NSTRIP = TM / WGM / SR;
@@ -221,12 +240,16 @@ __device__ __forceinline__ void store_tile(const hdet_bgemm_args& g, const f4 (&
   for (int strip = 0; strip < NSTRIP; ++strip) {
     if (kGate && strip + 1 < NSTRIP) fetch_gate(strip + 1, gate[(strip + 1) & 1]);
     if (kUpd) fetch_upd(strip);
-    // accumulator element e of lane l is C(row, col) with row = l % 16, col = (l / 16) * 4 + e inside its 16 x 16 block
+    // accumulator element e of lane l is C(row, col) with row = l % BLK, col = (e / 4) * 8 + (l / BLK) * 4 + e % 4 inside its block
 #pragma unroll
-    for (int ib = 0; ib < SR / 16; ++ib)
+    for (int ib = 0; ib < SR / BLK; ++ib)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        *reinterpret_cast<f4*>(stg + (ib * 16 + (lane & 15)) * EP + j * 16 + (lane >> 4) * 4) = acc[strip * (SR / 16) + ib][j];
+      for (int j = 0; j < CW / BLK; ++j) {
+        const typename block<BLK>::acc& x = acc[strip * (SR / BLK) + ib][j];
+#pragma unroll
+        for (int e = 0; e < BLK * BLK / 64; e += 4)
+          *reinterpret_cast<f4*>(stg + (ib * BLK + lane % BLK) * EP + j * BLK + e * 2 + (lane / BLK) * 4) = f4{x[e], x[e + 1], x[e + 2], x[e + 3]};
+      }
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
       f4 v = *reinterpret_cast<const f4*>(stg + (it * RPI + lr) * EP + lc);
@@ -362,97 +385,74 @@ void hdet_bgemm_dma_kernel(const hdet_bgemm_args g) {
   la.init(m0, g.m, g.lda, tid);
   lb.init(n0, g.n, g.ldb, tid);
 
-  constexpr int MB = TM / WGM / 16, NB = TN / WGN / 16;
-  f4 acc[MB][NB];
+  constexpr int BLK = kBlock<TK>, SK = block<BLK>::SK, MB = TM / WGM / BLK, NB = TN / WGN / BLK;
+  typename block<BLK>::acc acc[MB][NB];
 #pragma unroll
   for (int i = 0; i < MB; ++i)
 #pragma unroll
-    for (int j = 0; j < NB; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int e = 0; e < BLK * BLK / 64; ++e) acc[i][j][e] = 0.f;
 
   const int nk = (g.k + TK - 1) / TK;
 #define STAGE_PTR(s) (S + (s) * STAGE)
 #define STAGE_ADDR(s) (s_addr + (s) * STAGE * 2)
-  auto request = [&](int s, int kt) {
+  // K steps 0 .. NST-1 are requested up front; steps past the end load nothing (all chunks absent)
 #pragma unroll
-    for (int i = 0; i < ta::NI; ++i) la.issue_one(i, ra, STAGE_ADDR(s), kt, g.k, wave);
+  for (int s = 0; s < NST; ++s) {
 #pragma unroll
-    for (int i = 0; i < tb::NI; ++i) lb.issue_one(i, rb, STAGE_ADDR(s) + TM * TK * 2, kt, g.k, wave);
-  };
-  // rows of C are the second operand's, so that a lane's four accumulators are consecutive columns
-  auto multiply = [&](const bf16x8* a, const bf16x8* b, int q) {
-    acc[q / NB][q % NB] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[q % NB], a[q / NB], acc[q / NB][q % NB], 0, 0, 0);
-  };
-  if constexpr (TK == 32) {
-    bf16x8 fa[MB], fb[NB];
+    for (int i = 0; i < ta::NI; ++i) la.issue_one(i, ra, STAGE_ADDR(s), s, g.k, wave);
 #pragma unroll
-    for (int s = 0; s < NST - 1; ++s) request(s, s);
-    for (int kt0 = 0; kt0 < nk; kt0 += NST) {
-#pragma unroll
-      for (int s = 0; s < NST; ++s) {
-        const int kt = kt0 + s;
-        if (kt >= nk) break;
-        wait_and_barrier<(NST - 2) * LPT>();
-#pragma unroll
-        for (int i = 0; i < MB; ++i) fa[i] = ta::fragment(STAGE_PTR(s), wm + i * 16, 0, lane);
-#pragma unroll
-        for (int j = 0; j < NB; ++j) fb[j] = tb::fragment(STAGE_PTR(s) + TM * TK, wn + j * 16, 0, lane);
-        request((s + NST - 1) % NST, kt + NST - 1);
-#pragma unroll
-        for (int q = 0; q < MB * NB; ++q) multiply(fa, fb, q);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-  } else {
-#pragma unroll
-    for (int s = 0; s < NST; ++s) request(s, s);
-    wait_and_barrier<(NST - 1) * LPT>();
+    for (int i = 0; i < tb::NI; ++i) lb.issue_one(i, rb, STAGE_ADDR(s) + TM * TK * 2, s, g.k, wave);
+  }
+  wait_and_barrier<(NST - 1) * LPT>();
 
-    // Fragments are double-buffered in registers over the NSS = TK / 32 MFMA sub-steps of a K step:
-    // while the MFMAs of sub-step ss run on fa/fb[ss & 1], the fragments of the next sub-step (of
-    // the next stage after the last one) are read into the other set.
-    constexpr int NSS = TK / 32, NM = MB * NB, NR = MB + NB;
-    constexpr int IPA = (NR + NM - 1) / NM, IPB = (NR + LPT + NM - 1) / NM;
-    bf16x8 fa[2][MB], fb[2][NB];
-    auto read_frag = [&](bf16x8* a, bf16x8* b, const uint16_t* st, int ks, int idx) {
-      // order: a[0], b[0..], a[1..] -- what the first MFMAs of the next sub-step need first
-      if (idx == 0) a[0] = ta::fragment(st, wm, ks, lane);
-      else if (idx <= NB) b[idx - 1] = tb::fragment(st + TM * TK, wn + (idx - 1) * 16, ks, lane);
-      else if (idx < NR) a[idx - NB] = ta::fragment(st, wm + (idx - NB) * 16, ks, lane);
-    };
+  // Fragments are double-buffered in registers over the NSS = TK / SK MFMA sub-steps of a K step:
+  // while the MFMAs of sub-step ss run on fa/fb[ss & 1], the fragments of the next sub-step (of
+  // the next stage after the last one) are read into the other set.
+  constexpr int NSS = TK / SK, NM = MB * NB, NR = MB + NB;
+  constexpr int IPA = (NR + NM - 1) / NM, IPB = (NR + LPT + NM - 1) / NM;
+  bf16x8 fa[2][MB], fb[2][NB];
+  auto read_frag = [&](bf16x8* a, bf16x8* b, const uint16_t* st, int ks, int idx) {
+    // order: a[0], b[0..], a[1..] -- what the first MFMAs of the next sub-step need first
+    if (idx == 0) a[0] = ta::fragment(st, wm, ks, lane);
+    else if (idx <= NB) b[idx - 1] = tb::fragment(st + TM * TK, wn + (idx - 1) * BLK, ks, lane);
+    else if (idx < NR) a[idx - NB] = ta::fragment(st, wm + (idx - NB) * BLK, ks, lane);
+  };
+  auto multiply = [&](int set, int q) { acc[q / NB][q % NB] = block<BLK>::multiply(fa[set][q / NB], fb[set][q % NB], acc[q / NB][q % NB]); };
 #pragma unroll
-    for (int idx = 0; idx < NR; ++idx) read_frag(fa[0], fb[0], S, 0, idx);
+  for (int idx = 0; idx < NR; ++idx) read_frag(fa[0], fb[0], S, 0, idx);
 
-    for (int kt0 = 0; kt0 < nk; kt0 += NST) {
+  for (int kt0 = 0; kt0 < nk; kt0 += NST) {
 #pragma unroll
-      for (int s = 0; s < NST; ++s) {
-        const int kt = kt0 + s;
-        if (kt >= nk) break;
-        const uint16_t* cur = STAGE_PTR(s);
-        const uint16_t* nxt = STAGE_PTR((s + 1) % NST);
+    for (int s = 0; s < NST; ++s) {
+      const int kt = kt0 + s;
+      if (kt >= nk) break;
+      const uint16_t* cur = STAGE_PTR(s);
+      const uint16_t* nxt = STAGE_PTR((s + 1) % NST);
 #pragma unroll
-        for (int ss = 0; ss < NSS - 1; ++ss) {
-#pragma unroll
-          for (int q = 0; q < NM; ++q) {
-            multiply(fa[ss & 1], fb[ss & 1], q);
-#pragma unroll
-            for (int u = 0; u < IPA; ++u) read_frag(fa[(ss + 1) & 1], fb[(ss + 1) & 1], cur, (ss + 1) * 32, q * IPA + u);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        }
-        // every wavefront has read all of stage `cur`; stage `nxt` (K step kt + 1) has landed
-        wait_and_barrier<(NST - 2) * LPT>();
+      for (int ss = 0; ss < NSS - 1; ++ss) {
 #pragma unroll
         for (int q = 0; q < NM; ++q) {
-          multiply(fa[(NSS - 1) & 1], fb[(NSS - 1) & 1], q);
+          multiply(ss & 1, q);
 #pragma unroll
-          for (int u = 0; u < IPB; ++u) {
-            const int it = q * IPB + u;
-            if (it < ta::NI) la.issue_one(it, ra, STAGE_ADDR(s), kt + NST, g.k, wave);
-            else if (it < LPT) lb.issue_one(it - ta::NI, rb, STAGE_ADDR(s) + TM * TK * 2, kt + NST, g.k, wave);
-            else read_frag(fa[0], fb[0], nxt, 0, it - LPT);
-          }
+          for (int u = 0; u < IPA; ++u) read_frag(fa[(ss + 1) & 1], fb[(ss + 1) & 1], cur, (ss + 1) * SK, q * IPA + u);
           __builtin_amdgcn_sched_barrier(0);
         }
+      }
+      // every wavefront has read all of stage `cur`; stage `nxt` (K step kt + 1) has landed
+      wait_and_barrier<(NST - 2) * LPT>();
+#pragma unroll
+      for (int q = 0; q < NM; ++q) {
+        multiply((NSS - 1) & 1, q);
+#pragma unroll
+        for (int u = 0; u < IPB; ++u) {
+          const int it = q * IPB + u;
+          if (it < ta::NI) la.issue_one(it, ra, STAGE_ADDR(s), kt + NST, g.k, wave);
+          else if (it < LPT) lb.issue_one(it - ta::NI, rb, STAGE_ADDR(s) + TM * TK * 2, kt + NST, g.k, wave);
+          else read_frag(fa[0], fb[0], nxt, 0, it - LPT);
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
@@ -462,7 +462,7 @@ void hdet_bgemm_dma_kernel(const hdet_bgemm_args g) {
   // they become the staging area of the epilogue
   wait_and_barrier<0>();
 
-  store_tile<EPI, TM, TN, WGM, WGN, STREAM, NST * STAGE * 2>(g, acc, S, bx, by, z, c_base, tid);
+  store_tile<EPI, TM, TN, WGM, WGN, BLK, STREAM, NST * STAGE * 2>(g, acc, S, bx, by, z, c_base, tid);
 }
 
 namespace {
@@ -609,7 +609,7 @@ __global__ __launch_bounds__(512, 2) void hdet_bgemm_alt_kernel(const hdet_bgemm
   }
   if (wave < 4) meet();
   wait_and_barrier<0>();
-  store_tile<EPI, TM, TN, WGM, WGN, STREAM, 8 * HALF * 2>(g, acc, S, id.bx, id.by, bi.z0, c_base, tid);
+  store_tile<EPI, TM, TN, WGM, WGN, 16, STREAM, 8 * HALF * 2>(g, acc, S, id.bx, id.by, bi.z0, c_base, tid);
 }
 
 namespace {
