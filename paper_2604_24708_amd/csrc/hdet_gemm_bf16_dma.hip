@@ -680,11 +680,6 @@ bool stream_result(const hdet_bgemm_args& g, int epi, int batch) {
 // epilogue takes as long as 1024 of K: 719 against 690 us for 8192 x 4096 x 8 in a step), where the model flatters it.
 struct tile_shape { int tm, tn, per_cu; float base, share, slope, least; };
 constexpr tile_shape kAlternating = {256, 256, 1, 1.6f, 1.f, 19.f, 1.f};       // hdet_bgemm_alt_kernel
-// ... of weight gradients, which beyond K = 4096 take longer than the sweeps below it say.  Between one round of 256 x 256 tiles and one and a half
-// the pair tiles are the faster ones at every K from 2048 on; a slope of 19 gets that wrong from 6144 on.  us in a step, alternating / pair:
-//   3072 x 1024, K = 8192, 6, 7, 8 items (288, 336, 384 tiles) 350 / 319, 364 / 337, 413 / 375;  8 items, K = 6144 297 / 279, K = 12288 536 / 518;
-//   2304 x 2048, K = 8192, 4 items (288) 336 / 307;  6144 x 2048, K = 6144, 2 items (384) 277 / 257
-constexpr tile_shape kAlternatingWgrad = {256, 256, 1, 1.6f, 1.f, 21.f, 1.f};
 constexpr tile_shape kPair = {256, 128, 2, 3.6f, 0.53f, 32.f, 0.52f};          // K step 32, three stages, two blocks a CU
 constexpr tile_shape kPairWgrad = {256, 128, 2, 3.6f, 0.53f, 27.3f, 0.52f};
 constexpr tile_shape kLong = {256, 128, 1, 2.35f, 0.51f, 13.6f, 1.f};          // K step 64, three stages
@@ -705,15 +700,19 @@ hipError_t launch_shape(const hdet_bgemm_args& g, int batch, hipStream_t s) {
   constexpr bool wgrad = !AK && !BK, update = EPI == HDET_EPI_ADAMW;
   const int cus = compute_units();
   const float epi = kEpiTime<EPI>;
-  auto time_of = [&](const tile_shape& t) {
+  auto time_of = [&](const tile_shape& t, float more_k = 0.f) {
     const int64_t tiles = (int64_t)((g.m + t.tm - 1) / t.tm) * ((g.n + t.tn - 1) / t.tn) * batch;
     const float rounds = (float)((tiles + cus - 1) / cus) / t.per_cu;
-    return t.base + (rounds > t.least ? rounds : t.least) * (epi * t.share + t.slope * 1e-3f * g.k);
+    return t.base + (rounds > t.least ? rounds : t.least) * (epi * t.share + t.slope * 1e-3f * (g.k + more_k));
   };
   // the alternating kernel leaves the far edge of its tiles to the bounds of the buffer: no offset of a tile may wrap
   const int64_t a_ext = ((int64_t)(AK ? g.m : g.k) + 256) * g.lda * 2, b_ext = ((int64_t)(BK ? g.n : g.k) + 256) * g.ldb * 2;
   const bool alternating = g.k >= (update ? 1 : EPI == HDET_EPI_GELUGRAD_BF16 ? 2048 : wgrad ? 1024 : 512) && a_ext < (int64_t)1 << 31 && b_ext < (int64_t)1 << 31;
-  const float t_alt = alternating ? time_of(wgrad && !update ? kAlternatingWgrad : kAlternating) : 3e38f;
+  // Weight gradients in it take longer beyond K = 4096 than the sweeps up to there say: between one round of 256 x 256 tiles and one and a half,
+  // the pair tiles stay the faster ones.  us in a step, alternating / pair:  3072 x 1024, K = 8192, 6, 7, 8 items (288, 336, 384 tiles) 350 / 319,
+  // 364 / 337, 413 / 375;  8 items, K = 6144 297 / 279, K = 12288 536 / 518;  2304 x 2048, K = 8192, 4 items (288) 336 / 307;  6144 x 2048,
+  // K = 6144, 2 items (384) 277 / 257.  With every K beyond 4096 counted 1.2 times the line lies there.
+  const float t_alt = alternating ? time_of(kAlternating, wgrad && !update && g.k > 4096 ? 0.2f * (g.k - 4096) : 0.f) : 3e38f;
   const bool stream = kAlwaysStream<EPI> || stream_result(g, EPI, batch);
   auto launch = [&](auto kernel, const tile_shape& t, int threads) {
     const dim3 grid((g.n + t.tn - 1) / t.tn, (g.m + t.tm - 1) / t.tm, batch);
