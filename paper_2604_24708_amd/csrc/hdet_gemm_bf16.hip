@@ -109,6 +109,20 @@ struct operand {
   static constexpr int NCH = ROWS * 4 / THREADS;   // 8-element chunks per thread and K step
   static constexpr int RCH = ROWS / 8;         // chunks per k-row of a [k][row] tile
   us8 reg[NCH];
+  // K step that lies inside the matrix and is not its last one: rows beyond `rows` repeat others
+  __device__ __forceinline__ void fetch(const uint16_t* src, int64_t ld, int row0, int rows, int k0, bool odd, int tid) {
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) {
+      const int c = tid + i * THREADS;
+      if (KMAJOR) {
+        const int row = row0 + (c >> 2);
+        reg[i] = load8_any(src, (int64_t)(row < rows ? row : rows - 1) * ld + k0 + ((c & 3) << 3), odd);
+      } else {
+        const int row = row0 + ((c % RCH) << 3);
+        reg[i] = load8_any(src, (int64_t)(k0 + c / RCH) * ld + (row < rows ? row : row0), odd);
+      }
+    }
+  }
   // last K step: zeros beyond the contraction, nothing beyond the operand's extent is read
   __device__ __forceinline__ void fetch_last(const uint16_t* src, int64_t ld, int row0, int rows, int k0, int kdim, bool odd, int tid) {
     const int64_t extent = (int64_t)((KMAJOR ? rows : kdim) - 1) * ld + (KMAJOR ? kdim : rows);
@@ -233,10 +247,10 @@ __device__ __forceinline__ bf16x8 ones() {
 }
 
 // WT x WT: 32x32 MFMA blocks per wavefront; 2 x 2 wavefronts per block, block tile (64 WT) x (64 WT).
-// PIECES: the contraction is summed in that many pieces, each from zero, and the pieces are added in ascending order (launch_general).
-template <bool A_KMAJOR, bool B_KMAJOR, int EPI, int WT, int PIECES = 1>
+// DEPTH: K steps whose loads are in flight, 4 or 1 (one_step says when).  PIECES: the contraction is summed in that many pieces, each from zero, and the pieces are added in ascending order (launch_general).
+template <bool A_KMAJOR, bool B_KMAJOR, int EPI, int WT, int DEPTH, int PIECES = 1>
 __global__ __launch_bounds__(256, 2) void hdet_bgemm_kernel(const hdet_bgemm_args g) {
-  constexpr int TM = 64 * WT, TN = TM, THREADS = 256, DEPTH = 4;
+  constexpr int TM = 64 * WT, TN = TM, THREADS = 256;
   __shared__ __attribute__((aligned(16))) uint16_t As[2][tile_elems(TM)];
   __shared__ __attribute__((aligned(16))) uint16_t Bs[2][tile_elems(TN)];
   // Workgroups are dealt round-robin to the 8 XCDs (each with its own L2) in launch order.
@@ -335,80 +349,110 @@ __global__ __launch_bounds__(256, 2) void hdet_bgemm_kernel(const hdet_bgemm_arg
       }
     }
   };
-  // The last K step, which alone looks at the extent of anything, is requested first and stays in registers until its turn.
-  ta la;
-  tb lb;
-  la.fetch_last(A, g.lda, m0, g.m, (nk - 1) * TK, g.k, a_odd, tid);
-  lb.fetch_last(B, g.ldb, n0, g.n, (nk - 1) * TK, g.k, b_odd, tid);
   // a chunk at the end of a k-row reads on into the next one, which has to be long enough for that
   const bool roomy = (A_KMAJOR || g.lda >= 8) && (B_KMAJOR || g.ldb >= 8);
-  // DEPTH register stages: the loads of a K step are requested DEPTH steps before it is written to LDS, one step before its
-  // MFMAs; two LDS buffers, one barrier a step.
-  auto pipelined = [&](auto odd_) {
-    constexpr bool ODD = decltype(odd_)::value;
-    const int nf = nk - 1;
-    chunk_stream<A_KMAJOR, TM, THREADS, ODD> ca;
-    chunk_stream<B_KMAJOR, TN, THREADS, ODD> cb;
-    ca.init(A, g.lda, m0, g.m, tid);
-    cb.init(B, g.ldb, n0, g.n, tid);
-    typename decltype(ca)::stage ra[DEPTH];
-    typename decltype(cb)::stage rb[DEPTH];
-    auto request = [&](int s, int kt) {            // past the end: the last whole step again, not used
-      const int k = kt < nf ? kt : nf - 1;
-      ca.request(ra[s], k);
-      cb.request(rb[s], k);
+  if constexpr (DEPTH == 1) {
+    // the loads of the next K step are in flight during the MFMAs of this one; other blocks on the CU cover the rest of their latency
+    ta oa;
+    tb ob;
+    auto request = [&](int kt) {
+      if (kt + 1 < nk && roomy) {
+        oa.fetch(A, g.lda, m0, g.m, kt * TK, a_odd, tid);
+        ob.fetch(B, g.ldb, n0, g.n, kt * TK, b_odd, tid);
+      } else {
+        oa.fetch_last(A, g.lda, m0, g.m, kt * TK, g.k, a_odd, tid);
+        ob.fetch_last(B, g.ldb, n0, g.n, kt * TK, g.k, b_odd, tid);
+      }
     };
-    auto commit = [&](int s) {
-      ca.commit(ra[s], As[s & 1], tid);
-      cb.commit(rb[s], Bs[s & 1], tid);
+    auto commit = [&](int buf) {
+      oa.commit(As[buf], tid);
+      ob.commit(Bs[buf], tid);
     };
-    auto commit_last = [&](int s) {
-      la.commit(As[s & 1], tid);
-      lb.commit(Bs[s & 1], tid);
-    };
-    if (nf > 0) {
-#pragma unroll
-      for (int s = 0; s < DEPTH; ++s) request(s, s);
-      commit(0);
-      request(0, DEPTH);
-    } else {
-      commit_last(0);
-    }
+    request(0);
+    commit(0);
     __syncthreads();
-    int kt0 = 0;
-    for (; kt0 + DEPTH < nf; kt0 += DEPTH) {        // no branch inside: it would have the compiler wait for every load
+    for (int kt = 0; kt < nk; ++kt) {
+      if (kt + 1 < nk) request(kt + 1);
+      __builtin_amdgcn_sched_barrier(0);     // keep the loads ahead of the MFMAs ...
+      multiply(kt & 1);
+      __builtin_amdgcn_sched_barrier(0);     // ... and every use of the loaded data behind them
+      commit((kt & 1) ^ 1);                  // last read before the previous barrier
+      __syncthreads();
+    }
+  } else {
+    // The last K step, which alone looks at the extent of anything, is requested first and stays in registers until its turn.
+    ta la;
+    tb lb;
+    la.fetch_last(A, g.lda, m0, g.m, (nk - 1) * TK, g.k, a_odd, tid);
+    lb.fetch_last(B, g.ldb, n0, g.n, (nk - 1) * TK, g.k, b_odd, tid);
+    // DEPTH register stages: the loads of a K step are requested DEPTH steps before it is written to LDS, one step before its
+    // MFMAs; two LDS buffers, one barrier a step.
+    auto pipelined = [&](auto odd_) {
+      constexpr bool ODD = decltype(odd_)::value;
+      const int nf = nk - 1;
+      chunk_stream<A_KMAJOR, TM, THREADS, ODD> ca;
+      chunk_stream<B_KMAJOR, TN, THREADS, ODD> cb;
+      ca.init(A, g.lda, m0, g.m, tid);
+      cb.init(B, g.ldb, n0, g.n, tid);
+      typename decltype(ca)::stage ra[DEPTH];
+      typename decltype(cb)::stage rb[DEPTH];
+      auto request = [&](int s, int kt) {            // past the end: the last whole step again, not used
+        const int k = kt < nf ? kt : nf - 1;
+        ca.request(ra[s], k);
+        cb.request(rb[s], k);
+      };
+      auto commit = [&](int s) {
+        ca.commit(ra[s], As[s & 1], tid);
+        cb.commit(rb[s], Bs[s & 1], tid);
+      };
+      auto commit_last = [&](int s) {
+        la.commit(As[s & 1], tid);
+        lb.commit(Bs[s & 1], tid);
+      };
+      if (nf > 0) {
+#pragma unroll
+        for (int s = 0; s < DEPTH; ++s) request(s, s);
+        commit(0);
+        request(0, DEPTH);
+      } else {
+        commit_last(0);
+      }
+      __syncthreads();
+      int kt0 = 0;
+      for (; kt0 + DEPTH < nf; kt0 += DEPTH) {        // no branch inside: it would have the compiler wait for every load
+#pragma unroll
+        for (int s = 0; s < DEPTH; ++s) {
+          multiply(s & 1);
+          commit((s + 1) % DEPTH);                    // last read before the previous barrier
+          request((s + 1) % DEPTH, kt0 + s + 1 + DEPTH);
+          __syncthreads();
+        }
+      }
 #pragma unroll
       for (int s = 0; s < DEPTH; ++s) {
+        if (kt0 + s >= nf) break;
         multiply(s & 1);
-        commit((s + 1) % DEPTH);                    // last read before the previous barrier
-        request((s + 1) % DEPTH, kt0 + s + 1 + DEPTH);
+        if (kt0 + s + 1 < nf) commit((s + 1) % DEPTH);
+        else commit_last((s + 1) % DEPTH);
         __syncthreads();
       }
-    }
-#pragma unroll
-    for (int s = 0; s < DEPTH; ++s) {
-      if (kt0 + s >= nf) break;
-      multiply(s & 1);
-      if (kt0 + s + 1 < nf) commit((s + 1) % DEPTH);
-      else commit_last((s + 1) % DEPTH);
-      __syncthreads();
-    }
-    multiply(nf & 1);
-  };
-  if (roomy) {
-    if (a_odd || b_odd) pipelined(std::true_type{});
-    else pipelined(std::false_type{});
-  } else {
-    for (int kt = 0; kt < nk; ++kt) {
-      ta xa;
-      tb xb;
-      xa.fetch_last(A, g.lda, m0, g.m, kt * TK, g.k, a_odd, tid);
-      xb.fetch_last(B, g.ldb, n0, g.n, kt * TK, g.k, b_odd, tid);
-      if (kt) __syncthreads();
-      xa.commit(As[0], tid);
-      xb.commit(Bs[0], tid);
-      __syncthreads();
-      multiply(0);
+      multiply(nf & 1);
+    };
+    if (roomy) {
+      if (a_odd || b_odd) pipelined(std::true_type{});
+      else pipelined(std::false_type{});
+    } else {
+      for (int kt = 0; kt < nk; ++kt) {
+        ta xa;
+        tb xb;
+        xa.fetch_last(A, g.lda, m0, g.m, kt * TK, g.k, a_odd, tid);
+        xb.fetch_last(B, g.ldb, n0, g.n, kt * TK, g.k, b_odd, tid);
+        if (kt) __syncthreads();
+        xa.commit(As[0], tid);
+        xb.commit(Bs[0], tid);
+        __syncthreads();
+        multiply(0);
+      }
     }
   }
 
@@ -577,22 +621,53 @@ int64_t tiles(const hdet_bgemm_args& g, int batch, int tm, int tn) {
 // zero, which moves single entries of a small batch's gradients by more than their tensor's root mean square.)
 bool few_tiles(const hdet_bgemm_args& g, int batch) { return tiles(g, batch, 64, 64) * 5 < 2 * (int64_t)hdet_compute_units(); }
 
+// Whether the LDS kernel keeps one K step in flight instead of four, which need half again as many registers (4 blocks a CU in 64 x 64 tiles instead
+// of 6, 2 instead of 3 in 128 x 128) and begin a block later.  By who else is there to cover the latency of the loads; chunks at odd elements, whose
+// funnel shift would wait at once, have more of it.  us, one / four in flight, items of one step:
+//   128 x 128, rows of A: even 2184 x 2122, K = 830, 5 items 115 / 133;  3460 x 2682, K = 3238, 6 items 742 / 832;  7600 x 1280 gradient, K = 16,
+//     5 items 104 / 140;  odd 3460 x 3238, K = 137, 6 items 138 / 177;  9326 x 570, K = 309, 6 items 116 / 132;  1508 x 2164, K = 1537, 6 items 235 / 210
+//   128 x 128 weight gradients, even 2880 x 2468, K = 1661, 8 items 387 / 288, odd 2723 x 1277, K = 1599, 6 items 288 / 136
+//   64 x 64 (tiles a CU): 623 x 350, K = 3320, 8 items (1.9) 84 / 56;  351 x 3124, K = 404, 5 items (5.7) 32.7 / 35.7;  1274 x 1949 gradient, K = 896,
+//     odd, 2 items (4.8) 35 / 43;  3034 x 324, K = 1220, 6 items (6.8) 74 / 56;  2056 x 1540 gradient, K = 28, 4 items (12.9) 30 / 36;  weight
+//     gradients, even 404 x 2152, K = 351, 5 items (4.6) 17.2 / 20.4, 1280 x 1812, K = 7600, 5 items (11.3) 532 / 778, odd 1277 x 650, K = 1599,
+//     6 items (5.2) 90 / 62, 856 x 3437, K = 71, 4 items (11.8) 18.5 / 20.1
+// Of 467 products of 122 random networks none but 20 lose more than 6 % by this rule, most of them in 64 x 64 tiles at 9 a CU and more with K from 1800 on
+// (666 x 2025, K = 6626, 8 items 550 / 666), where as many others gain as much.
+bool one_step(const hdet_bgemm_args& g, bool wgrad, int wt, int64_t blocks) {
+  const int64_t cus = hdet_compute_units();
+  const bool odd = ((g.lda | g.ldb | g.a_s[0] | g.a_s[1] | g.a_s[2] | g.b_s[0] | g.b_s[1] | g.b_s[2]) & 1) != 0 ||
+                   ((reinterpret_cast<uintptr_t>(g.a) | reinterpret_cast<uintptr_t>(g.b)) & 3) != 0;
+  if (wt == 2) return !odd || g.k < 768;             // (weight gradients never: launch_general)
+  if (blocks <= 3 * cus) return false;
+  if (g.k < 256) return true;
+  return wgrad ? !odd : blocks > 4 * cus && blocks <= 6 * cus;
+}
+
 // `aligned`: the LDS-direct kernel could form the product as well, whose sums are not split.
 template <bool AK, bool BK, int EPI>
 hipError_t launch_general(const hdet_bgemm_args& g, int batch, bool aligned, hipStream_t s) {
 #define HDET_LDS(WT, ...)                                                                             \
-  hipLaunchKernelGGL((hdet_bgemm_kernel<AK, BK, EPI, WT, ##__VA_ARGS__>), dim3((g.n + 64 * WT - 1) / (64 * WT), (g.m + 64 * WT - 1) / (64 * WT), batch), dim3(256), 0, s, g)
+  hipLaunchKernelGGL((hdet_bgemm_kernel<AK, BK, EPI, WT, __VA_ARGS__>), dim3((g.n + 64 * WT - 1) / (64 * WT), (g.m + 64 * WT - 1) / (64 * WT), batch), dim3(256), 0, s, g)
   const int64_t cus = hdet_compute_units();
   if (few_tiles(g, batch)) hipLaunchKernelGGL((hdet_bgemm_frag_kernel<AK, BK, EPI, 4>), dim3((g.n + 31) / 32, (g.m + 31) / 32, batch), dim3(256), 0, s, g);
   // less than one 64 x 64 block per CU and a long contraction: the sums of K in 8, by one block that walks the eighths one after the
   // other.  (Eight wavefronts of the fragment kernel, an eighth each, give the same bits.  us, so / in this kernel: 96 x 700, K = 1500,
   // 6 items 24.4 / 19.7;  97 x 2111, K = 1501, 3 items 58.7 / 23.3;  64 x 1500, K = 2047, 5 items 46.7 / 35.6;  130 x 1001, K = 4095, 4 items
   // 119 / 45.8;  96 x 1500, K = 1500 gradient, 4 items 32.9 / 19.2.  Summed in one piece 18.9, 25.7, 39.6, 52.7, 16.7: see few_tiles.)
-  else if (!aligned && g.k >= 1024 && tiles(g, batch, 64, 64) < cus) HDET_LDS(1, 8);
+  else if (!aligned && g.k >= 1024 && tiles(g, batch, 64, 64) < cus) HDET_LDS(1, 4, 8);
   // 128 x 128 tiles once there are several rounds of them (256 x 4095, K = 4095, 8 items: 337 | 64 x 64 441; 700 x 1500, K = 576:
   // 14.8 | 10.1; 1788 x 3193, K = 222: 18.4 | 14.7), unless they would be half empty
-  else if (tiles(g, batch, 128, 128) >= 4 * cus && g.m > 64 && g.n > 64) HDET_LDS(2);
-  else HDET_LDS(1);
+  else if (tiles(g, batch, 128, 128) >= 4 * cus && g.m > 64 && g.n > 64) {
+    if constexpr (AK) {
+      if (one_step(g, false, 2, tiles(g, batch, 128, 128))) HDET_LDS(2, 1);
+      else HDET_LDS(2, 4);
+    } else {
+      HDET_LDS(2, 4);
+    }
+  } else {
+    if (one_step(g, !AK, 1, tiles(g, batch, 64, 64))) HDET_LDS(1, 1);
+    else HDET_LDS(1, 4);
+  }
 #undef HDET_LDS
   return hipGetLastError();
 }
