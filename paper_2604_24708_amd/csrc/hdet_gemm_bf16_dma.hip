@@ -707,12 +707,19 @@ hipError_t launch_shape(const hdet_bgemm_args& g, int batch, hipStream_t s) {
   };
   // the alternating kernel leaves the far edge of its tiles to the bounds of the buffer: no offset of a tile may wrap
   const int64_t a_ext = ((int64_t)(AK ? g.m : g.k) + 256) * g.lda * 2, b_ext = ((int64_t)(BK ? g.n : g.k) + 256) * g.ldb * 2;
-  const bool alternating = g.k >= (update ? 1 : EPI == HDET_EPI_GELUGRAD_BF16 ? 2048 : wgrad ? 1024 : 512) && a_ext < (int64_t)1 << 31 && b_ext < (int64_t)1 << 31;
+  const bool fits = a_ext < (int64_t)1 << 31 && b_ext < (int64_t)1 << 31;
+  const bool alternating = g.k >= (update ? 1 : EPI == HDET_EPI_GELUGRAD_BF16 ? 2048 : wgrad ? 1024 : 512) && fits;
   // Weight gradients in it take longer beyond K = 4096 than the sweeps up to there say: between one round of 256 x 256 tiles and one and a half,
   // the pair tiles stay the faster ones.  us in a step, alternating / pair:  3072 x 1024, K = 8192, 6, 7, 8 items (288, 336, 384 tiles) 350 / 319,
   // 364 / 337, 413 / 375;  8 items, K = 6144 297 / 279, K = 12288 536 / 518;  2304 x 2048, K = 8192, 4 items (288) 336 / 307;  6144 x 2048,
   // K = 6144, 2 items (384) 277 / 257.  With every K beyond 4096 counted 1.2 times the line lies there.
   const float t_alt = alternating ? time_of(kAlternating, wgrad && !update && g.k > 4096 ? 0.2f * (g.k - 4096) : 0.f) : 3e38f;
+  // Forward products with fp32 results of three rounds of 256 x 256 tiles and more, from K = 384 on: there the pair tiles fall 20 to 30 % behind their
+  // cost, and the last round counts for less than a whole one.  us, alternating / pair: 8192 x 2048, 4 items, K = 256 68 / 62, K = 384 81 / 99,
+  // K = 448 84 / 111;  12410 x 1296, 7 items (8.04 rounds), K = 256 128 / 115, K = 384 152 / 192, K = 640 212 / 259, K = 768 221 / 289;
+  // 9064 x 3776, 7 items, K = 384 252 / 247, K = 448 276 / 287.  (With ReLU, K = 384: 8192 x 1600, 4 items 65 / 57.)
+  const bool long_logits = AK && BK && (EPI == HDET_EPI_F32 || EPI == HDET_EPI_BIAS_F32) && g.k >= 384 && fits &&
+                           (int64_t)((g.m + 255) / 256) * ((g.n + 255) / 256) * batch >= 3 * (int64_t)cus;
   const bool stream = kAlwaysStream<EPI> || stream_result(g, EPI, batch);
   auto launch = [&](auto kernel, const tile_shape& t, int threads) {
     const dim3 grid((g.n + t.tn - 1) / t.tn, (g.m + t.tm - 1) / t.tm, batch);
@@ -738,7 +745,7 @@ hipError_t launch_shape(const hdet_bgemm_args& g, int batch, hipStream_t s) {
       if (g.k >= 512) HDET_TILE(kDeep, 256, hdet_bgemm_dma_kernel, 128, 128, 2, 2, 4, 64,);
       else HDET_TILE(kSmall, 256, hdet_bgemm_dma_kernel, 128, 128, 2, 2, 2, 64,);
     }
-    else if (t_alt <= t_pair && t_alt <= t_small && t_alt <= t_long) HDET_TILE(kAlternating, 512, hdet_bgemm_alt_kernel, );
+    else if (long_logits || (t_alt <= t_pair && t_alt <= t_small && t_alt <= t_long)) HDET_TILE(kAlternating, 512, hdet_bgemm_alt_kernel, );
     else if (t_pair <= t_small && t_pair <= t_long)
       HDET_TILE(kPair, 512, hdet_bgemm_dma_kernel, 256, 128, 4, 2, 3, 32,);
     else if (t_small <= t_long) HDET_TILE(kSmall, 256, hdet_bgemm_dma_kernel, 128, 128, 2, 2, 2, 64,);
