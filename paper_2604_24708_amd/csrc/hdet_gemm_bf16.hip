@@ -682,16 +682,17 @@ hipError_t hdet_launch_bgemm(const hdet_bgemm_args& g_in, bool a_kmajor, bool b_
   // The LDS-direct kernel where the operands allow it, except for products of few tiles in the epilogues that the general kernels
   // have.  Weight gradients stay: the update that the LDS-direct kernel can apply to them (HDET_EPI_ADAMW) has to see the same sums.
   const bool plain = epi <= HDET_EPI_BIAS_BF16 && !g.colsum && a_kmajor;
-  // Forward products of up to two 64 x 64 tiles a CU, of one row of tiles up to one: their time is the chain of one block, and four times
+  // Forward products of up to two 64 x 64 tiles a CU, of one row or column of tiles up to one: their time is the chain of one block, and four times
   // the blocks of 128 x 128 count for more than loads that pass the registers by.  us, this file's kernel / LDS-direct, operands cold:
   // 200 x 1000, K = 3000, 2 items 23.5 / 42.7;  96 x 704, K = 1504, 6 items 16.8 / 25.4;  96 x 1504, K = 784 16.0 / 19.0;  128 x 1024, K = 1024,
   // 8 items 16.4 / 19.5;  256 x 640, K = 640, 5 items 11.5 / 14.0;  200 x 512, K = 512, 6 items 9.9 / 12.4;  32 x 2048, K = 512, 4 items
   // 10.2 / 9.8;  256 x 2048, K = 256, 3 items 9.8 / 9.8;  beyond 256 tiles 128 x 2048, K = 4096, 6 items 65 / 73;  512 x 512, K = 4096, 6 items
-  // 48 / 64;  256 x 768, K = 1536, 8 items 25 / 29;  256 x 1024, K = 8192, 6 items 91 / 122.  One row of tiles streams each weight once in
-  // either kernel, and beyond a tile a CU the 128 x 128 tiles keep more of it in flight: 64 x 2048, K = 2048, 8 items (256 tiles) 33 / 40;
-  // 64 x 4096, K = 4096, 5 items (320) 83 / 66;  K = 1024, 8 items (512) 30.5 / 26.8;  64 x 2048, K = 1024, 9 items (288) 25.9 / 19.3.
+  // 48 / 64;  256 x 768, K = 1536, 8 items 25 / 29;  256 x 1024, K = 8192, 6 items 91 / 122.  One row or column of tiles reads its long
+  // operand once in either kernel, and beyond a tile a CU the 128 x 128 tiles keep more of it in flight: 64 x 2048, K = 2048, 8 items (256 tiles)
+  // 33 / 40;  64 x 4096, K = 4096, 5 items (320) 83 / 66;  K = 1024, 8 items (512) 30.5 / 26.8;  64 x 2048, K = 1024, 9 items (288) 25.9 / 19.3;
+  // 8192 x 64, K = 1600, 4 items (512) 41.4 / 28.8;  2600 x 64, K = 2560, 8 items (328) 57.6 / 42.4;  3000 x 40, K = 512, 6 items (282) 11.6 / 12.2.
   // (Gradients of such layers stay: 96 x 1500, K = 700 16.4 / 14.5.)
-  const bool small_grid = plain && b_kmajor && tiles(g, batch, 64, 64) <= (g.m > 64 ? 2 : 1) * (int64_t)hdet_compute_units();
+  const bool small_grid = plain && b_kmajor && tiles(g, batch, 64, 64) <= (g.m > 64 && g.n > 64 ? 2 : 1) * (int64_t)hdet_compute_units();
   const bool aligned = hdet_bgemm_dma_eligible(g, a_kmajor, b_kmajor, epi);
   if (aligned && !small_grid && !(plain && few_tiles(g, batch)))
     return hdet_launch_bgemm_dma(g, a_kmajor, b_kmajor, epi, batch, s);
