@@ -10,8 +10,9 @@ import torch
 import paper_2604_24708_amd as H
 
 # (widths, batch, replicas): logits 1500 x 2056 over K = 520 and their weight gradient over K = 1500, 432 and 216 tiles;
-# ReLU outputs 2000 x 2040 over K = 520 and the gradient through them over K = 1000, 256 tiles each
-CASES = [([520, 2056], 1500, 8), ([520, 2040, 1000], 2000, 4)]
+# ReLU outputs 2000 x 2040 over K = 520 and the gradient through them over K = 1000, 256 tiles each;
+# logits 3000 x 2056 over K = 392, 864 tiles
+CASES = [([520, 2056], 1500, 8), ([520, 2040, 1000], 2000, 4), ([392, 2056], 3000, 8)]
 
 
 @pytest.mark.gpu
