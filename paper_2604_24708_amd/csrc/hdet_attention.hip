@@ -5,7 +5,7 @@
 // three kernels that stream 64-row tiles of k, v (or q and the output gradient) through LDS.
 //
 // Arithmetic: products and sums as the unfused path forms them, with bf16 operands and fp32 accumulation:
-//   forward   s = (q k^T) * scale (fp32), causal mask, p = exp(s - log sum exp s), a = bf16(p) v
+//   forward   s = (q k^T) * scale (fp32), causal mask, p = exp(s - max s) / sum exp(s - max s), a = bf16(p) v
 //   backward  dot = sum_c da_c a_c (fp32, a before it was rounded), dp = da v^T - dot,
 //             ds = bf16(bf16(p) dp), dq = (ds k) scale, dk = (ds^T q) scale, dv = bf16(p)^T da
 // with scale = 1 / (sqrt(d_head) tau_r), tau_r the replica's attention temperature when that is
@@ -15,15 +15,16 @@
 // form p by the same operations, hence bit for bit alike, and what rounding took off a (a_rest), so that dot
 // comes from the fp32 a and the backward kernels walk their tiles once.  The dp accumulators start at minus dot.
 //
-// What bounds them: neither pipe is full (matrix cores busy 29 to 42 % of the cycles, VALU 39 to 60 %); a wavefront's chain from its LDS reads
-// over the products and the exponentials to the next products, with the 2 to 4 wavefronts a SIMD holds, and below S = 512 what a block does before
-// and after its few tiles.  us, forward / dq / dk and dv:
-//   8 replicas x 16 sequences x 16 heads, S = 512   199 / 338 / 305 -> 195 / 234 / 265
-//   4 x 2 x 8, S = 2048                             112 / 187 / 143 -> 79 / 79 / 91
-//   8 x 16 x 8, S = 256                             43 / 67 / 55 -> 44 / 56 / 51
-// (with the column sums of sum_columns dq and dk, dv take 2 to 7 % longer)
-// (before: dq walked its tiles twice, tiles went through registers into LDS, results of the paths of a tile were copied together, p was formed from
-// maximum and sum, and every grid had the first order of remap_block.)  Measured and not kept: both 32 x 32 blocks of a
+// What bounds them: neither pipe is full (matrix cores busy 21 to 24 % of the cycles at S = 512, 10 to 14 % at S = 256); a wavefront's chain from
+// its LDS reads over the products and the exponentials to the next products, with the 2 to 4 wavefronts a SIMD holds, and below S = 512 what a block
+// does before and after its few tiles.  us in a step, forward / dq / dk and dv:
+//   8 replicas x 16 sequences x 16 heads, S = 512   198 / 338 / 305 -> 204 / 241 / 293
+//   4 x 2 x 8, S = 2048                             107 / 179 / 134 -> 80 / 81 / 91
+//   8 x 16 x 8, S = 256                             43 / 66 / 54 -> 48 / 57 / 58
+// The backward kernels' include the column sums of sum_columns (1 to 2 % of dq, 3 to 6 % of dk and dv), which were a pass of their own of 77 us at
+// S = 512 and 23 at S = 256.  The forward has become slower up to S = 512: it writes what rounding took off a beside a, for one walk less in dq.
+// (before: dq walked its tiles twice, tiles went through registers into LDS, results of the paths of a tile were copied together, and every grid
+// had the first order of remap_block.)  Measured and not kept: both 32 x 32 blocks of a
 // tile in one basic block, 211 to 256 registers, 20 to 30 % slower in the backward kernels; dk and dv with 3 wavefronts
 // a SIMD, 313 us (registers spill); launches of 1 to 4 replicas at a time, so that dk and dv find in the memory-side cache what dq read, 5 to 50 %
 // slower; ds from the unrounded p, which moves the gradients of a small model by 5e-3.
@@ -251,7 +252,8 @@ __device__ __forceinline__ void store_rows(const f16v (&o)[2], F&& to16, uint16_
 }
 
 // The block's 64 column sums over its 128 rows, as stored, from the wavefronts' strips (stage 1 of the qkv bias gradient, which was a pass
-// over dqkv of 75 us at S = 512, where the two kernels grow by 19; 21 against 7 at S = 256): one product of each strip against ones, then the four wavefronts in the order of their rows.
+// over dqkv of 77 us at S = 512, where the two kernels grow by 13; 23 against 4 at S = 256): one product of each strip against ones, then the
+// four wavefronts in the order of their rows.
 // Every thread calls it; all 128 rows exist.
 __device__ __forceinline__ void sum_columns(const uint16_t* strips, float* sums, float* dst, int tid) {
   const int lane = tid & 63, w = tid >> 6, p = lane & 15;

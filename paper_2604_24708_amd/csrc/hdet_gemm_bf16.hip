@@ -22,9 +22,9 @@
 //
 // Tiling: each wavefront owns a 64x64 (or 32x32) output tile (2x2 blocks or one of v_mfma_f32_32x32x16_bf16);
 // a block is 2x2 wavefronts (128x128 or 64x64 tile).  K step 32, LDS double-buffered (one barrier per K
-// step), the global loads of the next four steps in flight in registers; launch indices are remapped so
-// that each XCD's L2 serves a contiguous range of tiles.  What bounds it is the latency of those loads: with one step in flight, and the
-// funnel shift waiting for its data at once, 0.9 us a step.  96 x 1500, K = 700 gradient, 6 items 20.1 -> 15.9 us, 1500 x 784, K = 576
+// step), the global loads of the next four steps (of the next one in grids of many blocks: one_step) in flight in registers; launch
+// indices are remapped so that each XCD's L2 serves a contiguous range of tiles.  What bounds it is the latency of those loads: with one
+// step in flight, and the funnel shift waiting for its data at once, 0.9 us a step of a block that is alone.  96 x 1500, K = 700 gradient, 6 items 20.1 -> 15.9 us, 1500 x 784, K = 576
 // 13.4 -> 10.6, odd rows 96 x 1501, K = 703, 4 items 23.0 -> 14.1.
 //
 // Loads of operands that are not made of aligned chunks: memory is read in aligned dwords (16 bytes per
@@ -247,7 +247,8 @@ __device__ __forceinline__ bf16x8 ones() {
 }
 
 // WT x WT: 32x32 MFMA blocks per wavefront; 2 x 2 wavefronts per block, block tile (64 WT) x (64 WT).
-// DEPTH: K steps whose loads are in flight, 4 or 1 (one_step says when).  PIECES: the contraction is summed in that many pieces, each from zero, and the pieces are added in ascending order (launch_general).
+// DEPTH: K steps whose loads are in flight, 4 or 1 (one_step says when).  PIECES: the contraction is summed in that many pieces, each from
+// zero, and the pieces are added in ascending order (launch_general).
 template <bool A_KMAJOR, bool B_KMAJOR, int EPI, int WT, int DEPTH, int PIECES = 1>
 __global__ __launch_bounds__(256, 2) void hdet_bgemm_kernel(const hdet_bgemm_args g) {
   constexpr int TM = 64 * WT, TN = TM, THREADS = 256;

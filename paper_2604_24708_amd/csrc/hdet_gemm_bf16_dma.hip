@@ -677,7 +677,7 @@ bool stream_result(const hdet_bgemm_args& g, int epi, int batch) {
 // read their operands more often, look 10 to 30 % better than they are in a training step).  Against the fastest tile of each product in that
 // range this choice loses 0.2 to 1 % on average by epilogue, 21 % at most (384 tiles at K = 1024 with both GELU outputs); lines by K and tile
 // count lost up to 34 %.  The alternating kernel is left out below K = 512 (1024 for weight gradients, 2048 for the GELU gradient, whose
-// epilogue takes as long as 1024 of K: 719 against 690 us for 8192 x 4096 x 8 in a step), where the model flatters it.
+// epilogue takes as long as 1024 of K: 719 against 690 us for 8192 x 4096 x 8 in a step), where the model flatters it; but see long_logits.
 struct tile_shape { int tm, tn, per_cu; float base, share, slope, least; };
 constexpr tile_shape kAlternating = {256, 256, 1, 1.6f, 1.f, 19.f, 1.f};       // hdet_bgemm_alt_kernel
 constexpr tile_shape kPair = {256, 128, 2, 3.6f, 0.53f, 32.f, 0.52f};          // K step 32, three stages, two blocks a CU
