@@ -95,16 +95,8 @@ def disagreements(loss, grads, ref):
     return bad
 
 
-# bf16 operands of every alignment, one and two layers: few tiles (K in 4), long contractions over few tiles (K in 8), 64- and
-# 128-wide tiles staged through LDS, and the LDS-direct kernel with rows of whole and of partial lines
-CASES = [([33, 9], 7, 2), ([1503, 100], 97, 3), ([130, 36], 66, 3), ([4097, 1000], 37, 2), ([1031, 2111], 65, 2), ([512, 520], 300, 4), ([264, 2056], 130, 4),
-         ([33, 31, 9], 7, 2), ([1503, 702, 100], 97, 6), ([130, 702, 36], 66, 3), ([1031, 2111, 10], 65, 2), ([787, 1501, 99], 96, 6),
-         ([516, 2052, 12], 200, 5), ([999, 2055, 130], 260, 8), ([512, 1032, 264], 520, 4)]
-
-
-@pytest.mark.gpu
-@pytest.mark.parametrize("widths,batch,n", CASES)
-def test_loss_and_gradients_entry_by_entry(widths, batch, n):
+def compare_entry_by_entry(widths, batch, n, replicas):
+    """The library's loss and gradients of a network against the reference, for the named replicas; all of them are finite."""
     theta, x, y = inputs(widths, batch, n)
     P = theta.shape[1]
     stride, dev = (P + 3) // 4 * 4, "cuda:0"
@@ -118,8 +110,22 @@ def test_loss_and_gradients_entry_by_entry(widths, batch, n):
     losses = H.hdet_forward_backward(h, torch.from_numpy(x).to(dev), torch.from_numpy(y).to(dev), want_losses=True)
     got = g[:, :P].double().cpu().numpy()
     H.hdet_destroy(h)
-    for r in range(n):
+    for r in replicas:
         assert disagreements(losses[r], got[r], reference(theta[r], x[r], y[r], widths)) == []
+    assert np.isfinite(got).all()
+
+
+# bf16 operands of every alignment, one and two layers: few tiles (K in 4), long contractions over few tiles (K in 8), 64- and
+# 128-wide tiles staged through LDS, and the LDS-direct kernel with rows of whole and of partial lines
+CASES = [([33, 9], 7, 2), ([1503, 100], 97, 3), ([130, 36], 66, 3), ([4097, 1000], 37, 2), ([1031, 2111], 65, 2), ([512, 520], 300, 4), ([264, 2056], 130, 4),
+         ([33, 31, 9], 7, 2), ([1503, 702, 100], 97, 6), ([130, 702, 36], 66, 3), ([1031, 2111, 10], 65, 2), ([787, 1501, 99], 96, 6),
+         ([516, 2052, 12], 200, 5), ([999, 2055, 130], 260, 8), ([512, 1032, 264], 520, 4)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("widths,batch,n", CASES)
+def test_loss_and_gradients_entry_by_entry(widths, batch, n):
+    compare_entry_by_entry(widths, batch, n, range(n))
 
 
 @pytest.mark.parametrize("widths,batch,n", [c for c in CASES if max(c[0]) < 1600])
