@@ -624,14 +624,16 @@ bool few_tiles(const hdet_bgemm_args& g, int batch) { return tiles(g, batch, 64,
 
 // Whether the LDS kernel keeps one K step in flight instead of four, which need half again as many registers (4 blocks a CU in 64 x 64 tiles instead
 // of 6, 2 instead of 3 in 128 x 128) and begin a block later.  By who else is there to cover the latency of the loads; chunks at odd elements, whose
-// funnel shift would wait at once, have more of it.  us, one / four in flight, items of one step:
+// funnel shift would wait at once, have more of it.  (4 to 6 tiles a CU, 4 to 5 of even weight gradients, are one round of the one and two of the
+// other.)  us, one / four in flight, items of one step:
 //   128 x 128, rows of A: even 2184 x 2122, K = 830, 5 items 115 / 133;  3460 x 2682, K = 3238, 6 items 742 / 832;  7600 x 1280 gradient, K = 16,
 //     5 items 104 / 140;  odd 3460 x 3238, K = 137, 6 items 138 / 177;  9326 x 570, K = 309, 6 items 116 / 132;  1508 x 2164, K = 1537, 6 items 235 / 210
 //   128 x 128 weight gradients, even 2880 x 2468, K = 1661, 8 items 387 / 288, odd 2723 x 1277, K = 1599, 6 items 288 / 136
 //   64 x 64 (tiles a CU): 623 x 350, K = 3320, 8 items (1.9) 84 / 56;  351 x 3124, K = 404, 5 items (5.7) 32.7 / 35.7;  1274 x 1949 gradient, K = 896,
 //     odd, 2 items (4.8) 35 / 43;  3034 x 324, K = 1220, 6 items (6.8) 74 / 56;  2056 x 1540 gradient, K = 28, 4 items (12.9) 30 / 36;  weight
 //     gradients, even 404 x 2152, K = 351, 5 items (4.6) 17.2 / 20.4, 1280 x 1812, K = 7600, 5 items (11.3) 532 / 778, odd 1277 x 650, K = 1599,
-//     6 items (5.2) 90 / 62, 856 x 3437, K = 71, 4 items (11.8) 18.5 / 20.1
+//     6 items (5.2) 90 / 62, 856 x 3437, K = 71, 4 items (11.8) 18.5 / 20.1;  even, 900 x 1284, K = 6000, 4 items (4.9) 160 / 263, 1028 x 1028,
+//     K = 2600, 5 items (5.6) 109 / 108, 2872 x 196, K = 9657, 8 items (5.6) 517 / 356, 2100 x 452, K = 4000, 6 items (6.2) 205 / 149
 // Of 467 products of 122 random networks none but 20 lose more than 6 % by this rule, most of them in 64 x 64 tiles at 9 a CU and more with K from 1800 on
 // (666 x 2025, K = 6626, 8 items 550 / 666), where as many others gain as much.
 bool one_step(const hdet_bgemm_args& g, bool wgrad, int wt, int64_t blocks) {
@@ -641,7 +643,8 @@ bool one_step(const hdet_bgemm_args& g, bool wgrad, int wt, int64_t blocks) {
   if (wt == 2) return !odd || g.k < 768;             // (weight gradients never: launch_general)
   if (blocks <= 3 * cus) return false;
   if (g.k < 256) return true;
-  return wgrad ? !odd : blocks > 4 * cus && blocks <= 6 * cus;
+  if (!wgrad) return blocks > 4 * cus && blocks <= 6 * cus;
+  return !odd && (blocks <= 5 * cus || blocks > 7 * cus);
 }
 
 // `aligned`: the LDS-direct kernel could form the product as well, whose sums are not split.
