@@ -137,30 +137,54 @@ struct lds_tile {
   }
 };
 
+// What lanes 32 .. 63 of a hold for what lanes 0 .. 31 of b hold; odd rows of 16 lanes of a for even rows of b
+__device__ __forceinline__ void swap32(unsigned& a, unsigned& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  a = r[0]; b = r[1];
+}
+__device__ __forceinline__ void swap16(unsigned& a, unsigned& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+  a = r[0]; b = r[1];
+}
+
+// a reduction over the four groups of 16 lanes, the same value in each
+template <typename F>
+__device__ __forceinline__ float over_groups(float x, F op) {
+  unsigned a = __float_as_uint(x), b = a;
+  swap32(a, b);
+  x = op(__uint_as_float(a), __uint_as_float(b));
+  a = b = __float_as_uint(x);
+  swap16(a, b);
+  return op(__uint_as_float(a), __uint_as_float(b));
+}
+
 // Launch order -> tile: each XCD (own L2; blocks are dealt to the XCDs round-robin) works through a contiguous
 // range of tiles, and inside a batch item consecutive tiles walk groups of tile_group tile rows column by column,
 // so that the blocks an XCD runs at one time share operand tiles of both kinds in its L2.
 struct tile_id { int bx, by, bz; };
-__device__ __forceinline__ tile_id tile_of_block(int tile_group) {
-  const unsigned total = gridDim.x * gridDim.y * gridDim.z;
-  unsigned t = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
+__device__ __forceinline__ tile_id tile_of_index(unsigned t, unsigned gx, unsigned gy, unsigned total, int tile_group) {
   {   // XCD x = launch index mod 8 takes the x-th of eight contiguous ranges (the first total mod 8 ranges one tile longer)
     const unsigned x = t & 7u, rem = total & 7u;
     t = x * (total >> 3) + (x < rem ? x : rem) + (t >> 3);
   }
   tile_id id;
-  const unsigned per = gridDim.x * gridDim.y;
+  const unsigned per = gx * gy;
   id.bz = t / per;
   const unsigned r = t - id.bz * per;
   const unsigned gm = tile_group > 1 ? (unsigned)tile_group : 1u;
-  const unsigned gsz = gm * gridDim.x;
+  const unsigned gsz = gm * gx;
   const unsigned grp = r / gsz, first = grp * gm;
-  const unsigned rows = gridDim.y - first < gm ? gridDim.y - first : gm;
+  const unsigned rows = gy - first < gm ? gy - first : gm;
   const unsigned q = r - grp * gsz;
   id.by = first + q % rows;
   id.bx = q / rows;
   return id;
 }
+__device__ __forceinline__ tile_id tile_of_block(int tile_group) {
+  return tile_of_index(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z), gridDim.x, gridDim.y, gridDim.x * gridDim.y * gridDim.z, tile_group);
+}
+
+constexpr float kLog2e = 1.4426950408889634f;
 
 // The block's TM x TN tile to memory.  Accumulators go through LDS as fp32, the wavefront's own 32 rows x 64 columns at a time, and are read
 // back with 4 consecutive columns a lane, so that every global access is made of whole rows of the strip.  (Strips of 16 rows x 256 columns
@@ -612,6 +636,334 @@ __global__ __launch_bounds__(512, 2) void hdet_bgemm_alt_kernel(const hdet_bgemm
   store_tile<EPI, TM, TN, WGM, WGN, 16, STREAM, 8 * HALF * 2>(g, acc, S, id.bx, id.by, bi.z0, c_base, tid);
 }
 
+// Forward products whose blocks walk over tiles of 256 x 256: the main loop of the kernel above, with the next tile's first two K steps requested in
+// the last two of the tile before, so that the pipeline never drains, and a tile's end in registers alone, under the loads in flight.
+//  * The bias is what the first MFMAs add to (it lies in LDS, requested a tile ahead).
+//  * Results change places between the four groups of 16 lanes (v_permlane32_swap, v_permlane16_swap) until a lane has 16 consecutive columns
+//    of its row: two 16-byte stores, no LDS.
+//  * Stores count in vmcnt with the loads: they are always issued (rows and columns that do not exist lie outside the descriptor), and the first
+//    K step of the next tile waits for the loads before them, not for them (kStores).
+//  * The group that is a turn behind ends its tile as soon as its products are done, beside the other group, not after it.
+// Built for the output layer with its loss (hdet_launch_head_loss), whose two passes cost less than writing and reading fp32 logits:  K = 512,
+// 4096 x 32000, 8 replicas, 1502 to 1575 us of product and 1152 of loss kernel -> 918 (statistics) + 19 (merge) + 1190 (gradient).  Of a tile's
+// 14.7 and 19 us the main loop takes 11 (1.6 PFLOP/s, 70 % of the matrix cores' cycles), exponentials 3.4, stores 3.5.  Not kept, gradient pass:
+// results through LDS 1216 (rows of bf16), past the L2 1358 (pieces of 16 bytes), both groups' ends in turn 1240; the kernel above with these
+// epilogues 1019 and 1400.
+template <int EPI>
+__global__ __launch_bounds__(512, 2) void hdet_bgemm_walk_kernel(const hdet_bgemm_args g, unsigned gx, unsigned gy, unsigned total) {
+  constexpr int TM = 256, TN = 256, TK = 64, HALF = 128 * TK;
+  constexpr bool kStat = EPI == HDET_EPI_XENT_STAT, kGrad = EPI == HDET_EPI_XENT_GRAD;
+  constexpr int kStores = kStat ? 0 : 16;
+  constexpr int kBiasAt = 8 * HALF * 2, kRowsAt = kBiasAt + 2 * TN * 4;           // bytes: bias [2][TN], then what the epilogue needs
+  constexpr int kExtra = 2 * TN * 4 + (kStat ? 4 * TM * 8 : 3 * TM * 4);
+  __shared__ __attribute__((aligned(1024))) uint16_t S[8 * HALF + kExtra / 2];
+  typedef lds_tile<true, 128, 512, TK> ta;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wn = (wave % 4) * 64, hr = (wave / 4) * 64, wm = (wave / 4) * 128;
+  // what a lane derives from its number outside the K loop is computed where it is used: kept over the tiles it would spill
+  auto fresh = [](int x) { asm volatile("" : "+v"(x)); return x; };
+  const uint32_t s_addr = lds_addr_of(S);
+  float* const s_bias = reinterpret_cast<float*>(S) + kBiasAt / 4;
+  float* const s_rows = reinterpret_cast<float*>(S) + kRowsAt / 4;
+  const int nk = ((g.k + TK - 1) / TK + 1) & ~1;                 // K steps of a tile, an even number (steps beyond K are zeros)
+
+  struct tile { int m0, n0, bx, z; i4 ra, rb, rbias; };
+  auto tile_at = [&](unsigned t) {
+    tile r;
+    const tile_id id = tile_of_index(t < total ? t : total - 1, gx, gy, total, g.tile_group);
+    r.m0 = id.by * TM; r.n0 = id.bx * TN; r.bx = id.bx; r.z = id.bz;
+    const bool ok = t < total;
+    r.ra = make_rsrc(g.a + id.bz * g.a_s[0] + (int64_t)r.m0 * g.lda, ok ? (uint32_t)(((int64_t)(g.m - r.m0 - 1) * g.lda + g.k) * 2) : 0u);
+    r.rb = make_rsrc(g.b + id.bz * g.b_s[0] + (int64_t)r.n0 * g.ldb, ok ? (uint32_t)(((int64_t)(g.n - r.n0 - 1) * g.ldb + g.k) * 2) : 0u);
+    r.rbias = make_rsrc(g.bias + id.bz * g.bias_bs + r.n0, ok ? (uint32_t)(g.n - r.n0) * 4u : 0u);
+    return r;
+  };
+  const int ck = ((tid & 7) ^ ta::swz(tid >> 3)) * 8;            // k of this thread's chunks inside a K step
+  uint32_t off_a = (uint32_t)(((tid >> 3) * g.lda + ck) * 2), off_b = (uint32_t)(((tid >> 3) * g.ldb + ck) * 2);
+  // LDS, in units of 128 rows x 64: half h of A of stage s at 2 h + s (its rows 64 .. 127 are the tile's 128 .. 191 of that half), B at 4 + 2 s
+  auto load_a = [&](const i4& r, int h, int s, int kt) {
+    const uint32_t at = s_addr + (2 * h + s) * HALF * 2;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      lds_load16(r, at + (i * 512 + wave * 64) * 16, ck + kt * TK < g.k ? off_a + (uint32_t)(kt * 128 + (64 * h + 128 * i) * g.lda * 2) : kAbsent);
+  };
+  auto load_b = [&](const i4& r, int s, int kt) {
+    const uint32_t at = s_addr + (4 + 2 * s) * HALF * 2;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      lds_load16(r, at + (i * 512 + wave * 64) * 16, ck + kt * TK < g.k ? off_b + (uint32_t)(kt * 128 + 64 * i * g.ldb * 2) : kAbsent);
+  };
+  auto load_bias = [&](const tile& t, int slot) {
+    if (wave < 4) lds_load4(t.rbias, s_addr + kBiasAt + slot * TN * 4 + wave * 256, (uint32_t)fresh(tid) * 4u);
+  };
+  auto load_rows = [&](const tile& t) {                          // maximum, factor and label of the tile's rows
+    const int ln = fresh(lane);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int q = wave + 8 * u, row = t.m0 + (q & 3) * 64 + ln;
+      if (q < 12) {
+        const void* src = q < 4 ? (const void*)g.xent.row_maxl : q < 8 ? (const void*)g.xent.row_a : (const void*)g.xent.labels;
+        lds_load4(make_rsrc((const float*)src + (int64_t)t.z * g.m, (uint32_t)g.m * 4u), s_addr + kRowsAt + q * 256, row < g.m ? (uint32_t)row * 4u : kAbsent);
+      }
+    }
+  };
+  f4 acc[8][4], bias[4];
+  bf16x8 fa[2][4], fb[2][4];
+  // fragment i of sub-step ss is 16 i rows behind fragment 0, whose chunk permutation it shares: two addresses an operand
+  const uint16_t *pa[2], *pb[2];
+#pragma unroll
+  for (int ss = 0; ss < 2; ++ss) {
+    const int at = (lane & 15) * TK + (((ss * 4 + (lane >> 4)) ^ ta::swz(lane & 15)) << 3);
+    pa[ss] = S + hr * TK + at;
+    pb[ss] = S + 4 * HALF + wn * TK + at;
+  }
+  auto read_a = [&](int h, int s) {
+#pragma unroll
+    for (int ss = 0; ss < 2; ++ss)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) fa[ss][i] = *reinterpret_cast<const bf16x8*>(pa[ss] + (2 * h + s) * HALF + i * 16 * TK);
+  };
+  auto read_b = [&](int s) {
+#pragma unroll
+    for (int ss = 0; ss < 2; ++ss)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) fb[ss][j] = *reinterpret_cast<const bf16x8*>(pb[ss] + 2 * s * HALF + j * 16 * TK);
+  };
+  auto multiply = [&](int h, bool first) {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int ss = 0; ss < 2; ++ss)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          acc[4 * h + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[ss][j], fa[ss][i], first && ss == 0 ? bias[j] : acc[4 * h + i][j], 0, 0, 0);
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto meet = [] {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // a group's four wavefronts have left max and sum of their 64 columns for the group's 128 rows; 32 rows each
+  auto put_stats = [&](const auto& t) {
+    const int ln = fresh(lane), tr = wm + (wave % 4) * 32 + (ln & 31);
+    const float2* buf = reinterpret_cast<const float2*>(s_rows) + tr;
+    float2 p[4];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) p[w] = buf[w * TM];
+    const float mx = fmaxf(fmaxf(p[0].x, p[1].x), fmaxf(p[2].x, p[3].x));
+    float s = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) s += p[w].x == -INFINITY ? p[w].y : p[w].y * __builtin_amdgcn_exp2f((p[w].x - mx) * kLog2e);
+    if (ln < 32 && t.m0 + tr < g.m) g.xent.part[((int64_t)t.z * gx + t.bx) * g.m + t.m0 + tr] = float2{mx, s};
+  };
+  auto finish = [&](const tile& t) {
+    __builtin_amdgcn_sched_barrier(0);
+    const int ln = fresh(lane), cg = ln >> 4, lr = ln & 15;
+    if constexpr (kStat) {
+      float mx[8], sum[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        mx[i] = acc[i][0][0];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) mx[i] = fmaxf(mx[i], acc[i][j][e]);
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) mx[i] = over_groups(mx[i], [](float x, float y) { return fmaxf(x, y); });
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float ml = mx[i] == -INFINITY ? 0.f : mx[i] * kLog2e;
+        sum[i] = 0.f;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) sum[i] += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][e], kLog2e, -ml));
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) sum[i] = over_groups(sum[i], [](float x, float y) { return x + y; });
+      if (ln < 16) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) reinterpret_cast<float2*>(s_rows)[(wave % 4) * TM + wm + i * 16 + ln] = float2{mx[i], sum[i]};
+      }
+    } else {
+      const auto rc = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<uint16_t*>(g.c) + t.z * g.c_s[0] + (int64_t)t.m0 * g.ldc + t.n0, 0, 0x7fffffff, 0x00020000);
+      const int col = wn + cg * 16;
+      const bool ok0 = t.n0 + col < g.n, ok1 = t.n0 + col + 8 < g.n;
+      f4 csum[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) csum[j] = f4{0.f, 0.f, 0.f, 0.f};
+      float rmax[8], ra[8];
+      int rlab[8];
+      if (kGrad) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const int tr = wm + i * 16 + lr;
+          rmax[i] = s_rows[tr]; ra[i] = s_rows[TM + tr]; rlab[i] = __float_as_int(s_rows[2 * TM + tr]);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int tr = wm + i * 16 + lr;
+        const bool row_ok = t.m0 + tr < g.m;
+        f4 v[4];
+        if constexpr (kGrad) {
+          const float maxl = row_ok ? rmax[i] : INFINITY, a = ra[i];
+          const int yc = row_ok ? rlab[i] - (t.n0 + wn + cg * 4) : -1;
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[j][e] = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][e], kLog2e, -maxl)) * a;
+          if (__builtin_expect((unsigned)yc < 64u && (yc & 12) == 0, 0)) {      // the row's label is among this lane's columns
+            float zy = 0.f;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                if (yc == j * 16 + e) { zy = acc[i][j][e]; v[j][e] -= g.xent.invb; }
+            const int64_t at = (int64_t)t.z * g.m + t.m0 + tr;
+            const float2 lse = g.xent.row_lse[at];
+            g.xent.row_loss[at] = lse.y - (zy - lse.x);
+          }
+#pragma unroll
+          for (int j = 0; j < 4; ++j) csum[j] += v[j];
+        }
+        unsigned d[4][2];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { d[j][0] = hdet_bf16_pack(v[j][0], v[j][1]); d[j][1] = hdet_bf16_pack(v[j][2], v[j][3]); }
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+          swap32(d[0][w], d[2][w]); swap32(d[1][w], d[3][w]);
+          swap16(d[0][w], d[1][w]); swap16(d[2][w], d[3][w]);
+        }
+        const uint32_t at = (uint32_t)((tr * (int)g.ldc + col) * 2);
+        __builtin_amdgcn_raw_buffer_store_b128(hdet_u4v{d[0][0], d[0][1], d[1][0], d[1][1]}, rc, row_ok && ok0 ? at : kAbsent, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(hdet_u4v{d[2][0], d[2][1], d[3][0], d[3][1]}, rc, row_ok && ok1 ? at + 16 : kAbsent, 0, 0);
+      }
+      if (kGrad && g.colsum) {                                   // a wavefront's 128 rows are one chunk of the column sums
+        f4 out = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            float x = csum[j][e];
+            x += hdet_dpp<0xB1>(x);
+            x += hdet_dpp<0x4E>(x);
+            x += hdet_dpp<0x141>(x);
+            x += hdet_dpp<0x140>(x);
+            if (lr == j) out[e] = x;
+          }
+        const int nchunks = (g.m + 127) / 128, chunk = (t.m0 + wm) / 128, c = t.n0 + wn + lr * 16 + cg * 4;
+        if (lr < 4 && chunk < nchunks && c < g.n) *reinterpret_cast<f4*>(g.colsum + ((int64_t)t.z * nchunks + chunk) * g.n + c) = out;
+      }
+    }
+  };
+
+  unsigned t = blockIdx.x;
+  tile cur = tile_at(t);
+  struct { int m0, bx, z; } prev = {0, 0, 0};
+  int slot = 0;
+  load_bias(cur, 0);
+  load_a(cur.ra, 0, 0, 0); load_b(cur.rb, 0, 0); load_a(cur.ra, 1, 0, 0);
+  load_a(cur.ra, 0, 1, 1); load_b(cur.rb, 1, 1);
+  wait_and_barrier<8>();
+  if (wave >= 4) meet();
+  for (bool begun = false;; begun = true) {
+    tile nxt;
+    asm volatile("" : "+v"(off_a), "+v"(off_b));
+    const int cg = fresh(lane) >> 4;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      bias[j] = *reinterpret_cast<const f4*>(s_bias + slot * TN + wn + j * 16 + cg * 4);
+      if (kStat && cur.n0 + wn + j * 16 + cg * 4 >= g.n) bias[j] = f4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    }
+    auto pair = [&](int kt0, bool first) {
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const int kt = kt0 + s;
+        const bool fs = first && s == 0;
+        auto wait = [&] {
+          if (kStores && fs && begun) wait_and_barrier<8 + kStores>();
+          else wait_and_barrier<8>();
+        };
+        read_a(0, s);
+        read_b(s);
+        if (first || kt + 1 < nk) load_a(cur.ra, 1, s ^ 1, kt + 1); else load_a(nxt.ra, 1, s ^ 1, 0);
+        wait();
+        multiply(0, fs);
+        meet();
+        read_a(1, s);
+        if (first || kt + 2 < nk) { load_a(cur.ra, 0, s, kt + 2); load_b(cur.rb, s, kt + 2); }
+        else { load_a(nxt.ra, 0, s, kt + 2 - nk); load_b(nxt.rb, s, kt + 2 - nk); }
+        if (first && s == 0) {                                   // under the other group's products
+          t += gridDim.x;
+          nxt = tile_at(t);
+          if (kStat && begun) put_stats(prev);
+        }
+        if (first && s == 1) {
+          load_bias(nxt, slot ^ 1);
+          if (kGrad) load_rows(cur);
+        }
+        wait();
+        multiply(1, fs);
+        if (s == 0) meet();
+      }
+    };
+    pair(0, true);
+    for (int kt0 = 2; kt0 < nk; kt0 += 2) { meet(); pair(kt0, false); }
+    // the first group ends its tile under the second's last products, the second at once, not when the first is done
+    if (wave < 4) meet();
+    finish(cur);
+    if (wave >= 4) meet();
+    if (t >= total) break;
+    prev = {cur.m0, cur.bx, cur.z};
+    cur = nxt;
+    slot ^= 1;
+  }
+  if (wave < 4) meet();
+  wait_and_barrier<0>();
+  if (kStat) put_stats(cur);
+}
+
+// The rows' max and sum from the column tiles' (hdet_launch_head_loss).  Block = 64 rows x 4 phases; phase q takes tiles q, q + 4, ..., the
+// phases are added in their order.
+__global__ __launch_bounds__(256) void hdet_head_rows_kernel(const hdet_xent_epi x, int m, int tiles) {
+  __shared__ float2 buf[4][64];
+  const int lane = threadIdx.x & 63, q = threadIdx.x >> 6, z = blockIdx.y, row = blockIdx.x * 64 + lane;
+  float mx = -INFINITY, s = 0.f;
+  if (row < m) {
+    const float2* p = x.part + (int64_t)z * tiles * m + row;
+#pragma unroll 8
+    for (int t = q; t < tiles; t += 4) {
+      const float2 v = p[(int64_t)t * m];
+      const float mn = fmaxf(mx, v.x);
+      if (v.x != -INFINITY) s = s * __builtin_amdgcn_exp2f((mx - mn) * kLog2e) + v.y * __builtin_amdgcn_exp2f((v.x - mn) * kLog2e);
+      else s += v.y;
+      mx = mn;
+    }
+  }
+  buf[q][lane] = float2{mx, s};
+  __syncthreads();
+  if (q == 0 && row < m) {
+    float2 p[4];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) p[w] = buf[w][lane];
+    const float top = fmaxf(fmaxf(p[0].x, p[1].x), fmaxf(p[2].x, p[3].x));
+    float sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) sum += p[w].x == -INFINITY && p[w].y == 0.f && top != -INFINITY ? 0.f : p[w].y * __builtin_amdgcn_exp2f((p[w].x - top) * kLog2e);
+    const int64_t at = (int64_t)z * m + row;
+    x.row_maxl[at] = top * kLog2e;
+    x.row_a[at] = x.invb / sum;
+    x.row_lse[at] = float2{top, logf(sum)};
+  }
+}
+
 namespace {
 
 bool chunk_regular(const void* base, int64_t ld, const int64_t* bs, int chunk_extent) {
@@ -820,4 +1172,33 @@ hipError_t hdet_launch_bgemm_dma(const hdet_bgemm_args& g_in, bool a_kmajor, boo
   if (epi == HDET_EPI_F32) return launch_shape<false, false, HDET_EPI_F32>(g, batch, s);   // wgrad
   if (epi == HDET_EPI_ADAMW) return launch_shape<false, false, HDET_EPI_ADAMW>(g, batch, s);
   return launch_shape<false, false, HDET_EPI_BF16>(g, batch, s);
+}
+
+bool hdet_head_loss_eligible(const hdet_bgemm_args& g, int batch) {
+  const int64_t ext = ((int64_t)g.m + 256) * g.lda * 2, b_ext = ((int64_t)g.n + 256) * g.ldb * 2;
+  return g.n1 * g.n2 == 1 && hdet_bgemm_dma_eligible(g, true, true, HDET_EPI_BIAS_BF16) && ext < (int64_t)1 << 31 && b_ext < (int64_t)1 << 31 &&
+         g.m < 1 << 28 && g.k >= 192 && (g.n & 7) == 0 && ((g.ldc | g.c_s[0]) & 7) == 0 && (reinterpret_cast<uintptr_t>(g.c) & 15) == 0 && g.ldc < 1 << 22;
+}
+
+size_t hdet_head_loss_scratch(int m, int n, int batch) {
+  return (size_t)batch * m * (8 * (size_t)((n + 255) / 256) + 16) + 1024;
+}
+
+hipError_t hdet_launch_head_loss(const hdet_bgemm_args& g_in, int batch, void* scratch, hipStream_t s) {
+  hdet_bgemm_args g = g_in;
+  if (!hdet_head_loss_eligible(g, batch) || !scratch || !g.xent.labels || !g.xent.row_loss) return hipErrorInvalidValue;
+  const unsigned gx = (g.n + 255) / 256, gy = (g.m + 255) / 256, total = gx * gy * (unsigned)batch;
+  const size_t rows = (size_t)batch * g.m;
+  char* at = (char*)scratch;
+  g.xent.part = (float2*)at; at += rows * gx * sizeof(float2);
+  g.xent.row_lse = (float2*)at; at += rows * sizeof(float2);
+  g.xent.row_maxl = (float*)at; at += rows * sizeof(float);
+  g.xent.row_a = (float*)at;
+  g.xent.invb = 1.f / (float)g.m;
+  g.tile_group = gx >= 64 ? 4 : gx >= 12 ? 2 : 1;
+  const unsigned cus = (unsigned)compute_units(), blocks = total < cus ? total : cus;
+  hipLaunchKernelGGL(hdet_bgemm_walk_kernel<HDET_EPI_XENT_STAT>, dim3(blocks), dim3(512), 0, s, g, gx, gy, total);
+  hipLaunchKernelGGL(hdet_head_rows_kernel, dim3((g.m + 63) / 64, batch), dim3(256), 0, s, g.xent, g.m, (int)gx);
+  hipLaunchKernelGGL(hdet_bgemm_walk_kernel<HDET_EPI_XENT_GRAD>, dim3(blocks), dim3(512), 0, s, g, gx, gy, total);
+  return hipGetLastError();
 }

@@ -165,7 +165,21 @@ enum { HDET_EPI_F32 = 0, HDET_EPI_BIAS_F32 = 1, HDET_EPI_BIAS_RELU_BF16 = 2, HDE
        HDET_EPI_GELUGRAD_BF16 = 7,    // c = bf16(bf16(acc) * gelu'(mask)): gradient through the GELU at pre-activation `mask`
        HDET_EPI_BIAS_RESID_BF16 = 8,  // c = bf16(mask + bf16(acc + bias)): a Linear layer added to its residual stream `mask`
        HDET_EPI_BIAS_DROP_RESID_BF16 = 9,     // the same with dropout of the layer's output before the sum
-       HDET_EPI_ADAMW = 10 };         // weight gradient that is applied at once: the AdamW update of `upd` on the tile (c is not written)
+       HDET_EPI_ADAMW = 10,           // weight gradient that is applied at once: the AdamW update of `upd` on the tile (c is not written)
+       // output layer whose logits z = acc + bias stay on the chip (hdet_launch_head_loss only):
+       HDET_EPI_XENT_STAT = 11,       // max and sum of exp(z - max) of a tile's rows (c is not written)
+       HDET_EPI_XENT_GRAD = 12 };     // c = bf16 gradient of the mean cross-entropy at z, from the whole rows' max and sum; row losses, column sums
+
+// Cross-entropy inside the output layer's product: what its two passes and the merge between them exchange.  Row scalars are [replica][row].
+struct hdet_xent_epi {
+  float2* part;            // [replica][column tile][row]: max, sum of a tile's part of the row
+  float* row_maxl;         // max * log2(e)
+  float* row_a;            // 1 / (rows * sum)
+  float2* row_lse;         // max, log(sum)
+  const int32_t* labels;
+  float* row_loss;
+  float invb;              // 1 / rows
+};
 
 struct hdet_bgemm_args {
   const uint16_t* a;       // bf16
@@ -187,6 +201,7 @@ struct hdet_bgemm_args {
   // sum of C as stored over that 128-row block of the column (stage 1 of the bias gradient of the layer whose
   // pre-activation gradient C is); colsum_bs is unused padding for alignment
   float* colsum;
+  hdet_xent_epi xent;      // HDET_EPI_XENT_*
   float* rowsum; int64_t rowsum_bs;     // general kernels, weight gradients: rowsum[z0*rowsum_bs + m] = sum_k A(m,k), or null
   int tile_group;          // LDS-direct kernel: consecutive blocks walk groups of this many tile rows column by column (0, 1: row by row)
   // HDET_EPI_ADAMW (n1 = n2 = 1, batch item = replica): the product is the replica's gradient of a weight matrix;
@@ -231,6 +246,11 @@ hipError_t hdet_launch_bgemm(const hdet_bgemm_args& g, bool a_kmajor, bool b_kma
 // whole, 16-byte aligned chunks; C, bias and mask addressable 4 columns at a time; batch-item extents
 // below 2 GiB); n1, n2 >= 1 on entry.
 bool hdet_bgemm_dma_eligible(const hdet_bgemm_args& g, bool a_kmajor, bool b_kmajor, int epi);
+// Output layer with its softmax cross-entropy (forward order; g: operands, bias, c = dlogits bf16, colsum; xent: labels, row_loss): dlogits
+// and row losses without the logits ever being written.  scratch: hdet_head_loss_scratch(g, batch) bytes, 16-byte aligned.
+bool hdet_head_loss_eligible(const hdet_bgemm_args& g, int batch);
+size_t hdet_head_loss_scratch(int m, int n, int batch);
+hipError_t hdet_launch_head_loss(const hdet_bgemm_args& g, int batch, void* scratch, hipStream_t stream);
 int hdet_compute_units();     // compute units of the current device (queried once per device; 256 on MI355X)
 hipError_t hdet_launch_bgemm_dma(const hdet_bgemm_args& g, bool a_kmajor, bool b_kmajor, int epi, int batch,
                                  hipStream_t stream);

@@ -962,6 +962,7 @@ struct hdet_tf_plan {
   unsigned long long* tok_sorted;            // [N][M] keys (token id, row) in ascending order
   float* tok_seg;                            // [N][M][d] partial rows of the token-embedding gradient
   bool fused_attn;                           // bf16, head size 64, S a multiple of 64
+  bool head_loss;            // the loss is formed inside the output layer's product (tf_head_loss)
   float* part;               // partial column sums, one [N][row chunks][cols] array (two for LayerNorm) per reduction
   int nrc;                   // row chunks of the two-stage column sums
   std::vector<colsum_job> jobs;   // the two-stage reductions of a backward pass, by position in the parameter plane
@@ -1062,6 +1063,35 @@ static bool hdet_tf_ln_vector(const hdet_tf_plan* p, int64_t g_off) {
 }
 static bool hdet_tf_ln_fused(const hdet_tf_plan* p, int64_t g_off) { return hdet_tf_ln_vector(p, g_off) && p->d <= 1024; }
 
+// The output layer with its loss as one product in two passes (hdet_launch_head_loss), without labels and row losses
+static hdet_bgemm_args head_args(const hdet_tf_plan* p) {
+  hdet_bgemm_args g = {};
+  g.a = (const uint16_t*)p->hf; g.b = p->buf.params_bf16_dev + p->w_head; g.c = p->dlogits;
+  g.m = p->M; g.n = p->V; g.k = p->d; g.n1 = g.n2 = 1;
+  g.lda = p->d; g.ldb = p->d; g.ldc = p->V;
+  g.a_s[0] = (int64_t)p->M * p->d; g.b_s[0] = p->buf.plane_stride; g.c_s[0] = (int64_t)p->M * p->V;
+  g.bias = p->buf.params_dev + p->b_head; g.bias_bs = p->buf.plane_stride;
+  return g;
+}
+
+// Whether it is: the second product costs 2 K operations a logit, the logits it saves 8 bytes written and read and, below 2048 classes, the
+// wavefront-a-row loss kernel.  Blocks take whole tiles of 256 x 256, so that a last round of few tiles counts in full.  us, product with logits
+// and loss kernel / two products (replicas, rows, K, classes):
+//   classes >= 2048:  8 4096 256 32000 2211 / 1636;  8 4096 512 32000 2654 / 2127, 12000 958 / 850, 4096 318 / 282;  640, 32000 2973 / 2740;
+//     768, 32000 3019 / 3116;  1024, 8000 843 / 906;  two to four rounds: 4 2048 512 4000 92 / 86, 2 2048 512 7000 79 / 83, 9000 104 / 111,
+//     3 4096 256 2048 74 / 63, 5 2048 384 2560 91 / 71;  fewer: 2 1024 512 12000 65 / 78, 4000 28 / 44
+//   below:  8 4096 512 2000 296 / 150, 504 77 / 55;  1024, 2000 333 / 233, 1000 172 / 137;  one round: 4 2048 1024 1800 79 / 77;
+//     a quarter of one: 2 2048 512 1000 35 / 44
+static bool tf_head_loss(const hdet_tf_plan* p) {
+  if (!p->bf16 || p->ls_channel >= 0) return false;
+  const hdet_bgemm_args g = head_args(p);
+  if (!hdet_head_loss_eligible(g, p->N) || hdet_head_loss_scratch(g.m, g.n, p->N) > (size_t)p->N * p->M * p->V * 4) return false;
+  const int64_t cus = hdet_compute_units(), tiles = (int64_t)((g.m + 255) / 256) * ((g.n + 255) / 256) * p->N;
+  const double used = (double)tiles / (double)((tiles + cus - 1) / cus * cus);      // of the rounds' tiles
+  if (!hdet_xent_wide(p->V)) return p->V < 2048 && g.k <= 1024 && used >= 0.85;
+  return (g.k <= 640 && tiles >= 4 * cus) || (g.k <= 384 && used >= 0.75 && 5 * tiles >= 7 * cus);
+}
+
 hdet_tf_plan* hdet_tf_create(const hdet_config& cfg, const hdet_buffers& buf, int drop_channel, int ls_channel,
                              int temp_channel, std::string* err) {
   if (hdet_tf_validate(cfg, err) != HDET_OK) return nullptr;
@@ -1108,7 +1138,8 @@ hdet_tf_plan* hdet_tf_create(const hdet_config& cfg, const hdet_buffers& buf, in
     part_off += (int64_t)(mode == 1 ? 2 : 1) * p->N * nchunks * cols;
     first_block += (cols + 255) / 256;
   };
-  const int xr = xent_rows_per_block(p->M, p->N, V);
+  p->head_loss = tf_head_loss(p);
+  const int xr = p->head_loss ? 0 : xent_rows_per_block(p->M, p->N, V);
   add_job((int)V, 0, p->b_head, 0, d, -1, xr ? (p->M + xr - 1) / xr : 0);
   add_job((int)d, 1, p->lnf_g, p->lnf_b, 0);
   for (int l = 0; l < p->L; ++l) {
@@ -1455,14 +1486,23 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
     }
   }
   launch_ln_fwd<T>(p, p->x_in[L], p->lnf_g, p->lnf_b, p->hf, p->stf_mean, p->stf_rstd, s);
-  TF_CHECK(gemm<T>(p, NT, act(p->hf, d), wt(p->w_head, d), p->logits, V, act_v, false, M, V, d, 1, 1, theta + p->b_head, ps, s));
-  // the loss kernel for wide rows also forms stage 1 of the head bias gradient, xr rows per chunk
   float* head_part = nullptr;
-  const int xr = xent_rows_per_block(M, N, V);
-  if (xr)
+  if (p->head_loss) {
+    hdet_bgemm_args g = head_args(p);
+    g.xent.labels = targets; g.xent.row_loss = p->row_loss;
     for (const colsum_job& j : p->jobs)
-      if (j.out_off == p->b_head && j.mode == 0 && j.cols == V && j.nchunks == (M + xr - 1) / xr) { head_part = p->part + j.part_off; break; }
-  TF_CHECK(hdet_launch_xent(sizeof(T) == 2, p->logits, targets, M, V, p->dlogits, p->row_loss, N, ctrl, p->ls_channel, s, head_part, xr));
+      if (j.out_off == p->b_head && j.mode == 0 && j.cols == V) { head_part = p->part + j.part_off; break; }
+    g.colsum = head_part;
+    TF_CHECK(hdet_launch_head_loss(g, N, p->logits, s));
+  } else {
+    TF_CHECK(gemm<T>(p, NT, act(p->hf, d), wt(p->w_head, d), p->logits, V, act_v, false, M, V, d, 1, 1, theta + p->b_head, ps, s));
+    // the loss kernel for wide rows also forms stage 1 of the head bias gradient, xr rows per chunk
+    const int xr = xent_rows_per_block(M, N, V);
+    if (xr)
+      for (const colsum_job& j : p->jobs)
+        if (j.out_off == p->b_head && j.mode == 0 && j.cols == V && j.nchunks == (M + xr - 1) / xr) { head_part = p->part + j.part_off; break; }
+    TF_CHECK(hdet_launch_xent(sizeof(T) == 2, p->logits, targets, M, V, p->dlogits, p->row_loss, N, ctrl, p->ls_channel, s, head_part, xr));
+  }
   if (!f32) TF_CHECK(hdet_launch_loss_reduce(p->row_loss, M, ctrl, N, s));
 
   // ---- backward -----------------------------------------------------------------------
