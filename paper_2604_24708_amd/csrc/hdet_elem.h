@@ -112,15 +112,19 @@ __device__ __forceinline__ float hdet_wave_max(float x) {
   return x;
 }
 
-// GELU in its tanh form and its derivative (the transformer's MLP activation)
+// GELU in its tanh form and its derivative (the transformer's MLP activation).  With u = c (z + 0.044715 z^3) and e = exp(-2u):
+// 0.5 (1 + tanh u) = 1 / (1 + e) = s, and gelu' = s (1 + z (1 - s) 2 u'), 1 - s = e s, so that nothing cancels where tanh is close to -1 or 1.
+__device__ __forceinline__ float hdet_gelu_exp(float z, float z2) {
+  const float k1 = -1.5957691216057308f, k2 = -0.07135481282592269f;      // -2 c, -2 c 0.044715
+  return expf(z * __builtin_fmaf(k2, z2, k1));
+}
 __device__ __forceinline__ float hdet_gelu_tanh(float z) {
-  const float c = 0.7978845608028654f;
-  return 0.5f * z * (1.f + tanhf(c * (z + 0.044715f * z * z * z)));
+  return z / (1.f + hdet_gelu_exp(z, z * z));
 }
 __device__ __forceinline__ float hdet_gelu_tanh_grad(float z) {
-  const float c = 0.7978845608028654f;
-  const float t = tanhf(c * (z + 0.044715f * z * z * z));
-  return 0.5f * (1.f + t) + 0.5f * z * (1.f - t * t) * c * (1.f + 3.f * 0.044715f * z * z);
+  const float k3 = 1.5957691216057308f, k4 = 0.21406444881780076f;        // 2 u' = k3 + k4 z^2
+  const float z2 = z * z, e = fminf(hdet_gelu_exp(z, z2), 1e37f), s = 1.f / (1.f + e);
+  return s * __builtin_fmaf(z * (e * s), __builtin_fmaf(k4, z2, k3), 1.f);
 }
 
 // The same two functions for results that are rounded to bfloat16 anyway, on the hardware exp2 and reciprocal
