@@ -13,7 +13,8 @@
 //  * The wavefronts of a block may split K (WK > 1): each walks its own contiguous part, the partial tiles meet in
 //    LDS and are added in ascending order of k, every wavefront finishing 1 / WK of the tile.  A 32 x 32 tile with
 //    K = 1024 in 4 parts is 32 steps per wavefront instead of 128.
-// Loads are dword aligned only (odd leading dimensions are common here); rows beyond the matrix are clamped to its
+// That is how small products and those of odd leading dimensions or addresses are formed (loads are dword aligned only); a product from about one tile
+// a CU on whose operands are whole 16-byte chunks goes through LDS (sgemm_lds_tile).  Here rows beyond the matrix are clamped to its
 // last row (their results are not stored), the K mod 8 tail is a separate masked step.
 // Measured against a 64 x 64 tile staged through LDS on the vector units (us per launch, 4 replicas, same machine):
 //   512 x 256, K = 1024 (NT)  152 -> 17;   512 x 256, K = 4000 (NN)  270 -> 46;   4000 x 256, K = 512 (TN)  104 -> 46 (91 TFLOP/s);
@@ -24,11 +25,13 @@
 
 #include "hdet_elem.h"
 #include "hdet_internal.h"
+#include "hdet_lds.h"
 
 namespace {
 
 typedef float f16v __attribute__((ext_vector_type(16)));
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f4a __attribute__((ext_vector_type(4)));
 
 // 32 rows x 8 k of an operand as the four MFMAs' fragments.  KFAST: element (row, k) at [row * ld + k], else [k * ld + row].
 // `base` is uniform and points at (first row of the tile, k of the step); `lane_off` is the lane's own element offset.
@@ -262,6 +265,245 @@ __global__ __launch_bounds__(kThreads) void sgemm_kernel(const hdet_sgemm_args g
   sgemm_tile<FORM != kTN, FORM == kNT, WTM, WTN, WM, WN, WK, U>(g, epi, blockIdx.x, tx, ty, gridDim.x, part);
 }
 
+// ---- products of many tiles -----------------------------------------------------------------------------------------------------
+// Operand tiles go straight into LDS (hdet_lds.h), NST stages of TK k, where the wavefronts share them.  What bounds such a product when
+// wavefronts load their own fragments is the addresses: an operand contiguous along k costs a lane a row of its own, 32 lines a
+// load, each of which is fetched again for every 8 k.  LDS holds
+//  * an operand contiguous along k as [row][TK], the 16-byte chunks of a row XOR-permuted by the row: one 128-bit read a lane is four k of its row;
+//  * one contiguous along its rows as [k][ROWS], odd groups of four k with the halves of 64 rows exchanged: four 32-bit reads.
+// us, 4 replicas, fragments from global memory / through LDS:  512 x 4000, K = 256 85 / 50 (84 TFLOP/s);  512 x 1024, K = 256, both GELU outputs
+// 27.9 / 19.5;  512 x 768, K = 256 21.6 / 15.1;  512 x 256, K = 256 and 1024 14.8 / 12;  weight gradients 4000 x 256, K = 512 53 / 45, 1024 x 256 15.9 / 14.9;
+// 512 x 4096, K = 4096 428 / 321;  8 replicas, 1024 x 32000, K = 256 2459 / 1470.  Below two rounds of blocks some 6 us of each are launch, first
+// loads and last stores.  Three or four stages instead of two, fragments read one group ahead, 32 x 32 tiles with K in 4 in place of 64 x 32: the
+// same to 5 % slower; 128 x 64 tiles 2 to 60 % slower, for want of blocks.
+constexpr uint32_t kAbsent = 0x80000000u;   // offset beyond every extent the host lets through
+template <bool KMAJOR, int ROWS, int TK>
+struct stage_tile {
+  static constexpr int NI = ROWS * TK / (kThreads * 4), CPR = KMAJOR ? TK / 4 : ROWS / 4;     // loads a thread and stage, chunks a row
+  uint32_t off[NI], kstep;
+  int kofs[NI];
+  __device__ __forceinline__ void init(int row0, int rows, int64_t ld, int tid) {
+    kstep = KMAJOR ? TK * 4 : (uint32_t)(ld * TK * 4);
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int c = tid + i * kThreads, hi = c / CPR, lo = c % CPR;
+      if (KMAJOR) {
+        kofs[i] = (lo ^ (hi & 7)) * 4;
+        off[i] = row0 + hi < rows ? (uint32_t)(((row0 + hi) * ld + kofs[i]) * 4) : kAbsent;
+      } else {
+        const int row = row0 + (lo ^ (ROWS >= 64 ? (hi & 4) << 1 : 0)) * 4;
+        kofs[i] = hi;
+        off[i] = row < rows ? (uint32_t)((hi * ld + row) * 4) : kAbsent;
+      }
+    }
+  }
+  __device__ __forceinline__ void issue(hdet_rsrc rsrc, uint32_t addr, int kt, int kdim, int wave) const {
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+      lds_load16(rsrc, addr + (i * kThreads + wave * 64) * 16, kofs[i] + kt * TK < kdim ? off[i] + (uint32_t)kt * kstep : kAbsent);
+  }
+  // the four MFMAs' fragments of eight k (group q of the stage) and 32 rows from r0 on
+  static __device__ __forceinline__ void fragment(float (&v)[4], const float* tile, int r0, int q, int lane) {
+    if (KMAJOR) {
+      const f4a x = *reinterpret_cast<const f4a*>(tile + (r0 + (lane & 31)) * TK + (((2 * q + (lane >> 5)) ^ (lane & 7)) << 2));
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = x[j];
+    } else {
+      const int h = lane >> 5, row = (r0 + (lane & 31)) ^ (ROWS >= 64 ? h << 5 : 0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = tile[(8 * q + 4 * h + j) * ROWS + row];
+    }
+  }
+};
+
+// Block tile (32 WTM WM) x (32 WTN WN) by WM x WN x WK wavefronts of (32 WTM) x (32 WTN) each; with WK > 1 a stage's k are shared out.
+template <int WTM, int WTN, int WM, int WN, int WK, int NST> constexpr int stage_floats() { return NST * 32 * (WTM * WM + WTN * WN) * 32 * WK; }
+template <int FORM, int WTM, int WTN, int WM, int WN, int WK, int NST>
+__device__ __forceinline__ void sgemm_lds_tile(const hdet_sgemm_args& g, int epi, unsigned t, unsigned tx, unsigned ty, unsigned total, float* S) {
+  constexpr bool AK = FORM != kTN, BK = FORM == kNT;
+  constexpr int BM = 32 * WTM * WM, BN = 32 * WTN * WN, TK = 32 * WK, STAGE = (BM + BN) * TK, NW = WTM * WTN * 16;
+  static_assert(WM * WN * WK * 64 == kThreads, "four wavefronts");
+  static_assert(WK == 1 || kThreads * NW <= NST * STAGE, "the parts of a K split meet in the stages");
+  typedef stage_tile<AK, BM, TK> ta;
+  typedef stage_tile<BK, BN, TK> tb;
+  constexpr int LPT = ta::NI + tb::NI;
+  {
+    const unsigned x = t & 7u, rem = total & 7u;                      // as in sgemm_tile
+    t = x * (total >> 3) + (x < rem ? x : rem) + (t >> 3);
+  }
+  const unsigned bx = t % tx, by = (t / tx) % ty, bz = t / (tx * ty);
+  const hdet_batch_index bi = hdet_split_batch(bz, g.n1, g.n2);
+  const int z = bi.z0, tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wk = w % WK, wmn = w / WK, wm = (wmn / WN) * (32 * WTM), wn = (wmn % WN) * (32 * WTN);
+  const int m0 = by * BM, n0 = bx * BN;
+  const int64_t lda = AK ? g.a_rs : g.a_cs, ldb = BK ? g.b_cs : g.b_rs;
+  const hdet_rsrc ra = make_rsrc(g.a + hdet_batch_offset(bi, g.a_s), (uint32_t)((((AK ? g.m : g.k) - 1) * lda + (AK ? g.k : g.m)) * 4));
+  const hdet_rsrc rb = make_rsrc(g.b + hdet_batch_offset(bi, g.b_s), (uint32_t)((((BK ? g.n : g.k) - 1) * ldb + (BK ? g.k : g.n)) * 4));
+  const uint32_t s_addr = lds_addr_of(reinterpret_cast<const uint16_t*>(S));
+  ta la; tb lb;
+  la.init(m0, g.m, lda, tid);
+  lb.init(n0, g.n, ldb, tid);
+  const bool block_sums = !AK && g.rowsum && bx == 0, sums = block_sums && wmn % WN == 0;
+  // four sums over K, whichever wavefronts they are in: one long chain of additions is further from the exact sum (2-layer d = 256 transformer: 8.5e-7
+  // of the gradients, 6e-7 with four)
+  constexpr int NC = 4 / WK;
+  float rs[WTM][NC];
+  f16v chain[NC][WTM][WTN], (&acc)[WTM][WTN] = chain[0];
+#pragma unroll
+  for (int i = 0; i < WTM; ++i) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      rs[i][c] = 0.f;
+#pragma unroll
+      for (int j = 0; j < WTN; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) chain[c][i][j][e] = 0.f;
+    }
+  }
+  const int nk = (g.k + TK - 1) / TK;
+  auto load = [&](int kt, int s) {
+    la.issue(ra, s_addr + s * STAGE * 4, kt, g.k, w);
+    lb.issue(rb, s_addr + (s * STAGE + BM * TK) * 4, kt, g.k, w);
+  };
+#pragma unroll
+  for (int s = 0; s < NST - 1; ++s) load(s, s);
+  for (int kt0 = 0; kt0 < nk; kt0 += NST) {
+#pragma unroll
+    for (int s = 0; s < NST; ++s) {
+      if (kt0 + s >= nk) break;
+      wait_and_barrier<(NST - 2) * LPT>();                 // this stage has landed, and every wavefront has read the one before
+      load(kt0 + s + NST - 1, (s + NST - 1) % NST);
+      const float* at = S + s * STAGE;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        float a[WTM][4], b[WTN][4];
+#pragma unroll
+        for (int i = 0; i < WTM; ++i) ta::fragment(a[i], at, wm + 32 * i, 4 * wk + q, lane);
+#pragma unroll
+        for (int j = 0; j < WTN; ++j) tb::fragment(b[j], at + BM * TK, wn + 32 * j, 4 * wk + q, lane);
+        if (!AK && sums) {
+#pragma unroll
+          for (int i = 0; i < WTM; ++i) rs[i][q % NC] += (a[i][0] + a[i][1]) + (a[i][2] + a[i][3]);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int i = 0; i < WTM; ++i)
+#pragma unroll
+            for (int j = 0; j < WTN; ++j) chain[q % NC][i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][u], b[j][u], chain[q % NC][i][j], 0, 0, 0);
+      }
+    }
+  }
+#pragma unroll
+  for (int c = 1; c < NC; ++c)
+#pragma unroll
+    for (int i = 0; i < WTM; ++i)
+#pragma unroll
+      for (int j = 0; j < WTN; ++j) acc[i][j] += chain[c][i][j];
+  wait_and_barrier<0>();
+  // rows of A summed: the two halves of a group's k, then the parts of the K split
+  if (block_sums) {
+    if (sums) {
+#pragma unroll
+      for (int i = 0; i < WTM; ++i) {
+        float v = rs[i][0];
+#pragma unroll
+        for (int c = 1; c < NC; ++c) v += rs[i][c];
+        v += __shfl_xor(v, 32);
+        if (lane < 32) S[(wk * WM + wmn / WN) * (WTM * 32) + 32 * i + lane] = v;
+      }
+    }
+    __syncthreads();
+    if (tid < BM && m0 + tid < g.m) {
+      float v = S[tid];
+#pragma unroll
+      for (int p = 1; p < WK; ++p) v += S[p * BM + tid];
+      g.rowsum[(int64_t)z * g.rowsum_bs + m0 + tid] = v;
+    }
+    __syncthreads();
+  }
+  if (WK > 1) {
+    float* mine = S + (wmn * WK + wk) * (NW * 64) + lane;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) mine[q * 64] = acc[q / (16 * WTN)][(q / 16) % WTN][q % 16];
+    __syncthreads();
+  }
+  const float* all = S + wmn * WK * (NW * 64) + lane;
+  float* C = g.c + hdet_batch_offset(bi, g.c_s);
+  float* C2 = g.c2 + hdet_batch_offset(bi, g.c_s);
+  auto finish = [&](auto kind) {
+    constexpr int EPI = decltype(kind)::value;
+    constexpr bool kBias = EPI == HDET_SEPI_BIAS || EPI == HDET_SEPI_BIAS_RELU || EPI == HDET_SEPI_BIAS_GELU || EPI == HDET_SEPI_BIAS_RESID;
+    constexpr bool kMask = EPI == HDET_SEPI_MASK || EPI == HDET_SEPI_BIAS_RESID || EPI == HDET_SEPI_GELUGRAD;
+    constexpr int PER = NW / WK, CH = PER < 8 ? PER : 8;
+    float bias[WTN];
+#pragma unroll
+    for (int j = 0; j < WTN; ++j) bias[j] = kBias && n0 + wn + 32 * j + (lane & 31) < g.n ? g.bias[(int64_t)z * g.bias_bs + n0 + wn + 32 * j + (lane & 31)] : 0.f;
+#pragma unroll
+    for (int t0 = 0; t0 < PER; t0 += CH) {
+      float x[CH];
+#pragma unroll
+      for (int u = 0; u < CH; ++u) {
+        const int q = wk * PER + t0 + u, e = q % 16;
+        const int row = m0 + wm + 32 * (q / (16 * WTN)) + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3), col = n0 + wn + 32 * ((q / 16) % WTN) + (lane & 31);
+        if (kMask && row < g.m && col < g.n) x[u] = g.mask[(int64_t)z * g.mask_bs + (int64_t)row * g.mask_rs + col];
+      }
+#pragma unroll
+      for (int u = 0; u < CH; ++u) {
+        const int q = wk * PER + t0 + u, e = q % 16;
+        float v;
+        if (WK > 1) {
+          v = all[q * 64];
+#pragma unroll
+          for (int p = 1; p < WK; ++p) v += all[(p * NW + q) * 64];
+        } else {
+          const int r = t0 + u;
+          v = acc[r / (16 * WTN)][(r / 16) % WTN][r % 16];
+        }
+        const int row = m0 + wm + 32 * (q / (16 * WTN)) + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3), col = n0 + wn + 32 * ((q / 16) % WTN) + (lane & 31);
+        if (row >= g.m || col >= g.n) continue;
+        const int64_t to = (int64_t)row * g.c_rs + col;
+        if (kBias) v += WK > 1 ? bias[(q / 16) % WTN] : bias[((t0 + u) / 16) % WTN];
+        if (EPI == HDET_SEPI_BIAS_RELU) v = v > 0.f ? v : 0.f;
+        if (EPI == HDET_SEPI_MASK) v = x[u] > 0.f ? v : 0.f;
+        if (EPI == HDET_SEPI_BIAS_RESID) v += x[u];
+        if (EPI == HDET_SEPI_GELUGRAD) v *= hdet_gelu_tanh_grad(x[u]);
+        C[to] = v;
+        if (EPI == HDET_SEPI_BIAS_GELU) C2[to] = hdet_gelu_tanh(v);
+      }
+    }
+  };
+  switch (epi) {
+    case HDET_SEPI_NONE: finish(std::integral_constant<int, HDET_SEPI_NONE>{}); break;
+    case HDET_SEPI_BIAS: if (AK && BK) finish(std::integral_constant<int, HDET_SEPI_BIAS>{}); break;
+    case HDET_SEPI_BIAS_RELU: if (AK && BK) finish(std::integral_constant<int, HDET_SEPI_BIAS_RELU>{}); break;
+    case HDET_SEPI_BIAS_GELU: if (AK && BK) finish(std::integral_constant<int, HDET_SEPI_BIAS_GELU>{}); break;
+    case HDET_SEPI_BIAS_RESID: if (AK && BK) finish(std::integral_constant<int, HDET_SEPI_BIAS_RESID>{}); break;
+    case HDET_SEPI_MASK: if (AK && !BK) finish(std::integral_constant<int, HDET_SEPI_MASK>{}); break;
+    case HDET_SEPI_GELUGRAD: if (AK && !BK) finish(std::integral_constant<int, HDET_SEPI_GELUGRAD>{}); break;
+  }
+}
+
+template <int FORM, int WTM, int WTN, int WM, int WN, int WK, int NST>
+__global__ __launch_bounds__(kThreads) void sgemm_lds_kernel(const hdet_sgemm_args g, int epi, unsigned tx, unsigned ty) {
+  __shared__ __attribute__((aligned(1024))) float S[stage_floats<WTM, WTN, WM, WN, WK, NST>()];
+  sgemm_lds_tile<FORM, WTM, WTN, WM, WN, WK, NST>(g, epi, blockIdx.x, tx, ty, gridDim.x, S);
+}
+// The two tiles: 64 x 64, and 64 x 32 whose wavefronts share K
+#define HDET_SGEMM_LDS(WIDE, CALL) \
+  if (WIDE) { CALL(1, 1, 2, 2, 1, 2); } else { CALL(1, 1, 2, 1, 2, 2); }
+
+// Whether an operand is made of whole 16-byte chunks, 16-byte aligned, within the 2 GiB that a descriptor's offsets reach (with a stage's step beyond)
+bool chunked(const float* p, bool kmajor, int rows, int k, int64_t ld, const int64_t* bs) {
+  const int64_t ext = ((kmajor ? rows : k) + 128) * ld + 256;
+  return ((uintptr_t)p & 15) == 0 && (ld & 3) == 0 && ((bs[0] | bs[1] | bs[2]) & 3) == 0 && ((kmajor ? k : rows) & 3) == 0 && ld > 0 && ext < (int64_t)1 << 29;
+}
+template <int FORM>
+bool lds_eligible(const hdet_sgemm_args& g) {
+  return chunked(g.a, FORM != kTN, g.m, g.k, FORM != kTN ? g.a_rs : g.a_cs, g.a_s) && chunked(g.b, FORM == kNT, g.n, g.k, FORM == kNT ? g.b_cs : g.b_rs, g.b_s);
+}
+
 constexpr int64_t kMaxBlocks = 0xffffff;      // blocks of 256 threads in a grid of less than 2^32 threads
 struct tiles { unsigned x, y, total; };
 template <int WTM, int WTN, int WM, int WN>
@@ -270,7 +512,8 @@ tiles tile_grid(const hdet_sgemm_args& g, int batch) {
   return {x, y, x * y * (unsigned)batch};
 }
 
-// Tile and K split by the number of blocks a launch would have, b(tm x tn) = tiles over the whole batch, on 256 CUs
+// Tile and K split by the number of blocks a launch would have, b(tm x tn) = tiles over the whole batch, on 256 CUs.  Through LDS there are two
+// tiles, 64 x 32 where this says so and 64 x 64 for all larger ones; the figures are those of fragments from global memory
 // (microseconds over 8 replicas or as given, same machine; chosen | other candidates):
 //   few tiles: 32 x 32, K in 4.        128 x 64, K = 64, 4 items: 3.9 | 64 x 32 4.3 | 64 x 64 5.2 (K in 8: 4.3, in 16: 4.1)
 //   up to one 64 x 32 block per CU (and at least 5/8 of them), K in 4:
@@ -330,6 +573,30 @@ __global__ __launch_bounds__(kThreads) void sgemm_pair_kernel(const hdet_sgemm_a
 #undef OTHER
 }
 
+// The same for two products of many tiles (sgemm_lds_tile): what the launch, the first loads and the last stores take is paid once, and one product's
+// blocks work while the other's wait.  wcfg, ocfg: 64 x 64 tiles or 64 x 32.  One after the other / together, us, 4 replicas: 4000 outputs of 256, 512 rows
+// 93 / 85;  1024 of 256 27.7 / 25.7;  256 of 1024 through the GELU 35.3 / 30.8;  768 of 256 26.9 / 23.1.
+template <bool NT>
+__global__ __launch_bounds__(kThreads) void sgemm_lds_pair_kernel(const hdet_sgemm_args w, const hdet_sgemm_args o, int epi, const pair_grid pg,
+                                                                 const hdet_loss_args loss) {
+  constexpr int kFloats = std::max(stage_floats<1, 1, 2, 2, 1, 2>(), stage_floats<1, 1, 2, 1, 2, 2>());
+  __shared__ __attribute__((aligned(1024))) float S[kFloats];
+  unsigned t = blockIdx.x;
+  if (t >= pg.wt + pg.ot) {
+    hdet_reduce_loss(loss.row_loss, loss.rows, loss.ctrl, (int)(t - pg.wt - pg.ot), reinterpret_cast<double*>(S));
+    return;
+  }
+  const unsigned first = pg.wgrad_first ? pg.wt : pg.ot;
+  const bool wgrad = (t < first) == (pg.wgrad_first != 0);
+  if (t >= first) t -= first;
+#define WGRAD(WTM, WTN, WM, WN, WK, NST) sgemm_lds_tile<kTN, WTM, WTN, WM, WN, WK, NST>(w, HDET_SEPI_NONE, t, pg.wx, pg.wy, pg.wt, S)
+#define OTHER(WTM, WTN, WM, WN, WK, NST) sgemm_lds_tile<NT ? kNT : kNN, WTM, WTN, WM, WN, WK, NST>(o, epi, t, pg.ox, pg.oy, pg.ot, S)
+  if (wgrad) { HDET_SGEMM_LDS(pg.wcfg, WGRAD) }
+  else { HDET_SGEMM_LDS(pg.ocfg, OTHER) }
+#undef WGRAD
+#undef OTHER
+}
+
 template <int FORM>
 hipError_t launch_form(const hdet_sgemm_args& g, int epi, int batch, hipStream_t s) {
   const int cfg = choose_cfg([&](int tm, int tn) { return count_blocks(g, batch, tm, tn); }, FORM != kTN);
@@ -338,6 +605,16 @@ hipError_t launch_form(const hdet_sgemm_args& g, int epi, int batch, hipStream_t
   {                                                                                                                              \
     const tiles t = tile_grid<WTM, WTN, WM, WN>(g, batch);                                                                       \
     hipLaunchKernelGGL((sgemm_kernel<FORM, WTM, WTN, WM, WN, WK, U>), dim3(t.total), dim3(kThreads), 0, s, g, epi, t.x, t.y);    \
+  }
+  if (cfg >= kCfg64x32 && lds_eligible<FORM>(g)) {
+#define LDS(WTM, WTN, WM, WN, WK, NST)                                                                                           \
+  {                                                                                                                              \
+    const tiles t = tile_grid<WTM, WTN, WM, WN>(g, batch);                                                                       \
+    hipLaunchKernelGGL((sgemm_lds_kernel<FORM, WTM, WTN, WM, WN, WK, NST>), dim3(t.total), dim3(kThreads), 0, s, g, epi, t.x, t.y); \
+  }
+    HDET_SGEMM_LDS(cfg >= kCfg64, LDS)
+#undef LDS
+    return hipGetLastError();
   }
   switch (cfg) { HDET_SGEMM_SMALL(CALL) HDET_SGEMM_LARGE(CALL) }
 #undef CALL
@@ -357,6 +634,15 @@ hipError_t launch_pair(const hdet_sgemm_args& w, int wb, int wcfg, const hdet_sg
 #undef OTHER
   const pair_grid pg = {tw.x, tw.y, tw.total, to.x, to.y, to.total, w.k >= o.k, wcfg, ocfg};
   hipLaunchKernelGGL(sgemm_pair_kernel<NT>, dim3(tw.total + to.total + (unsigned)loss.n_replicas), dim3(kThreads), lds, s, w, o, epi, pg, loss);
+  return hipGetLastError();
+}
+
+template <bool NT>
+hipError_t launch_lds_pair(const hdet_sgemm_args& w, int wb, bool wwide, const hdet_sgemm_args& o, int epi, int ob, bool owide,
+                           const hdet_loss_args& loss, hipStream_t s) {
+  const tiles tw = wwide ? tile_grid<1, 1, 2, 2>(w, wb) : tile_grid<1, 1, 2, 1>(w, wb), to = owide ? tile_grid<1, 1, 2, 2>(o, ob) : tile_grid<1, 1, 2, 1>(o, ob);
+  const pair_grid pg = {tw.x, tw.y, tw.total, to.x, to.y, to.total, w.k >= o.k, wwide, owide};
+  hipLaunchKernelGGL(sgemm_lds_pair_kernel<NT>, dim3(tw.total + to.total + (unsigned)loss.n_replicas), dim3(kThreads), 0, s, w, o, epi, pg, loss);
   return hipGetLastError();
 }
 
@@ -396,6 +682,11 @@ hipError_t hdet_launch_sgemm_pair(const hdet_sgemm_args& wgrad, int wgrad_batch,
   const int ocfg = ob ? choose_cfg([&](int tm, int tn) { return count_blocks(o, ob, tm, tn); }, true) : kCfg32;
   if (wcfg <= kCfg64x32 && ocfg <= kCfg64x32)
     return other_nt ? launch_pair<true>(w, wgrad_batch, wcfg, o, epi, ob, ocfg, l, s) : launch_pair<false>(w, wgrad_batch, wcfg, o, epi, ob, ocfg, l, s);
+  if (ob && lds_eligible<kTN>(w) && (other_nt ? lds_eligible<kNT>(o) : lds_eligible<kNN>(o)) &&
+      count_blocks(w, wgrad_batch, 64, 32) + count_blocks(o, ob, 64, 32) <= kMaxBlocks) {
+    const bool ww = wcfg >= kCfg64, ow = ocfg >= kCfg64;
+    return other_nt ? launch_lds_pair<true>(w, wgrad_batch, ww, o, epi, ob, ow, l, s) : launch_lds_pair<false>(w, wgrad_batch, ww, o, epi, ob, ow, l, s);
+  }
   if (hipError_t e = launch_form<kTN>(w, HDET_SEPI_NONE, wgrad_batch, s)) return e;
   if (ob)
     if (hipError_t e = other_nt ? launch_form<kNT>(o, epi, ob, s) : launch_form<kNN>(o, epi, ob, s)) return e;
