@@ -312,6 +312,22 @@ bool hdet_attn_fusable(int seq_len, int d_model, int heads, int batch);     // h
 hipError_t hdet_launch_attn_fwd(const hdet_attn_desc& a, hipStream_t stream);
 hipError_t hdet_launch_attn_bwd(const hdet_attn_desc& a, hipStream_t stream);
 
+// Causal attention in fp32 (hdet_attention_f32.hip): head size a multiple of 8 up to 64, sequences up to 512
+struct hdet_attn_f32_desc {
+  const float* qkv;         // [N][B][S][3 d_model]: q | k | v
+  float* a;                 // forward output, read by the backward: [N][B][S][d_model]
+  float* p;                 // probabilities, written by the forward (32 x 32 blocks at and below the diagonal): [N][B][heads][S][S]
+  const float* da;          // backward: gradient at a
+  float* dqkv;              // backward output, layout of qkv
+  const hdet_ctrl* ctrl;
+  int temp_channel;         // attention-temperature channel or -1
+  float scale;              // 1 / sqrt(d_head)
+  int n_replicas, batch, seq_len, heads, d_model;
+};
+bool hdet_attn_f32_fusable(int seq_len, int d_model, int heads);
+hipError_t hdet_launch_attn_f32_fwd(const hdet_attn_f32_desc& a, hipStream_t stream);
+hipError_t hdet_launch_attn_f32_bwd(const hdet_attn_f32_desc& a, hipStream_t stream);
+
 // ---------------------------------------------------------------------------------------
 // Host handle
 // ---------------------------------------------------------------------------------------

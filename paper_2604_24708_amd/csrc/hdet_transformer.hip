@@ -961,7 +961,7 @@ struct hdet_tf_plan {
   float* att_ndot;
   unsigned long long* tok_sorted;            // [N][M] keys (token id, row) in ascending order
   float* tok_seg;                            // [N][M][d] partial rows of the token-embedding gradient
-  bool fused_attn;                           // bf16, head size 64, S a multiple of 64
+  bool fused_attn;                           // bf16: head size 64, S a multiple of 64; fp32: hdet_attn_f32_fusable
   bool head_loss;            // the loss is formed inside the output layer's product (tf_head_loss)
   float* part;               // partial column sums, one [N][row chunks][cols] array (two for LayerNorm) per reduction
   int nrc;                   // row chunks of the two-stage column sums
@@ -1022,13 +1022,17 @@ static size_t tf_carve(hdet_tf_plan* p, char* base) {
   return off;
 }
 
+static bool tf_attn_fusable(const hdet_tf_plan* p) {
+  return p->bf16 ? hdet_attn_fusable(p->S, p->d, p->nh, p->B) : hdet_attn_f32_fusable(p->S, p->d, p->nh);
+}
+
 static void tf_dims(hdet_tf_plan* p, const hdet_config& cfg) {
   p->cfg = cfg;
   p->bf16 = cfg.precision == HDET_BF16_GEMM_FP32_MASTER;
   p->N = cfg.n_replicas; p->B = cfg.dims.batch; p->S = cfg.dims.seq_len; p->M = p->B * p->S;
   p->d = cfg.dims.d_model; p->nh = cfg.dims.n_heads; p->dh = p->d / p->nh; p->ff = cfg.dims.d_ff;
   p->V = cfg.dims.vocab; p->L = cfg.dims.n_blocks;
-  p->fused_attn = p->bf16 && hdet_attn_fusable(p->S, p->d, p->nh, p->B);
+  p->fused_attn = tf_attn_fusable(p);
 }
 
 int64_t hdet_tf_param_count(const hdet_config& cfg) {
@@ -1176,7 +1180,7 @@ void hdet_tf_destroy(hdet_tf_plan* p) { delete p; }
 void hdet_tf_summed_slices(const hdet_tf_plan* p, std::vector<std::pair<int64_t, int64_t>>* out) { *out = p->summed; }
 
 void hdet_tf_set_fused_attention(hdet_tf_plan* p, bool on) {
-  p->fused_attn = on && p->bf16 && hdet_attn_fusable(p->S, p->d, p->nh, p->B);
+  p->fused_attn = on && tf_attn_fusable(p);
 }
 
 namespace {
@@ -1420,6 +1424,13 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
     ad.n_replicas = N; ad.batch = B; ad.seq_len = S; ad.heads = nh; ad.d_model = d;
     return ad;
   };
+  auto attn_f32_desc = [&](int l) {
+    hdet_attn_f32_desc ad;
+    ad.qkv = (const float*)p->qkv[l]; ad.a = (float*)p->a[l]; ad.p = (float*)p->p[l]; ad.da = (const float*)p->dtmp; ad.dqkv = (float*)p->dqkv;
+    ad.ctrl = ctrl; ad.temp_channel = p->temp_channel; ad.scale = scale;
+    ad.n_replicas = N; ad.batch = B; ad.seq_len = S; ad.heads = nh; ad.d_model = d;
+    return ad;
+  };
   const int64_t act_d[3] = {(int64_t)M * d, 0, 0}, act_3d[3] = {(int64_t)M * 3 * d, 0, 0}, act_ff[3] = {(int64_t)M * ff, 0, 0},
                 act_v[3] = {(int64_t)M * V, 0, 0}, plane[3] = {ps, 0, 0};
 
@@ -1446,8 +1457,8 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
     launch_ln_fwd<T>(p, p->x_in[l], o.ln1_g, o.ln1_b, p->h1[l], p->st1_mean[l], p->st1_rstd[l], s);
     TF_CHECK(gemm<T>(p, NT, act(p->h1[l], d), wt(o.w_qkv, d), p->qkv[l], 3 * d, act_3d, true, M, 3 * d, d, 1, 1, theta + o.b_qkv, ps, s));
     if (p->fused_attn) {
-      hdet_attn_desc ad = attn_desc(l);
-      TF_CHECK(hdet_launch_attn_fwd(ad, s));
+      if constexpr (f32) TF_CHECK(hdet_launch_attn_f32_fwd(attn_f32_desc(l), s));
+      else TF_CHECK(hdet_launch_attn_fwd(attn_desc(l), s));
     } else {
       {   // scores = q k^T per (replica, sequence, head)
         const mat sc = head_sq(p->scores);
@@ -1639,7 +1650,9 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
       TF_CHECK(wgrad(dob, d, p->a[l], d, o.w_o));
     }
     bool bqkv_done = false;                        // stage 1 of the qkv bias gradient comes from the attention's backward kernels
-    if (p->fused_attn) {
+    if (f32 && p->fused_attn) {
+      TF_CHECK(hdet_launch_attn_f32_bwd(attn_f32_desc(l), s));
+    } else if (p->fused_attn) {
       hdet_attn_desc ad = attn_desc(l);
       if (S % kColsumRows == 0)
         for (const colsum_job& j : p->jobs)
