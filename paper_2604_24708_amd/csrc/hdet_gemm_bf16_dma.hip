@@ -644,7 +644,7 @@ __global__ __launch_bounds__(512, 2) void hdet_bgemm_alt_kernel(const hdet_bgemm
 //  * Stores count in vmcnt with the loads: they are always issued (rows and columns that do not exist lie outside the descriptor), and the first
 //    K step of the next tile waits for the loads before them, not for them (kStores).
 //  * The group that is a turn behind ends its tile as soon as its products are done, beside the other group, not after it.
-// Built for the output layer with its loss (hdet_launch_head_loss), whose two passes cost less than writing and reading fp32 logits:  K = 512,
+// Built for the output layer with its loss (hdet_launch_head_loss; products with a bias take it too, launch_shape), whose two passes cost less than writing and reading fp32 logits:  K = 512,
 // 4096 x 32000, 8 replicas, 1502 to 1575 us of product and 1152 of loss kernel -> 918 (statistics) + 19 (merge) + 1190 (gradient).  Of a tile's
 // 14.7 and 19 us the main loop takes 11 (1.6 PFLOP/s, 70 % of the matrix cores' cycles), exponentials 3.4, stores 3.5.  Not kept, gradient pass:
 // results through LDS 1216 (rows of bf16), past the L2 1358 (pieces of 16 bytes), both groups' ends in turn 1240; the kernel above with these
@@ -655,14 +655,18 @@ __global__ __launch_bounds__(512, 2) void hdet_bgemm_walk_kernel(const hdet_bgem
   constexpr bool kStat = EPI == HDET_EPI_XENT_STAT, kGrad = EPI == HDET_EPI_XENT_GRAD;
   constexpr int kStores = kStat ? 0 : 16;
   constexpr int kBiasAt = 8 * HALF * 2, kRowsAt = kBiasAt + 2 * TN * 4;           // bytes: bias [2][TN], then what the epilogue needs
-  constexpr int kExtra = 2 * TN * 4 + (kStat ? 4 * TM * 8 : 3 * TM * 4);
+  constexpr int kExtra = 2 * TN * 4 + (kStat ? 4 * TM * 8 : kGrad ? 3 * TM * 4 : 0);
   __shared__ __attribute__((aligned(1024))) uint16_t S[8 * HALF + kExtra / 2];
   typedef lds_tile<true, 128, 512, TK> ta;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wn = (wave % 4) * 64, hr = (wave / 4) * 64, wm = (wave / 4) * 128;
-  // what a lane derives from its number outside the K loop is computed where it is used: kept over the tiles it would spill
-  auto fresh = [](int x) { asm volatile("" : "+v"(x)); return x; };
+  // what a lane derives from its number outside the K loop is computed where it is used, the number itself too: kept over the tiles it would spill
+  auto lane_now = [] {
+    int x;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(x));
+    return x;
+  };
   const uint32_t s_addr = lds_addr_of(S);
   float* const s_bias = reinterpret_cast<float*>(S) + kBiasAt / 4;
   float* const s_rows = reinterpret_cast<float*>(S) + kRowsAt / 4;
@@ -695,10 +699,10 @@ __global__ __launch_bounds__(512, 2) void hdet_bgemm_walk_kernel(const hdet_bgem
       lds_load16(r, at + (i * 512 + wave * 64) * 16, ck + kt * TK < g.k ? off_b + (uint32_t)(kt * 128 + 64 * i * g.ldb * 2) : kAbsent);
   };
   auto load_bias = [&](const tile& t, int slot) {
-    if (wave < 4) lds_load4(t.rbias, s_addr + kBiasAt + slot * TN * 4 + wave * 256, (uint32_t)fresh(tid) * 4u);
+    if (wave < 4) lds_load4(t.rbias, s_addr + kBiasAt + slot * TN * 4 + wave * 256, (uint32_t)(wave * 64 + lane_now()) * 4u);
   };
   auto load_rows = [&](const tile& t) {                          // maximum, factor and label of the tile's rows
-    const int ln = fresh(lane);
+    const int ln = lane_now();
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const int q = wave + 8 * u, row = t.m0 + (q & 3) * 64 + ln;
@@ -750,7 +754,7 @@ __global__ __launch_bounds__(512, 2) void hdet_bgemm_walk_kernel(const hdet_bgem
   };
   // a group's four wavefronts have left max and sum of their 64 columns for the group's 128 rows; 32 rows each
   auto put_stats = [&](const auto& t) {
-    const int ln = fresh(lane), tr = wm + (wave % 4) * 32 + (ln & 31);
+    const int ln = lane_now(), tr = wm + (wave % 4) * 32 + (ln & 31);
     const float2* buf = reinterpret_cast<const float2*>(s_rows) + tr;
     float2 p[4];
 #pragma unroll
@@ -763,7 +767,7 @@ __global__ __launch_bounds__(512, 2) void hdet_bgemm_walk_kernel(const hdet_bgem
   };
   auto finish = [&](const tile& t) {
     __builtin_amdgcn_sched_barrier(0);
-    const int ln = fresh(lane), cg = ln >> 4, lr = ln & 15;
+    const int ln = lane_now(), cg = ln >> 4, lr = ln & 15;
     if constexpr (kStat) {
       float mx[8], sum[8];
 #pragma unroll
@@ -833,6 +837,10 @@ __global__ __launch_bounds__(512, 2) void hdet_bgemm_walk_kernel(const hdet_bgem
 #pragma unroll
           for (int j = 0; j < 4; ++j) csum[j] += v[j];
         }
+        if constexpr (!kGrad) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) v[j] = acc[i][j];
+        }
         unsigned d[4][2];
 #pragma unroll
         for (int j = 0; j < 4; ++j) { d[j][0] = hdet_bf16_pack(v[j][0], v[j][1]); d[j][1] = hdet_bf16_pack(v[j][2], v[j][3]); }
@@ -876,7 +884,7 @@ __global__ __launch_bounds__(512, 2) void hdet_bgemm_walk_kernel(const hdet_bgem
   for (bool begun = false;; begun = true) {
     tile nxt;
     asm volatile("" : "+v"(off_a), "+v"(off_b));
-    const int cg = fresh(lane) >> 4;
+    const int cg = lane_now() >> 4;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       bias[j] = *reinterpret_cast<const f4*>(s_bias + slot * TN + wn + j * 16 + cg * 4);
@@ -1047,6 +1055,20 @@ template <int EPI> constexpr float kEpiTime =
     : EPI == HDET_EPI_MASK_BF16 || EPI == HDET_EPI_BIAS_RESID_BF16 || EPI == HDET_EPI_BIAS_GELU_BF16 ? 15.f
     : EPI == HDET_EPI_F32 || EPI == HDET_EPI_BIAS_F32 ? 12.f : EPI == HDET_EPI_BIAS_RELU_BF16 ? 9.f : 8.f;
 
+// What hdet_bgemm_walk_kernel asks for beyond the LDS-direct kernels: whole groups of 8 columns, results and their rows 16-byte aligned, four K steps
+bool walkable(const hdet_bgemm_args& g) {
+  return g.n1 * g.n2 == 1 && g.k >= 192 && (g.n & 7) == 0 && ((g.ldc | g.c_s[0]) & 7) == 0 &&
+         (reinterpret_cast<uintptr_t>(g.c) & 15) == 0 && g.ldc < 1 << 22 && g.m < 1 << 28 &&
+         ((int64_t)g.m + 256) * g.lda * 2 < (int64_t)1 << 31 && ((int64_t)g.n + 256) * g.ldb * 2 < (int64_t)1 << 31;
+}
+int tile_group_of(unsigned columns) { return columns >= 64 ? 4 : columns >= 12 ? 2 : 1; }
+template <int EPI>
+void launch_walk(hdet_bgemm_args g, int batch, hipStream_t s) {
+  const unsigned gx = (g.n + 255) / 256, gy = (g.m + 255) / 256, total = gx * gy * (unsigned)batch, cus = (unsigned)compute_units();
+  g.tile_group = tile_group_of(gx);
+  hipLaunchKernelGGL(hdet_bgemm_walk_kernel<EPI>, dim3(total < cus ? total : cus), dim3(512), 0, s, g, gx, gy, total);
+}
+
 template <bool AK, bool BK, int EPI>
 hipError_t launch_shape(const hdet_bgemm_args& g, int batch, hipStream_t s) {
   constexpr bool wgrad = !AK && !BK, update = EPI == HDET_EPI_ADAMW;
@@ -1080,7 +1102,7 @@ hipError_t launch_shape(const hdet_bgemm_args& g, int batch, hipStream_t s) {
     // operand tile of A and none of B; walking groups of 4 (2) tile rows column by column cuts the operand bytes its L2
     // has to fetch by up to two thirds (head product of the transformer, 125 tile columns: 1505 us row by row, 1346 in groups of 4).
     // Updates go row by row: what they stream is theta and the moments (4096 x 4096 x 8, K = 256: 638 us, 668 in groups of 2).
-    ga.tile_group = update ? 1 : grid.x >= 64 ? 4 : grid.x >= 12 ? 2 : 1;
+    ga.tile_group = update ? 1 : tile_group_of(grid.x);
     hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, ga);
   };
 #define HDET_TILE(SHAPE, THREADS, KERNEL, ...)                                                        \
@@ -1097,7 +1119,16 @@ hipError_t launch_shape(const hdet_bgemm_args& g, int batch, hipStream_t s) {
       if (g.k >= 512) HDET_TILE(kDeep, 256, hdet_bgemm_dma_kernel, 128, 128, 2, 2, 4, 64,);
       else HDET_TILE(kSmall, 256, hdet_bgemm_dma_kernel, 128, 128, 2, 2, 2, 64,);
     }
-    else if (long_logits || (t_alt <= t_pair && t_alt <= t_small && t_alt <= t_long)) HDET_TILE(kAlternating, 512, hdet_bgemm_alt_kernel, );
+    else if (long_logits || (t_alt <= t_pair && t_alt <= t_small && t_alt <= t_long)) {
+      // From two rounds of tiles on a product with bias goes to blocks that walk over them: 4096 x 1536, K = 512, 8 items (3 rounds) 63 -> 57 us, 8192 x 3072,
+      // K = 1024 (12) 376 -> 346.  With both GELU outputs, twice the stores in pieces of 16 bytes, K = 512 104 -> 106, K = 1024 629 -> 616: left as it was.
+      bool walk = false;
+      if constexpr (EPI == HDET_EPI_BIAS_BF16) {
+        walk = walkable(g) && (int64_t)((g.m + 255) / 256) * ((g.n + 255) / 256) * batch >= 2 * (int64_t)cus;
+        if (walk) launch_walk<EPI>(g, batch, s);
+      }
+      if (!walk) HDET_TILE(kAlternating, 512, hdet_bgemm_alt_kernel, );
+    }
     else if (t_pair <= t_small && t_pair <= t_long)
       HDET_TILE(kPair, 512, hdet_bgemm_dma_kernel, 256, 128, 4, 2, 3, 32,);
     else if (t_small <= t_long) HDET_TILE(kSmall, 256, hdet_bgemm_dma_kernel, 128, 128, 2, 2, 2, 64,);
@@ -1175,9 +1206,7 @@ hipError_t hdet_launch_bgemm_dma(const hdet_bgemm_args& g_in, bool a_kmajor, boo
 }
 
 bool hdet_head_loss_eligible(const hdet_bgemm_args& g, int batch) {
-  const int64_t ext = ((int64_t)g.m + 256) * g.lda * 2, b_ext = ((int64_t)g.n + 256) * g.ldb * 2;
-  return g.n1 * g.n2 == 1 && hdet_bgemm_dma_eligible(g, true, true, HDET_EPI_BIAS_BF16) && ext < (int64_t)1 << 31 && b_ext < (int64_t)1 << 31 &&
-         g.m < 1 << 28 && g.k >= 192 && (g.n & 7) == 0 && ((g.ldc | g.c_s[0]) & 7) == 0 && (reinterpret_cast<uintptr_t>(g.c) & 15) == 0 && g.ldc < 1 << 22;
+  return walkable(g) && hdet_bgemm_dma_eligible(g, true, true, HDET_EPI_BIAS_BF16);
 }
 
 size_t hdet_head_loss_scratch(int m, int n, int batch) {
@@ -1187,7 +1216,7 @@ size_t hdet_head_loss_scratch(int m, int n, int batch) {
 hipError_t hdet_launch_head_loss(const hdet_bgemm_args& g_in, int batch, void* scratch, hipStream_t s) {
   hdet_bgemm_args g = g_in;
   if (!hdet_head_loss_eligible(g, batch) || !scratch || !g.xent.labels || !g.xent.row_loss) return hipErrorInvalidValue;
-  const unsigned gx = (g.n + 255) / 256, gy = (g.m + 255) / 256, total = gx * gy * (unsigned)batch;
+  const unsigned gx = (g.n + 255) / 256;
   const size_t rows = (size_t)batch * g.m;
   char* at = (char*)scratch;
   g.xent.part = (float2*)at; at += rows * gx * sizeof(float2);
@@ -1195,10 +1224,8 @@ hipError_t hdet_launch_head_loss(const hdet_bgemm_args& g_in, int batch, void* s
   g.xent.row_maxl = (float*)at; at += rows * sizeof(float);
   g.xent.row_a = (float*)at;
   g.xent.invb = 1.f / (float)g.m;
-  g.tile_group = gx >= 64 ? 4 : gx >= 12 ? 2 : 1;
-  const unsigned cus = (unsigned)compute_units(), blocks = total < cus ? total : cus;
-  hipLaunchKernelGGL(hdet_bgemm_walk_kernel<HDET_EPI_XENT_STAT>, dim3(blocks), dim3(512), 0, s, g, gx, gy, total);
+  launch_walk<HDET_EPI_XENT_STAT>(g, batch, s);
   hipLaunchKernelGGL(hdet_head_rows_kernel, dim3((g.m + 63) / 64, batch), dim3(256), 0, s, g.xent, g.m, (int)gx);
-  hipLaunchKernelGGL(hdet_bgemm_walk_kernel<HDET_EPI_XENT_GRAD>, dim3(blocks), dim3(512), 0, s, g, gx, gy, total);
+  launch_walk<HDET_EPI_XENT_GRAD>(g, batch, s);
   return hipGetLastError();
 }

@@ -39,3 +39,19 @@ def test_loss_and_gradients(n, batch, cfg, compared):
         assert abs(losses[r] - ref_losses[i]) <= 1e-3
         check_bf16_gradients(cfg, got[r, :run.P], ref[i], 4e-2, ("head loss", cfg["vocab"], r))
     run.close()
+
+
+def test_bias_product_of_several_rounds():
+    """qkv of 3500 x 1584 over K = 528 in 686 tiles: rows, columns and K end inside the last tiles and steps of blocks that walk over them."""
+    cfg, n, batch = dict(n_blocks=1, d_model=528, n_heads=8, d_ff=64, seq_len=70, vocab=96), 7, 50
+    run = TfRun(base(n_replicas=n), cfg, batch, bf16=True)
+    ids, tgt, losses = run.forward_backward(1)
+    r = n - 1
+    run.n = 1
+    run.orc.dropout_table = lambda: np.zeros(1)
+    run.orc.label_smoothing_table = lambda: np.zeros(1)
+    run.orc.attn_temp_table = lambda: np.ones(1)
+    ref_loss, ref = run.oracle_grads(run.orc.theta[r:], ids[r:], tgt[r:], 1)
+    assert abs(losses[r] - ref_loss[0]) <= 1e-3
+    check_bf16_gradients(cfg, run.g.cpu().numpy()[r, :run.P], ref[0], 4e-2, ("walk", r))
+    run.close()
