@@ -1078,22 +1078,20 @@ static hdet_bgemm_args head_args(const hdet_tf_plan* p) {
   return g;
 }
 
-// Whether it is: the second product costs 2 K operations a logit, the logits it saves 8 bytes written and read and, below 2048 classes, the
-// wavefront-a-row loss kernel.  Blocks take whole tiles of 256 x 256, so that a last round of few tiles counts in full.  us, product with logits
-// and loss kernel / two products (replicas, rows, K, classes):
-//   classes >= 2048:  8 4096 256 32000 2211 / 1636;  8 4096 512 32000 2654 / 2127, 12000 958 / 850, 4096 318 / 282;  640, 32000 2973 / 2740;
-//     768, 32000 3019 / 3116;  1024, 8000 843 / 906;  two to four rounds: 4 2048 512 4000 92 / 86, 2 2048 512 7000 79 / 83, 9000 104 / 111,
-//     3 4096 256 2048 74 / 63, 5 2048 384 2560 91 / 71;  fewer: 2 1024 512 12000 65 / 78, 4000 28 / 44
-//   below:  8 4096 512 2000 296 / 150, 504 77 / 55;  1024, 2000 333 / 233, 1000 172 / 137;  one round: 4 2048 1024 1800 79 / 77;
-//     a quarter of one: 2 2048 512 1000 35 / 44
+// Whether it is: the second product costs 2 K operations a logit, the logits it saves 8 bytes written and read.  Blocks take whole tiles of
+// 256 x 256, so that a last round of few tiles counts in full.  us, product with logits and loss kernel / two products (replicas, rows, K, classes):
+//   from four rounds on:  8 4096 256 32000 2211 / 1636;  8 4096 512 32000 2654 / 2107, 12000 958 / 850, 4096 318 / 282, 2000 160 / 140;
+//     640, 32000 2973 / 2740;  768, 32000 3019 / 3116, 2000 181 / 182;  1024, 8000 843 / 906, 2000 198 / 220
+//   one and a half to three:  K = 256 and 384 3 4096 256 2048 74 / 63, 8 4096 256 1000 74 / 60, 5 2048 384 2560 91 / 71;  K = 512 4 2048 512 4000 92 / 86,
+//     8 4096 512 1000 91 / 80, of a round's tiles unused 2 2048 512 7000 79 / 83, 9000 104 / 111, 3 4096 512 1800 67 / 72
+//   fewer:  8 4096 256 504 45 / 39, 8 4096 512 504 51 / 51, 2 1024 512 12000 65 / 78, 4 1024 256 1800 29 / 38, 2 2048 512 1000 23 / 43
 static bool tf_head_loss(const hdet_tf_plan* p) {
   if (!p->bf16 || p->ls_channel >= 0) return false;
   const hdet_bgemm_args g = head_args(p);
   if (!hdet_head_loss_eligible(g, p->N) || hdet_head_loss_scratch(g.m, g.n, p->N) > (size_t)p->N * p->M * p->V * 4) return false;
   const int64_t cus = hdet_compute_units(), tiles = (int64_t)((g.m + 255) / 256) * ((g.n + 255) / 256) * p->N;
   const double used = (double)tiles / (double)((tiles + cus - 1) / cus * cus);      // of the rounds' tiles
-  if (!hdet_xent_wide(p->V)) return p->V < 2048 && g.k <= 1024 && used >= 0.85;
-  return (g.k <= 640 && tiles >= 4 * cus) || (g.k <= 384 && used >= 0.75 && 5 * tiles >= 7 * cus);
+  return (g.k <= 640 && tiles >= 4 * cus) || (g.k <= 512 && used >= 0.9 && 5 * tiles >= 9 * cus) || (g.k <= 384 && used >= 0.75 && 5 * tiles >= 7 * cus);
 }
 
 hdet_tf_plan* hdet_tf_create(const hdet_config& cfg, const hdet_buffers& buf, int drop_channel, int ls_channel,

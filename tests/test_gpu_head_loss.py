@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 # (replicas, batch, model, replicas compared)
 CASES = [
     # 1800 x 1992: eight rows in the last tile, 200 columns; K = 192 is three K steps, the fourth empty
-    (4, 36, dict(n_blocks=1, d_model=192, n_heads=3, d_ff=64, seq_len=50, vocab=1992), (0, 3)),
+    (6, 36, dict(n_blocks=1, d_model=192, n_heads=3, d_ff=64, seq_len=50, vocab=1992), (0, 5)),
     # wide rows, 8 columns in the last tile, K no multiple of a step
     (4, 52, dict(n_blocks=1, d_model=200, n_heads=4, d_ff=64, seq_len=50, vocab=2056), (1, 3)),
     # more than four rounds of tiles, K of nine steps
