@@ -4,9 +4,9 @@
 // What bounds it: the sizes of this path (a few dozen to a few hundred rows) make it latency, one dependent launch after the other.  Three launches
 // each way with the scores, probabilities and their gradients going through memory between them become one; only the probabilities are kept, for the
 // backward.  us, three launches -> one, forward / backward, gaps between the launches not counted (heads over all replicas and sequences, S, head size):
-//   64, 32, 16 11.8 -> 5.0 / 11.5 -> 5.7;  64, 128, 64 16.8 -> 8.8 / 20.3 -> 17.0;  288, 192, 32 57 -> 24 / 92 -> 47;  288, 192, 64 69 -> 43 / 101 -> 102;
-//   64, 256, 64 30 -> 17 / 40 -> 36;  64, 512, 64 78 -> 49 / 136 -> 102;  256, 512, 64 312 -> 211 / 507 -> 391
-// The backward is told to take registers for two wavefronts a SIMD: with 256 the loads of a whole tile are in flight (102 us at S = 512; 125 with the
+//   64, 32, 16 11.8 -> 5.0 / 11.5 -> 5.7;  64, 128, 64 16.8 -> 9 / 20.3 -> 16.5;  288, 192, 32 57 -> 24 / 92 -> 50;  288, 192, 64 69 -> 44 / 101 -> 100;
+//   64, 256, 64 30 -> 17 / 40 -> 35;  64, 512, 64 78 -> 45 / 136 -> 95;  256, 512, 64 312 -> 163 / 507 -> 384
+// The backward is told to take registers for two wavefronts a SIMD: with 256 the loads of a whole tile are in flight (95 us at S = 512; 125 with the
 // 180 that the compiler takes by itself, 134 with 168).
 //
 // fp32 products on the matrix cores (v_mfma_f32_32x32x2_f32), a block of four wavefronts to 32 queries (or keys) of a head:
@@ -47,14 +47,17 @@ __device__ __forceinline__ void load_row(float (&v)[G][4], const float* row, int
     for (int j = 0; j < 4; ++j) v[c][j] = x[j];
   }
 }
-template <int G>
+// NC: sums over the row, each half as long with two
+template <int G, int NC = 1>
 __device__ __forceinline__ f16v product(const float (&a)[G][4], const float (&b)[G][4]) {
-  f16v acc = zero16();
+  f16v acc[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) acc[c] = zero16();
 #pragma unroll
   for (int c = 0; c < G; ++c)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[c][j], b[c][j], acc, 0, 0, 0);
-  return acc;
+    for (int j = 0; j < 4; ++j) acc[c % NC] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[c][j], b[c][j], acc[c % NC], 0, 0, 0);
+  return NC > 1 && G > 1 ? acc[0] + acc[NC - 1] : acc[0];
 }
 // the second product's other operand: rows r0 .. r0 + 31 (at most `last`) of an [S][DH] matrix, columns 32 n + lane % 32
 template <int NB>
@@ -129,7 +132,7 @@ __global__ __launch_bounds__(kThreads) void attn_f32_fwd_kernel(const hdet_attn_
     const int j = kt * 32 + (lane & 31);
     load_row<G>(kf, hd.k + (int64_t)(j < last ? j : last) * hd.ld, half);
     load_cols<NB>(vf[u], hd.v, hd.ld, kt * 32, last, DH, lane);      // on their way under the softmax
-    s[u] = product<G>(kf, qf);
+    s[u] = product<G, 2>(kf, qf);
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       s[u][e] = kt * 32 + acc_row(e, half) <= i ? s[u][e] * hd.scale : -INFINITY;
@@ -181,13 +184,14 @@ __global__ __launch_bounds__(kThreads) void attn_f32_fwd_kernel(const hdet_attn_
 // da . a of the lane's row (the same in both halves)
 template <int G>
 __device__ __forceinline__ float row_dot(const float (&da)[G][4], const float* a, int half) {
-  float af[G][4], d = 0.f;
+  float af[G][4];
+  double d = 0.0;                                                    // what it is off by, every entry of the row's ds is off by
   load_row<G>(af, a, half);
 #pragma unroll
   for (int c = 0; c < G; ++c)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) d += da[c][j] * af[c][j];
-  return d + __shfl_xor(d, 32);
+    for (int j = 0; j < 4; ++j) d += (double)da[c][j] * (double)af[c][j];
+  return (float)(d + __shfl_xor(d, 32));
 }
 
 template <int G>
