@@ -11,8 +11,8 @@
 // pass from Philox-4x32-10 keyed on (seed, step, replica, site, element), never stored.
 //
 // All matrix products go through the replica-batched GEMMs (matrix cores, on bf16 operands in mixed precision
-// or in fp32 otherwise); attention is the unfused chain scores -> softmax -> P V with the
-// (replica, sequence, head) triple as the batch index.  Activations that go to memory are of
+// or in fp32 otherwise); attention is one kernel each way where its shape allows (hdet_attention.hip, hdet_attention_f32.hip), else the
+// chain scores -> softmax -> P V with the (replica, sequence, head) triple as the batch index.  Activations that go to memory are of
 // type T: float, or bfloat16 in mixed precision (logits, attention scores and LayerNorm
 // statistics stay fp32).
 
