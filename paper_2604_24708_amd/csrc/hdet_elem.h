@@ -121,10 +121,12 @@ __device__ __forceinline__ float hdet_gelu_exp(float z, float z2) {
 __device__ __forceinline__ float hdet_gelu_tanh(float z) {
   return z / (1.f + hdet_gelu_exp(z, z * z));
 }
+// Below -10 the derivative is less than 1e-35 in size and s runs out of exponents while the rest still grows with z^3: 0 from there on.  Above 10 it
+// is 1 and formed at 10, where nothing overflows.  (NaN takes neither branch.)
 __device__ __forceinline__ float hdet_gelu_tanh_grad(float z) {
   const float k3 = 1.5957691216057308f, k4 = 0.21406444881780076f;        // 2 u' = k3 + k4 z^2
-  const float z2 = z * z, e = fminf(hdet_gelu_exp(z, z2), 1e37f), s = 1.f / (1.f + e);
-  return s * __builtin_fmaf(z * (e * s), __builtin_fmaf(k4, z2, k3), 1.f);
+  const float x = z > 10.f ? 10.f : z, x2 = x * x, e = hdet_gelu_exp(x, x2), s = 1.f / (1.f + e);
+  return z < -10.f ? 0.f : s * __builtin_fmaf(x * (e * s), __builtin_fmaf(k4, x2, k3), 1.f);
 }
 
 // The same two functions for results that are rounded to bfloat16 anyway, on the hardware exp2 and reciprocal

@@ -1,0 +1,70 @@
+"""The fp32 GELU and its derivative as the kernels have them (compiled for the host), over the whole range of fp32 arguments, against
+64 bits.  Beyond |z| = 14 the derivative is 0 or 1 to the last bit: a diverging replica, or a bias used as a switch, must not turn it into
+something that grows with z."""
+import ctypes
+import os
+import re
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def gelu(tmp_path_factory):
+    text = open(os.path.join(ROOT, "paper_2604_24708_amd", "csrc", "hdet_elem.h")).read()
+    names = ("hdet_gelu_exp", "hdet_gelu_tanh", "hdet_gelu_tanh_grad")
+    bodies = [re.search(r"__device__ __forceinline__ float %s\(.*?\n}\n" % n, text, re.S).group(0) for n in names]
+    loops = "".join('extern "C" void %s_all(const float* x, float* y, long n) { for (long i = 0; i < n; ++i) y[i] = %s(x[i]); }\n' % (n, n)
+                    for n in names[1:])
+    d = tmp_path_factory.mktemp("gelu")
+    src = d / "gelu.cpp"
+    src.write_text("#include <cmath>\n#define __device__\n#define __forceinline__ inline\n" + "".join(bodies) + loops)
+    cc = shutil.which("g++")
+    assert cc, "g++ not found"
+    lib = str(d / "gelu.so")
+    subprocess.run([cc, "-O1", "-ffp-contract=off", "-shared", "-fPIC", str(src), "-o", lib], check=True)
+    dll = ctypes.CDLL(lib)
+
+    def call(name, x):
+        x = np.ascontiguousarray(x, np.float32)
+        y = np.empty_like(x)
+        f = getattr(dll, name + "_all")
+        f.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_long]
+        f(x.ctypes.data, y.ctypes.data, x.size)
+        return y
+
+    return call
+
+
+def exact(z):
+    z = np.asarray(z, np.float64)
+    c = np.sqrt(2.0 / np.pi)
+    with np.errstate(over="ignore", invalid="ignore"):
+        e = np.exp(np.minimum(-2.0 * c * (z + 0.044715 * z ** 3), 700.0))
+        s = 1.0 / (1.0 + e)
+        value = np.where(z < -14, 0.0, z * s)
+        grad = np.where(z < -14, 0.0, np.where(z > 14, 1.0, s * (1.0 + z * (e * s) * 2.0 * c * (1.0 + 3 * 0.044715 * z * z))))
+    return value, grad
+
+
+def test_range(gelu):
+    size = np.concatenate([np.logspace(-38, np.log10(3.4e38), 4001), np.linspace(0.01, 14, 4001), [9.99, 10.0, 10.01, np.inf]]).astype(np.float32)
+    z = np.concatenate([-size, size])
+    value, grad = exact(z)
+    got = gelu("hdet_gelu_tanh_grad", z)
+    # the derivative is between -0.13 and 1.13: a few roundings of numbers of that size
+    assert np.all(np.isfinite(got)) and np.max(np.abs(got - grad)) <= 5e-7, z[np.argmax(np.abs(got - grad))]
+    assert np.all(got[z < -14] == 0) and np.all(got[z > 14] == 1)
+    ok = np.isfinite(z)
+    got = gelu("hdet_gelu_tanh", z)[ok]
+    # exp(-2u) carries the rounding of 2u, which is at most 14 where the value matters
+    assert np.all(np.isfinite(got)) and np.max(np.abs(got - value[ok]) / (np.abs(value[ok]) + 1e-5)) <= 5e-6
+
+
+def test_nan_stays(gelu):
+    z = np.array([np.nan, -np.nan], np.float32)
+    assert np.all(np.isnan(gelu("hdet_gelu_tanh", z))) and np.all(np.isnan(gelu("hdet_gelu_tanh_grad", z)))
