@@ -547,9 +547,9 @@ int choose_cfg(F blocks, bool k_contiguous) {
 // Two products of few blocks and the loss reduction: blocks [0, wt) form the weight gradient, [wt, wt + ot) the other product
 // (the one with the longer contraction comes first), the rest reduce a replica's loss each.  Small layers' backward is bound by
 // launches and by CUs left idle, and its two products and the bias gradient need nothing of each other.  Each product keeps the
-// tile it would have alone.  Only the two small tiles share a launch: with the larger ones a launch fills the chip by itself,
-// and one kernel that holds them all needs 284 registers, a wavefront per SIMD (2-layer d = 256 transformer 962 to 993 us a
-// step with larger tiles in pairs, 830 without).
+// tile it would have alone.  Only the two small tiles share this kernel: with the larger tiles of fragments from global memory it
+// needs 284 registers, a wavefront per SIMD (2-layer d = 256 transformer 962 to 993 us a step with them in pairs, 830 without).
+// Larger products share sgemm_lds_pair_kernel where they can go through LDS.
 // Per training step: MLP 64-128-10, batch 32, 4 replicas 39 -> 34 us; 2-layer d = 64 transformer 350 -> 261,
 // d = 256 890 -> 868 (bias gradients, GELU and residual sums without passes of their own).
 struct pair_grid { unsigned wx, wy, wt, ox, oy, ot; int wgrad_first, wcfg, ocfg; };
@@ -576,6 +576,7 @@ __global__ __launch_bounds__(kThreads) void sgemm_pair_kernel(const hdet_sgemm_a
 // The same for two products of many tiles (sgemm_lds_tile): what the launch, the first loads and the last stores take is paid once, and one product's
 // blocks work while the other's wait.  wcfg, ocfg: 64 x 64 tiles or 64 x 32.  One after the other / together, us, 4 replicas: 4000 outputs of 256, 512 rows
 // 93 / 85;  1024 of 256 27.7 / 25.7;  256 of 1024 through the GELU 35.3 / 30.8;  768 of 256 26.9 / 23.1.
+// A product of few tiles beside a larger one: lds_pair_pays.
 template <bool NT>
 __global__ __launch_bounds__(kThreads) void sgemm_lds_pair_kernel(const hdet_sgemm_args w, const hdet_sgemm_args o, int epi, const pair_grid pg,
                                                                  const hdet_loss_args loss) {
@@ -637,6 +638,15 @@ hipError_t launch_pair(const hdet_sgemm_args& w, int wb, int wcfg, const hdet_sg
   return hipGetLastError();
 }
 
+// Whether a product of few tiles (32 x 32, K in 4, if alone) goes beside a larger one, which costs it half its blocks and half its K split: a chain of 6.7 ns
+// for each of its k, to be hidden by the larger product (at the 100 TFLOP/s of such tiles) and what a launch of its own would add (4 us).  A training
+// step in us, apart / together (replicas, rows, layer):  4 512 128 -> 2000 221 / 214;  4 512 128 -> 1000 191 / 188;  8 512 64 -> 2000 219 / 212;  MLPs
+// 64-1024-64, 4 256 52 / 46;  32-512-32, 4 512 47 / 42;  level 4 512 128 -> 4000 260 / 260, 4 512 64 -> 2000 178 / 179;
+// 4 256 64 -> 4000 167 / 176;  4 512 32 -> 8000 240 / 261;  2 64 64 -> 32000 347 / 466;  MLP 4096-128-4096, 2 128 106 / 116.
+bool lds_pair_pays(const hdet_sgemm_args& few, const hdet_sgemm_args& many, int many_batch) {
+  return 6.7e-3 * few.k <= 2e-8 * many.m * many.n * (double)many.k * many_batch + 4.0;
+}
+
 template <bool NT>
 hipError_t launch_lds_pair(const hdet_sgemm_args& w, int wb, bool wwide, const hdet_sgemm_args& o, int epi, int ob, bool owide,
                            const hdet_loss_args& loss, hipStream_t s) {
@@ -683,6 +693,7 @@ hipError_t hdet_launch_sgemm_pair(const hdet_sgemm_args& wgrad, int wgrad_batch,
   if (wcfg <= kCfg64x32 && ocfg <= kCfg64x32)
     return other_nt ? launch_pair<true>(w, wgrad_batch, wcfg, o, epi, ob, ocfg, l, s) : launch_pair<false>(w, wgrad_batch, wcfg, o, epi, ob, ocfg, l, s);
   if (ob && lds_eligible<kTN>(w) && (other_nt ? lds_eligible<kNT>(o) : lds_eligible<kNN>(o)) &&
+      (wcfg != kCfg32 || lds_pair_pays(w, o, ob)) && (ocfg != kCfg32 || lds_pair_pays(o, w, wgrad_batch)) &&
       count_blocks(w, wgrad_batch, 64, 32) + count_blocks(o, ob, 64, 32) <= kMaxBlocks) {
     const bool ww = wcfg >= kCfg64, ow = ocfg >= kCfg64;
     return other_nt ? launch_lds_pair<true>(w, wgrad_batch, ww, o, epi, ob, ow, l, s) : launch_lds_pair<false>(w, wgrad_batch, ww, o, epi, ob, ow, l, s);

@@ -16,6 +16,8 @@ pytestmark = pytest.mark.gpu
     ([36, 1028, 324, 4], 196, 6),       # K of 4 and of 36, a product of four columns
     ([64, 2048, 96], 64, 4),            # whole tiles
     ([260, 1032, 7], 100, 5),           # one operand of odd rows beside whole ones
+    ([64, 1024, 68], 256, 4),           # a product of few tiles beside a large one: K of 256, which the large one hides
+    ([48, 68, 8004], 252, 4),           # K of 8004, which it does not: in a launch of its own
 ])
 def test_mlp_gradients(widths, batch, n, shared):
     got, ref, slices = mlp_grads(widths, batch, n, shared=shared)
