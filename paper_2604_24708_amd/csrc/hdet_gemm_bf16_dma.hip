@@ -638,7 +638,8 @@ __global__ __launch_bounds__(512, 2) void hdet_bgemm_alt_kernel(const hdet_bgemm
 
 // Forward products whose blocks walk over tiles of 256 x 256: the main loop of the kernel above, with the next tile's first two K steps requested in
 // the last two of the tile before, so that the pipeline never drains, and a tile's end in registers alone, under the loads in flight.
-//  * The bias is what the first MFMAs add to (it lies in LDS, requested a tile ahead).
+//  * The bias (in LDS, requested a tile ahead) is added to the finished sums, as the other kernels do: the same bits.  As what the first MFMAs add to
+//    it cost no addition, but every partial sum was rounded at its size.
 //  * Results change places between the four groups of 16 lanes (v_permlane32_swap, v_permlane16_swap) until a lane has 16 consecutive columns
 //    of its row: two 16-byte stores, no LDS.
 //  * Stores count in vmcnt with the loads: they are always issued (rows and columns that do not exist lie outside the descriptor), and the first
@@ -712,7 +713,7 @@ __global__ __launch_bounds__(512, 2) void hdet_bgemm_walk_kernel(const hdet_bgem
       }
     }
   };
-  f4 acc[8][4], bias[4];
+  f4 acc[8][4];
   bf16x8 fa[2][4], fb[2][4];
   // fragment i of sub-step ss is 16 i rows behind fragment 0, whose chunk permutation it shares: two addresses an operand
   const uint16_t *pa[2], *pb[2];
@@ -743,7 +744,7 @@ __global__ __launch_bounds__(512, 2) void hdet_bgemm_walk_kernel(const hdet_bgem
       for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-          acc[4 * h + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[ss][j], fa[ss][i], first && ss == 0 ? bias[j] : acc[4 * h + i][j], 0, 0, 0);
+          acc[4 * h + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[ss][j], fa[ss][i], first && ss == 0 ? f4{0.f, 0.f, 0.f, 0.f} : acc[4 * h + i][j], 0, 0, 0);
     __builtin_amdgcn_s_setprio(0);
     __builtin_amdgcn_sched_barrier(0);
   };
@@ -765,9 +766,16 @@ __global__ __launch_bounds__(512, 2) void hdet_bgemm_walk_kernel(const hdet_bgem
     for (int w = 0; w < 4; ++w) s += p[w].x == -INFINITY ? p[w].y : p[w].y * __builtin_amdgcn_exp2f((p[w].x - mx) * kLog2e);
     if (ln < 32 && t.m0 + tr < g.m) g.xent.part[((int64_t)t.z * gx + t.bx) * g.m + t.m0 + tr] = float2{mx, s};
   };
-  auto finish = [&](const tile& t) {
+  auto finish = [&](const tile& t, int slot) {
     __builtin_amdgcn_sched_barrier(0);
     const int ln = lane_now(), cg = ln >> 4, lr = ln & 15;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      f4 bias = *reinterpret_cast<const f4*>(s_bias + slot * TN + wn + j * 16 + cg * 4);
+      if (kStat && t.n0 + wn + j * 16 + cg * 4 >= g.n) bias = f4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[i][j] += bias;
+    }
     if constexpr (kStat) {
       float mx[8], sum[8];
 #pragma unroll
@@ -884,12 +892,6 @@ __global__ __launch_bounds__(512, 2) void hdet_bgemm_walk_kernel(const hdet_bgem
   for (bool begun = false;; begun = true) {
     tile nxt;
     asm volatile("" : "+v"(off_a), "+v"(off_b));
-    const int cg = lane_now() >> 4;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      bias[j] = *reinterpret_cast<const f4*>(s_bias + slot * TN + wn + j * 16 + cg * 4);
-      if (kStat && cur.n0 + wn + j * 16 + cg * 4 >= g.n) bias[j] = f4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-    }
     auto pair = [&](int kt0, bool first) {
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
@@ -926,7 +928,7 @@ __global__ __launch_bounds__(512, 2) void hdet_bgemm_walk_kernel(const hdet_bgem
     for (int kt0 = 2; kt0 < nk; kt0 += 2) { meet(); pair(kt0, false); }
     // the first group ends its tile under the second's last products, the second at once, not when the first is done
     if (wave < 4) meet();
-    finish(cur);
+    finish(cur, slot);
     if (wave >= 4) meet();
     if (t >= total) break;
     prev = {cur.m0, cur.bx, cur.z};

@@ -4,7 +4,8 @@ import numpy as np
 import pytest
 import torch
 
-from test_gpu_transformer import TfRun, base, check_bf16_gradients
+import hdet_inputs as I
+from test_gpu_transformer import TfRun, base, check_bf16_gradients, norm_err
 
 pytestmark = pytest.mark.gpu
 
@@ -54,4 +55,42 @@ def test_bias_product_of_several_rounds():
     ref_loss, ref = run.oracle_grads(run.orc.theta[r:], ids[r:], tgt[r:], 1)
     assert abs(losses[r] - ref_loss[0]) <= 1e-3
     check_bf16_gradients(cfg, run.g.cpu().numpy()[r, :run.P], ref[0], 4e-2, ("walk", r))
+    run.close()
+
+
+def slices(cfg):
+    """Where the tensors lie in a plane, and their shapes."""
+    out, off = {}, 0
+    for name, shape in I.transformer_shapes(cfg):
+        k = int(np.prod(shape))
+        out[name] = slice(off, off + k), shape
+        off += k
+    return out
+
+
+def test_bias_is_added_to_the_finished_sum():
+    """Values 1 + (16 terms of 0.375 or 0.25 units in the last place of 1) - 1, each term in another step of the contraction: 6 and 4 such units when
+    the bias comes last, nothing when the terms are added to it one by one.  The gradient of the output projection is proportional to them."""
+    d = 528
+    cfg, n, batch = dict(n_blocks=1, d_model=d, n_heads=8, d_ff=64, seq_len=70, vocab=96), 7, 50
+    run = TfRun(base(n_replicas=n), cfg, batch, bf16=True)
+    flat, part = run.orc.theta[0].copy(), slices(cfg)
+    par = {k: flat[at].reshape(shape) for k, (at, shape) in part.items()}
+    par["ln1_g.0"][:], par["ln1_b.0"][:] = 0.0, 1.0                  # every operand of the product is one
+    par["w_qkv.0"][2 * d:], par["b_qkv.0"][2 * d:] = 0.0, 1.0
+    for c in range(d):
+        par["w_qkv.0"][2 * d + c, 0:512:32] = (0.375 if c % 2 else 0.25) * 2.0 ** -23
+    par["w_qkv.0"][2 * d:, 527] = -1.0
+    run.orc.theta[:] = flat
+    run.theta[:, :run.P] = torch.from_numpy(flat).to(run.theta.device)
+    run.shadow[:, :run.P] = run.theta[:, :run.P].to(torch.bfloat16)
+    ids, tgt, _ = run.forward_backward(1)
+    r = n - 1
+    run.n = 1
+    run.orc.dropout_table = lambda: np.zeros(1)
+    run.orc.label_smoothing_table = lambda: np.zeros(1)
+    run.orc.attn_temp_table = lambda: np.ones(1)
+    _, ref = run.oracle_grads(run.orc.theta[r:], ids[r:], tgt[r:], 1)
+    w_o = part["w_o.0"][0]
+    assert norm_err(run.g.cpu().numpy()[r, w_o], ref[0][w_o]) <= 4e-2          # the bound of these models' tensors
     run.close()
