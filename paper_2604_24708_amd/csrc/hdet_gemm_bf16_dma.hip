@@ -185,6 +185,7 @@ __device__ __forceinline__ tile_id tile_of_block(int tile_group) {
 }
 
 constexpr float kLog2e = 1.4426950408889634f;
+constexpr double kLn2 = 0.6931471805599453;
 
 // The block's TM x TN tile to memory.  Accumulators go through LDS as fp32, the wavefront's own 32 rows x 64 columns at a time, and are read
 // back with 4 consecutive columns a lane, so that every global access is made of whole rows of the strip.  (Strips of 16 rows x 256 columns
@@ -645,6 +646,11 @@ __global__ __launch_bounds__(512, 2) void hdet_bgemm_alt_kernel(const hdet_bgemm
 //  * Stores count in vmcnt with the loads: they are always issued (rows and columns that do not exist lie outside the descriptor), and the first
 //    K step of the next tile waits for the loads before them, not for them (kStores).
 //  * The group that is a turn behind ends its tile as soon as its products are done, beside the other group, not after it.
+//  * Exponentials of logits are exp2(z log2(e) - r), one fused operation and the hardware's exp2, with r the whole number next to max log2(e): what tiles
+//    and rows refer to differs by exact powers of two, and nothing that is rounded once for the maximum fails to cancel between the sums and the
+//    gradient.  Simulated against 64 bits, logits of size 0.5 to 30, 1000 to 16000 classes: probabilities off by 3e-8 to 1.1e-7 (rms, relative), those of the
+//    loss kernels (hdet_mlp.hip) by 4e-8 to 3.6e-7; row losses by 0.6 to 0.9 times as much as theirs.  With r = max log2(e) rounded, a tile's own for its
+//    sum and the row's for the gradient, 1.0e-7 to 7e-7, and 2e-5 where the maxima of several tiles lie next to each other at 300.
 // Built for the output layer with its loss (hdet_launch_head_loss; products with a bias take it too, launch_shape), whose two passes cost less than writing and reading fp32 logits:  K = 512,
 // 4096 x 32000, 8 replicas, 1502 to 1575 us of product and 1152 of loss kernel -> 918 (statistics) + 19 (merge) + 1190 (gradient).  Of a tile's
 // 14.7 and 19 us the main loop takes 11 (1.6 PFLOP/s, 70 % of the matrix cores' cycles), exponentials 3.4, stores 3.5.  Not kept, gradient pass:
@@ -702,13 +708,13 @@ __global__ __launch_bounds__(512, 2) void hdet_bgemm_walk_kernel(const hdet_bgem
   auto load_bias = [&](const tile& t, int slot) {
     if (wave < 4) lds_load4(t.rbias, s_addr + kBiasAt + slot * TN * 4 + wave * 256, (uint32_t)(wave * 64 + lane_now()) * 4u);
   };
-  auto load_rows = [&](const tile& t) {                          // maximum, factor and label of the tile's rows
+  auto load_rows = [&](const tile& t) {                          // reference, factor and label of the tile's rows
     const int ln = lane_now();
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const int q = wave + 8 * u, row = t.m0 + (q & 3) * 64 + ln;
       if (q < 12) {
-        const void* src = q < 4 ? (const void*)g.xent.row_maxl : q < 8 ? (const void*)g.xent.row_a : (const void*)g.xent.labels;
+        const void* src = q < 4 ? (const void*)g.xent.row_ref : q < 8 ? (const void*)g.xent.row_a : (const void*)g.xent.labels;
         lds_load4(make_rsrc((const float*)src + (int64_t)t.z * g.m, (uint32_t)g.m * 4u), s_addr + kRowsAt + q * 256, row < g.m ? (uint32_t)row * 4u : kAbsent);
       }
     }
@@ -753,7 +759,7 @@ __global__ __launch_bounds__(512, 2) void hdet_bgemm_walk_kernel(const hdet_bgem
     asm volatile("s_barrier" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
   };
-  // a group's four wavefronts have left max and sum of their 64 columns for the group's 128 rows; 32 rows each
+  // a group's four wavefronts have left reference and sum of their 64 columns for the group's 128 rows; 32 rows each
   auto put_stats = [&](const auto& t) {
     const int ln = lane_now(), tr = wm + (wave % 4) * 32 + (ln & 31);
     const float2* buf = reinterpret_cast<const float2*>(s_rows) + tr;
@@ -763,7 +769,7 @@ __global__ __launch_bounds__(512, 2) void hdet_bgemm_walk_kernel(const hdet_bgem
     const float mx = fmaxf(fmaxf(p[0].x, p[1].x), fmaxf(p[2].x, p[3].x));
     float s = 0.f;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) s += p[w].x == -INFINITY ? p[w].y : p[w].y * __builtin_amdgcn_exp2f((p[w].x - mx) * kLog2e);
+    for (int w = 0; w < 4; ++w) s += p[w].x == -INFINITY ? p[w].y : p[w].y * __builtin_amdgcn_exp2f(p[w].x - mx);
     if (ln < 32 && t.m0 + tr < g.m) g.xent.part[((int64_t)t.z * gx + t.bx) * g.m + t.m0 + tr] = float2{mx, s};
   };
   auto finish = [&](const tile& t, int slot) {
@@ -790,7 +796,8 @@ __global__ __launch_bounds__(512, 2) void hdet_bgemm_walk_kernel(const hdet_bgem
       for (int i = 0; i < 8; ++i) mx[i] = over_groups(mx[i], [](float x, float y) { return fmaxf(x, y); });
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const float ml = mx[i] == -INFINITY ? 0.f : mx[i] * kLog2e;
+        mx[i] = rintf(mx[i] * kLog2e);
+        const float ml = mx[i] == -INFINITY ? 0.f : mx[i];
         sum[i] = 0.f;
 #pragma unroll
         for (int j = 0; j < 4; ++j)
@@ -810,13 +817,13 @@ __global__ __launch_bounds__(512, 2) void hdet_bgemm_walk_kernel(const hdet_bgem
       f4 csum[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) csum[j] = f4{0.f, 0.f, 0.f, 0.f};
-      float rmax[8], ra[8];
+      float rref[8], ra[8];
       int rlab[8];
       if (kGrad) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
           const int tr = wm + i * 16 + lr;
-          rmax[i] = s_rows[tr]; ra[i] = s_rows[TM + tr]; rlab[i] = __float_as_int(s_rows[2 * TM + tr]);
+          rref[i] = s_rows[tr]; ra[i] = s_rows[TM + tr]; rlab[i] = __float_as_int(s_rows[2 * TM + tr]);
         }
       }
 #pragma unroll
@@ -825,12 +832,12 @@ __global__ __launch_bounds__(512, 2) void hdet_bgemm_walk_kernel(const hdet_bgem
         const bool row_ok = t.m0 + tr < g.m;
         f4 v[4];
         if constexpr (kGrad) {
-          const float maxl = row_ok ? rmax[i] : INFINITY, a = ra[i];
+          const float ref = row_ok ? rref[i] : INFINITY, a = ra[i];
           const int yc = row_ok ? rlab[i] - (t.n0 + wn + cg * 4) : -1;
 #pragma unroll
           for (int j = 0; j < 4; ++j)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[j][e] = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][e], kLog2e, -maxl)) * a;
+            for (int e = 0; e < 4; ++e) v[j][e] = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][e], kLog2e, -ref)) * a;
           if (__builtin_expect((unsigned)yc < 64u && (yc & 12) == 0, 0)) {      // the row's label is among this lane's columns
             float zy = 0.f;
 #pragma unroll
@@ -839,8 +846,7 @@ __global__ __launch_bounds__(512, 2) void hdet_bgemm_walk_kernel(const hdet_bgem
               for (int e = 0; e < 4; ++e)
                 if (yc == j * 16 + e) { zy = acc[i][j][e]; v[j][e] -= g.xent.invb; }
             const int64_t at = (int64_t)t.z * g.m + t.m0 + tr;
-            const float2 lse = g.xent.row_lse[at];
-            g.xent.row_loss[at] = lse.y - (zy - lse.x);
+            g.xent.row_loss[at] = (float)((g.xent.row_lse[at] - (double)zy * (double)kLog2e) * kLn2);
           }
 #pragma unroll
           for (int j = 0; j < 4; ++j) csum[j] += v[j];
@@ -940,37 +946,42 @@ __global__ __launch_bounds__(512, 2) void hdet_bgemm_walk_kernel(const hdet_bgem
   if (kStat) put_stats(cur);
 }
 
-// The rows' max and sum from the column tiles' (hdet_launch_head_loss).  Block = 64 rows x 4 phases; phase q takes tiles q, q + 4, ..., the
-// phases are added in their order.
+// The rows' reference and sum from the column tiles' (hdet_launch_head_loss).  Block = 64 rows x 4 phases; phase q takes tiles q, q + 4, ..., the
+// phases are added in their order.  References are whole numbers, so that a tile's sum comes to the row's by an exact power of two, and the sum over a
+// hundred tiles is in 64 bits.
 __global__ __launch_bounds__(256) void hdet_head_rows_kernel(const hdet_xent_epi x, int m, int tiles) {
-  __shared__ float2 buf[4][64];
+  __shared__ float ref[4][64];
+  __shared__ double part[4][64];
   const int lane = threadIdx.x & 63, q = threadIdx.x >> 6, z = blockIdx.y, row = blockIdx.x * 64 + lane;
-  float mx = -INFINITY, s = 0.f;
+  float mx = -INFINITY;
+  double s = 0.0;
   if (row < m) {
     const float2* p = x.part + (int64_t)z * tiles * m + row;
 #pragma unroll 8
     for (int t = q; t < tiles; t += 4) {
       const float2 v = p[(int64_t)t * m];
       const float mn = fmaxf(mx, v.x);
-      if (v.x != -INFINITY) s = s * __builtin_amdgcn_exp2f((mx - mn) * kLog2e) + v.y * __builtin_amdgcn_exp2f((v.x - mn) * kLog2e);
+      if (v.x != -INFINITY) s = s * (double)__builtin_amdgcn_exp2f(mx - mn) + (double)(v.y * __builtin_amdgcn_exp2f(v.x - mn));
       else s += v.y;
       mx = mn;
     }
   }
-  buf[q][lane] = float2{mx, s};
+  ref[q][lane] = mx;
+  part[q][lane] = s;
   __syncthreads();
   if (q == 0 && row < m) {
-    float2 p[4];
+    float r[4];
+    double p[4];
 #pragma unroll
-    for (int w = 0; w < 4; ++w) p[w] = buf[w][lane];
-    const float top = fmaxf(fmaxf(p[0].x, p[1].x), fmaxf(p[2].x, p[3].x));
-    float sum = 0.f;
+    for (int w = 0; w < 4; ++w) { r[w] = ref[w][lane]; p[w] = part[w][lane]; }
+    const float top = fmaxf(fmaxf(r[0], r[1]), fmaxf(r[2], r[3]));
+    double sum = 0.0;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) sum += p[w].x == -INFINITY && p[w].y == 0.f && top != -INFINITY ? 0.f : p[w].y * __builtin_amdgcn_exp2f((p[w].x - top) * kLog2e);
+    for (int w = 0; w < 4; ++w) sum += r[w] == -INFINITY && p[w] == 0.0 && top != -INFINITY ? 0.0 : p[w] * (double)__builtin_amdgcn_exp2f(r[w] - top);
     const int64_t at = (int64_t)z * m + row;
-    x.row_maxl[at] = top * kLog2e;
-    x.row_a[at] = x.invb / sum;
-    x.row_lse[at] = float2{top, logf(sum)};
+    x.row_ref[at] = top;
+    x.row_a[at] = (float)((double)x.invb / sum);
+    x.row_lse[at] = (double)top + log2(sum);
   }
 }
 
@@ -1222,8 +1233,8 @@ hipError_t hdet_launch_head_loss(const hdet_bgemm_args& g_in, int batch, void* s
   const size_t rows = (size_t)batch * g.m;
   char* at = (char*)scratch;
   g.xent.part = (float2*)at; at += rows * gx * sizeof(float2);
-  g.xent.row_lse = (float2*)at; at += rows * sizeof(float2);
-  g.xent.row_maxl = (float*)at; at += rows * sizeof(float);
+  g.xent.row_lse = (double*)at; at += rows * sizeof(double);
+  g.xent.row_ref = (float*)at; at += rows * sizeof(float);
   g.xent.row_a = (float*)at;
   g.xent.invb = 1.f / (float)g.m;
   launch_walk<HDET_EPI_XENT_STAT>(g, batch, s);

@@ -167,15 +167,15 @@ enum { HDET_EPI_F32 = 0, HDET_EPI_BIAS_F32 = 1, HDET_EPI_BIAS_RELU_BF16 = 2, HDE
        HDET_EPI_BIAS_DROP_RESID_BF16 = 9,     // the same with dropout of the layer's output before the sum
        HDET_EPI_ADAMW = 10,           // weight gradient that is applied at once: the AdamW update of `upd` on the tile (c is not written)
        // output layer whose logits z = acc + bias stay on the chip (hdet_launch_head_loss only):
-       HDET_EPI_XENT_STAT = 11,       // max and sum of exp(z - max) of a tile's rows (c is not written)
-       HDET_EPI_XENT_GRAD = 12 };     // c = bf16 gradient of the mean cross-entropy at z, from the whole rows' max and sum; row losses, column sums
+       HDET_EPI_XENT_STAT = 11,       // reference and sum of a tile's rows (hdet_xent_epi; c is not written)
+       HDET_EPI_XENT_GRAD = 12 };     // c = bf16 gradient of the mean cross-entropy at z, from the whole rows' reference and sum; row losses, column sums
 
 // Cross-entropy inside the output layer's product: what its two passes and the merge between them exchange.  Row scalars are [replica][row].
 struct hdet_xent_epi {
-  float2* part;            // [replica][column tile][row]: max, sum of a tile's part of the row
-  float* row_maxl;         // max * log2(e)
-  float* row_a;            // 1 / (rows * sum)
-  float2* row_lse;         // max, log(sum)
+  float2* part;            // [replica][column tile][row]: reference r, a whole number next to max * log2(e), and sum of exp2(z log2(e) - r) of a tile's part of the row
+  float* row_ref;          // the row's reference
+  float* row_a;            // 1 / (rows * the row's sum)
+  double* row_lse;         // log2 of the sum of exp2(z log2(e))
   const int32_t* labels;
   float* row_loss;
   float invb;              // 1 / rows

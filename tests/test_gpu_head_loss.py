@@ -20,6 +20,16 @@ CASES = [
 ]
 
 
+def slices(cfg):
+    """Where the tensors lie in a plane, and their shapes."""
+    out, off = {}, 0
+    for name, shape in I.transformer_shapes(cfg):
+        k = int(np.prod(shape))
+        out[name] = slice(off, off + k), shape
+        off += k
+    return out
+
+
 @pytest.mark.parametrize("n,batch,cfg,compared", CASES)
 def test_loss_and_gradients(n, batch, cfg, compared):
     run = TfRun(base(n_replicas=n), cfg, batch, bf16=True)
@@ -42,6 +52,47 @@ def test_loss_and_gradients(n, batch, cfg, compared):
     run.close()
 
 
+@pytest.mark.parametrize("size", [1.0, 30.0, 300.0])
+@pytest.mark.parametrize("n,batch,cfg", [c[:3] for c in CASES[1:]])
+def test_loss_of_known_logits(n, batch, cfg, size):
+    """A head of no weights: every row's logits are the head's biases, known to the last bit, and so are the loss and the bias gradient in 64 bits.
+    Classes next to the row's maximum lie in all column tiles, a hundred others are masked by -inf, one tile's whole 256 among them (a loss kernel that reads
+    the logits from memory has no finite loss there)."""
+    run = TfRun(base(n_replicas=n), cfg, batch, bf16=True)
+    V, M = cfg["vocab"], batch * cfg["seq_len"]
+    part = slices(cfg)
+    ids, tgt = I.zipf_tokens(n, batch, cfg["seq_len"], V, I.SEED_DATA, 1)
+    rng = np.random.Generator(np.random.Philox(11))
+    flat = run.orc.theta.copy()
+    z = np.zeros((n, V))
+    for r in range(n):
+        b = (size * rng.standard_normal(V)).astype(np.float32)
+        top = rng.permutation(V)[:40]
+        b[top] = b.max() - rng.uniform(0, 3, 40).astype(np.float32)
+        b[1024:1280] = -np.inf
+        b[rng.permutation(V)[:100]] = -np.inf
+        seen = np.unique(tgt[r])
+        b[seen] = np.where(np.isfinite(b[seen]), b[seen], np.float32(0))
+        flat[r, part["w_head"][0]], flat[r, part["b_head"][0]], z[r] = 0.0, b, b
+    run.theta[:, :run.P] = torch.from_numpy(flat).to(run.theta.device)
+    run.shadow[:, :run.P] = run.theta[:, :run.P].to(torch.bfloat16)
+    _, _, losses = run.forward_backward(1)
+    got = run.g.cpu().numpy()[:, part["b_head"][0]]
+    for r in range(n):
+        e = np.exp(z[r] - z[r].max())
+        lse = z[r].max() + np.log(e.sum())
+        # a row's loss is rounded once, from sums that are off by a few 1e-7; the logits enter through a log2(e) rounded to 2^-26
+        want = lse - z[r][tgt[r].reshape(-1)].mean()
+        assert abs(losses[r] - want) <= 4e-7 * abs(want) + 3e-7
+        p = e / e.sum()
+        hits = np.bincount(tgt[r].reshape(-1), minlength=V)
+        # M equal terms, each with one rounding of its exponent (2^-24 of at most 8 where a probability counts), summed in fp32 in parts of 128
+        free = hits == 0
+        assert norm_err(got[r][free], p[free]) <= 8e-7
+        assert np.max(np.abs(got[r] - (p - hits / M))) <= 2e-6
+    run.close()
+
+
 def test_bias_product_of_several_rounds():
     """qkv of 3500 x 1584 over K = 528 in 686 tiles: rows, columns and K end inside the last tiles and steps of blocks that walk over them."""
     cfg, n, batch = dict(n_blocks=1, d_model=528, n_heads=8, d_ff=64, seq_len=70, vocab=96), 7, 50
@@ -56,16 +107,6 @@ def test_bias_product_of_several_rounds():
     assert abs(losses[r] - ref_loss[0]) <= 1e-3
     check_bf16_gradients(cfg, run.g.cpu().numpy()[r, :run.P], ref[0], 4e-2, ("walk", r))
     run.close()
-
-
-def slices(cfg):
-    """Where the tensors lie in a plane, and their shapes."""
-    out, off = {}, 0
-    for name, shape in I.transformer_shapes(cfg):
-        k = int(np.prod(shape))
-        out[name] = slice(off, off + k), shape
-        off += k
-    return out
 
 
 def test_bias_is_added_to_the_finished_sum():
