@@ -948,11 +948,11 @@ __global__ __launch_bounds__(512, 2) void hdet_bgemm_walk_kernel(const hdet_bgem
 
 // The rows' reference and sum from the column tiles' (hdet_launch_head_loss).  Block = 64 rows x 4 phases; phase q takes tiles q, q + 4, ..., the
 // phases are added in their order.  References are whole numbers, so that a tile's sum comes to the row's by an exact power of two, and the sum over a
-// hundred tiles is in 64 bits.
-__global__ __launch_bounds__(256) void hdet_head_rows_kernel(const hdet_xent_epi x, int m, int tiles) {
+// hundred tiles is in 64 bits.  A label that names no class has no column that would write the row's loss: it counts as a logit of 0.
+__global__ __launch_bounds__(256) void hdet_head_rows_kernel(const hdet_xent_epi x, int m, int classes) {
   __shared__ float ref[4][64];
   __shared__ double part[4][64];
-  const int lane = threadIdx.x & 63, q = threadIdx.x >> 6, z = blockIdx.y, row = blockIdx.x * 64 + lane;
+  const int lane = threadIdx.x & 63, q = threadIdx.x >> 6, z = blockIdx.y, row = blockIdx.x * 64 + lane, tiles = (classes + 255) / 256;
   float mx = -INFINITY;
   double s = 0.0;
   if (row < m) {
@@ -981,7 +981,9 @@ __global__ __launch_bounds__(256) void hdet_head_rows_kernel(const hdet_xent_epi
     const int64_t at = (int64_t)z * m + row;
     x.row_ref[at] = top;
     x.row_a[at] = (float)((double)x.invb / sum);
-    x.row_lse[at] = (double)top + log2(sum);
+    const double lse = (double)top + log2(sum);
+    x.row_lse[at] = lse;
+    if ((unsigned)x.labels[at] >= (unsigned)classes) x.row_loss[at] = (float)(lse * kLn2);
   }
 }
 
@@ -1238,7 +1240,7 @@ hipError_t hdet_launch_head_loss(const hdet_bgemm_args& g_in, int batch, void* s
   g.xent.row_a = (float*)at;
   g.xent.invb = 1.f / (float)g.m;
   launch_walk<HDET_EPI_XENT_STAT>(g, batch, s);
-  hipLaunchKernelGGL(hdet_head_rows_kernel, dim3((g.m + 63) / 64, batch), dim3(256), 0, s, g.xent, g.m, (int)gx);
+  hipLaunchKernelGGL(hdet_head_rows_kernel, dim3((g.m + 63) / 64, batch), dim3(256), 0, s, g.xent, g.m, g.n);
   launch_walk<HDET_EPI_XENT_GRAD>(g, batch, s);
   return hipGetLastError();
 }

@@ -5,6 +5,7 @@ import pytest
 import torch
 
 import hdet_inputs as I
+import paper_2604_24708_amd as H
 from test_gpu_transformer import TfRun, base, check_bf16_gradients, norm_err
 
 pytestmark = pytest.mark.gpu
@@ -90,6 +91,26 @@ def test_loss_of_known_logits(n, batch, cfg, size):
         free = hits == 0
         assert norm_err(got[r][free], p[free]) <= 8e-7
         assert np.max(np.abs(got[r] - (p - hits / M))) <= 2e-6
+    run.close()
+
+
+def test_label_that_is_no_class():
+    """-1 in the label's place (rows that a caller pads): the row's loss is log sum exp of its logits, whatever the call before left there."""
+    n, batch, cfg = CASES[1][:3]
+    run = TfRun(base(n_replicas=n), cfg, batch, bf16=True)
+    part = slices(cfg)
+    ids, tgt = I.zipf_tokens(n, batch, cfg["seq_len"], cfg["vocab"], I.SEED_DATA, 1)
+    b = np.random.Generator(np.random.Philox(12)).standard_normal(cfg["vocab"]).astype(np.float32)
+    flat = run.orc.theta[0].copy()
+    flat[part["w_head"][0]], flat[part["b_head"][0]] = 0.0, b
+    run.theta[:, :run.P] = torch.from_numpy(flat).to(run.theta.device)
+    run.shadow[:, :run.P] = run.theta[:, :run.P].to(torch.bfloat16)
+    run.forward_backward(1)
+    tgt[:, 1::3, ::5] = -1
+    out = H.hdet_forward_backward(run.h, torch.from_numpy(ids).to("cuda:0"), torch.from_numpy(tgt).to("cuda:0"), want_losses=True)
+    for r in range(n):
+        want = np.log(np.exp(b.astype(np.float64)).sum()) - np.where(tgt[r] >= 0, b[tgt[r]], 0.0).mean()
+        assert abs(out[r] - want) <= 4e-7 * abs(want) + 3e-7
     run.close()
 
 
