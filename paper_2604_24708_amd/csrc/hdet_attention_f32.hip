@@ -113,9 +113,8 @@ __global__ __launch_bounds__(kThreads) void attn_f32_fwd_kernel(const hdet_attn_
   constexpr int NB = (G + 3) / 4, DH = 8 * G;
   __shared__ float red[kWaves * NB * 16 * 64];
   __shared__ float rmax[kWaves][32], rsum[kWaves][32];
-  const int heads = t.n_replicas * t.batch * t.heads;
-  const int qb = nblk - 1 - (int)(blockIdx.x / heads);               // the longest rows first
-  const head hd = head_of(t, (int)(blockIdx.x % heads));
+  const int qb = nblk - 1 - (int)blockIdx.y;                         // the longest rows first
+  const head hd = head_of(t, (int)blockIdx.x);
   const int S = t.seq_len, last = S - 1, lane = threadIdx.x & 63, half = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int i = qb * 32 + (lane & 31);
@@ -198,9 +197,8 @@ template <int G>
 __global__ __launch_bounds__(kThreads, 2) void attn_f32_bwd_kernel(const hdet_attn_f32_desc t, int nblk) {
   constexpr int NB = (G + 3) / 4, DH = 8 * G;
   __shared__ float red[kWaves * NB * 16 * 64];
-  const int heads = t.n_replicas * t.batch * t.heads;
-  const int rank = (int)(blockIdx.x / heads), S = t.seq_len, last = S - 1;
-  const head hd = head_of(t, (int)(blockIdx.x % heads));
+  const int rank = (int)blockIdx.y, S = t.seq_len, last = S - 1;
+  const head hd = head_of(t, (int)blockIdx.x);
   const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const float* da = t.da + hd.at_a;
@@ -285,10 +283,11 @@ bool hdet_attn_f32_fusable(int seq_len, int d_model, int heads) {
   switch (dh) { case 8: CALL(1); break; case 16: CALL(2); break; case 24: CALL(3); break; case 32: CALL(4); break; \
                 case 40: CALL(5); break; case 48: CALL(6); break; case 56: CALL(7); break; default: CALL(8); break; }
 
+// Heads along the grid's x, which takes as many as the separate products take; row blocks along y, at most 32, so that all of a rank come before the next.
 hipError_t hdet_launch_attn_f32_fwd(const hdet_attn_f32_desc& t, hipStream_t s) {
   if (!hdet_attn_f32_fusable(t.seq_len, t.d_model, t.heads)) return hipErrorInvalidValue;
   const int nblk = (t.seq_len + 31) / 32;
-  const dim3 grid((unsigned)(nblk * t.n_replicas * t.batch * t.heads));
+  const dim3 grid((unsigned)(t.n_replicas * t.batch * t.heads), nblk);
 #define FWD(G)                                                                                                              \
   if (nblk <= 4) hipLaunchKernelGGL((attn_f32_fwd_kernel<G, 1>), grid, dim3(kThreads), 0, s, t, nblk);                      \
   else if (nblk <= 8) hipLaunchKernelGGL((attn_f32_fwd_kernel<G, 2>), grid, dim3(kThreads), 0, s, t, nblk);                 \
@@ -301,7 +300,7 @@ hipError_t hdet_launch_attn_f32_fwd(const hdet_attn_f32_desc& t, hipStream_t s) 
 hipError_t hdet_launch_attn_f32_bwd(const hdet_attn_f32_desc& t, hipStream_t s) {
   if (!hdet_attn_f32_fusable(t.seq_len, t.d_model, t.heads)) return hipErrorInvalidValue;
   const int nblk = (t.seq_len + 31) / 32;
-  const dim3 grid((unsigned)(2 * nblk * t.n_replicas * t.batch * t.heads));
+  const dim3 grid((unsigned)(t.n_replicas * t.batch * t.heads), 2 * nblk);
 #define BWD(G) hipLaunchKernelGGL((attn_f32_bwd_kernel<G>), grid, dim3(kThreads), 0, s, t, nblk)
   HDET_ATTN_HEAD(t.d_model / t.heads, BWD)
 #undef BWD

@@ -42,3 +42,25 @@ def test_against_oracle_and_unfused_path(seq, heads, dh, batch, temp):
             assert norm_err(got[r, part], other[r, part]) <= 3e-5, (name, r, "unfused")
     run.close()
     plain.close()
+
+
+def test_as_many_heads_as_the_separate_products_take():
+    """2^23 heads, whose blocks of both kinds are more than a grid's 2^32 threads along one axis."""
+    cfg, batch = dict(n_blocks=1, d_model=64, n_heads=8, d_ff=8, seq_len=1, vocab=9), 1 << 20
+    got = []
+    for variant in (0, 2):
+        run = TfRun(base(n_replicas=1), cfg, batch)
+        H.hdet_set_launch_shape(run.h, variant, 0)
+        _, _, losses = run.forward_backward(1)
+        got.append((losses[0], run.g.cpu().numpy()[0, :run.P]))
+        run.close()
+        del run
+    assert abs(got[0][0] - got[1][0]) <= 1e-5
+    off = 0
+    for name, shape in I.transformer_shapes(cfg):
+        k = int(np.prod(shape))
+        part = slice(off + (2 * k // 3 if name.split(".")[0] in ("w_qkv", "b_qkv") else 0), off + k)     # one key: no gradient of queries and keys
+        off += k
+        # sums over 2^20 rows in four chains of 2^17 additions: independent roundings make 2^-24 sqrt(2^17) = 2.2e-5 on either side, of the size of the
+        # largest partial sum, which is a few times the result's
+        assert norm_err(got[0][1][part], got[1][1][part]) <= 2e-4, name
