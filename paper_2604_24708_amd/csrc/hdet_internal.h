@@ -318,6 +318,7 @@ struct hdet_attn_f32_desc {
   float* a;                 // forward output, read by the backward: [N][B][S][d_model]
   float* p;                 // probabilities, written by the forward (32 x 32 blocks at and below the diagonal): [N][B][heads][S][S]
   const float* da;          // backward: gradient at a
+  float* ds;                // backward scratch, layout of p (sequences beyond 32)
   float* dqkv;              // backward output, layout of qkv
   const hdet_ctrl* ctrl;
   int temp_channel;         // attention-temperature channel or -1

@@ -1424,7 +1424,7 @@ hipError_t run(hdet_tf_plan* p, const int32_t* ids, const int32_t* targets, hdet
   };
   auto attn_f32_desc = [&](int l) {
     hdet_attn_f32_desc ad;
-    ad.qkv = (const float*)p->qkv[l]; ad.a = (float*)p->a[l]; ad.p = (float*)p->p[l]; ad.da = (const float*)p->dtmp; ad.dqkv = (float*)p->dqkv;
+    ad.qkv = (const float*)p->qkv[l]; ad.a = (float*)p->a[l]; ad.p = (float*)p->p[l]; ad.da = (const float*)p->dtmp; ad.ds = (float*)p->ds; ad.dqkv = (float*)p->dqkv;
     ad.ctrl = ctrl; ad.temp_channel = p->temp_channel; ad.scale = scale;
     ad.n_replicas = N; ad.batch = B; ad.seq_len = S; ad.heads = nh; ad.d_model = d;
     return ad;

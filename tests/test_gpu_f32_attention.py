@@ -2,6 +2,7 @@
 blocks and the tiles a wavefront holds, every head size it takes, with the temperature channel; and against the unfused path."""
 import numpy as np
 import pytest
+import torch
 
 import hdet_inputs as I
 import paper_2604_24708_amd as H
@@ -35,13 +36,54 @@ def test_against_oracle_and_unfused_path(seq, heads, dh, batch, temp):
             off += k
             if seq == 1 and name in ("w_qkv.0", "b_qkv.0"):     # one key: the gradients of queries and keys are zero
                 part = slice(part.start + 2 * k // 3, part.stop)
+                parts = [part]
             elif name.split(".")[0] == "b_qkv":                 # the keys' third is zero but for rounding
-                continue
-            # a dozen fp32 products in a chain
-            assert norm_err(got[r, part], grads[r, part]) <= 3e-5, (name, r)
-            assert norm_err(got[r, part], other[r, part]) <= 3e-5, (name, r, "unfused")
+                parts = [slice(part.start, part.start + k // 3), slice(part.start + 2 * k // 3, part.stop)]
+            else:
+                parts = [part]
+            for part in parts:
+                # a dozen fp32 products in a chain
+                assert norm_err(got[r, part], grads[r, part]) <= 3e-5, (name, r)
+                assert norm_err(got[r, part], other[r, part]) <= 3e-5, (name, r, "unfused")
     run.close()
     plain.close()
+
+
+@pytest.mark.parametrize("seq,heads,dh,batch", [(32, 4, 16, 4), (64, 2, 32, 2), (128, 4, 64, 2), (192, 2, 64, 1), (512, 1, 64, 1)])
+@pytest.mark.parametrize("keys,values", [(30.0, 0.0), (0.0, 30.0)])
+def test_offsets_cancel_as_in_separate_products(seq, heads, dh, batch, keys, values):
+    """Keys or values with a common offset: the gradients of queries and keys are sums that cancel.  Distance from 64 bits, rms over replicas and batches,
+    against that of the path through separate products."""
+    cfg, n = model(seq, heads, dh), 2
+    d = heads * dh
+    err = {}
+    for variant in (0, 2):
+        run = TfRun(base(n_replicas=n), cfg, batch)
+        H.hdet_set_launch_shape(run.h, variant, 0)
+        flat, off = run.orc.theta.copy(), 0
+        for name, shape in I.transformer_shapes(cfg):
+            k = int(np.prod(shape))
+            if name == "b_qkv.0":
+                flat[:, off + d:off + 2 * d] += keys
+                flat[:, off + 2 * d:off + 3 * d] += values
+            if name in ("w_qkv.0", "w_o.0"):
+                flat[:, off:off + k] *= 10 / np.sqrt(d)          # outputs of the inputs' size
+            if name == "w_qkv.0":
+                w_qkv = slice(off, off + k)
+            off += k
+        run.orc.theta[:] = flat
+        run.theta[:, :run.P] = torch.from_numpy(flat).to(run.theta.device)
+        e = []
+        for t in (1, 2, 3):
+            ids, tgt, _ = run.forward_backward(t)
+            _, ref = run.oracle_grads(flat, ids, tgt, t)
+            got = run.g.cpu().numpy()
+            e += [[norm_err(a, b) for a, b in zip(got[r, w_qkv].reshape(3, -1), ref[r, w_qkv].reshape(3, -1))] for r in range(n)]
+        err[variant] = np.sqrt(np.mean(np.square(e), axis=0))
+        run.close()
+    # six samples of an error on either side: 0.7 to 1.1 of the separate products' where the row dots are sums of the dp that they are taken from,
+    # 1.4 to 3 for the queries where they are not
+    assert np.all(err[0] <= 1.25 * err[2]), (err[0], err[2])
 
 
 def test_as_many_heads_as_the_separate_products_take():
