@@ -118,8 +118,12 @@ __device__ __forceinline__ float hdet_gelu_exp(float z, float z2) {
   const float k1 = -1.5957691216057308f, k2 = -0.07135481282592269f;      // -2 c, -2 c 0.044715
   return expf(z * __builtin_fmaf(k2, z2, k1));
 }
+// With h = e(|z|) / (1 + e(|z|)), at most 1/2: z h below 0, z - z h above, so that only the last rounding is of the result's size.  Normal arguments of
+// size 1 and 2, rms from 64 bits: 1.9e-8 and 3.5e-8 (a last rounding alone 1.7e-8 and 3.4e-8; 0.5 z (1 + tanh u) 2.6e-8 and 4.8e-8; z / (1 + e(z)) 2.8e-8
+// and 5.7e-8).  Above 10 h is 0, also where z h would be infinity times that.
 __device__ __forceinline__ float hdet_gelu_tanh(float z) {
-  return z / (1.f + hdet_gelu_exp(z, z * z));
+  const float e = hdet_gelu_exp(fabsf(z), z * z), h = e / (1.f + e);
+  return z < 0.f ? z * h : __builtin_fmaf(z > 10.f ? -10.f : -z, h, z);
 }
 // Below -10 the derivative is less than 1e-35 in size and s runs out of exponents while the rest still grows with z^3: 0 from there on.  Above 10 it
 // is 1 and formed at 10, where nothing overflows.  (NaN takes neither branch.)

@@ -65,6 +65,20 @@ def test_range(gelu):
     assert np.all(np.isfinite(got)) and np.max(np.abs(got - value[ok]) / (np.abs(value[ok]) + 1e-5)) <= 5e-6
 
 
+@pytest.mark.parametrize("size,value_bound,grad_bound", [(1.0, 2.1e-8, 5e-8), (2.0, 3.9e-8, 5e-8)])
+def test_ordinary_arguments(gelu, size, value_bound, grad_bound):
+    """rms over normal arguments: little more than the result's own rounding (1.7e-8 and 3.4e-8) for the value, a few roundings of numbers up to 1
+    for the derivative."""
+    z = (size * np.random.Generator(np.random.Philox(5)).standard_normal(200000)).astype(np.float32)
+    value, grad = exact(z)
+    assert np.sqrt(np.mean((gelu("hdet_gelu_tanh", z) - value) ** 2)) <= value_bound
+    assert np.sqrt(np.mean((gelu("hdet_gelu_tanh_grad", z) - grad) ** 2)) <= grad_bound
+
+
+def test_infinity(gelu):
+    assert gelu("hdet_gelu_tanh", np.array([np.inf], np.float32))[0] == np.inf
+
+
 def test_nan_stays(gelu):
     z = np.array([np.nan, -np.nan], np.float32)
     assert np.all(np.isnan(gelu("hdet_gelu_tanh", z))) and np.all(np.isnan(gelu("hdet_gelu_tanh_grad", z)))
