@@ -16,13 +16,16 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 @pytest.fixture(scope="module")
 def gelu(tmp_path_factory):
     text = open(os.path.join(ROOT, "paper_2604_24708_amd", "csrc", "hdet_elem.h")).read()
-    names = ("hdet_gelu_exp", "hdet_gelu_tanh", "hdet_gelu_tanh_grad")
+    names = ("hdet_gelu_exp", "hdet_gelu_sigma_fast", "hdet_gelu_tanh", "hdet_gelu_tanh_grad", "hdet_gelu_tanh_fast", "hdet_gelu_tanh_grad_fast")
     bodies = [re.search(r"__device__ __forceinline__ float %s\(.*?\n}\n" % n, text, re.S).group(0) for n in names]
     loops = "".join('extern "C" void %s_all(const float* x, float* y, long n) { for (long i = 0; i < n; ++i) y[i] = %s(x[i]); }\n' % (n, n)
-                    for n in names[1:])
+                    for n in names[2:])
     d = tmp_path_factory.mktemp("gelu")
     src = d / "gelu.cpp"
-    src.write_text("#include <cmath>\n#define __device__\n#define __forceinline__ inline\n" + "".join(bodies) + loops)
+    builtins = ("static float __builtin_amdgcn_rcpf(float x) { return 1.f / x; }\n"
+                "static float __builtin_amdgcn_exp2f(float x) { return exp2f(x); }\n"
+                "static float __builtin_amdgcn_fmed3f(float x, float a, float b) { return fmaxf(fminf(fmaxf(x, a), b), a); }\n")
+    src.write_text("#include <cmath>\n#define __device__\n#define __forceinline__ inline\n" + builtins + "".join(bodies) + loops)
     cc = shutil.which("g++")
     assert cc, "g++ not found"
     lib = str(d / "gelu.so")
@@ -51,9 +54,20 @@ def exact(z):
     return value, grad
 
 
-def test_range(gelu):
+def everywhere():
     size = np.concatenate([np.logspace(-38, np.log10(3.4e38), 4001), np.linspace(0.01, 14, 4001), [9.99, 10.0, 10.01, np.inf]]).astype(np.float32)
-    z = np.concatenate([-size, size])
+    return np.concatenate([-size, size])
+
+
+def test_range_of_the_fast_derivative(gelu):
+    z = everywhere()
+    got, grad = gelu("hdet_gelu_tanh_grad_fast", z), exact(z)[1]
+    # 1 - sigma of a rounded sigma, times z 2 u' (up to 30 where it counts): rounded to bfloat16 afterwards
+    assert np.all(np.isfinite(got)) and np.max(np.abs(got - grad)) <= 5e-6, z[np.argmax(np.abs(got - grad))]
+
+
+def test_range(gelu):
+    z = everywhere()
     value, grad = exact(z)
     got = gelu("hdet_gelu_tanh_grad", z)
     # the derivative is between -0.13 and 1.13: a few roundings of numbers of that size
