@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 import hdet_inputs as I
+import paper_2604_24708_amd as H
 from test_gpu_products import mlp_grads
 from test_gpu_transformer import TfRun, base, norm_err
 
@@ -33,6 +34,7 @@ def test_mlp_gradients(widths, batch, n, shared):
 ])
 def test_transformer_gradients(cfg, batch, n):
     run = TfRun(base(n_replicas=n), cfg, batch)
+    H.hdet_set_launch_shape(run.h, 2, 0)               # attention as products, a batch item a head, also where one kernel would form it
     ids, tgt, gl = run.forward_backward(1)
     losses, grads = run.oracle_grads(run.orc.theta, ids, tgt, 1)
     assert np.max(np.abs(gl - losses)) <= 1e-5 * np.max(losses)

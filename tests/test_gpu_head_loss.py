@@ -6,6 +6,7 @@ import torch
 
 import hdet_inputs as I
 import paper_2604_24708_amd as H
+from oracle import hdet_oracle as O
 from test_gpu_transformer import TfRun, base, check_bf16_gradients, norm_err
 
 pytestmark = pytest.mark.gpu
@@ -13,7 +14,7 @@ pytestmark = pytest.mark.gpu
 # (replicas, batch, model, replicas compared)
 CASES = [
     # 1800 x 1992: eight rows in the last tile, 200 columns; K = 192 is three K steps, the fourth empty
-    (6, 36, dict(n_blocks=1, d_model=192, n_heads=3, d_ff=64, seq_len=50, vocab=1992), (0, 5)),
+    (7, 36, dict(n_blocks=1, d_model=192, n_heads=3, d_ff=64, seq_len=50, vocab=1992), (0, 6)),
     # wide rows, 8 columns in the last tile, K no multiple of a step
     (4, 52, dict(n_blocks=1, d_model=200, n_heads=4, d_ff=64, seq_len=50, vocab=2056), (1, 3)),
     # more than four rounds of tiles, K of nine steps
@@ -54,11 +55,11 @@ def test_loss_and_gradients(n, batch, cfg, compared):
 
 
 @pytest.mark.parametrize("size", [1.0, 30.0, 300.0])
-@pytest.mark.parametrize("n,batch,cfg", [c[:3] for c in CASES[1:]])
+@pytest.mark.parametrize("n,batch,cfg", [c[:3] for c in CASES])
 def test_loss_of_known_logits(n, batch, cfg, size):
     """A head of no weights: every row's logits are the head's biases, known to the last bit, and so are the loss and the bias gradient in 64 bits.
     Classes next to the row's maximum lie in all column tiles, a hundred others are masked by -inf, one tile's whole 256 among them (a loss kernel that reads
-    the logits from memory has no finite loss there)."""
+    the logits from memory has no finite loss there: these sizes do take the path)."""
     run = TfRun(base(n_replicas=n), cfg, batch, bf16=True)
     V, M = cfg["vocab"], batch * cfg["seq_len"]
     part = slices(cfg)
@@ -112,6 +113,36 @@ def test_label_that_is_no_class():
         want = np.log(np.exp(b.astype(np.float64)).sum()) - np.where(tgt[r] >= 0, b[tgt[r]], 0.0).mean()
         assert abs(out[r] - want) <= 4e-7 * abs(want) + 3e-7
     run.close()
+
+
+def test_one_call_equals_two_calls():
+    n, batch, cfg = CASES[1][:3]
+    two, one = (TfRun(base(n_replicas=n, optimizer=O.ADAMW, lr_max=2e-3), cfg, batch, bf16=True) for _ in range(2))
+    for t in (1, 2):
+        ids, tgt, losses = two.forward_backward(t)
+        H.hdet_fanout_step(two.h, None, 0)
+        got = H.hdet_train_step(one.h, torch.from_numpy(ids).to("cuda:0"), torch.from_numpy(tgt).to("cuda:0"), 0, want_losses=True)
+        assert [got[r] for r in range(n)] == losses.tolist()
+        for a, b in ((one.theta, two.theta), (one.m, two.m), (one.v, two.v)):
+            assert torch.equal(a.view(torch.int32), b.view(torch.int32)), t
+    one.close()
+    two.close()
+
+
+def test_shared_gradients():
+    """One weight gradient over all replicas' rows, from the same gradients of the logits; losses and head bias gradients stay per replica, bit for bit."""
+    n, batch, cfg = CASES[2][:3]
+    shared, own = (TfRun(base(n_replicas=n, optimizer=O.ADAMW, grad_mode=m), cfg, batch, bf16=True) for m in (O.GRAD_SHARED, O.GRAD_PER_REPLICA))
+    _, _, ls = shared.forward_backward(1)
+    _, _, lo = own.forward_backward(1)
+    assert np.array_equal(ls, lo)
+    part = slices(cfg)
+    assert torch.equal(shared.g[:, part["b_head"][0]], own.g[:, part["b_head"][0]])
+    a, b = shared.g[0, part["w_head"][0]].double(), own.g[:, part["w_head"][0]].double().sum(0)
+    # 5150 rows in another order: 2^-24 sqrt(5150) = 4e-6
+    assert float((a - b).norm() / b.norm()) <= 2e-5
+    shared.close()
+    own.close()
 
 
 def test_bias_product_of_several_rounds():
