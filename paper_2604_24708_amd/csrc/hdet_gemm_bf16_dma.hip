@@ -649,13 +649,13 @@ __global__ __launch_bounds__(512, 2) void hdet_bgemm_alt_kernel(const hdet_bgemm
 //  * Exponentials of logits are exp2(z log2(e) - r), one fused operation and the hardware's exp2, with r the whole number next to max log2(e): what tiles
 //    and rows refer to differs by exact powers of two, and nothing that is rounded once for the maximum fails to cancel between the sums and the
 //    gradient.  Simulated against 64 bits, logits of size 0.5 to 30, 1000 to 16000 classes: probabilities off by 3e-8 to 1.1e-7 (rms, relative), those of the
-//    loss kernels (hdet_mlp.hip) by 4e-8 to 3.6e-7; row losses by 0.6 to 0.9 times as much as theirs.  With r = max log2(e) rounded, a tile's own for its
+//    loss kernels (hdet_mlp.hip) by 4e-8 to 3.6e-7; row losses by 0.6 to 1.0 times as much as theirs.  With r = max log2(e) rounded, a tile's own for its
 //    sum and the row's for the gradient, 1.0e-7 to 7e-7, and 2e-5 where the maxima of several tiles lie next to each other at 300.
 // Built for the output layer with its loss (hdet_launch_head_loss; products with a bias take it too, launch_shape), whose two passes cost less than writing and reading fp32 logits:  K = 512,
-// 4096 x 32000, 8 replicas, 1502 to 1575 us of product and 1152 of loss kernel -> 918 (statistics) + 19 (merge) + 1190 (gradient).  Of a tile's
-// 14.7 and 19 us the main loop takes 11 (1.6 PFLOP/s, 70 % of the matrix cores' cycles), exponentials 3.4, stores 3.5.  Not kept, gradient pass:
-// results through LDS 1216 (rows of bf16), past the L2 1358 (pieces of 16 bytes), both groups' ends in turn 1240; the kernel above with these
-// epilogues 1019 and 1400.
+// 4096 x 32000, 8 replicas, 1502 to 1575 us of product and 1152 of loss kernel -> 948 (statistics) + 19 (merge) + 1205 (gradient) in a training step
+// (cards differ by up to 10 % in these).  Of a tile's 15 and 19 us the main loop takes 11 (1.6 PFLOP/s, 70 % of the matrix cores' cycles), exponentials
+// 3.4, stores 3.5.  Not kept, gradient pass, beside 1190 on one card: results through LDS 1216 (rows of bf16), past the L2 1358 (pieces of 16 bytes), both
+// groups' ends in turn 1240; the kernel above with these epilogues 1019 and 1400.
 template <int EPI>
 __global__ __launch_bounds__(512, 2) void hdet_bgemm_walk_kernel(const hdet_bgemm_args g, unsigned gx, unsigned gy, unsigned total) {
   constexpr int TM = 256, TN = 256, TK = 64, HALF = 128 * TK;

@@ -523,6 +523,10 @@ tiles tile_grid(const hdet_sgemm_args& g, int batch) {
 //   more: 64 x 128, K in 2             512 x 1024, K = 256, 4 items: 18.0 | 64 x 64 24.6 | 64 x 32 27.2
 //   many, an operand contiguous along k: 64 x 64 with two steps in flight instead of four, whose smaller register count lets a
 //         CU hold more of them         4096 x 2048, K = 512, 8 items: 798 | 64 x 128 910 (wgrad: 914 | 64 x 128 588)
+// The two tiles through LDS, 64 x 64 | 64 x 32, by tiles of 64 x 32 a CU (forward products; weight gradients alike).  K = 256: one 11.8 | 8.0, 1.5
+// 12.4 | 12.0, 2.5 16.6 | 14.2, 3 16.9 | 14.9, 4 16.7 | 21.8, 8 31.4 | 32.0, 16 54 | 57, 128 397 | 451;  K = 1024: one 26.4 | 16.8, 1.5 26.8 | 24.2, 2.5
+// 39.9 | 32.5, 3 40.3 | 33.2, 4 41.7 | 50.6, 8 92 | 86, 16 162 | 173, 128 1282 | 1320.  So the line at one tile a CU, drawn for fragments from global
+// memory, lies too low for these by a factor of three: 3 to 20 % between them.
 enum { kCfg32, kCfg64x32, kCfg64, kCfg64x128, kCfg64Light };
 int64_t count_blocks(const hdet_sgemm_args& g, int batch, int tm, int tn) {
   return (int64_t)((g.m + tm - 1) / tm) * ((g.n + tn - 1) / tn) * batch;

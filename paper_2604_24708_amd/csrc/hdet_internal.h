@@ -197,9 +197,10 @@ struct hdet_bgemm_args {
   // replica * 65536 + drop_site, drop_stream) and key drop_seed; element = row * ldc + column
   const hdet_ctrl* drop_ctrl; int drop_channel;
   uint32_t drop_step, drop_site, drop_stream, drop_seed_lo, drop_seed_hi;
-  // HDET_EPI_GELUGRAD_BF16 and HDET_EPI_MASK_BF16 on the LDS-direct kernel, optional (n1 = n2 = 1): colsum[(replica * ceil(m / 128) + m / 128) * n + column] receives the
-  // sum of C as stored over that 128-row block of the column (stage 1 of the bias gradient of the layer whose
-  // pre-activation gradient C is); colsum_bs is unused padding for alignment
+  // HDET_EPI_GELUGRAD_BF16, HDET_EPI_MASK_BF16 on the LDS-direct kernel and HDET_EPI_XENT_GRAD, optional (n1 = n2 = 1):
+  // colsum[(replica * ceil(m / 128) + m / 128) * n + column] receives the sum of C over that 128-row block of the column (stage 1 of
+  // the bias gradient of the layer whose pre-activation gradient C is): of C as stored, but for HDET_EPI_XENT_GRAD of C before it is
+  // rounded (where logits go through memory, xent_row_kernel adds what it stores)
   float* colsum;
   hdet_xent_epi xent;      // HDET_EPI_XENT_*
   float* rowsum; int64_t rowsum_bs;     // general kernels, weight gradients: rowsum[z0*rowsum_bs + m] = sum_k A(m,k), or null
@@ -247,7 +248,7 @@ hipError_t hdet_launch_bgemm(const hdet_bgemm_args& g, bool a_kmajor, bool b_kma
 // below 2 GiB); n1, n2 >= 1 on entry.
 bool hdet_bgemm_dma_eligible(const hdet_bgemm_args& g, bool a_kmajor, bool b_kmajor, int epi);
 // Output layer with its softmax cross-entropy (forward order; g: operands, bias, c = dlogits bf16, colsum; xent: labels, row_loss): dlogits
-// and row losses without the logits ever being written.  scratch: hdet_head_loss_scratch(g, batch) bytes, 16-byte aligned.
+// and row losses without the logits ever being written.  scratch: hdet_head_loss_scratch(m, n, batch) bytes, 16-byte aligned.
 bool hdet_head_loss_eligible(const hdet_bgemm_args& g, int batch);
 size_t hdet_head_loss_scratch(int m, int n, int batch);
 hipError_t hdet_launch_head_loss(const hdet_bgemm_args& g, int batch, void* scratch, hipStream_t stream);

@@ -1080,11 +1080,11 @@ static hdet_bgemm_args head_args(const hdet_tf_plan* p) {
 
 // Whether it is: the second product costs 2 K operations a logit, the logits it saves 8 bytes written and read.  Blocks take whole tiles of
 // 256 x 256, so that a last round of few tiles counts in full.  us, product with logits and loss kernel / two products (replicas, rows, K, classes):
-//   from four rounds on:  8 4096 256 32000 2211 / 1636;  8 4096 512 32000 2654 / 2107, 12000 958 / 850, 4096 318 / 282, 2000 160 / 140;
-//     640, 32000 2973 / 2740;  768, 32000 3019 / 3116, 2000 181 / 182;  1024, 8000 843 / 906, 2000 198 / 220
-//   one and a half to three:  K = 256 and 384 3 4096 256 2048 74 / 63, 8 4096 256 1000 74 / 60, 5 2048 384 2560 91 / 71;  K = 512 4 2048 512 4000 92 / 86,
-//     8 4096 512 1000 91 / 80, of a round's tiles unused 2 2048 512 7000 79 / 83, 9000 104 / 111, 3 4096 512 1800 67 / 72
-//   fewer:  8 4096 256 504 45 / 39, 8 4096 512 504 51 / 51, 2 1024 512 12000 65 / 78, 4 1024 256 1800 29 / 38, 2 2048 512 1000 23 / 43
+//   from four rounds on:  8 4096 256 32000 2234 / 1620;  8 4096 512 32000 2780 / 2210, 12000 986 / 846, 4096 332 / 290, 2000 170 / 155;
+//     640, 32000 2931 / 2569, 2000 178 / 172;  768, 32000 3097 / 2934, 2000 189 / 198;  1024, 8000 869 / 897, 2000 208 / 239
+//   one and a half to three:  K = 256 and 384 3 4096 256 2048 71 / 58, 8 4096 256 1000 77 / 64, 5 2048 384 2560 88 / 67;  K = 512 4 2048 512 4000 92 / 82,
+//     8 4096 512 1000 90 / 87, of a round's tiles unused 2 2048 512 7000 77 / 79, 9000 104 / 108, 3 4096 512 1800 69 / 78
+//   fewer:  8 4096 256 504 46 / 41, 8 4096 512 504 52 / 53, 2 1024 512 12000 68 / 77, 4 1024 256 1800 27 / 36, 2 2048 512 1000 22 / 41
 static bool tf_head_loss(const hdet_tf_plan* p) {
   if (!p->bf16 || p->ls_channel >= 0) return false;
   const hdet_bgemm_args g = head_args(p);
